@@ -310,40 +310,6 @@ __global__ __launch_bounds__(256) void linear_scalar_kernel(
     if (acc_out) acc_out[idx] = acc;
 }
 
-// Grouped form (Sec. 3, Eq. 3) for shapes the MFMA kernel does not take: per group an exact int32
-// product, folded into fp32 with one fused multiply-add per group in ascending order.
-template <int DT, bool INT4>
-__global__ __launch_bounds__(256) void linear_grouped_scalar_kernel(
-    const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq, const float* __restrict__ s_g,
-    const float* __restrict__ s_w, const float* __restrict__ bias, uint16_t* __restrict__ y,
-    float* __restrict__ f_out, int64_t M, int64_t N, int64_t K, int64_t group)
-{
-    using S = Store16<DT>;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= M * N) return;
-    const int64_t m = idx / N, n = idx % N;
-    const int8_t* xr = xq + m * K;
-    float f = 0.0f;
-    for (int64_t g0 = 0; g0 < K; g0 += group) {
-        int acc = 0;
-        for (int64_t k = g0; k < g0 + group; ++k) {
-            int w;
-            if (INT4) {
-                const int b = wq[n * (K / 2) + k / 2];
-                w = (((k & 1) ? (b >> 4) : (b & 15)) ^ 8) - 8;
-            } else {
-                w = reinterpret_cast<const int8_t*>(wq)[n * K + k];
-            }
-            acc += (int)xr[k] * w;
-        }
-        f = __builtin_fmaf((float)acc, s_g[g0 / group], f);
-    }
-    if (f_out) f_out[idx] = f;
-    float yv = f * s_w[n];
-    if (bias) yv = yv + bias[n];
-    y[idx] = S::enc(yv);
-}
-
 // ---------------------------------------------------------------------------------------------
 // int8 MFMA GEMM over pre-quantized activations.
 //
@@ -1088,11 +1054,9 @@ static void run_linear_grouped(const void* x, const float* s_g, const void* wq, 
         }
     } else {
         quantize_rowmajor(xq_ws);
-        const int64_t blocks = (M * N + 255) / 256;
-        auto W = static_cast<const uint8_t*>(wq);
-        auto Y = static_cast<uint16_t*>(y);
-        if (wf == SASQ_W_INT4_PACKED) linear_grouped_scalar_kernel<DT, true><<<(int)blocks, 256, 0, st>>>(xq_ws, W, s_g, s_w, bias, Y, f_out, M, N, K, group);
-        else                          linear_grouped_scalar_kernel<DT, false><<<(int)blocks, 256, 0, st>>>(xq_ws, W, s_g, s_w, bias, Y, f_out, M, N, K, group);
+        GemmK64Args a{xq_ws, static_cast<const uint8_t*>(wq), s_g, s_w, bias, static_cast<uint16_t*>(y),
+                      reinterpret_cast<int32_t*>(f_out), M, N, K};
+        launch_grouped_valu(a, (sasq_dtype)DT, wf == SASQ_W_INT4_PACKED, group, st);
     }
 }
 

@@ -109,6 +109,27 @@ def test_grouped_linear_scalar_path(shape, group, dtype, fmt):
         assert_same_values(y, ref["y"], dtype, "Y")
 
 
+@pytest.mark.parametrize("fmt", ["int8", "int4"])
+@pytest.mark.parametrize("shape,group", [
+    ((5, 70, 1), 1), ((9, 65, 130), 1), ((33, 130, 64), 1),      # four rows per wave: row, column and slab remainders
+    ((200, 3600, 66), 1),                                        # eight rows per wave
+    ((390, 4100, 70), 1), ((780, 4101, 34), 1), ((1500, 4200, 36), 1),   # 32x64, 64x64 and 64x128 tiles
+    ((7, 90, 36), 4), ((70, 3000, 40), 8), ((300, 4090, 52), 4), ((1025, 4100, 24), 12),   # packed sums of four, every tile
+    ((17, 66, 54), 6), ((65, 4099, 50), 10), ((300, 4000, 42), 3), ((900, 4200, 14), 7)])  # any other group, every tile
+def test_grouped_linear_small_groups_every_kernel(shape, group, fmt):
+    """Group sizes without a matrix-unit form: each kernel and tile the dispatch can choose, at sizes that leave rows,
+    columns and part of a K slab over.  Bit for bit: the chain of fused multiply-adds is part of the contract."""
+    if fmt == "int4" and shape[2] % 2:
+        pytest.skip("packed int4 needs an even K")
+    dtype = "f16" if fmt == "int8" else "bf16"
+    xb, wq, s_w, bias, s_g = problem(54, shape, group, dtype, fmt)
+    ref = oracle.static_linear_grouped(xb, s_g, wq, s_w, bias, group, 8, fmt, dtype)
+    y, f, xq = run_grouped(xb, s_g, wq, s_w, bias, group, fmt, dtype, False)
+    assert np.array_equal(xq, ref["xq"])
+    assert np.array_equal(f, ref["f"])
+    assert_same_values(y, ref["y"], dtype, "Y")
+
+
 def test_grouped_linear_rejects():
     x = torch.zeros((4, 128), dtype=torch.float16, device="cuda")
     y = torch.zeros((4, 4), dtype=torch.float16, device="cuda")
