@@ -939,6 +939,35 @@ static void launch_mfma(const void* xin, const void* wq, const float* s, const f
     }
 }
 
+// Few rows: the kernels of static_linear_skinny.hip, unless a knob asks for a variant of the tiled ones.  Row-major packed
+// int4 keeps the tiled kernel (its codes are not in operand order).
+static bool use_skinny(int64_t rows, sasq_wfmt wf)
+{
+    return rows <= kSkinnyRows && wf != SASQ_W_INT4_PACKED && tuning(SASQ_TUNE_LINEAR_PATH) == 0 &&
+           tuning(SASQ_TUNE_LINEAR_TILE) == 0 && tuning(SASQ_TUNE_LINEAR_MFMA) == 0;
+}
+
+// Whether such a call quantizes in the kernel: at most 16 rows everywhere, and no output over an input (the pre-pass has
+// read every x before the first y is written; workgroups that quantize for themselves have not).
+static bool skinny_quantizes(const LinBatch& g, const int32_t* acc_out)
+{
+    auto overlap = [](const void* a, size_t an, const void* b, size_t bn) {
+        const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
+        return pa < pb + bn && pb < pa + an;
+    };
+    for (int i = 0; i < g.count; ++i) {
+        const LinItem& in = g.it[i];
+        if (in.M > kSkinnyQuantRows) return false;
+        const size_t xbytes = (size_t)in.M * in.K * 2;
+        for (int j = 0; j < g.count; ++j) {
+            const LinItem& out = g.it[j];
+            if (overlap(in.x, xbytes, out.y, (size_t)out.M * out.N * 2)) return false;
+            if (acc_out && overlap(in.x, xbytes, acc_out, (size_t)out.M * out.N * 4)) return false;
+        }
+    }
+    return true;
+}
+
 // the staged (tiled) activation pre-pass of one tensor: one wave per 1 KB block
 template <int DT, bool PERM8>
 static void launch_quantize_blocks(const void* x, const float* s, int8_t* xq, int64_t M, int64_t K, int a_bits, hipStream_t st)
@@ -969,7 +998,17 @@ static void run_linear(const void* x, const float* s, const void* wq, const floa
 
     const bool mfma_ok = (K % kBK) == 0;
     const bool int4 = wf == SASQ_W_INT4_PACKED;
-    if (wf == SASQ_W_INT8_BLOCKED || wf == SASQ_W_INT4_BLOCKED) {
+    if (mfma_ok && use_skinny(M, wf)) {
+        LinBatch g{};
+        g.count = 1;
+        LinItem& li = g.it[0];
+        li.x = x; li.xq = xq_ws; li.s = s; li.wq = static_cast<const uint8_t*>(wq); li.s_w = s_w; li.bias = bias;
+        li.y = static_cast<uint16_t*>(y);
+        li.M = (int)M; li.N = (int)N; li.K = (int)K;
+        const bool qx = skinny_quantizes(g, acc_out);
+        if (!qx) launch_quantize_blocks<DT, false>(x, s, xq_ws, M, K, a_bits, st);
+        launch_linear_skinny(g, (sasq_dtype)DT, (int)wf, qx, a_bits, acc_out, st);
+    } else if (wf == SASQ_W_INT8_BLOCKED || wf == SASQ_W_INT4_BLOCKED) {
         // pre-arranged weights (K % 64 == 0 was checked by the caller): always the two-pass MFMA path
         launch_quantize_blocks<DT, false>(x, s, xq_ws, M, K, a_bits, st);
         if (wf == SASQ_W_INT8_BLOCKED) launch_mfma<DT, X_PREQ, W_I8B>(xq_ws, wq, s, s_w, bias, y, acc_out, M, N, K, a_bits, st);
@@ -1274,6 +1313,15 @@ extern "C" int sasq_static_linear_batch(const sasq_linear_item* items, int count
     }
     for (int i = count; i < kMaxLinearBatch; ++i) g.first_block[i + 1] = g.first_block[count];
 
+    hipStream_t st = as_stream(stream);
+    int64_t rows = 0;
+    for (int i = 0; i < count; ++i) rows = items[i].M > rows ? items[i].M : rows;
+    const bool skinny = use_skinny(rows, wf);
+    if (skinny && skinny_quantizes(g, nullptr)) {
+        launch_linear_skinny(g, dt, (int)wf, true, a_bits, nullptr, st);
+        return hipGetLastError() == hipSuccess ? SASQ_OK : SASQ_ERR_LAUNCH;
+    }
+
     // the pre-passes: projections on the same X (same pointer, M and K) share one entry
     QuantBatch q{};
     bool taken[kMaxLinearBatch] = {false};
@@ -1306,14 +1354,15 @@ extern "C" int sasq_static_linear_batch(const sasq_linear_item* items, int count
     }
     for (int i = q.count; i < kMaxLinearBatch; ++i) q.first_block[i + 1] = q.first_block[q.count];
 
-    hipStream_t st = as_stream(stream);
     const int qgrid = q.first_block[q.count], ggrid = g.first_block[count];
     const bool perm8 = wf == SASQ_W_INT4_PACKED;      // row-major packed int4 unpacks in (0,2,4,6,1,3,5,7) order
 #define SASQ_LAUNCH_BATCH(DTV)                                                                                          \
     do {                                                                                                                \
         if (perm8) quantize_act_batch_kernel<DTV, true><<<qgrid, 256, 0, st>>>(q, a_bits);                              \
         else       quantize_act_batch_kernel<DTV, false><<<qgrid, 256, 0, st>>>(q, a_bits);                             \
-        if (use_k64(X_PREQ, (int)wf)) {          /* the sasq_wfmt values are those of the kernels' weight paths */     \
+        if (skinny) {                                                                                                   \
+            launch_linear_skinny(g, dt, (int)wf, false, a_bits, nullptr, st);                                           \
+        } else if (use_k64(X_PREQ, (int)wf)) {   /* the sasq_wfmt values are those of the kernels' weight paths */     \
             launch_gemm_k64_batch(g, ggrid, dt, (int)wf, tuning(SASQ_TUNE_LINEAR_TILE) == 0, st);                       \
         } else switch (wf) {                                                                                            \
             case SASQ_W_INT8:         linear_mfma_batch_kernel<DTV, W_I8><<<ggrid, kGemmThreads, 0, st>>>(g, a_bits); break;   \

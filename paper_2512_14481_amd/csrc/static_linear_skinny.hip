@@ -1,0 +1,275 @@
+// int8 linear for few rows (token generation): Y = X . W^T where M is a handful of rows and the weights are what is read.
+//
+// What bounds it: the weight bytes (a 7B layer's seven projections at 8 rows, int8: 202 MB in 36 us = 5.6 TB/s, the GEMM's
+// tiles took 93; a 13B layer's at one row, int4: 159 MB in 30 us, from 128; row-major int8, whose rows are gathered in
+// 64-byte pieces: 51 us).  The tiled GEMM hands out 256 (or 128) weight rows per workgroup, which at small M is
+// a few dozen workgroups with a K loop that nothing overlaps.  Here a workgroup owns 16 NT weight rows and its NW waves
+// share out K: a wave streams its part of the weights straight from memory into MFMA operand registers (a pre-arranged
+// 1 KB block IS one operand read of a wave), D K tiles ahead, with no LDS and no barrier until the waves' int32 sums are
+// added up at the end, so that some thousand waves each keep several KB in flight.  Integer sums make the split exact.
+// QX: the activations are quantized on the way into the operand registers, 16 elements per lane and K tile, which takes
+// the pre-pass's launch out of the call; each workgroup repeats that work, so it is for at most 16 rows.  Otherwise the
+// codes come from the pre-pass in their staging blocks.
+#include "sasq_device.h"
+#include "gemm_tile.h"
+#include "gemm_k64.h"
+#include <type_traits>
+
+namespace sasq {
+
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX>
+__device__ __forceinline__
+void skinny_body(const LinItem& it, int nblk, int a_bits, int32_t* __restrict__ acc_out, char* lds)
+{
+    using S = Store16<DT>;
+    constexpr bool I4 = WMODE == 3, ROWMAJOR = WMODE == 0;
+    static_assert(!I4 || NT % 2 == 0, "int4 blocks hold 32 weight rows");
+    constexpr int WL = I4 ? NT / 2 : NT;               // 128-bit weight loads per lane and K tile
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int frow = lane & 15, fq = lane >> 4;
+    const int M = it.M, N = it.N, K = it.K, KT = K >> 6;
+    const int n0 = nblk * 16 * NT;
+
+    // This wave's K tiles: an equal run of consecutive ones.
+    const int per = (KT + NW - 1) / NW;
+    const int t0 = min(wave * per, KT), count = min(per, KT - t0);
+
+    // Scalar base + 32-bit lane offset for every stream; a base advances 1 KB (or 64 bytes of a row) per K tile.
+    const char* wbase[WL];
+    uint32_t woff;
+    if (I4) {
+        // Lane l takes 16 bytes: the K tile's codes 16 (l/16) .. + 15 of the weight rows 2 (l%16) and 2 (l%16) + 1.
+        woff = 256 * fq + 16 * frow;
+    } else if (ROWMAJOR) {
+        woff = (uint32_t)(16 * fq);                     // + the row, below
+    } else {
+        woff = (4 * frow + (fq ^ swz64(frow))) * 16;
+    }
+#pragma unroll
+    for (int j = 0; j < WL; ++j) {
+        const char* w = reinterpret_cast<const char*>(it.wq);
+        if (I4)            wbase[j] = w + ((int64_t)min((n0 >> 5) + j, (N - 1) >> 5) * KT + t0) * 1024;
+        else if (ROWMAJOR) wbase[j] = w + (int64_t)min(n0 + 16 * j, ((N - 1) >> 4) << 4) * K + (int64_t)t0 * 64;
+        else               wbase[j] = w + ((int64_t)min((n0 >> 4) + j, (N - 1) >> 4) * KT + t0) * 1024;
+    }
+    uint32_t wrow[ROWMAJOR ? NT : 1];                   // row-major: this lane's row inside each 16-row tile, clamped to N - 1
+    if (ROWMAJOR) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int first = min(n0 + 16 * j, ((N - 1) >> 4) << 4);
+            wrow[j] = (uint32_t)min(frow, N - 1 - first) * (uint32_t)K + woff;
+        }
+    }
+    constexpr int kWStep = ROWMAJOR ? 64 : 1024;
+    const char* xbase[MT];
+    uint32_t xoff[MT];
+#pragma unroll
+    for (int b = 0; b < MT; ++b) {
+        const int first = min(16 * b, ((M - 1) >> 4) << 4);
+        if (QX) {
+            xbase[b] = reinterpret_cast<const char*>(it.x) + ((int64_t)first * K + (int64_t)t0 * 64) * 2;
+            xoff[b] = (uint32_t)min(frow, M - 1 - first) * (uint32_t)K * 2 + fq * 32;
+        } else {
+            xbase[b] = reinterpret_cast<const char*>(it.xq) + ((int64_t)(first >> 4) * KT + t0) * 1024;
+            xoff[b] = (4 * frow + (fq ^ swz64(frow))) * 16;
+        }
+    }
+    constexpr int kXStep = QX ? 128 : 1024;
+    const QConst qk = make_qconst(*it.s, a_bits);
+
+    struct Frag {
+        u32x4 w[WL];
+        u32x4 x[MT][QX ? 2 : 1];
+    };
+    auto load = [&](Frag& f, int t) {
+#pragma unroll
+        for (int j = 0; j < WL; ++j) {
+            const u32x4* p = reinterpret_cast<const u32x4*>(wbase[j] + (int64_t)t * kWStep + (ROWMAJOR ? wrow[ROWMAJOR ? j : 0] : woff));
+            // Row-major: a K tile is half a 128-byte line of each row, the other half is the next K tile's; it has to stay cached
+            // until then (non-temporal: 54 us for the 7B layer below, cached: 51).
+            f.w[j] = ROWMAJOR ? *p : __builtin_nontemporal_load(p);
+        }
+#pragma unroll
+        for (int b = 0; b < MT; ++b)
+#pragma unroll
+            for (int h = 0; h < (QX ? 2 : 1); ++h)
+                f.x[b][h] = *reinterpret_cast<const u32x4*>(xbase[b] + (int64_t)t * kXStep + xoff[b] + 16 * h);
+    };
+    i32x4 acc[NT][MT];
+#pragma unroll
+    for (int g = 0; g < NT; ++g)
+#pragma unroll
+        for (int b = 0; b < MT; ++b) acc[g][b] = i32x4{0, 0, 0, 0};
+    auto multiply = [&](const Frag& f) {
+        i32x4 xv[MT];
+#pragma unroll
+        for (int b = 0; b < MT; ++b) {
+            if constexpr (QX) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    float c[8];
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        c[2 * w] = quantize(S::lo(f.x[b][h][w]), qk).c;
+                        c[2 * w + 1] = quantize(S::hi(f.x[b][h][w]), qk).c;
+                    }
+                    xv[b][2 * h] = (int)pack_codes4(c[0], c[1], c[2], c[3]);
+                    xv[b][2 * h + 1] = (int)pack_codes4(c[4], c[5], c[6], c[7]);
+                }
+            } else {
+                xv[b] = __builtin_bit_cast(i32x4, f.x[b][0]);
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < NT; ++g) {
+            i32x4 wv;
+            if constexpr (I4) {
+                const uint32_t p0 = f.w[g / 2][2 * (g & 1)], p1 = f.w[g / 2][2 * (g & 1) + 1];   // 16 x the code in every byte
+                wv = i32x4{(int)((p0 << 4) & 0xF0F0F0F0u), (int)(p0 & 0xF0F0F0F0u), (int)((p1 << 4) & 0xF0F0F0F0u), (int)(p1 & 0xF0F0F0F0u)};
+            } else {
+                wv = __builtin_bit_cast(i32x4, f.w[g]);
+            }
+#pragma unroll
+            for (int b = 0; b < MT; ++b) acc[g][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wv, xv[b], acc[g][b], 0, 0, 0);
+        }
+    };
+
+    Frag ring[D];
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+        if (j < count) load(ring[j], j);
+    int i = 0;
+#pragma unroll 1
+    for (; i + 2 * D <= count; i += D) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            multiply(ring[j]);
+            load(ring[j], i + j + D);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+        if (i + j < count) {
+            multiply(ring[j]);
+            if (i + j + D < count) load(ring[j], i + j + D);
+        }
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+        if (i + D + j < count) multiply(ring[j]);
+
+    // The waves' sums meet in LDS; wave w finishes the output tiles w, w + NW, ...
+    constexpr int kTiles = (I4 ? NT / 2 : NT) * MT, kRegs = I4 ? 2 : 1;      // int4: two tiles interleave into 32 columns
+    i32x4* part = reinterpret_cast<i32x4*>(lds);
+#pragma unroll
+    for (int g = 0; g < NT; ++g)
+#pragma unroll
+        for (int b = 0; b < MT; ++b) part[((wave * NT + g) * MT + b) * 64 + lane] = acc[g][b];
+    __syncthreads();
+    const float s = qk.s;
+#pragma unroll
+    for (int t = wave; t < kTiles; t += NW) {
+        const int b = t % MT, g0 = t / MT * kRegs;
+        int v[4 * kRegs];
+#pragma unroll
+        for (int r = 0; r < kRegs; ++r) {
+            i32x4 sum = {0, 0, 0, 0};
+#pragma unroll
+            for (int w = 0; w < NW; ++w) sum += part[((w * NT + g0 + r) * MT + b) * 64 + lane];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[kRegs * e + r] = I4 ? sum[e] >> 4 : sum[e];
+        }
+        const int m = 16 * b + frow, n = n0 + 16 * g0 + 4 * kRegs * fq;      // 4 (8) consecutive columns of one row
+        if (m >= M || n >= N) continue;
+        uint16_t* dst = it.y + (int64_t)m * N + n;
+        float yv[4 * kRegs];
+#pragma unroll
+        for (int e = 0; e < 4 * kRegs; ++e) {
+            const int ne = min(n + e, N - 1);
+            float f = (float)v[e] * (s * it.s_w[ne]);
+            if (it.bias) f = f + it.bias[ne];
+            yv[e] = f;
+        }
+        if ((N & 7) == 0) {                                                  // then every full run is aligned to its own size
+#pragma unroll
+            for (int h = 0; h < kRegs; ++h)
+                *reinterpret_cast<u32x2*>(dst + 4 * h) = u32x2{S::pack(yv[4 * h], yv[4 * h + 1]), S::pack(yv[4 * h + 2], yv[4 * h + 3])};
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4 * kRegs; ++e)
+                if (n + e < N) dst[e] = S::enc(yv[e]);
+        }
+        if (acc_out) {
+#pragma unroll
+            for (int e = 0; e < 4 * kRegs; ++e)
+                if (n + e < N) acc_out[(int64_t)m * N + n + e] = v[e];
+        }
+    }
+}
+
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX>
+__global__ __launch_bounds__(64 * NW)
+void skinny_kernel(const LinBatch b, int a_bits, int32_t* __restrict__ acc_out)
+{
+    __shared__ __attribute__((aligned(1024))) char lds[NW * NT * MT * 1024];
+    const int k = lin_item_of(b, (int)blockIdx.x);
+    skinny_body<DT, WMODE, MT, NT, NW, D, QX>(b.it[k], (int)blockIdx.x - b.first_block[k], a_bits, acc_out, lds);
+}
+
+
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX>
+static void launch_one(LinBatch& b, int a_bits, int32_t* acc_out, hipStream_t st)
+{
+    b.first_block[0] = 0;
+    for (int i = 0; i < kMaxLinearBatch; ++i)
+        b.first_block[i + 1] = b.first_block[i] + (i < b.count ? (b.it[i].N + 16 * NT - 1) / (16 * NT) : 0);
+    skinny_kernel<DT, WMODE, MT, NT, NW, D, QX><<<b.first_block[b.count], 64 * NW, 0, st>>>(b, a_bits, acc_out);
+}
+
+// Wide or narrow workgroups: the narrow form (16 weight rows, K over eight waves) gives four times the waves for the same
+// weights, the wide one reads the activations half or a quarter as often.  Measured at 8 rows, int8, wide | narrow:
+// 4096 x 4096 (256 tiles of 16 rows) 8.3 | 6.5 us, 4096 x 11008 17.3 | 12.8, 11008 x 4096 (688 tiles) 12.3 | 13.4, the 7B
+// layer (2656 tiles) 36 | 51; the line lies at two workgroups of the wide form per CU.
+template <int DT, int WMODE, int MT, bool QX>
+static void launch_mt(LinBatch& b, int64_t tiles16, int a_bits, int32_t* acc_out, hipStream_t st)
+{
+    const bool wide = tiles16 >= 512;
+    if constexpr (WMODE == 3) {                        // int4: half the bytes per tile, a block is two tiles
+        if (!wide)             launch_one<DT, WMODE, MT, 2, 8, 2, QX>(b, a_bits, acc_out, st);
+        else if constexpr (QX) launch_one<DT, WMODE, MT, 4, 8, 2, QX>(b, a_bits, acc_out, st);
+        else                   launch_one<DT, WMODE, MT, 4, 4, 2, QX>(b, a_bits, acc_out, st);
+    } else {
+        if (!wide)               launch_one<DT, WMODE, MT, 1, 8, 4, QX>(b, a_bits, acc_out, st);
+        else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX>(b, a_bits, acc_out, st);
+        else                     launch_one<DT, WMODE, MT, 2, 4, 4, QX>(b, a_bits, acc_out, st);
+    }
+}
+
+template <int DT, int WMODE>
+static void launch_wmode(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, hipStream_t st)
+{
+    int64_t tiles16 = 0;
+    int rows = 0;
+    for (int i = 0; i < b.count; ++i) {
+        tiles16 += (b.it[i].N + 15) / 16;
+        rows = b.it[i].M > rows ? b.it[i].M : rows;
+    }
+    if (qx)              launch_mt<DT, WMODE, 1, true>(b, tiles16, a_bits, acc_out, st);
+    else if (rows <= 32) launch_mt<DT, WMODE, 2, false>(b, tiles16, a_bits, acc_out, st);
+    else if (rows <= 48) launch_mt<DT, WMODE, 3, false>(b, tiles16, a_bits, acc_out, st);
+    else                 launch_mt<DT, WMODE, 4, false>(b, tiles16, a_bits, acc_out, st);
+}
+
+void launch_linear_skinny(LinBatch& b, sasq_dtype dt, int wmode, bool qx, int a_bits, int32_t* acc_out, hipStream_t st)
+{
+    auto by_wmode = [&](auto dt_tag) {
+        constexpr int DT = decltype(dt_tag)::value;
+        if (wmode == 0)      launch_wmode<DT, 0>(b, qx, a_bits, acc_out, st);
+        else if (wmode == 2) launch_wmode<DT, 2>(b, qx, a_bits, acc_out, st);
+        else                 launch_wmode<DT, 3>(b, qx, a_bits, acc_out, st);
+    };
+    if (dt == SASQ_F16) by_wmode(std::integral_constant<int, SASQ_F16>{});
+    else                by_wmode(std::integral_constant<int, SASQ_BF16>{});
+}
+
+}  // namespace sasq

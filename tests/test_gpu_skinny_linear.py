@@ -1,0 +1,80 @@
+"""GPU parity of the few-row linear kernels (M <= 64) against the CPU oracle: accumulators bit for bit, Y equal by value, for
+every weight layout that reaches them, at the edges of their row tiles (16, 32, 48, 64), of the split of K over the waves
+(fewer K tiles than waves, remainders), of the column tiles and of the narrow / wide choice; mixed batches; in-place calls."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2512_14481_amd import binding as B
+from paper_2512_14481_amd import workloads as wl
+from tests.gpu_util import TDT, assert_same_values, dev_scalar, set_tuning, to_bits, to_dev
+from tests.test_gpu_grouped_linear import WF, device_weights
+
+pytestmark = pytest.mark.gpu
+
+LAYOUTS = [("int8", False), ("int8", True), ("int4", True)]
+SHAPES = [(1, 1, 64), (3, 47, 576), (15, 130, 128), (16, 512, 1088), (17, 33, 64), (32, 96, 704), (33, 72, 2112), (48, 250, 640),
+          (49, 31, 192), (64, 264, 1024), (65, 64, 128), (16, 8200, 192), (2, 8185, 320), (30, 8192, 128), (64, 8189, 192)]
+
+
+def problem(seed, shape, fmt, dtype):
+    M, N, K = shape
+    xb = wl.random_bits(seed, f"sx{shape}{dtype}", (M, K), dtype, gain=2.0)
+    wq, s_w = oracle.quantize_weight(wl.random_f32(seed, f"sw{shape}", (N, K), 0.02), fmt)
+    return xb, wq, s_w, wl.random_f32(seed, f"sb{shape}", (N,), 0.3), np.float32(oracle.absmax_scale(xb, 8, dtype) * 0.4)
+
+
+@pytest.mark.parametrize("fmt,blocked", LAYOUTS)
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_few_rows_match_oracle(shape, dtype, fmt, blocked):
+    set_tuning()
+    M, N, K = shape
+    xb, wq, s_w, bias, s = problem(61, shape, fmt, dtype)
+    wf, wd, swd = WF[(fmt, blocked)], device_weights(wq, fmt, blocked), torch.from_numpy(s_w).cuda()
+    x = to_dev(xb, dtype)
+    ws = B.new_workspace(B.sasq_static_linear_workspace(M, N, K, wf))
+    for b in (None, bias):
+        ref = oracle.static_linear(xb, s, wq, s_w, b, 8, fmt, dtype)
+        y = torch.full((M, N), float("nan"), dtype=TDT[dtype], device="cuda")
+        acc = torch.zeros((M, N), dtype=torch.int32, device="cuda")
+        bd = None if b is None else torch.from_numpy(b).cuda()
+        B.sasq_static_linear(x, dev_scalar(s), wd, swd, bd, y, wf, ws, acc, None)
+        assert np.array_equal(acc.cpu().numpy(), ref["acc"])
+        assert_same_values(to_bits(y), ref["y"], dtype, "Y")
+        y2 = torch.full_like(y, float("nan"))
+        B.sasq_static_linear(x, dev_scalar(s), wd, swd, bd, y2, wf, ws)
+        assert np.array_equal(to_bits(y2), to_bits(y))
+
+
+@pytest.mark.parametrize("rows", [(5, 16, 1), (9, 64, 20)])
+@pytest.mark.parametrize("fmt,blocked", LAYOUTS)
+def test_batch_of_few_rows_matches_oracle(rows, fmt, blocked):
+    set_tuning()
+    dims = [(96, 640), (300, 64), (41, 1984)]
+    items, refs = [], []
+    for i, (m, (n, k)) in enumerate(zip(rows, dims)):
+        xb, wq, s_w, bias, s = problem(70 + i, (m, n, k), fmt, "bf16")
+        b = bias if i == 1 else None
+        refs.append(oracle.static_linear(xb, s, wq, s_w, b, 8, fmt, "bf16")["y"])
+        items.append((to_dev(xb, "bf16"), dev_scalar(s), device_weights(wq, fmt, blocked), torch.from_numpy(s_w).cuda(),
+                      None if b is None else torch.from_numpy(b).cuda(), torch.empty((m, n), dtype=torch.bfloat16, device="cuda")))
+    wf = WF[(fmt, blocked)]
+    B.sasq_static_linear_batch(items, wf, B.new_workspace(B.sasq_static_linear_batch_workspace(items, wf)))
+    for it, ref in zip(items, refs):
+        assert_same_values(to_bits(it[5]), ref, "bf16", "Y")
+
+
+def test_output_over_input_at_few_rows():
+    """An output that is the input's own buffer: the activations are quantized before the first output is written."""
+    set_tuning()
+    shape = (8, 2048, 2048)
+    xb, wq, s_w, _, s = problem(80, shape, "int8", "f16")
+    ref = oracle.static_linear(xb, s, wq, s_w, None, 8, "int8", "f16")
+    wd, x = device_weights(wq, "int8", True), to_dev(xb, "f16")
+    ws = B.new_workspace(B.sasq_static_linear_workspace(*shape, B.SASQ_W_INT8_BLOCKED))
+    B.sasq_static_linear(x, dev_scalar(s), wd, torch.from_numpy(s_w).cuda(), None, x, B.SASQ_W_INT8_BLOCKED, ws)
+    assert_same_values(to_bits(x), ref["y"], "f16", "Y")
