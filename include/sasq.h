@@ -256,8 +256,8 @@ size_t sasq_static_linear_workspace(int64_t M, int64_t N, int64_t K, sasq_wfmt w
  *   y        [M, N] device 16-bit `dt`, written
  *   acc_out  [M, N] device int32 or NULL; xq_out [M, K] device int8 or NULL (inspection/tests;
  *            requesting either selects a slower code path)
- *   K        multiple of 2 for int4.  Any M, N, K > 0 is accepted; the MFMA path is taken when
- *            K is a multiple of 64, other shapes use a scalar kernel.
+ *   K        multiple of 2 for int4.  Any M, N, K > 0 is accepted; K not a multiple of 64 takes
+ *            a matrix-unit kernel that reads rows at any alignment.
  *   M*K, N*K, M*N must each be < 2^40; |acc| cannot overflow for K <= 131071.
  *   workspace  >= sasq_static_linear_workspace(M, N, K, wf) bytes (NULL allowed when that is 0);
  *              holds the int8 activation codes in a library-internal blocked order between the

@@ -26,6 +26,9 @@ void launch_gemm_k64_grouped(const GemmK64Args& a, sasq_dtype dt, int wmode, int
 // Group sizes without a matrix-unit form (grouped_valu.hip): row-major weights, row-major activation codes in a.xq, any
 // group that divides K.
 void launch_grouped_valu(const GemmK64Args& a, sasq_dtype dt, bool int4, int64_t group, hipStream_t st);
+// K not a multiple of 64 (static_linear_anyk.hip): row-major activation codes in a.xq, row-major int8 or packed int4 weights.
+// rows: one activation factor per row.
+void launch_linear_anyk(const GemmK64Args& a, sasq_dtype dt, bool int4, bool rows, hipStream_t st);
 // At most kSkinnyRows rows (static_linear_skinny.hip): the items of `b` (first_block is filled in here), weight layouts 0, 2
 // and 3.  qx: quantize the activations in the kernel (at most kSkinnyQuantRows rows, and no output may overlap an input, as
 // workgroups read x while others write y); otherwise the items' xq hold the staged codes.

@@ -110,6 +110,69 @@ __device__ __forceinline__ uint32_t pack_codes4(float c0, float c1, float c2, fl
     return a | b;
 }
 
+// ---- rows of codes at any alignment ----------------------------------------------------------
+// A piece of 16 bytes (int8 codes) or 8 (packed int4) at any address: one unaligned load, which the memory pipeline splits
+// where it has to.
+template <typename V>
+__device__ __forceinline__ V load_piece(const uint8_t* __restrict__ p)
+{
+    V v;
+    __builtin_memcpy(&v, p, sizeof(V));
+    return v;
+}
+// The piece at byte `at` of a row of `len` bytes, zeros past the row's end; nothing outside the row is read.
+template <typename V>
+__device__ __forceinline__ V load_piece_edge(const uint8_t* __restrict__ row, int64_t at, int64_t len)
+{
+    constexpr int PIECE = (int)sizeof(V);
+    if (len >= PIECE) {
+        const int64_t from = min(at, len - PIECE);                              // load inside the row, drop what lies before `at`
+        const int drop = (int)min(at - from, (int64_t)PIECE);
+        const V raw = load_piece<V>(row + from);
+        uint64_t lo, hi = 0;
+        lo = (uint64_t)raw[0] | ((uint64_t)raw[1] << 32);
+        if constexpr (PIECE == 16) {
+            hi = (uint64_t)raw[2] | ((uint64_t)raw[3] << 32);
+            if (drop >= 8) { lo = hi; hi = 0; }
+        } else if (drop >= 8) {
+            lo = 0;
+        }
+        const int sh = (drop & 7) * 8;
+        if (sh) { lo = (lo >> sh) | (hi << (64 - sh)); hi >>= sh; }
+        V v;
+        v[0] = (uint32_t)lo; v[1] = (uint32_t)(lo >> 32);
+        if constexpr (PIECE == 16) {
+            if (drop == 16) { v[0] = 0u; v[1] = 0u; }
+            v[2] = (uint32_t)hi; v[3] = (uint32_t)(hi >> 32);
+        }
+        return v;
+    }
+    V v;
+#pragma unroll
+    for (int d = 0; d < PIECE / 4; ++d) v[d] = 0u;
+#pragma unroll 1
+    for (int b = 0; b < PIECE; ++b)
+        if (at + b < len) {
+            const uint32_t t = (uint32_t)row[at + b] << (8 * (b & 3));
+#pragma unroll
+            for (int d = 0; d < PIECE / 4; ++d) v[d] |= (b >> 2) == d ? t : 0u;
+        }
+    return v;
+}
+
+// 16 packed int4 codes -> 16 bytes, natural order, sign-extended
+__device__ __forceinline__ u32x4 widen_int4(const u32x2& q)
+{
+    u32x4 v;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const uint32_t h = q[d >> 1] >> (16 * (d & 1));
+        const uint32_t n4 = (h & 0xFu) | ((h & 0xF0u) << 4) | ((h & 0xF00u) << 8) | ((h & 0xF000u) << 12);
+        v[d] = n4 | ((n4 & 0x08080808u) * 0x1Eu);
+    }
+    return v;
+}
+
 // ---- reductions -----------------------------------------------------------------------------
 __device__ __forceinline__ double wave_sum(double v)
 {

@@ -279,38 +279,6 @@ __device__ __forceinline__ float dequant(int acc, float c, float bias, bool has_
 }
 
 // ---------------------------------------------------------------------------------------------
-// Scalar kernel for shapes the MFMA kernel does not take (K not a multiple of 64): one thread
-// per output element over pre-quantized activations.
-// ---------------------------------------------------------------------------------------------
-template <int DT, bool INT4, bool ROWS = false>
-__global__ __launch_bounds__(256) void linear_scalar_kernel(
-    const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq, const float* __restrict__ s_ptr,
-    const float* __restrict__ s_w, const float* __restrict__ bias, uint16_t* __restrict__ y,
-    int32_t* __restrict__ acc_out, int64_t M, int64_t N, int64_t K)
-{
-    using S = Store16<DT>;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= M * N) return;
-    const int64_t m = idx / N, n = idx % N;
-    const int8_t* xr = xq + m * K;
-    int acc = 0;
-    if (INT4) {
-        const uint8_t* wr = wq + n * (K / 2);
-        for (int64_t j = 0; j < K / 2; ++j) {
-            int b = wr[j];
-            int lo = ((b & 15) ^ 8) - 8, hi = ((b >> 4) ^ 8) - 8;
-            acc += (int)xr[2 * j] * lo + (int)xr[2 * j + 1] * hi;
-        }
-    } else {
-        const int8_t* wr = reinterpret_cast<const int8_t*>(wq) + n * K;
-        for (int64_t k = 0; k < K; ++k) acc += (int)xr[k] * (int)wr[k];
-    }
-    const float c = s_ptr[ROWS ? m : 0] * s_w[n];      // ROWS: one factor per row (dynamic per-token)
-    y[idx] = S::enc(dequant(acc, c, bias ? bias[n] : 0.0f, bias != nullptr));
-    if (acc_out) acc_out[idx] = acc;
-}
-
-// ---------------------------------------------------------------------------------------------
 // int8 MFMA GEMM over pre-quantized activations.
 //
 // Workgroup tile 256 (m) x 256 (n), 4 waves in a 2x2 arrangement, each wave owns a 128x128 block
@@ -1031,11 +999,8 @@ static void run_linear(const void* x, const float* s, const void* wq, const floa
         }
     } else {
         quantize_act_kernel<DT, false, false><<<qgrid, 256, 0, st>>>(X, s, reinterpret_cast<u32x2*>(xq_ws), nvec, n, (int)K, a_bits);
-        const int64_t blocks = (M * N + 255) / 256;
-        auto W = static_cast<const uint8_t*>(wq);
-        auto Y = static_cast<uint16_t*>(y);
-        if (int4) linear_scalar_kernel<DT, true><<<(int)blocks, 256, 0, st>>>(xq_ws, W, s, s_w, bias, Y, acc_out, M, N, K);
-        else      linear_scalar_kernel<DT, false><<<(int)blocks, 256, 0, st>>>(xq_ws, W, s, s_w, bias, Y, acc_out, M, N, K);
+        GemmK64Args a{xq_ws, static_cast<const uint8_t*>(wq), s, s_w, bias, static_cast<uint16_t*>(y), acc_out, M, N, K};
+        launch_linear_anyk(a, (sasq_dtype)DT, int4, false, st);
     }
 }
 
@@ -1134,11 +1099,8 @@ static void run_dynamic(const void* x, const void* wq, const float* s_w, const f
         }
     } else {
         quantize_rowmajor(xq_ws);
-        const int64_t blocks = (M * N + 255) / 256;
-        auto W = static_cast<const uint8_t*>(wq);
-        auto Y = static_cast<uint16_t*>(y);
-        if (wf == SASQ_W_INT4_PACKED) linear_scalar_kernel<DT, true, true><<<(int)blocks, 256, 0, st>>>(xq_ws, W, s_row, s_w, bias, Y, acc_out, M, N, K);
-        else                          linear_scalar_kernel<DT, false, true><<<(int)blocks, 256, 0, st>>>(xq_ws, W, s_row, s_w, bias, Y, acc_out, M, N, K);
+        GemmK64Args a{xq_ws, static_cast<const uint8_t*>(wq), s_row, s_w, bias, static_cast<uint16_t*>(y), acc_out, M, N, K};
+        launch_linear_anyk(a, (sasq_dtype)DT, wf == SASQ_W_INT4_PACKED, true, st);
     }
 }
 

@@ -1,0 +1,213 @@
+// int8 linear for contraction lengths that are not whole 64-channel tiles (a projection sharded over GPUs: 11008 / 8 =
+// 1376), row-major weights with any row alignment, over row-major activation codes.
+//
+// What bounds it: at 1000 x 4096 x 1376 the 17 MB of operands and output take 3 us and the 11.3 G operations as much; the
+// rest is the latency of a short K loop.  One thread per output walking its row and column byte by byte took 10.65 ms
+// there, this kernel with its pre-pass 19.4 us (0.58 POP/s).
+// The pre-arranged formats and the direct memory -> LDS loads of the other GEMMs need rows of whole 16-byte pieces.  Here a
+// row starts at any byte, so 16 codes travel through registers: an unaligned 128-bit load (the memory pipeline splits it
+// where it has to), requested D stages ahead, then an aligned LDS write.  A stage is 128 channels, so that a row's piece is
+// a whole cache line.  The last stage of a row loads its last 16 codes and shifts them into place, zeros behind: nothing
+// outside a row is read.  Integer sums, so the order is free.
+#include "sasq_device.h"
+#include "gemm_tile.h"
+#include "gemm_k64.h"
+#include <type_traits>
+
+namespace sasq {
+
+constexpr int kAnyStage = 128;                     // channels per LDS stage
+
+// Four waves, 2 x 2, each (BM/2) x (BN/2) of the tile as 16x16 tiles of v_mfma_i32_16x16x64_i8; two LDS buffers, D stages
+// in flight in registers.  LDS rows are 128 bytes, 16-byte chunk c of row r at position c ^ (r & 7).
+template <int DT, bool INT4, bool ROWS, int BM, int BN, int D>
+__global__ __launch_bounds__(256, 2) void linear_anyk_kernel(
+    const uint8_t* __restrict__ xq, const uint8_t* __restrict__ wq, const float* __restrict__ s_ptr,
+    const float* __restrict__ s_w, const float* __restrict__ bias, uint16_t* __restrict__ y,
+    int32_t* __restrict__ acc_out, int M, int N, int K, int tiles_m, int tiles_n)
+{
+    using S = Store16<DT>;
+    using WPiece = std::conditional_t<INT4, u32x2, u32x4>;
+    constexpr int MF = BM / 32, NF = BN / 32, XL = BM / 32, WL = BN / 32;
+    constexpr int kXBytes = BM * kAnyStage, kBufBytes = (BM + BN) * kAnyStage;
+    static_assert(D % 2 == 0, "the unrolled loop knows its LDS buffer at compile time");
+    __shared__ __attribute__((aligned(128))) char lds[2 * kBufBytes];
+
+    int tm, tn;
+    if (!tile_of_block((int)blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int stages = (K + kAnyStage - 1) / kAnyStage;
+    const int wlen = INT4 ? K / 2 : K;                             // bytes of a weight row
+
+    // thread t moves chunk t%8 of rows t/8 + 32 j; rows past the edge repeat the last one
+    const int lrow = tid >> 3, lch = tid & 7;
+    const uint8_t* xb = xq + (int64_t)m0 * K;
+    const uint8_t* wb = wq + (int64_t)n0 * wlen;
+    uint32_t xo[XL], wo[WL];                                       // at most 128 rows of 131071 bytes
+#pragma unroll
+    for (int j = 0; j < XL; ++j) xo[j] = (uint32_t)min(lrow + 32 * j, M - 1 - m0) * (uint32_t)K;
+#pragma unroll
+    for (int j = 0; j < WL; ++j) wo[j] = (uint32_t)min(lrow + 32 * j, N - 1 - n0) * (uint32_t)wlen;
+    struct Regs { u32x4 x[XL]; WPiece w[WL]; };
+    Regs ring[D];
+    constexpr int kWPiece = (int)sizeof(WPiece);
+    auto fetch = [&](Regs& r, int st) {
+        if ((st + 1) * kAnyStage <= K) {
+#pragma unroll
+            for (int j = 0; j < XL; ++j) r.x[j] = load_piece<u32x4>(xb + st * kAnyStage + (xo[j] + lch * 16));
+#pragma unroll
+            for (int j = 0; j < WL; ++j) r.w[j] = load_piece<WPiece>(wb + st * 8 * kWPiece + (wo[j] + lch * kWPiece));
+        } else {
+#pragma unroll
+            for (int j = 0; j < XL; ++j) r.x[j] = load_piece_edge<u32x4>(xb + xo[j], st * kAnyStage + lch * 16, K);
+#pragma unroll
+            for (int j = 0; j < WL; ++j) r.w[j] = load_piece_edge<WPiece>(wb + wo[j], (st * 8 + lch) * kWPiece, wlen);
+        }
+    };
+    const int slot = lrow * kAnyStage + ((lch ^ (lrow & 7)) << 4);
+    auto put = [&](const Regs& r, int buf) {
+        char* base = &lds[buf * kBufBytes];
+#pragma unroll
+        for (int j = 0; j < XL; ++j) *reinterpret_cast<u32x4*>(base + slot + j * 32 * kAnyStage) = r.x[j];
+#pragma unroll
+        for (int j = 0; j < WL; ++j) {
+            u32x4 v;
+            if constexpr (INT4) v = widen_int4(r.w[j]);
+            else                v = r.w[j];
+            *reinterpret_cast<u32x4*>(base + kXBytes + slot + j * 32 * kAnyStage) = v;
+        }
+    };
+    // this wave's LDS traffic is done, then everyone's
+    auto sync = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+
+    const int frow = lane & 15, fq = lane >> 4;
+    const int xbase = (wave & 1) * (BM / 2) * kAnyStage, wbase = kXBytes + (wave >> 1) * (BN / 2) * kAnyStage;
+    i32x4 acc[NF][MF];
+#pragma unroll
+    for (int g = 0; g < NF; ++g)
+#pragma unroll
+        for (int b = 0; b < MF; ++b) acc[g][b] = i32x4{0, 0, 0, 0};
+    auto multiply = [&](int buf) {
+        const char* base = &lds[buf * kBufBytes];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int off = frow * kAnyStage + (((4 * h + fq) ^ (frow & 7)) << 4);
+            i32x4 fx[MF], fw[NF];
+#pragma unroll
+            for (int b = 0; b < MF; ++b) fx[b] = *reinterpret_cast<const i32x4*>(base + xbase + b * 16 * kAnyStage + off);
+#pragma unroll
+            for (int g = 0; g < NF; ++g) fw[g] = *reinterpret_cast<const i32x4*>(base + wbase + g * 16 * kAnyStage + off);
+#pragma unroll
+            for (int g = 0; g < NF; ++g)
+#pragma unroll
+                for (int b = 0; b < MF; ++b) acc[g][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fw[g], fx[b], acc[g][b], 0, 0, 0);
+        }
+    };
+
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+        if (j < stages) fetch(ring[j], j);
+    put(ring[0], 0);
+    if (D < stages) fetch(ring[0], D);
+    sync();
+    // Stage i is in LDS buffer i & 1.  Its products are issued, stage i + 1 goes into the other buffer (whose readers passed
+    // the last barrier), and its registers take stage i + 1 + D.
+    for (int i = 0; i < stages; i += D) {
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            if (i + j < stages) {
+                multiply(j & 1);
+                if (i + j + 1 < stages) {
+                    put(ring[(j + 1) % D], (j + 1) & 1);
+                    if (i + j + 1 + D < stages) fetch(ring[(j + 1) % D], i + j + 1 + D);
+                    sync();
+                }
+            }
+        }
+    }
+
+    // D[i][j]: i <-> n, j <-> m; a lane holds four consecutive columns of one row per 16x16 tile
+    const int wn0 = n0 + (wave >> 1) * (BN / 2), wm0 = m0 + (wave & 1) * (BM / 2);
+    const bool vec = (N & 3) == 0;
+    float srow[MF];
+#pragma unroll
+    for (int b = 0; b < MF; ++b) srow[b] = s_ptr[ROWS ? min(wm0 + b * 16 + frow, M - 1) : 0];
+#pragma unroll
+    for (int g = 0; g < NF; ++g) {
+        const int n = wn0 + g * 16 + 4 * fq;
+        float sw[4], bv[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int ne = min(n + e, N - 1);
+            sw[e] = s_w[ne];
+            bv[e] = bias ? bias[ne] : 0.0f;
+        }
+#pragma unroll
+        for (int b = 0; b < MF; ++b) {
+            const int m = wm0 + b * 16 + frow;
+            if (m >= M || n >= N) continue;
+            float yv[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                yv[e] = (float)acc[g][b][e] * (srow[b] * sw[e]);
+                if (bias) yv[e] = yv[e] + bv[e];
+            }
+            const int64_t o = (int64_t)m * N + n;
+            if (vec) {
+                *reinterpret_cast<u32x2*>(y + o) = u32x2{S::pack(yv[0], yv[1]), S::pack(yv[2], yv[3])};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < N) y[o + e] = S::enc(yv[e]);
+            }
+            if (acc_out) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < N) acc_out[o + e] = acc[g][b][e];
+            }
+        }
+    }
+}
+
+template <int DT, bool INT4, bool ROWS, int BM, int BN, int D>
+static void launch_anyk_one(const GemmK64Args& a, hipStream_t st)
+{
+    const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (int)((a.N + BN - 1) / BN);
+    const int grid = (tiles_m * tiles_n + 7) / 8 * 8;
+    linear_anyk_kernel<DT, INT4, ROWS, BM, BN, D><<<grid, 256, 0, st>>>(
+        reinterpret_cast<const uint8_t*>(a.xq), a.wq, a.s, a.s_w, a.bias, a.y, a.acc_out, (int)a.M, (int)a.N, (int)a.K, tiles_m, tiles_n);
+}
+
+// Big tiles read the operands less often, small ones put more CUs to work.  Measured, int8, us on 128x128 / 64x128 / 64x64 /
+// 32x64 tiles: 4096 x 4096 x 1376 (1024 tiles of 128x128) 48.0 / 52.5 / 65.3, 2000 x 4096 x 1376 (512) 28.2 / 33.1 / 36.5,
+// 1500 x 4096 x 4000 (384) 49.7 / 49.3 / 60.9, 1000 x 4096 x 1376 (256; 512 of 64x128) 20.0 / 19.4 / 23.2 / 26.4;
+// 512 x 1024 x 3000 (64 of 64x128, 256 of 32x64) 28.2 / 21.5 / 16.3 / 14.9, 64 x 4096 x 3976 (128 of 32x64) 31.3 / 24.8 /
+// 19.4 / 16.7.
+template <int DT, bool INT4, bool ROWS>
+static void launch_anyk_w(const GemmK64Args& a, hipStream_t st)
+{
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
+    if (tiles(128, 128) >= 512)     launch_anyk_one<DT, INT4, ROWS, 128, 128, 2>(a, st);
+    else if (tiles(64, 128) >= 256) launch_anyk_one<DT, INT4, ROWS, 64, 128, 2>(a, st);
+    else if (tiles(64, 64) >= 256)  launch_anyk_one<DT, INT4, ROWS, 64, 64, 4>(a, st);
+    else                            launch_anyk_one<DT, INT4, ROWS, 32, 64, 4>(a, st);
+}
+
+void launch_linear_anyk(const GemmK64Args& a, sasq_dtype dt, bool int4, bool rows, hipStream_t st)
+{
+    auto by_dt = [&](auto dt_tag) {
+        constexpr int DT = decltype(dt_tag)::value;
+        if (int4) { if (rows) launch_anyk_w<DT, true, true>(a, st);  else launch_anyk_w<DT, true, false>(a, st); }
+        else      { if (rows) launch_anyk_w<DT, false, true>(a, st); else launch_anyk_w<DT, false, false>(a, st); }
+    };
+    if (dt == SASQ_F16) by_dt(std::integral_constant<int, SASQ_F16>{});
+    else                by_dt(std::integral_constant<int, SASQ_BF16>{});
+}
+
+}  // namespace sasq
