@@ -1,11 +1,14 @@
 // Set-up operations: workspace initialisation, frozen-weight quantization and re-arrangement,
 // absmax initial scale.
 #include "sasq_device.h"
+#include <type_traits>
 
 namespace sasq {
 
 constexpr int kPrepThreads = 256;
-constexpr int kMaxAbsmaxBlocks = 2048;
+constexpr int kMaxAbsmaxBlocks = 2048;       // partials the workspace has room for
+constexpr int kAbsmaxBlocks = 256;           // one per CU: every block ends with a ticket on one address
+constexpr int kAbsmaxThreads = 512, kAbsmaxUnroll = 4;   // 128-bit loads in flight per thread
 
 __global__ void fill_zero_kernel(uint32_t* p, int64_t nwords)
 {
@@ -13,6 +16,7 @@ __global__ void fill_zero_kernel(uint32_t* p, int64_t nwords)
     if (i < nwords) p[i] = 0u;
 }
 
+template <int THREADS>
 __device__ __forceinline__ float block_max(float v, float* sh)
 {
     uint32_t w = wave_max(__float_as_uint(v));      // non-negative floats order like their bits
@@ -20,12 +24,17 @@ __device__ __forceinline__ float block_max(float v, float* sh)
     __syncthreads();
     float m = sh[0];
 #pragma unroll
-    for (int i = 1; i < kPrepThreads / kWave; ++i) m = fmaxf(m, sh[i]);
-    __syncthreads();
+    for (int i = 1; i < THREADS / kWave; ++i) m = fmaxf(m, sh[i]);
     return m;
 }
 
-// One block per output channel n (row of W[N,K]): Sec. 3, Eq. 1 applied to the row.
+__device__ __forceinline__ float weight_factor(float amax, int bits)
+{
+    return amax == 0.0f ? 1.0f : amax / (float)((1 << (bits - 1)) - 1);
+}
+
+// One block per output channel n (row of W[N,K]): Sec. 3, Eq. 1 applied to the row.  The general form: any K, the row is
+// read twice.
 template <bool INT4>
 __global__ __launch_bounds__(kPrepThreads) void quantize_weight_kernel(
     const float* __restrict__ w, uint8_t* __restrict__ wq, float* __restrict__ s_w, int64_t K)
@@ -35,10 +44,9 @@ __global__ __launch_bounds__(kPrepThreads) void quantize_weight_kernel(
     const float* row = w + n * K;
     float amax = 0.0f;
     for (int64_t k = threadIdx.x; k < K; k += kPrepThreads) amax = fmaxf(amax, fabsf(row[k]));
-    amax = block_max(amax, sh);
+    amax = block_max<kPrepThreads>(amax, sh);
     const int bits = INT4 ? 4 : 8;
-    const float Qp = (float)((1 << (bits - 1)) - 1);
-    const float sw = amax == 0.0f ? 1.0f : amax / Qp;
+    const float sw = weight_factor(amax, bits);
     if (threadIdx.x == 0) s_w[n] = sw;
     const QConst kc = make_qconst(sw, bits);
     if (INT4) {
@@ -52,6 +60,43 @@ __global__ __launch_bounds__(kPrepThreads) void quantize_weight_kernel(
         uint8_t* out = wq + n * K;
         for (int64_t k = threadIdx.x; k < K; k += kPrepThreads)
             out[k] = (uint8_t)(code_of(quantize(row[k], kc)) & 0xFF);
+    }
+}
+
+// The same for rows of whole 128-bit pieces (K % 4 == 0) that fit a block's registers, R pieces per thread: the row is read
+// once, all of it in flight, and the codes leave four at a time.  Bound by the 5 bytes a weight
+// moves: 11008 x 4096 and 4096 x 11008 37 us each, 6.1 TB/s (the general kernel, one float per load and one byte per store: 96).
+template <bool INT4, int THREADS, int R>
+__global__ __launch_bounds__(THREADS) void quantize_weight_vec_kernel(
+    const f32x4* __restrict__ w, uint8_t* __restrict__ wq, float* __restrict__ s_w, int pieces)
+{
+    __shared__ float sh[THREADS / kWave];
+    const int64_t n = blockIdx.x;
+    const f32x4* row = w + n * pieces;
+    f32x4 v[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j)                       // past the end: the last piece again, which cannot change a maximum
+        v[j] = __builtin_nontemporal_load(&row[min(j * THREADS + (int)threadIdx.x, pieces - 1)]);
+    float amax = 0.0f;
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) amax = fmaxf(amax, fabsf(v[j][e]));
+    amax = block_max<THREADS>(amax, sh);
+    const int bits = INT4 ? 4 : 8;
+    const float sw = weight_factor(amax, bits);
+    if (threadIdx.x == 0) s_w[n] = sw;
+    const QConst kc = make_qconst(sw, bits);
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+        const int i = j * THREADS + (int)threadIdx.x;
+        if (i >= pieces) break;
+        const uint32_t c = pack_codes4(quantize(v[j][0], kc).c, quantize(v[j][1], kc).c, quantize(v[j][2], kc).c, quantize(v[j][3], kc).c);
+        if (INT4)
+            reinterpret_cast<uint16_t*>(wq)[n * pieces + i] =
+                (uint16_t)((c & 0xFu) | ((c >> 4) & 0xF0u) | ((c >> 8) & 0xF00u) | ((c >> 12) & 0xF000u));
+        else
+            reinterpret_cast<uint32_t*>(wq)[n * pieces + i] = c;
     }
 }
 
@@ -102,9 +147,13 @@ __global__ __launch_bounds__(kPrepThreads) void pack_weight_i4_kernel(
 }
 
 // max |x| over a flat 16-bit tensor: magnitudes of finite values and infinities order like their
-// 15 low bits, so the reduction is an integer max (exact and order-independent).
+// 15 low bits, so the reduction is an integer max (exact and order-independent).  Bound by memory latency and the ticket tail:
+// each block keeps the next kAbsmaxUnroll loads per thread in flight under the current ones, and there is one block per CU, as
+// every block adds its ticket to one address.  45 MB 13 us, 17 MB 9 (one load at a time from 2048 blocks: 34 and 18; 256
+// threads with eight loads but no loads ahead: 19 and 6; the set-up of a 7B MLP as a whole: 270 us with 512 blocks of those,
+// 262 with 256, 260 with this).
 template <int DT>
-__global__ __launch_bounds__(kPrepThreads) void absmax_kernel(
+__global__ __launch_bounds__(kAbsmaxThreads) void absmax_kernel(
     const uint16_t* __restrict__ x, float* __restrict__ s, uint32_t* __restrict__ ws_head,
     uint32_t* __restrict__ partials, int64_t n, int bits)
 {
@@ -112,27 +161,41 @@ __global__ __launch_bounds__(kPrepThreads) void absmax_kernel(
     uint32_t m = 0;
     const int64_t nvec = n / 8;
     const u32x4* xv = reinterpret_cast<const u32x4*>(x);
-    for (int64_t i = (int64_t)blockIdx.x * kPrepThreads + threadIdx.x; i < nvec;
-         i += (int64_t)gridDim.x * kPrepThreads) {
-        u32x4 v = xv[i];
+    if (nvec > 0) {
+        const int64_t step = (int64_t)gridDim.x * kAbsmaxThreads * kAbsmaxUnroll;
+        int64_t base = (int64_t)blockIdx.x * kAbsmaxThreads * kAbsmaxUnroll + threadIdx.x;
+        u32x4 cur[kAbsmaxUnroll], next[kAbsmaxUnroll];
+        auto load = [&](u32x4 (&v)[kAbsmaxUnroll], int64_t from) {
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            uint32_t lo = v[w] & 0x7FFFu, hi = (v[w] >> 16) & 0x7FFFu;
-            m = lo > m ? lo : m;
-            m = hi > m ? hi : m;
+            for (int u = 0; u < kAbsmaxUnroll; ++u)      // past the end: the last vector again, which cannot change a maximum
+                v[u] = __builtin_nontemporal_load(&xv[min(from + u * kAbsmaxThreads, nvec - 1)]);
+        };
+        load(cur, base);
+        for (; base - (int64_t)threadIdx.x < nvec; base += step) {
+            load(next, base + step);
+#pragma unroll
+            for (int u = 0; u < kAbsmaxUnroll; ++u) {
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    uint32_t lo = cur[u][w] & 0x7FFFu, hi = (cur[u][w] >> 16) & 0x7FFFu;
+                    m = lo > m ? lo : m;
+                    m = hi > m ? hi : m;
+                }
+                cur[u] = next[u];
+            }
         }
     }
     if (blockIdx.x == 0 && threadIdx.x < (unsigned)(n - nvec * 8)) {
         uint32_t a = x[nvec * 8 + threadIdx.x] & 0x7FFFu;
         m = a > m ? a : m;
     }
-    __shared__ uint32_t sh[kPrepThreads / kWave];
+    __shared__ uint32_t sh[kAbsmaxThreads / kWave];
     __shared__ bool is_last;
     m = wave_max(m);
     if (threadIdx.x % kWave == 0) sh[threadIdx.x / kWave] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 1; i < kPrepThreads / kWave; ++i) m = sh[i] > m ? sh[i] : m;
+        for (int i = 1; i < kAbsmaxThreads / kWave; ++i) m = sh[i] > m ? sh[i] : m;
         const uint32_t ticket = publish_then_ticket(&partials[blockIdx.x], m, &ws_head[0]);
         is_last = (ticket == kTicketBase + gridDim.x - 1);
         if (ticket - kTicketBase >= gridDim.x) *s = __uint_as_float(0x7FC00000u);
@@ -140,26 +203,49 @@ __global__ __launch_bounds__(kPrepThreads) void absmax_kernel(
     __syncthreads();
     if (!is_last) return;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    constexpr int kPer = kMaxAbsmaxBlocks / kPrepThreads;
-    uint32_t pv[kPer];
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        const int i = j * kPrepThreads + threadIdx.x;
-        pv[j] = __hip_atomic_load(&partials[i < (int)gridDim.x ? i : 0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    uint32_t t = 0;
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) t = pv[j] > t ? pv[j] : t;     // a duplicate of partial 0 cannot change a max
-    t = wave_max(t);
+    static_assert(kAbsmaxBlocks <= kAbsmaxThreads, "one partial per thread");
+    uint32_t t = __hip_atomic_load(&partials[threadIdx.x < gridDim.x ? threadIdx.x : 0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    t = wave_max(t);                                              // a duplicate of partial 0 cannot change a max
     __syncthreads();
     if (threadIdx.x % kWave == 0) sh[threadIdx.x / kWave] = t;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 0; i < kPrepThreads / kWave; ++i) t = sh[i] > t ? sh[i] : t;
+        for (int i = 0; i < kAbsmaxThreads / kWave; ++i) t = sh[i] > t ? sh[i] : t;
         float amax = S::one((uint16_t)t);
         *s = amax / (float)((1 << (bits - 1)) - 1);
         __hip_atomic_store(&ws_head[0], kTicketBase, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+}
+
+// Rows of up to 8192 weights: 256 threads, up to 32768: 1024 (eight pieces per thread at most); longer or ragged ones take the
+// general kernel.
+template <bool INT4>
+static void quantize_weight(const float* w, uint8_t* wq, float* s_w, int64_t N, int64_t K, hipStream_t st)
+{
+    if ((K & 3) || K > 32768) {
+        quantize_weight_kernel<INT4><<<(int)N, kPrepThreads, 0, st>>>(w, wq, s_w, K);
+        return;
+    }
+    const int pieces = (int)(K >> 2);
+    auto launch = [&](auto threads_tag, auto r_tag) {
+        constexpr int T = decltype(threads_tag)::value, R = decltype(r_tag)::value;
+        quantize_weight_vec_kernel<INT4, T, R><<<(int)N, T, 0, st>>>(reinterpret_cast<const f32x4*>(w), wq, s_w, pieces);
+    };
+    auto by_pieces = [&](auto threads_tag) {
+        constexpr int T = decltype(threads_tag)::value;
+        switch ((pieces + T - 1) / T) {
+            case 1: launch(threads_tag, std::integral_constant<int, 1>{}); break;
+            case 2: launch(threads_tag, std::integral_constant<int, 2>{}); break;
+            case 3: launch(threads_tag, std::integral_constant<int, 3>{}); break;
+            case 4: launch(threads_tag, std::integral_constant<int, 4>{}); break;
+            case 5: launch(threads_tag, std::integral_constant<int, 5>{}); break;
+            case 6: launch(threads_tag, std::integral_constant<int, 6>{}); break;
+            case 7: launch(threads_tag, std::integral_constant<int, 7>{}); break;
+            default: launch(threads_tag, std::integral_constant<int, 8>{}); break;
+        }
+    };
+    if (K <= 8192) by_pieces(std::integral_constant<int, 256>{});
+    else           by_pieces(std::integral_constant<int, 1024>{});
 }
 
 }  // namespace sasq
@@ -211,10 +297,8 @@ extern "C" int sasq_quantize_weight(const float* w, void* wq, float* s_w, int64_
     if (wf == SASQ_W_INT4_PACKED && (K & 1)) return SASQ_ERR_SHAPE;
     if (!aligned16(w) || !aligned16(wq)) return SASQ_ERR_ALIGN;
     hipStream_t st = as_stream(stream);
-    if (wf == SASQ_W_INT8)
-        quantize_weight_kernel<false><<<(int)N, kPrepThreads, 0, st>>>(w, static_cast<uint8_t*>(wq), s_w, K);
-    else
-        quantize_weight_kernel<true><<<(int)N, kPrepThreads, 0, st>>>(w, static_cast<uint8_t*>(wq), s_w, K);
+    if (wf == SASQ_W_INT8) quantize_weight<false>(w, static_cast<uint8_t*>(wq), s_w, N, K, st);
+    else                   quantize_weight<true>(w, static_cast<uint8_t*>(wq), s_w, N, K, st);
     return hipGetLastError() == hipSuccess ? SASQ_OK : SASQ_ERR_LAUNCH;
 }
 
@@ -263,14 +347,14 @@ extern "C" int sasq_absmax_scale(const void* x, float* s, int64_t rows, int64_t 
     if (!workspace || workspace_bytes < sasq_absmax_scale_workspace(rows, cols)) return SASQ_ERR_WORKSPACE;
     if (!aligned16(workspace)) return SASQ_ERR_ALIGN;
     const int64_t n = rows * cols;
-    int64_t need = (n / 8 + kPrepThreads * 4 - 1) / (kPrepThreads * 4);
-    int grid = (int)(need < 1 ? 1 : (need > kMaxAbsmaxBlocks ? kMaxAbsmaxBlocks : need));
+    const int64_t need = (n / 8 + kAbsmaxThreads * kAbsmaxUnroll - 1) / (kAbsmaxThreads * kAbsmaxUnroll);
+    const int grid = (int)(need < 1 ? 1 : (need > kAbsmaxBlocks ? kAbsmaxBlocks : need));
     auto head = static_cast<uint32_t*>(workspace);
     auto parts = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + kWsHeaderBytes);
     hipStream_t st = as_stream(stream);
     if (dt == SASQ_F16)
-        absmax_kernel<SASQ_F16><<<grid, kPrepThreads, 0, st>>>(static_cast<const uint16_t*>(x), s, head, parts, n, bits);
+        absmax_kernel<SASQ_F16><<<grid, kAbsmaxThreads, 0, st>>>(static_cast<const uint16_t*>(x), s, head, parts, n, bits);
     else
-        absmax_kernel<SASQ_BF16><<<grid, kPrepThreads, 0, st>>>(static_cast<const uint16_t*>(x), s, head, parts, n, bits);
+        absmax_kernel<SASQ_BF16><<<grid, kAbsmaxThreads, 0, st>>>(static_cast<const uint16_t*>(x), s, head, parts, n, bits);
     return hipGetLastError() == hipSuccess ? SASQ_OK : SASQ_ERR_LAUNCH;
 }
