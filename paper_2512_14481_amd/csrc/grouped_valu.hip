@@ -1,17 +1,16 @@
-// Grouped-factor linear (Sec. 3, Eq. 3) for the group sizes the matrix units cannot take: groups of one channel (the
-// strict per-channel factors that Sec. 4 trains), and every other group that is not whole 32- or 64-channel pieces.
+// Grouped-factor linear (Sec. 3, Eq. 3) for the group sizes the int8 GEMM cannot take: groups of one channel (the strict
+// per-channel factors that Sec. 4 trains), and every other group that is not whole 32- or 64-channel pieces.
 //
 //     acc_i = sum over the k of group i of xq[m,k] * Wq[n,k]   (exact)      f = fma(fl32(acc_i), s_g[i], f)
 //
-// The chain of fused multiply-adds is part of the contract, so the work is fp32 VALU work: with one channel per group
-// two operations per multiply-add, the exact product of two codes and the fused multiply-add with the factor.  What the
-// kernels have to do is keep the VALU issuing: codes are widened once, on their way into LDS (each then serves 64 or 128
-// outputs) or out of it; a thread owns a block of outputs, so that a step of k reads TM + TN values for 2 TM TN
-// operations; the factors come from LDS with the codes (read as scalars they cost a memory latency every few k, because
-// scalar loads share their counter with LDS); products are formed before the adds that depend on them; the next slab is
-// fetched into registers while the current one is multiplied.
-// Measured, group 1: 512 x 4096 x 4096 414 us (42 T operations/s of the 79 that the VALUs issue at full rate; one thread
-// per output reading global memory took 32.2 ms), 2048 x 4096 x 11008 3.31 ms (56 T), 64 x 4096 x 4096 122 us.
+// The chain of fused multiply-adds is part of the contract, so at least one fp32 VALU operation per output and group is due;
+// the kernels differ in who makes the group sums.  Groups of 1, 2, 4, 8, 16: the matrix units (linear_small_group_kernel;
+// single channels with few rows: the VALUs, with a lane broadcast, linear_per_channel_kernel).  Other sizes: the VALUs, from
+// codes in LDS, a thread owning a block of outputs, so that a step of k reads TM + TN values for TM TN operations; the next
+// slab is fetched into registers while the current one is multiplied.
+// Measured, us, group 1: 512 x 4096 x 4096 282 (sums made by VALU multiplies, two operations per multiply-add: 414; one thread
+// per output reading global memory: 32.2 ms), 2048 x 4096 x 11008 2590 (3310), 64 x 4096 x 4096 122; 512 x 4096 x 4096, group 2
+// 170 (739), group 4 103 (301), group 8 83 (218), group 16 74 (182).
 #include "sasq_device.h"
 #include "gemm_k64.h"
 #include <type_traits>
@@ -19,11 +18,10 @@
 namespace sasq {
 
 constexpr int kSlab = 32;                          // k per LDS slab
-constexpr int64_t kOneMinTiles = 768;              // group 1: tiles a launch needs for a tile shape to be chosen (three per CU)
 
-// How a group is summed.  ONE: one channel, codes in LDS as floats.  DOT4: a multiple of four channels, codes stay
+// How a group is summed.  DOT4: a multiple of four channels, codes stay
 // packed and v_dot4 sums four products exactly.  ANY: codes as 32-bit integers, one multiply-add each.
-enum { GV_ONE = 0, GV_DOT4 = 1, GV_ANY = 2 };
+enum { GV_DOT4 = 1, GV_ANY = 2 };
 
 // 16 consecutive codes of a row from k0 on, as bytes; zeros past K or outside the matrix
 template <bool INT4>
@@ -69,12 +67,10 @@ __global__ __launch_bounds__(256) void linear_grouped_valu_kernel(
     float* __restrict__ f_out, int M, int N, int K, int group, int tiles_m)
 {
     using S = Store16<DT>;
-    using Elem = std::conditional_t<MODE == GV_ONE, float, int>;
     constexpr int TM = BM / 16, TN = BN / 16, TNV = TN / 4;
     constexpr int kSteps = MODE == GV_DOT4 ? kSlab / 4 : kSlab;          // LDS rows per slab
-    __shared__ __attribute__((aligned(16))) Elem lx[2][kSteps][BM];
-    __shared__ __attribute__((aligned(16))) Elem lw[2][kSteps][BN];
-    __shared__ __attribute__((aligned(16))) float ls[2][kSlab];
+    __shared__ __attribute__((aligned(16))) int lx[2][kSteps][BM];
+    __shared__ __attribute__((aligned(16))) int lw[2][kSteps][BN];
     const int tid = threadIdx.x;
     const int tx = tid & 15, ty = tid >> 4;
     const int tm = (int)blockIdx.x % tiles_m, tn = (int)blockIdx.x / tiles_m;
@@ -88,14 +84,11 @@ __global__ __launch_bounds__(256) void linear_grouped_valu_kernel(
     const int wrow = tid % BN, whalf = tid / BN;
     const int xi = tid - (256 - kXItems), xrow = has_x ? xi % BM : 0, xhalf = has_x ? xi / BM : 0;
     u32x4 rw, rx;
-    float rs = 0.0f;
     auto fetch = [&](int k0) {
-        if (MODE == GV_ONE) rs = s_g[min(k0 + (tid & (kSlab - 1)), K - 1)];
         if (has_w) rw = load_codes16<INT4>(wq, n0 + wrow, n0 + wrow < N, k0 + 16 * whalf, K, vec);
         if (has_x) rx = load_codes16<false>(reinterpret_cast<const uint8_t*>(xq), m0 + xrow, m0 + xrow < M, k0 + 16 * xhalf, K, vec);
     };
     auto put = [&](int buf) {
-        if (MODE == GV_ONE && tid < kSlab) ls[buf][tid] = rs;
         if constexpr (MODE == GV_DOT4) {
             if (has_w) {
 #pragma unroll
@@ -108,11 +101,11 @@ __global__ __launch_bounds__(256) void linear_grouped_valu_kernel(
         } else {
             if (has_w) {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) lw[buf][16 * whalf + e][wrow] = (Elem)sext_byte(rw[e >> 2], e & 3);
+                for (int e = 0; e < 16; ++e) lw[buf][16 * whalf + e][wrow] = sext_byte(rw[e >> 2], e & 3);
             }
             if (has_x) {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) lx[buf][16 * xhalf + e][xrow] = (Elem)sext_byte(rx[e >> 2], e & 3);
+                for (int e = 0; e < 16; ++e) lx[buf][16 * xhalf + e][xrow] = sext_byte(rx[e >> 2], e & 3);
             }
         }
     };
@@ -141,58 +134,29 @@ __global__ __launch_bounds__(256) void linear_grouped_valu_kernel(
     for (int k0 = 0; k0 < K; k0 += kSlab, buf ^= 1) {
         const bool more = k0 + kSlab < K;
         if (more) fetch(k0 + kSlab);
-        auto step = [&](int st, float sk) {
-            Elem a[TM], b[TN];
+        auto step = [&](int st) {
+            int a[TM], b[TN];
 #pragma unroll
             for (int i = 0; i < TM; ++i) a[i] = lx[buf][st][ty * TM + i];
 #pragma unroll
             for (int v = 0; v < TNV; ++v)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) b[4 * v + j] = lw[buf][st][64 * v + tx * 4 + j];
-            if constexpr (MODE == GV_ONE) {
-                float p[TM][TN];
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) p[i][j] = a[i] * b[j];
-                __builtin_amdgcn_sched_barrier(0x0100);                    // only LDS reads may move across
-#pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) f[i][j] = __builtin_fmaf(p[i][j], sk, f[i][j]);
-                __builtin_amdgcn_sched_barrier(0x0100);
-            } else
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
-                    if constexpr (MODE == GV_DOT4) {
-                        acc[i][j] = __builtin_amdgcn_sdot4(a[i], b[j], acc[i][j], false);
-                    } else {
-                        acc[i][j] += __mul24(a[i], b[j]);
-                    }
+                    if constexpr (MODE == GV_DOT4) acc[i][j] = __builtin_amdgcn_sdot4(a[i], b[j], acc[i][j], false);
+                    else                           acc[i][j] += __mul24(a[i], b[j]);
                 }
         };
-        if constexpr (MODE == GV_ONE) {
-            if (more || K - k0 == kSlab) {
-#pragma unroll 2
-                for (int s4 = 0; s4 < kSteps / 4; ++s4) {
-                    const f32x4 sv = *reinterpret_cast<const f32x4*>(&ls[buf][4 * s4]);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) step(4 * s4 + q, sv[q]);
-                }
-            } else {
-                for (int st = 0; st < K - k0; ++st) step(st, ls[buf][st]);
-            }
-        } else {
-            constexpr int kPer = MODE == GV_DOT4 ? 4 : 1;
-            const int steps = more ? kSteps : (K - k0) / kPer;
+        constexpr int kPer = MODE == GV_DOT4 ? 4 : 1;
+        const int steps = more ? kSteps : (K - k0) / kPer;
 #pragma unroll 4
-            for (int st = 0; st < steps; ++st) {
-                step(st, 0.0f);
-                in_group += kPer;
-                if (in_group == group) fold();
-            }
+        for (int st = 0; st < steps; ++st) {
+            step(st);
+            in_group += kPer;
+            if (in_group == group) fold();
         }
         if (more) {
             put(buf ^ 1);              // the other buffer: its readers passed the barrier of the previous slab
@@ -240,9 +204,9 @@ __global__ __launch_bounds__(256) void linear_grouped_valu_kernel(
 
 // Groups of one channel.  A wave owns TM rows x 64 columns of the output: lane = column, and the codes of the TM rows sit
 // in the lanes of one register, from where the multiply takes row i with a lane broadcast inside its own operand fetch
-// (DPP row_newbcast) -- no LDS read per row and k, which is what bounded the tiled form above (3 x 128-bit reads for 64
-// operations) when there are too few rows for many waves.  LDS holds the codes as bytes, 64 k per slab, rows padded to 80 bytes so that 128-bit reads of consecutive
-// rows use all banks; a lane reads 16 codes at once and widens them as it goes (2 operations per 2 TM of useful work).
+// (DPP row_newbcast), with no LDS read per row and k.  For few rows: one wave per SIMD issues an operation every 6 cycles
+// whatever it is, and this form needs the fewest.  LDS holds the codes as bytes, 64 k per slab, rows padded to 80 bytes so
+// that 128-bit reads of consecutive rows use all banks; a lane reads 16 codes at once and widens them as it goes (2 operations per 2 TM of useful work).
 constexpr int kOneSlab = 64;
 constexpr int kOneStride = kOneSlab + 16;
 
@@ -348,11 +312,185 @@ __global__ __launch_bounds__(256) void linear_per_channel_kernel(
     }
 }
 
+// Groups of 1, 2, 4, 8 or 16 channels: the matrix units form the group sums while the VALUs run the chain of fused
+// multiply-adds, one operation per output and group instead of two or more.  v_mfma_f32_{32x32x4, 16x16x4, 4x4x4}_f16 with a
+// zero accumulator operand: 32, 16 or 4 rows, the activations' block broadcast to all column blocks, by 64 columns, four
+// channels; codes are exact in f16, their products and sums (below 2^19) in fp32.  Smaller groups zero the other channels'
+// halves of the activation operand, larger ones chain.  All three forms deliver 32 outputs a cycle and SIMD.
+// Measured on register loops, cycles per 16 x 64 products and adds, four | two waves per SIMD: multiply and multiply-add 72 | 85,
+// this 60 | 65 (the same with the fp32 outer product v_mfma_f32_16x16x1 70 | 73; a factor in a scalar register takes the
+// multiply-add from 2.4 cycles to 4.6, so the factors come from LDS into vector registers).
+// A wave owns F rows x 64 columns; LDS holds the codes as halves, 64 channels per slab, rows padded to 144 bytes so that the
+// 128-bit reads of 16 consecutive rows use all banks.
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+template <int F> struct Outer;
+template <> struct Outer<16> {
+    typedef float Vec __attribute__((ext_vector_type(16)));
+    static __device__ __forceinline__ Vec mma(const f16x4& a, const f16x4& b, const Vec& c) { return __builtin_amdgcn_mfma_f32_16x16x4f16(a, b, c, 2, 0, 0); }
+    static __device__ __forceinline__ int row(int r, int lane) { return 4 * (lane >> 4) + (r & 3); }
+    static __device__ __forceinline__ int col(int r, int lane) { return 16 * (r >> 2) + (lane & 15); }
+};
+template <> struct Outer<4> {
+    typedef float Vec __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ Vec mma(const f16x4& a, const f16x4& b, const Vec& c) { return __builtin_amdgcn_mfma_f32_4x4x4f16(a, b, c, 4, 0, 0); }
+    static __device__ __forceinline__ int row(int r, int lane) { return r; }
+    static __device__ __forceinline__ int col(int r, int lane) { return lane; }
+};
+
+constexpr int kSgSlab = 64;
+constexpr int kSgStride = 2 * kSgSlab + 16;        // bytes
+
+// four codes -> four halves: byte u = code + 128 under the exponent of 1024 is 1024 + u
+__device__ __forceinline__ u32x2 halves4(uint32_t codes)
+{
+    const uint32_t u = codes ^ 0x80808080u;
+    const f16x2 bias = {(_Float16)-1152.0f, (_Float16)-1152.0f};
+    const f16x2 lo = __builtin_bit_cast(f16x2, __builtin_amdgcn_perm(0x64646464u, u, 0x04010400u)) + bias;
+    const f16x2 hi = __builtin_bit_cast(f16x2, __builtin_amdgcn_perm(0x64646464u, u, 0x04030402u)) + bias;
+    return u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+}
+
+template <int DT, bool INT4, int G, int F>
+__global__ __launch_bounds__(256, F == 16 ? 3 : 4) void linear_small_group_kernel(
+    const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq, const float* __restrict__ s_g,
+    const float* __restrict__ s_w, const float* __restrict__ bias, uint16_t* __restrict__ y,
+    float* __restrict__ f_out, int M, int N, int K, int tiles_m)
+{
+    using S = Store16<DT>;
+    using O = Outer<F>;
+    constexpr int BM = 4 * F, BN = 64, kFactors = kSgSlab / G;
+    constexpr int U = 16 / F < kFactors ? 16 / F : kFactors;              // groups per batch: 16 sums per lane, two batches in turn
+    __shared__ __attribute__((aligned(16))) char lx[2][BM * kSgStride];
+    __shared__ __attribute__((aligned(16))) char lw[2][BN * kSgStride];
+    __shared__ __attribute__((aligned(16))) float ls[2][kSgSlab];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int m0 = ((int)blockIdx.x % tiles_m) * BM, n0 = ((int)blockIdx.x / tiles_m) * BN;
+    const bool vec = (K & 15) == 0;
+    // staging: 16 codes of weight row tid/4 per thread and, on the first 4 BM threads, of activation row tid/4; two slabs ahead
+    // in registers (one ahead left 64 x 4096 x 4096 waiting for memory in every slab: 133 us)
+    const int irow = tid >> 2, ich = tid & 3;
+    const bool has_x = tid < 4 * BM;
+    struct Slab { u32x4 w, x; float s; };
+    Slab ring[2];
+    auto fetch = [&](Slab& r, int k0) {
+        const int gi = k0 / G + tid;
+        if (tid < kFactors) r.s = gi < K / G ? s_g[gi] : 0.0f;            // past the end: 0 * 0 leaves every sum as it is
+        r.w = load_codes16<INT4>(wq, n0 + irow, n0 + irow < N, k0 + 16 * ich, K, vec);
+        if (has_x) r.x = load_codes16<false>(reinterpret_cast<const uint8_t*>(xq), m0 + irow, m0 + irow < M, k0 + 16 * ich, K, vec);
+    };
+    auto widen = [&](char* dst, const u32x4& v) {
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            const u32x2 p = halves4(v[2 * d]), q = halves4(v[2 * d + 1]);
+            *reinterpret_cast<u32x4*>(dst + 16 * d) = u32x4{p[0], p[1], q[0], q[1]};
+        }
+    };
+    auto put = [&](const Slab& r, int buf) {
+        if (tid < kFactors) ls[buf][tid] = r.s;
+        widen(&lw[buf][irow * kSgStride + 32 * ich], r.w);
+        if (has_x) widen(&lx[buf][irow * kSgStride + 32 * ich], r.x);
+    };
+    float f[F];
+#pragma unroll
+    for (int r = 0; r < F; ++r) f[r] = 0.0f;
+    const int slabs = (K + kSgSlab - 1) / kSgSlab;
+    auto multiply = [&](int buf) {
+        const char* pa = &lx[buf][(wave * F + lane % F) * kSgStride];
+        const char* pb = &lw[buf][lane * kSgStride];
+        constexpr int kPieces = kSgSlab / 8;                              // eight channels of codes per LDS read
+        u32x4 av[kPieces], bv[kPieces];
+        f32x4 sv[2];
+        auto read_s = [&](int q) { sv[q & 1] = *reinterpret_cast<const f32x4*>(&ls[buf][4 * q]); };
+        read_s(0);
+#pragma unroll
+        for (int p = 0; p < kPieces; ++p) {
+            av[p] = *reinterpret_cast<const u32x4*>(pa + 16 * p);
+            bv[p] = *reinterpret_cast<const u32x4*>(pb + 16 * p);
+        }
+        typename O::Vec sum[2][U];
+        auto form = [&](int batch) {                                       // the sums of U groups of this slab
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int c = 0; c < (G + 3) / 4; ++c) {
+                    const typename O::Vec zero = {0.0f};
+                    const int k = (batch * U + u) * G + 4 * c, h = (k >> 2) & 1;
+                    uint32_t a0 = av[k >> 3][2 * h], a1 = av[k >> 3][2 * h + 1];
+                    if (G == 1) {
+                        a0 = (k & 3) == 0 ? a0 & 0xFFFFu : (k & 3) == 1 ? a0 & 0xFFFF0000u : 0u;
+                        a1 = (k & 3) == 2 ? a1 & 0xFFFFu : (k & 3) == 3 ? a1 & 0xFFFF0000u : 0u;
+                    } else if (G == 2) {
+                        if (k & 2) a0 = 0u; else a1 = 0u;
+                    }
+                    // keeps the batches apart: left alone the compiler forms all sums of the slab first, in accumulator registers
+                    asm volatile("" : "+v"(a0), "+v"(a1));
+                    const f16x4 a = __builtin_bit_cast(f16x4, u32x2{a0, a1});
+                    const f16x4 b = __builtin_bit_cast(f16x4, u32x2{bv[k >> 3][2 * h], bv[k >> 3][2 * h + 1]});
+                    sum[batch & 1][u] = O::mma(a, b, c == 0 ? zero : sum[batch & 1][u]);
+                }
+        };
+        form(0);
+        // the sums of batch i + 1 are formed while those of batch i are added up
+#pragma unroll
+        for (int i = 0; i < kFactors / U; ++i) {
+            if (i + 1 < kFactors / U) form(i + 1);
+            __builtin_amdgcn_sched_barrier(0x0100);                        // only LDS reads may move across
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int g = i * U + u;
+                if ((g & 3) == 0 && g + 4 < kFactors) read_s((g >> 2) + 1);
+                const float sg = sv[(g >> 2) & 1][g & 3];
+#pragma unroll
+                for (int r = 0; r < F; ++r) f[r] = __builtin_fmaf(sum[i & 1][u][r], sg, f[r]);
+            }
+#pragma unroll
+            for (int r = 0; r < F; ++r) asm volatile("" : "+v"(f[r]));
+            __builtin_amdgcn_sched_barrier(0x0100);
+        }
+    };
+    fetch(ring[0], 0);
+    if (slabs > 1) fetch(ring[1], kSgSlab);
+    put(ring[0], 0);
+    if (slabs > 2) fetch(ring[0], 2 * kSgSlab);
+    __syncthreads();
+    for (int i = 0; i < slabs; i += 2) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            if (i + j >= slabs) break;
+            multiply(j);
+            if (i + j + 1 < slabs) {
+                put(ring[1 - j], 1 - j);           // the other buffer: its readers passed the barrier of the previous slab
+                if (i + j + 3 < slabs) fetch(ring[1 - j], (i + j + 3) * kSgSlab);
+                __syncthreads();
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < F; ++r) {
+        const int m = m0 + wave * F + O::row(r, lane), n = n0 + O::col(r, lane);
+        if (m >= M || n >= N) continue;
+        float yv = f[r] * s_w[n];
+        if (bias) yv = yv + bias[n];
+        const int64_t o = (int64_t)m * N + n;
+        y[o] = S::enc(yv);
+        if (f_out) f_out[o] = f[r];
+    }
+}
+
 template <int DT, bool INT4, int TM>
 static void launch_per_channel(const GemmK64Args& a, hipStream_t st)
 {
     const int64_t tm = (a.M + 4 * TM - 1) / (4 * TM), tn = (a.N + 63) / 64;
     linear_per_channel_kernel<DT, INT4, TM><<<(unsigned)(tm * tn), 256, 0, st>>>(
+        a.xq, a.wq, a.s, a.s_w, a.bias, a.y, reinterpret_cast<float*>(a.acc_out), (int)a.M, (int)a.N, (int)a.K, (int)tm);
+}
+
+template <int DT, bool INT4, int G, int F>
+static void launch_small_group(const GemmK64Args& a, hipStream_t st)
+{
+    const int64_t tm = (a.M + 4 * F - 1) / (4 * F), tn = (a.N + 63) / 64;
+    linear_small_group_kernel<DT, INT4, G, F><<<(unsigned)(tm * tn), 256, 0, st>>>(
         a.xq, a.wq, a.s, a.s_w, a.bias, a.y, reinterpret_cast<float*>(a.acc_out), (int)a.M, (int)a.N, (int)a.K, (int)tm);
 }
 
@@ -367,36 +505,41 @@ static void launch_gv(const GemmK64Args& a, int64_t group, hipStream_t st)
 template <int DT, bool INT4, int MODE>
 static void launch_gv_mode(const GemmK64Args& a, int64_t group, hipStream_t st)
 {
-    auto tiles = [&](int bm, int bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
     // The larger the thread's block, the fewer LDS reads per operation; the more workgroups, the more waves to issue from
-    // (one wave per SIMD issues a VALU operation every 6 cycles, three every 2.8).  Group 1: 2048 x 4096 x 11008 takes
-    // 3307 / 3391 / 3557 us on 64x128 / 64x64 / 32x64 tiles, 512 x 4096 x 4096 (256 / 512 / 1024 tiles) 630 / 429 / 414.
-    if constexpr (MODE == GV_ONE) {
-        if (tiles(64, 128) >= kOneMinTiles)     launch_gv<DT, INT4, MODE, 64, 128>(a, group, st);
-        else if (tiles(64, 64) >= kOneMinTiles) launch_gv<DT, INT4, MODE, 64, 64>(a, group, st);
-        else                                    launch_gv<DT, INT4, MODE, 32, 64>(a, group, st);
-    } else {
-        if (tiles(64, 128) >= 512)     launch_gv<DT, INT4, MODE, 64, 128>(a, group, st);
-        else if (tiles(64, 64) >= 256) launch_gv<DT, INT4, MODE, 64, 64>(a, group, st);
-        else if (tiles(32, 64) >= 256) launch_gv<DT, INT4, MODE, 32, 64>(a, group, st);
-        else                           launch_gv<DT, INT4, MODE, 16, 64>(a, group, st);
-    }
+    // (one wave per SIMD issues a VALU operation every 6 cycles, three every 2.8).
+    auto tiles = [&](int bm, int bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
+    if (tiles(64, 128) >= 512)     launch_gv<DT, INT4, MODE, 64, 128>(a, group, st);
+    else if (tiles(64, 64) >= 256) launch_gv<DT, INT4, MODE, 64, 64>(a, group, st);
+    else if (tiles(32, 64) >= 256) launch_gv<DT, INT4, MODE, 32, 64>(a, group, st);
+    else                           launch_gv<DT, INT4, MODE, 16, 64>(a, group, st);
+}
+
+// Sixteen rows per wave while that makes enough 64x64 tiles, below that four rows per wave or, for single channels, the
+// lane-broadcast kernel.  K = N = 4096 (64 tiles per 64 rows), sixteen rows against the other: group 1, M = 64 190 us and 122,
+// M = 128 190 and 175, M = 192 191 and 288; group 4, M = 64 76 and 52, M = 192 77 and 73, M = 256 78 and 87; group 16, M = 64
+// 60 and 47, M = 192 62 and 63, M = 256 62 and 73.
+template <int DT, bool INT4, int G>
+static void launch_small_group_rows(const GemmK64Args& a, hipStream_t st)
+{
+    const int64_t tiles = ((a.M + 63) / 64) * ((a.N + 63) / 64);
+    if (tiles > (G == 1 ? 128 : 192)) launch_small_group<DT, INT4, G, 16>(a, st);
+    else if constexpr (G == 1)        launch_per_channel<DT, INT4, 4>(a, st);
+    else                              launch_small_group<DT, INT4, G, 4>(a, st);
 }
 
 template <int DT, bool INT4>
 static void launch_gv_w(const GemmK64Args& a, int64_t group, hipStream_t st)
 {
-    // One channel per group: above two 32x64 tiles per CU the LDS-tiled kernel, below that the lane-broadcast one (its
-    // multiply with a broadcast operand runs at half rate, but it needs few waves to get there).  At K = N = 4096, tiled
-    // against broadcast: M = 512 414 us and 528, M = 300 340 and 407, M = 250 302 and 288, M = 128 333 and 175, M = 64 331
-    // and 122.  The latter with eight rows per wave while that gives 1.5 workgroups per CU (M = 250: 288 us, four rows
-    // 308), else with four (M = 128: 175, eight 183).
-    auto tiles = [&](int bm) { return ((a.M + bm - 1) / bm) * ((a.N + 63) / 64); };
-    if (group == 1 && tiles(32) > 512)           launch_gv_mode<DT, INT4, GV_ONE>(a, group, st);
-    else if (group == 1 && tiles(32) >= 384)     launch_per_channel<DT, INT4, 8>(a, st);
-    else if (group == 1)                         launch_per_channel<DT, INT4, 4>(a, st);
-    else if (group % 4 == 0) launch_gv_mode<DT, INT4, GV_DOT4>(a, group, st);
-    else                     launch_gv_mode<DT, INT4, GV_ANY>(a, group, st);
+    switch (group) {
+        case 1: launch_small_group_rows<DT, INT4, 1>(a, st); break;
+        case 2: launch_small_group_rows<DT, INT4, 2>(a, st); break;
+        case 4: launch_small_group_rows<DT, INT4, 4>(a, st); break;
+        case 8: launch_small_group_rows<DT, INT4, 8>(a, st); break;
+        case 16: launch_small_group_rows<DT, INT4, 16>(a, st); break;
+        default:
+            if (group % 4 == 0) launch_gv_mode<DT, INT4, GV_DOT4>(a, group, st);
+            else                launch_gv_mode<DT, INT4, GV_ANY>(a, group, st);
+    }
 }
 
 void launch_grouped_valu(const GemmK64Args& a, sasq_dtype dt, bool int4, int64_t group, hipStream_t st)

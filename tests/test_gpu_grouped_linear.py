@@ -130,6 +130,25 @@ def test_grouped_linear_small_groups_every_kernel(shape, group, fmt):
     assert_same_values(y, ref["y"], dtype, "Y")
 
 
+@pytest.mark.parametrize("fmt", ["int8", "int4"])
+@pytest.mark.parametrize("rows", [(9, 70), (64, 8192), (65, 4097), (200, 4100)])      # four and sixteen rows per wave, edges of the choice
+@pytest.mark.parametrize("group,k", [(1, 64), (1, 127), (1, 194), (2, 66), (2, 190), (4, 64), (4, 188), (8, 72), (8, 192), (16, 80), (16, 208)])
+def test_grouped_linear_group_sums_on_matrix_units(group, k, rows, fmt):
+    """Groups of 1, 2, 4, 8 and 16: part of a slab over, one slab to four, row and column remainders; codes -128 among them."""
+    if fmt == "int4" and k % 2:
+        pytest.skip("packed int4 needs an even K")
+    dtype = "bf16" if fmt == "int8" else "f16"
+    xb, wq, s_w, bias, s_g = problem(55, (*rows, k), group, dtype, fmt)
+    if fmt == "int8":
+        wq[:, ::5] = -128
+    s_g[0] *= 1e-3                                                 # the first group saturates: codes -128 and 127
+    ref = oracle.static_linear_grouped(xb, s_g, wq, s_w, bias, group, 8, fmt, dtype)
+    y, f, xq = run_grouped(xb, s_g, wq, s_w, bias, group, fmt, dtype, False)
+    assert np.array_equal(xq, ref["xq"])
+    assert np.array_equal(f, ref["f"])
+    assert_same_values(y, ref["y"], dtype, "Y")
+
+
 def test_grouped_linear_rejects():
     x = torch.zeros((4, 128), dtype=torch.float16, device="cuda")
     y = torch.zeros((4, 4), dtype=torch.float16, device="cuda")
