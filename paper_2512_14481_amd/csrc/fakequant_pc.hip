@@ -19,6 +19,13 @@ constexpr int kPcColsPerBlock = kWave * 8;        // 512
 constexpr int kPcRowUnroll = 4;                   // rows in flight per wave
 constexpr int kPcMaxRowChunks = 128;              // more row chunks than this lengthen the reduction tail (measured)
 constexpr int kPcTargetBlocks = 2048;             // 8 blocks per CU
+// Rows a block takes at least: it pays for its columns' factors (eight divisions a lane) and, backward, for its partial and
+// ticket once, and from two groups of rows on it has loads in flight under its arithmetic.  Measured, forward | backward us at
+// 16, 32, 64, 128 rows: seven tensors of 1777 x 5120 (one 13824) 57.8 | 111.6, 54.3 | 89.2, 55.4 | 84.6, 59.2 | 91.2; four of
+// 300 x 2048 6.5 | 12.3, 5.5 | 10.8, 6.6 | 11.6, 7.9 | 13.8: 32, and backward 64 where a launch still has kPcTargetBlocks.
+// (The long chunks' sums are no less exact: fp64 from four rows on; ds is off by 5.2e-8 of its norm, 5.9e-8 with fp32 chunks of
+// 16 rows, 8.8e-8 with those of 32.)
+constexpr int kPcMinRows = 32, kPcMinRowsLong = 64;
 
 struct PcConst {
     float inv_s[8];
@@ -128,14 +135,15 @@ __device__ __forceinline__ void bwd_pc_body(
     const uint16_t* __restrict__ x, const uint16_t* dy, const float* __restrict__ s,
     uint16_t* dx, float* __restrict__ ds, uint32_t* __restrict__ tickets, float* __restrict__ partials,
     int64_t rows, int64_t cols, int64_t rows_per_chunk, int bits,
-    int col_block, int row_chunk, int nchunks, float (&red)[kPcWaves][kPcColsPerBlock], bool& is_last)
+    int col_block, int row_chunk, int nchunks, double (&red)[kPcWaves][kPcColsPerBlock], bool& is_last)
 {
     using S = Store16<DT>;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t cbase = (int64_t)col_block * kPcColsPerBlock;
     const int64_t col0 = cbase + lane * 8;
     const bool active = col0 < cols;
-    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    // four rows are summed in fp32, everything above that in fp64 up to the block's partial
+    double sum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (active) {
         const int64_t r_begin = (int64_t)row_chunk * rows_per_chunk;
         const int64_t r_end = min(rows, r_begin + rows_per_chunk);
@@ -154,6 +162,11 @@ __device__ __forceinline__ void bwd_pc_body(
         bool have = full(r);
         if (have) load_group(xa_, ga_, r);
         const PcConst c = load_pc(s, col0, cols, bits);
+        float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        auto add_group = [&]() {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { sum[e] += (double)acc[e]; acc[e] = 0.0f; }
+        };
         auto one_row = [&](const u32x4 xin, const u32x4 gin, int64_t rr) {
             u32x4 out;
 #pragma unroll
@@ -176,6 +189,7 @@ __device__ __forceinline__ void bwd_pc_body(
             if (more) load_group(xb_, gb_, r + kStep);
 #pragma unroll
             for (int u = 0; u < kPcRowUnroll; ++u) one_row(xa_[u], ga_[u], r + u * kPcWaves);
+            add_group();
             r += kStep;
             have = more;
             if (!have) break;
@@ -183,16 +197,18 @@ __device__ __forceinline__ void bwd_pc_body(
             if (more) load_group(xa_, ga_, r + kStep);
 #pragma unroll
             for (int u = 0; u < kPcRowUnroll; ++u) one_row(xb_[u], gb_[u], r + u * kPcWaves);
+            add_group();
             r += kStep;
             have = more;
         }
         for (; r < r_end; r += kPcWaves)
             one_row(__builtin_nontemporal_load(reinterpret_cast<const u32x4*>(x + r * cols + col0)),
                     __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(dy + r * cols + col0)), r);
+        add_group();
     }
     // block partial per column: waves in fixed order
 #pragma unroll
-    for (int e = 0; e < 8; ++e) red[wave][lane * 8 + e] = acc[e];
+    for (int e = 0; e < 8; ++e) red[wave][lane * 8 + e] = sum[e];
     __syncthreads();
     // One 128-bit store per 4 columns, with the agent-scope cache policy the compiler gives its own
     // agent-scope atomic stores (sc1): 4-byte stores of the same data are four times as many
@@ -202,10 +218,10 @@ __device__ __forceinline__ void bwd_pc_body(
         f32x4 v;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            float a = 0.0f;
+            double a = 0.0;
 #pragma unroll
             for (int w = 0; w < kPcWaves; ++w) a += red[w][c4 + e];
-            v[e] = a;
+            v[e] = (float)a;
         }
         if (cbase + c4 < cols) {        // cols is a multiple of 8: a group of 4 is all in or all out
             float* dst = &partials[(int64_t)row_chunk * cols + cbase + c4];
@@ -253,7 +269,7 @@ __device__ __forceinline__ void bwd_pc_body(
                     for (int e = 0; e < 4; ++e) t[e] += (double)pv[j][e];
                 }
         }
-        double* meet = reinterpret_cast<double*>(&red[0][0]);            // 512 doubles of the 8 KB
+        double* meet = &red[0][0];
         __syncthreads();                                                 // red's earlier contents are consumed
         if (half) {
 #pragma unroll
@@ -276,7 +292,7 @@ __global__ __launch_bounds__(kPcThreads) void fakequant_bwd_pc_kernel(
     uint16_t* dx, float* __restrict__ ds, uint32_t* __restrict__ tickets, float* __restrict__ partials,
     int64_t rows, int64_t cols, int64_t rows_per_chunk, int bits)
 {
-    __shared__ float red[kPcWaves][kPcColsPerBlock];
+    __shared__ double red[kPcWaves][kPcColsPerBlock];
     __shared__ bool is_last;
     bwd_pc_body<DT, WRITE_DX>(x, dy, s, dx, ds, tickets, partials, rows, cols, rows_per_chunk, bits,
                               (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.y, red, is_last);
@@ -323,7 +339,7 @@ __global__ __launch_bounds__(kPcThreads) void fakequant_fwd_pc_batch_kernel(cons
 template <int DT>
 __global__ __launch_bounds__(kPcThreads) void fakequant_bwd_pc_batch_kernel(const PcBatch b, int bits)
 {
-    __shared__ float red[kPcWaves][kPcColsPerBlock];
+    __shared__ double red[kPcWaves][kPcColsPerBlock];
     __shared__ bool is_last;
     const int k = pc_item_of(b, (int)blockIdx.x);
     const PcItem& it = b.it[k];
@@ -364,22 +380,15 @@ __global__ void fakequant_pc_scalar_kernel(const uint16_t* __restrict__ x, const
     if (backward) ds[k] = (float)acc;
 }
 
-static int pc_row_chunks(int64_t rows, int64_t col_blocks)
-{
-    // enough blocks to fill the chip, at least 16 rows per block, at most kPcMaxRowChunks
-    int64_t want = (kPcTargetBlocks + col_blocks - 1) / col_blocks;
-    int64_t by_rows = (rows + 15) / 16;
-    int64_t rc = want < by_rows ? want : by_rows;
-    if (rc < 1) rc = 1;
-    if (rc > kPcMaxRowChunks) rc = kPcMaxRowChunks;
-    return (int)rc;
-}
-
-// rows per chunk: a multiple of 16 (whole unpredicated groups in every chunk but the last)
-static void pc_geometry(int64_t rows, int64_t cols, int64_t& col_blocks, int64_t& rpc, int& chunks)
+// Row chunks of a tensor, `rows_min` rows each at least: enough blocks to fill the chip, at most kPcMaxRowChunks (the
+// workspace has room for that many partials), whole unpredicated groups of 16 rows in every chunk but the last.
+static void pc_geometry(int64_t rows, int64_t cols, int64_t rows_min, int64_t& col_blocks, int64_t& rpc, int& chunks)
 {
     col_blocks = (cols + kPcColsPerBlock - 1) / kPcColsPerBlock;
-    const int want = pc_row_chunks(rows, col_blocks);
+    int64_t want = (kPcTargetBlocks + col_blocks - 1) / col_blocks;
+    const int64_t by_rows = (rows + rows_min - 1) / rows_min;
+    if (want > by_rows) want = by_rows;
+    if (want > kPcMaxRowChunks) want = kPcMaxRowChunks;
     rpc = ((rows + want - 1) / want + 15) / 16 * 16;
     chunks = (int)((rows + rpc - 1) / rpc);
 }
@@ -416,7 +425,7 @@ extern "C" int sasq_fakequant_fwd_pc(const void* x, const float* s, void* y, int
     }
     int64_t col_blocks, rpc;
     int chunks;
-    pc_geometry(rows, cols, col_blocks, rpc, chunks);
+    pc_geometry(rows, cols, kPcMinRows, col_blocks, rpc, chunks);
     dim3 grid((unsigned)col_blocks, (unsigned)chunks);
     if (dt == SASQ_F16) {
         if (codes) fakequant_fwd_pc_kernel<SASQ_F16, true><<<grid, kPcThreads, 0, st>>>(X, s, Y, codes, rows, cols, rpc, bits);
@@ -457,7 +466,7 @@ extern "C" int sasq_fakequant_bwd_pc(const void* x, const void* dy, const float*
     if (!aligned16(workspace)) return SASQ_ERR_ALIGN;
     int64_t col_blocks, rpc;
     int chunks;
-    pc_geometry(rows, cols, col_blocks, rpc, chunks);
+    pc_geometry(rows, cols, kPcMinRows, col_blocks, rpc, chunks);
     dim3 grid((unsigned)col_blocks, (unsigned)chunks);
     auto tickets = static_cast<uint32_t*>(workspace);
     auto parts = reinterpret_cast<float*>(static_cast<char*>(workspace) + kWsHeaderBytes);
@@ -523,12 +532,18 @@ static int launch_pc_batch(const sasq_fq_item* items, int i0, int i1, int bits, 
 {
     PcBatch b;
     memset(&b, 0, sizeof(b));
-    int64_t blocks = 0;
+    int64_t rows_min = kPcMinRows, blocks = 0;
+    if (BACKWARD) {
+        int64_t long_blocks = 0;
+        for (int i = i0; i < i1; ++i)
+            long_blocks += (items[i].cols + kPcColsPerBlock - 1) / kPcColsPerBlock * ((items[i].rows + kPcMinRowsLong - 1) / kPcMinRowsLong);
+        if (long_blocks >= kPcTargetBlocks) rows_min = kPcMinRowsLong;
+    }
     for (int i = i0; i < i1; ++i) {
         const sasq_fq_item& src = items[i];
         PcItem& it = b.it[i - i0];
         int64_t col_blocks;
-        pc_geometry(src.rows, src.cols, col_blocks, it.rpc, it.chunks);
+        pc_geometry(src.rows, src.cols, rows_min, col_blocks, it.rpc, it.chunks);
         it.col_blocks = (int)col_blocks;
         it.x = static_cast<const uint16_t*>(src.x);
         it.dy = static_cast<const uint16_t*>(src.dy);

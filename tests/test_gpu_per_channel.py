@@ -92,3 +92,32 @@ def test_pc_backward_workspace_reuse_with_different_data():
         ref = oracle.fakequant_bwd_pc(xb, dyb, s, 8, dtype)
         err = np.abs(ds.cpu().numpy().astype(np.float64) - ref["ds64"])
         assert (err <= 1e-4 * np.abs(ref["ds64"]) + 1e-6 * ref["sum_abs"]).all(), rep
+
+
+@pytest.mark.parametrize("rows", [15, 16, 31, 32, 33, 47, 63, 64, 65, 129, 2049])
+def test_per_channel_row_chunks(rows):
+    """Rows around the group of 16, the chunk of 32 and the cap on chunks.  Bound: four rows are summed in fp32 (a product, a
+    subtraction and three additions each rounded once), a partial and the result rounded once: 8 2^-24 of the sum of absolute
+    terms."""
+    dtype, shape = "bf16", (rows, 520)
+    xb, dyb = wl.random_bits(43, f"rcx{rows}", shape, dtype, gain=2.5), wl.random_bits(43, f"rcg{rows}", shape, dtype)
+    s = col_absmax_scales(xb, dtype, 2.0)
+    check(xb, dyb, s, dtype)
+    ref = oracle.fakequant_bwd_pc(xb, dyb, s, 8, dtype)
+    _, _, _, ds = run_pc(xb, dyb, s, dtype, want_dx=False)
+    assert (np.abs(ds - ref["ds64"]) <= 8 * 2.0 ** -24 * ref["sum_abs"]).all()
+
+
+def test_per_channel_batch_with_long_chunks():
+    """A batch large enough for chunks of 64 rows."""
+    dtype, shape = "f16", (2113, 4096)
+    xb, dyb = wl.random_bits(44, "lcx", shape, dtype, gain=2.5), wl.random_bits(44, "lcg", shape, dtype)
+    s = col_absmax_scales(xb, dtype, 2.0)
+    ref = oracle.fakequant_bwd_pc(xb, dyb, s, 8, dtype)
+    x, dy, sd = to_dev(xb, dtype), to_dev(dyb, dtype), torch.from_numpy(s).cuda()
+    items = [(x, dy, sd, torch.empty_like(x), torch.empty_like(sd)) for _ in range(8)]
+    B.sasq_fakequant_bwd_pc_batch(items, B.new_workspace(B.sasq_fakequant_bwd_pc_batch_workspace(items)))
+    for _, _, _, dx, ds in items:
+        assert torch.equal(dx, items[0][3]) and torch.equal(ds, items[0][4])
+    assert_same_values(to_bits(items[0][3]), ref["dx"], dtype, "dx")
+    assert (np.abs(items[0][4].cpu().numpy() - ref["ds64"]) <= 8 * 2.0 ** -24 * ref["sum_abs"]).all()
