@@ -907,11 +907,11 @@ static void launch_mfma(const void* xin, const void* wq, const float* s, const f
     }
 }
 
-// Few rows: the kernels of static_linear_skinny.hip, unless a knob asks for a variant of the tiled ones.  Row-major packed
-// int4 keeps the tiled kernel (its codes are not in operand order).
-static bool use_skinny(int64_t rows, sasq_wfmt wf)
+// Few rows, or few tiles: the kernels of static_linear_skinny.hip, unless a knob asks for a variant of the tiled ones.
+// Row-major packed int4 keeps the tiled kernel (its codes are not in operand order).
+static bool use_skinny(const LinBatch& g, sasq_wfmt wf)
 {
-    return rows <= kSkinnyRows && wf != SASQ_W_INT4_PACKED && tuning(SASQ_TUNE_LINEAR_PATH) == 0 &&
+    return linear_takes_skinny(g, wf == SASQ_W_INT4_BLOCKED) && wf != SASQ_W_INT4_PACKED && tuning(SASQ_TUNE_LINEAR_PATH) == 0 &&
            tuning(SASQ_TUNE_LINEAR_TILE) == 0 && tuning(SASQ_TUNE_LINEAR_MFMA) == 0;
 }
 
@@ -966,13 +966,13 @@ static void run_linear(const void* x, const float* s, const void* wq, const floa
 
     const bool mfma_ok = (K % kBK) == 0;
     const bool int4 = wf == SASQ_W_INT4_PACKED;
-    if (mfma_ok && use_skinny(M, wf)) {
-        LinBatch g{};
-        g.count = 1;
-        LinItem& li = g.it[0];
-        li.x = x; li.xq = xq_ws; li.s = s; li.wq = static_cast<const uint8_t*>(wq); li.s_w = s_w; li.bias = bias;
-        li.y = static_cast<uint16_t*>(y);
-        li.M = (int)M; li.N = (int)N; li.K = (int)K;
+    LinBatch g{};
+    g.count = 1;
+    LinItem& li = g.it[0];
+    li.x = x; li.xq = xq_ws; li.s = s; li.wq = static_cast<const uint8_t*>(wq); li.s_w = s_w; li.bias = bias;
+    li.y = static_cast<uint16_t*>(y);
+    li.M = (int)M; li.N = (int)N; li.K = (int)K;
+    if (mfma_ok && use_skinny(g, wf)) {
         const bool qx = skinny_quantizes(g, acc_out);
         if (!qx) launch_quantize_blocks<DT, false>(x, s, xq_ws, M, K, a_bits, st);
         launch_linear_skinny(g, (sasq_dtype)DT, (int)wf, qx, a_bits, acc_out, st);
@@ -1276,9 +1276,7 @@ extern "C" int sasq_static_linear_batch(const sasq_linear_item* items, int count
     for (int i = count; i < kMaxLinearBatch; ++i) g.first_block[i + 1] = g.first_block[count];
 
     hipStream_t st = as_stream(stream);
-    int64_t rows = 0;
-    for (int i = 0; i < count; ++i) rows = items[i].M > rows ? items[i].M : rows;
-    const bool skinny = use_skinny(rows, wf);
+    const bool skinny = use_skinny(g, wf);
     if (skinny && skinny_quantizes(g, nullptr)) {
         launch_linear_skinny(g, dt, (int)wf, true, a_bits, nullptr, st);
         return hipGetLastError() == hipSuccess ? SASQ_OK : SASQ_ERR_LAUNCH;

@@ -1,4 +1,5 @@
-// int8 linear for few rows (token generation): Y = X . W^T where M is a handful of rows and the weights are what is read.
+// int8 linear for few rows (token generation): Y = X . W^T where M is a handful of rows and the weights are what is read;
+// and for some hundred rows where the GEMM's tiles are too few to fill the chip (a chunk of a prefill), in row blocks.
 //
 // What bounds it: the weight bytes (a 7B layer's seven projections at 8 rows, int8: 202 MB in 36 us = 5.6 TB/s, the GEMM's
 // tiles took 93; a 13B layer's at one row, int4: 159 MB in 30 us, from 128; row-major int8, whose rows are gathered in
@@ -10,6 +11,8 @@
 // QX: the activations are quantized on the way into the operand registers, 16 elements per lane and K tile, which takes
 // the pre-pass's launch out of the call; each workgroup repeats that work, so it is for at most 16 rows.  Otherwise the
 // codes come from the pre-pass in their staging blocks.
+// Row blocks (more than 64 rows): what bounds them is the operands' delivery from L2, (BM + 64) K bytes per workgroup for
+// BM x 64 outputs; 333 x 4096 x 4096 takes 18.7 us with its pre-pass, 27.1 on 96 GEMM tiles of 128 x 128.
 #include "sasq_device.h"
 #include "gemm_tile.h"
 #include "gemm_k64.h"
@@ -19,7 +22,7 @@ namespace sasq {
 
 template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX>
 __device__ __forceinline__
-void skinny_body(const LinItem& it, int nblk, int a_bits, int32_t* __restrict__ acc_out, char* lds)
+void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __restrict__ acc_out, char* lds)
 {
     using S = Store16<DT>;
     constexpr bool I4 = WMODE == 3, ROWMAJOR = WMODE == 0;
@@ -29,7 +32,7 @@ void skinny_body(const LinItem& it, int nblk, int a_bits, int32_t* __restrict__ 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int frow = lane & 15, fq = lane >> 4;
     const int M = it.M, N = it.N, K = it.K, KT = K >> 6;
-    const int n0 = nblk * 16 * NT;
+    const int m0 = mblk * 16 * MT, n0 = nblk * 16 * NT;
 
     // This wave's K tiles: an equal run of consecutive ones.
     const int per = (KT + NW - 1) / NW;
@@ -66,7 +69,7 @@ void skinny_body(const LinItem& it, int nblk, int a_bits, int32_t* __restrict__ 
     uint32_t xoff[MT];
 #pragma unroll
     for (int b = 0; b < MT; ++b) {
-        const int first = min(16 * b, ((M - 1) >> 4) << 4);
+        const int first = min(m0 + 16 * b, ((M - 1) >> 4) << 4);
         if (QX) {
             xbase[b] = reinterpret_cast<const char*>(it.x) + ((int64_t)first * K + (int64_t)t0 * 64) * 2;
             xoff[b] = (uint32_t)min(frow, M - 1 - first) * (uint32_t)K * 2 + fq * 32;
@@ -179,7 +182,7 @@ void skinny_body(const LinItem& it, int nblk, int a_bits, int32_t* __restrict__ 
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[kRegs * e + r] = I4 ? sum[e] >> 4 : sum[e];
         }
-        const int m = 16 * b + frow, n = n0 + 16 * g0 + 4 * kRegs * fq;      // 4 (8) consecutive columns of one row
+        const int m = m0 + 16 * b + frow, n = n0 + 16 * g0 + 4 * kRegs * fq;      // 4 (8) consecutive columns of one row
         if (m >= M || n >= N) continue;
         uint16_t* dst = it.y + (int64_t)m * N + n;
         float yv[4 * kRegs];
@@ -213,7 +216,11 @@ void skinny_kernel(const LinBatch b, int a_bits, int32_t* __restrict__ acc_out)
 {
     __shared__ __attribute__((aligned(1024))) char lds[NW * NT * MT * 1024];
     const int k = lin_item_of(b, (int)blockIdx.x);
-    skinny_body<DT, WMODE, MT, NT, NW, D, QX>(b.it[k], (int)blockIdx.x - b.first_block[k], a_bits, acc_out, lds);
+    // Eight neighbours in the id go to the eight XCDs: the row blocks of one run of weight rows stay on one, 8 ids apart.
+    const int id = (int)blockIdx.x - b.first_block[k], octet = id >> 3, tiles_m = b.it[k].tiles_m;
+    const int mblk = octet % tiles_m, nblk = octet / tiles_m * 8 + (id & 7);
+    if (nblk >= b.it[k].tiles_n) return;
+    skinny_body<DT, WMODE, MT, NT, NW, D, QX>(b.it[k], mblk, nblk, a_bits, acc_out, lds);
 }
 
 
@@ -221,8 +228,16 @@ template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX>
 static void launch_one(LinBatch& b, int a_bits, int32_t* acc_out, hipStream_t st)
 {
     b.first_block[0] = 0;
-    for (int i = 0; i < kMaxLinearBatch; ++i)
-        b.first_block[i + 1] = b.first_block[i] + (i < b.count ? (b.it[i].N + 16 * NT - 1) / (16 * NT) : 0);
+    for (int i = 0; i < kMaxLinearBatch; ++i) {
+        int blocks = 0;
+        if (i < b.count) {
+            LinItem& it = b.it[i];
+            it.tiles_m = (int)(((int64_t)it.M + 16 * MT - 1) / (16 * MT));
+            it.tiles_n = (int)(((int64_t)it.N + 16 * NT - 1) / (16 * NT));
+            blocks = (it.tiles_n + 7) / 8 * 8 * it.tiles_m;
+        }
+        b.first_block[i + 1] = b.first_block[i] + blocks;
+    }
     skinny_kernel<DT, WMODE, MT, NT, NW, D, QX><<<b.first_block[b.count], 64 * NW, 0, st>>>(b, a_bits, acc_out);
 }
 
@@ -245,6 +260,44 @@ static void launch_mt(LinBatch& b, int64_t tiles16, int a_bits, int32_t* acc_out
     }
 }
 
+// Rows per workgroup (64 weight rows each, K over four waves) for more than kSkinnyRows rows, 0: the GEMM's tiles are better.
+// Such a call is a few dozen tiles of 128 x 128 with a long K loop; cut finer, without LDS in the loop, every CU has
+// operands in flight, until the operands' L2 reads (the smaller the block, the more of them) cost more than that.  A round is
+// 256 workgroups, one per CU.  Measured with the pre-pass, int8, us, GEMM tiles | 64 | 96 | 128 rows:
+//   4096 x 4096:  128 rows 25.9 | 15.2 | 17.5 | 20.9; 256 rows 26.6 | 15.1 (one round) | 17.3 | 20.0;
+//                 333 rows 27.1 | 21.0 | 18.7 (one round) | 21.3; 512 rows 27.5 | 24.2 (two) | 32.7; 768 rows 28.8 | 40.6 (three)
+//   11008 x 4096: 256 rows 56.0 | 34.6 | 40.2 | 45.7; 333 rows 57.4 | 54.6 | 42.6 | 47.4; 512 rows 57.4 | 57.0 | 71.3 | 49.0
+//   7B layer:     96 rows 93.6 | 83.3 | 66.1 | 69.7; 128 rows 94.3 | 80.2 | 103.6 | 75.0 (int4 100 | 60 | 83 | 61); 192 rows
+//                 95.1 | 107 | 106 | 121
+// So: one round of small blocks first; then blocks that take all rows at once and read the weights once, unless it is one
+// projection that fills more than half of the chip with 128 x 128 tiles (8192 x 28672, 224 of them: 96 rows 49.4 | - | 71.3); then
+// a round and a half (5056 x 5504, 227 rows: 39 | 28), with int4's shorter loads two (8192 x 1024, 2048 rows: 54.2 | 41.6; int8
+// 28672 x 8192, 256 rows, is better on the tiles: 135 | 154).  Fewer than eight runs of weight rows would leave XCDs without work.
+static int block_rows(const LinBatch& b, bool int4)
+{
+    int64_t blocks64 = 0, blocks96 = 0, tiles128 = 0;
+    int rows = 0;
+    for (int i = 0; i < b.count; ++i) {
+        const int64_t m = b.it[i].M, cols = ((int64_t)b.it[i].N + 63) / 64;
+        if (cols < 8) return 0;
+        blocks64 += (m + 63) / 64 * cols;
+        blocks96 += (m + 95) / 96 * cols;
+        tiles128 += (m + 127) / 128 * ((cols + 1) / 2);
+        rows = b.it[i].M > rows ? b.it[i].M : rows;
+    }
+    if (blocks64 <= 256) return 64;
+    if (blocks96 <= 256) return 96;
+    if (rows <= 128 && (b.count > 1 || tiles128 <= 128)) return rows <= 96 ? 96 : 128;
+    return blocks64 <= (int4 ? 512 : 384) ? 64 : 0;
+}
+
+bool linear_takes_skinny(const LinBatch& b, bool int4)
+{
+    int rows = 0;
+    for (int i = 0; i < b.count; ++i) rows = b.it[i].M > rows ? b.it[i].M : rows;
+    return rows <= kSkinnyRows || block_rows(b, int4) != 0;
+}
+
 template <int DT, int WMODE>
 static void launch_wmode(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, hipStream_t st)
 {
@@ -254,7 +307,13 @@ static void launch_wmode(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, hip
         tiles16 += (b.it[i].N + 15) / 16;
         rows = b.it[i].M > rows ? b.it[i].M : rows;
     }
-    if (qx)              launch_mt<DT, WMODE, 1, true>(b, tiles16, a_bits, acc_out, st);
+    if (rows > kSkinnyRows) {
+        switch (block_rows(b, WMODE == 3)) {
+        case 64:  launch_one<DT, WMODE, 4, 4, 4, 2, false>(b, a_bits, acc_out, st); break;
+        case 96:  launch_one<DT, WMODE, 6, 4, 4, 3, false>(b, a_bits, acc_out, st); break;
+        default:  launch_one<DT, WMODE, 8, 4, 4, 3, false>(b, a_bits, acc_out, st); break;
+        }
+    } else if (qx)       launch_mt<DT, WMODE, 1, true>(b, tiles16, a_bits, acc_out, st);
     else if (rows <= 32) launch_mt<DT, WMODE, 2, false>(b, tiles16, a_bits, acc_out, st);
     else if (rows <= 48) launch_mt<DT, WMODE, 3, false>(b, tiles16, a_bits, acc_out, st);
     else                 launch_mt<DT, WMODE, 4, false>(b, tiles16, a_bits, acc_out, st);

@@ -1,4 +1,4 @@
-"""GPU parity of the few-row linear kernels (M <= 64) against the CPU oracle: accumulators bit for bit, Y equal by value, for
+"""GPU parity of the few-row linear kernels (M <= 64, and row blocks of 64, 96 and 128) against the CPU oracle: accumulators bit for bit, Y equal by value, for
 every weight layout that reaches them, at the edges of their row tiles (16, 32, 48, 64), of the split of K over the waves
 (fewer K tiles than waves, remainders), of the column tiles and of the narrow / wide choice; mixed batches; in-place calls."""
 from __future__ import annotations
@@ -17,7 +17,9 @@ pytestmark = pytest.mark.gpu
 
 LAYOUTS = [("int8", False), ("int8", True), ("int4", True)]
 SHAPES = [(1, 1, 64), (3, 47, 576), (15, 130, 128), (16, 512, 1088), (17, 33, 64), (32, 96, 704), (33, 72, 2112), (48, 250, 640),
-          (49, 31, 192), (64, 264, 1024), (65, 64, 128), (16, 8200, 192), (2, 8185, 320), (30, 8192, 128), (64, 8189, 192)]
+          (49, 31, 192), (64, 264, 1024), (65, 64, 128), (16, 8200, 192), (2, 8185, 320), (30, 8192, 128), (64, 8189, 192),
+          # row blocks of 64 (one round, one and a half, int4's two), 96 (one round, all rows at once) and 128
+          (333, 1000, 704), (270, 4090, 128), (450, 4090, 128), (300, 3500, 192), (96, 16500, 64), (97, 9001, 128), (128, 8200, 320)]
 
 
 def problem(seed, shape, fmt, dtype):
@@ -50,11 +52,11 @@ def test_few_rows_match_oracle(shape, dtype, fmt, blocked):
         assert np.array_equal(to_bits(y2), to_bits(y))
 
 
-@pytest.mark.parametrize("rows", [(5, 16, 1), (9, 64, 20)])
+@pytest.mark.parametrize("rows", [(5, 16, 1), (9, 64, 20), (70, 3, 129)])
 @pytest.mark.parametrize("fmt,blocked", LAYOUTS)
 def test_batch_of_few_rows_matches_oracle(rows, fmt, blocked):
     set_tuning()
-    dims = [(96, 640), (300, 64), (41, 1984)]
+    dims = [(96, 640), (300, 64), (41, 1984)] if max(rows) <= 64 else [(520, 640), (600, 64), (513, 1984)]
     items, refs = [], []
     for i, (m, (n, k)) in enumerate(zip(rows, dims)):
         xb, wq, s_w, bias, s = problem(70 + i, (m, n, k), fmt, "bf16")
