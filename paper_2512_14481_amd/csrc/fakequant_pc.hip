@@ -20,12 +20,18 @@ constexpr int kPcRowUnroll = 4;                   // rows in flight per wave
 constexpr int kPcMaxRowChunks = 128;              // more row chunks than this lengthen the reduction tail (measured)
 constexpr int kPcTargetBlocks = 2048;             // 8 blocks per CU
 // Rows a block takes at least: it pays for its columns' factors (eight divisions a lane) and, backward, for its partial and
-// ticket once, and from two groups of rows on it has loads in flight under its arithmetic.  Measured, forward | backward us at
-// 16, 32, 64, 128 rows: seven tensors of 1777 x 5120 (one 13824) 57.8 | 111.6, 54.3 | 89.2, 55.4 | 84.6, 59.2 | 91.2; four of
-// 300 x 2048 6.5 | 12.3, 5.5 | 10.8, 6.6 | 11.6, 7.9 | 13.8: 32, and backward 64 where a launch still has kPcTargetBlocks.
+// ticket once, and from two groups of rows on it has loads in flight under its arithmetic.
+constexpr int kPcMinRows = 32;
+// Backward, where the rows per block decide how ds is rounded: they follow from the tensor alone, never from what shares its
+// launch, so that a batch gives the bits of the single calls.  16 for a tensor of at most 64 such blocks, 64 for one that has
+// 512 of those.  Measured, us with 16 | 32 | 64 rows, one tensor, then seven in a launch: 512 x 512 (32 blocks of 16) 8.3 | 9.3 |
+// 11.8, 12.0 | 11.5 | 13.3; 128 x 4096 (64) 8.4 | 9.5 | 11.6, 12.5 | 12.4 | 14.3; 256 x 4096 (128) 9.4 | 9.7 | 12.0, 19.6 | 15.6 |
+// 16.6; 1777 x 5120 (280 of 64) 26.3 | 19.8 | 20.3, 99.5 | 74.9 | 73.5; 4096 x 4096 (512) 28.9 | 29.0 | 25.9, 138 | 138 | 139;
+// 4096 x 5120 (640) 33.0 | 33.0 | 29.7, 169 | 169 | 165.
 // (The long chunks' sums are no less exact: fp64 from four rows on; ds is off by 5.2e-8 of its norm, 5.9e-8 with fp32 chunks of
 // 16 rows, 8.8e-8 with those of 32.)
-constexpr int kPcMinRows = 32, kPcMinRowsLong = 64;
+constexpr int kPcMinRowsShort = 16, kPcMinRowsLong = 64;
+constexpr int64_t kPcShortBlocks = 64, kPcLongBlocks = 512;
 
 struct PcConst {
     float inv_s[8];
@@ -393,6 +399,15 @@ static void pc_geometry(int64_t rows, int64_t cols, int64_t rows_min, int64_t& c
     chunks = (int)((rows + rpc - 1) / rpc);
 }
 
+// The backward's row chunks (rule and figures at kPcMinRowsShort)
+static void pc_geometry_bwd(int64_t rows, int64_t cols, int64_t& col_blocks, int64_t& rpc, int& chunks)
+{
+    auto blocks = [&](int64_t n) { return (cols + kPcColsPerBlock - 1) / kPcColsPerBlock * ((rows + n - 1) / n); };
+    const int64_t rows_min = blocks(kPcMinRowsShort) <= kPcShortBlocks ? kPcMinRowsShort
+                           : blocks(kPcMinRowsLong) >= kPcLongBlocks ? kPcMinRowsLong : kPcMinRows;
+    pc_geometry(rows, cols, rows_min, col_blocks, rpc, chunks);
+}
+
 static int check_pc(int64_t rows, int64_t cols, int bits, int dt)
 {
     if (rows <= 0 || cols <= 0) return SASQ_ERR_SHAPE;
@@ -466,7 +481,7 @@ extern "C" int sasq_fakequant_bwd_pc(const void* x, const void* dy, const float*
     if (!aligned16(workspace)) return SASQ_ERR_ALIGN;
     int64_t col_blocks, rpc;
     int chunks;
-    pc_geometry(rows, cols, kPcMinRows, col_blocks, rpc, chunks);
+    pc_geometry_bwd(rows, cols, col_blocks, rpc, chunks);
     dim3 grid((unsigned)col_blocks, (unsigned)chunks);
     auto tickets = static_cast<uint32_t*>(workspace);
     auto parts = reinterpret_cast<float*>(static_cast<char*>(workspace) + kWsHeaderBytes);
@@ -532,18 +547,13 @@ static int launch_pc_batch(const sasq_fq_item* items, int i0, int i1, int bits, 
 {
     PcBatch b;
     memset(&b, 0, sizeof(b));
-    int64_t rows_min = kPcMinRows, blocks = 0;
-    if (BACKWARD) {
-        int64_t long_blocks = 0;
-        for (int i = i0; i < i1; ++i)
-            long_blocks += (items[i].cols + kPcColsPerBlock - 1) / kPcColsPerBlock * ((items[i].rows + kPcMinRowsLong - 1) / kPcMinRowsLong);
-        if (long_blocks >= kPcTargetBlocks) rows_min = kPcMinRowsLong;
-    }
+    int64_t blocks = 0;
     for (int i = i0; i < i1; ++i) {
         const sasq_fq_item& src = items[i];
         PcItem& it = b.it[i - i0];
         int64_t col_blocks;
-        pc_geometry(src.rows, src.cols, rows_min, col_blocks, it.rpc, it.chunks);
+        if (BACKWARD) pc_geometry_bwd(src.rows, src.cols, col_blocks, it.rpc, it.chunks);
+        else          pc_geometry(src.rows, src.cols, kPcMinRows, col_blocks, it.rpc, it.chunks);
         it.col_blocks = (int)col_blocks;
         it.x = static_cast<const uint16_t*>(src.x);
         it.dy = static_cast<const uint16_t*>(src.dy);

@@ -121,3 +121,26 @@ def test_per_channel_batch_with_long_chunks():
         assert torch.equal(dx, items[0][3]) and torch.equal(ds, items[0][4])
     assert_same_values(to_bits(items[0][3]), ref["dx"], dtype, "dx")
     assert (np.abs(items[0][4].cpu().numpy() - ref["ds64"]) <= 8 * 2.0 ** -24 * ref["sum_abs"]).all()
+
+
+# rows per block of 16, 32 and 64 in the backward, at the edges of the rule; launches of few and of thousands of blocks
+BATCHES = [[(2113, 4096)] * 8, [(128, 4096), (129, 4096), (1024, 512), (1025, 512), (3, 8)], [(4096, 4096), (4032, 4096), (64, 264), (700, 2048)]]
+
+
+@pytest.mark.parametrize("shapes", BATCHES, ids=["many_blocks", "short", "long"])
+def test_per_channel_batch_equals_single_calls(shapes):
+    """An item's ds (and dx) has the bits of the single-tensor call whatever else is in the launch."""
+    g = torch.Generator(device="cuda").manual_seed(45)
+    distinct = {}
+    for sh in shapes:
+        if sh not in distinct:
+            x, dy = ((torch.randn(sh, device="cuda", generator=g) * k).half() for k in (2.0, 1.0))
+            s = torch.rand(sh[1], device="cuda", generator=g) * 0.05 + 0.01
+            dx, ds = torch.empty_like(x), torch.empty_like(s)
+            B.sasq_fakequant_bwd_pc(x, dy, s, dx, ds, B.new_workspace(B.sasq_fakequant_bwd_pc_workspace(*sh)))
+            distinct[sh] = (x, dy, s, dx, ds)
+    items = [(x, dy, s, torch.empty_like(dx), torch.empty_like(ds)) for x, dy, s, dx, ds in (distinct[sh] for sh in shapes)]
+    B.sasq_fakequant_bwd_pc_batch(items, B.new_workspace(B.sasq_fakequant_bwd_pc_batch_workspace(items)))
+    for sh, (_, _, _, dx, ds) in zip(shapes, items):
+        assert torch.equal(ds, distinct[sh][4]), sh
+        assert torch.equal(dx, distinct[sh][3]), sh
