@@ -21,7 +21,15 @@ constexpr int kPcMaxRowChunks = 128;              // more row chunks than this l
 constexpr int kPcTargetBlocks = 2048;             // 8 blocks per CU
 // Rows a block takes at least: it pays for its columns' factors (eight divisions a lane) and, backward, for its partial and
 // ticket once, and from two groups of rows on it has loads in flight under its arithmetic.
+// Forward, by the launch as a whole: 16 rows while that makes at most one block per CU, or nearly fills a second round of
+// them.  Measured, us with 16 | 32 rows: 512 x 512 (32 blocks of 16) 3.8 | 4.3, 512 x 4096 (256) 4.4 | 5.0, two of 200 x 5120
+// (260) 6.3 | 5.1, four of 300 x 2048 (304) 7.1 | 5.6, seven of 128 x 4096 (448) 5.9 | 6.1, 1024 x 4096 (512) 5.8 | 6.2,
+// 2048 x 4096 (1024) 9.0 | 8.4, seven of 512 x 4096 (1792) 13.9 | 13.3, seven of 1777 x 5120 47.2 | 45.2.
 constexpr int kPcMinRows = 32;
+static int64_t pc_fwd_rows(int64_t blocks16)
+{
+    return blocks16 <= 256 || (blocks16 > 384 && blocks16 <= 512) ? 16 : kPcMinRows;
+}
 // Backward, where the rows per block decide how ds is rounded: they follow from the tensor alone, never from what shares its
 // launch, so that a batch gives the bits of the single calls.  16 for a tensor of at most 64 such blocks, 64 for one that has
 // 512 of those.  Measured, us with 16 | 32 | 64 rows, one tensor, then seven in a launch: 512 x 512 (32 blocks of 16) 8.3 | 9.3 |
@@ -399,6 +407,11 @@ static void pc_geometry(int64_t rows, int64_t cols, int64_t rows_min, int64_t& c
     chunks = (int)((rows + rpc - 1) / rpc);
 }
 
+static int64_t pc_blocks16(int64_t rows, int64_t cols)
+{
+    return (cols + kPcColsPerBlock - 1) / kPcColsPerBlock * ((rows + 15) / 16);
+}
+
 // The backward's row chunks (rule and figures at kPcMinRowsShort)
 static void pc_geometry_bwd(int64_t rows, int64_t cols, int64_t& col_blocks, int64_t& rpc, int& chunks)
 {
@@ -440,7 +453,7 @@ extern "C" int sasq_fakequant_fwd_pc(const void* x, const float* s, void* y, int
     }
     int64_t col_blocks, rpc;
     int chunks;
-    pc_geometry(rows, cols, kPcMinRows, col_blocks, rpc, chunks);
+    pc_geometry(rows, cols, pc_fwd_rows(pc_blocks16(rows, cols)), col_blocks, rpc, chunks);
     dim3 grid((unsigned)col_blocks, (unsigned)chunks);
     if (dt == SASQ_F16) {
         if (codes) fakequant_fwd_pc_kernel<SASQ_F16, true><<<grid, kPcThreads, 0, st>>>(X, s, Y, codes, rows, cols, rpc, bits);
@@ -547,13 +560,14 @@ static int launch_pc_batch(const sasq_fq_item* items, int i0, int i1, int bits, 
 {
     PcBatch b;
     memset(&b, 0, sizeof(b));
-    int64_t blocks = 0;
+    int64_t blocks = 0, blocks16 = 0;
+    for (int i = i0; i < i1; ++i) blocks16 += pc_blocks16(items[i].rows, items[i].cols);
     for (int i = i0; i < i1; ++i) {
         const sasq_fq_item& src = items[i];
         PcItem& it = b.it[i - i0];
         int64_t col_blocks;
         if (BACKWARD) pc_geometry_bwd(src.rows, src.cols, col_blocks, it.rpc, it.chunks);
-        else          pc_geometry(src.rows, src.cols, kPcMinRows, col_blocks, it.rpc, it.chunks);
+        else          pc_geometry(src.rows, src.cols, pc_fwd_rows(blocks16), col_blocks, it.rpc, it.chunks);
         it.col_blocks = (int)col_blocks;
         it.x = static_cast<const uint16_t*>(src.x);
         it.dy = static_cast<const uint16_t*>(src.dy);

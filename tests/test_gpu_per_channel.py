@@ -144,3 +144,20 @@ def test_per_channel_batch_equals_single_calls(shapes):
     for sh, (_, _, _, dx, ds) in zip(shapes, items):
         assert torch.equal(ds, distinct[sh][4]), sh
         assert torch.equal(dx, distinct[sh][3]), sh
+
+
+@pytest.mark.parametrize("rows", [31, 511, 512, 513, 769, 785, 1024, 1025])
+def test_per_channel_forward_rows_per_block(rows):
+    """Launches around the lines of the forward's rule (256, 384 and 512 blocks of 16 rows x 512 columns): every row comes out
+    as in a call on a few rows alone."""
+    g = torch.Generator(device="cuda").manual_seed(46)
+    x = (torch.randn((rows, 4096), device="cuda", generator=g) * 2).bfloat16()
+    s = torch.rand(4096, device="cuda", generator=g) * 0.05 + 0.01
+    y, want = torch.empty_like(x), torch.empty_like(x)
+    B.sasq_fakequant_fwd_pc(x, s, y)
+    for r in range(0, rows, 100):
+        B.sasq_fakequant_fwd_pc(x[r:r + 100], s, want[r:r + 100])
+    assert torch.equal(y, want)
+    y2 = [torch.full_like(x, float("nan")) for _ in range(2)]
+    B.sasq_fakequant_fwd_pc_batch([(x, s, t) for t in y2])
+    assert all(torch.equal(t, want) for t in y2)
