@@ -30,10 +30,11 @@ void launch_grouped_valu(const GemmK64Args& a, sasq_dtype dt, bool int4, int64_t
 // rows: one activation factor per row.
 void launch_linear_anyk(const GemmK64Args& a, sasq_dtype dt, bool int4, bool rows, hipStream_t st);
 // At most kSkinnyRows rows, or too few tiles for the GEMM (static_linear_skinny.hip; linear_takes_skinny says whether the
-// sizes are such): the items of `b` (first_block and the tile counts are filled in here), weight layouts 0, 2 and 3.  qx: quantize the activations in the kernel (at most kSkinnyQuantRows rows, and no output may overlap an input, as
-// workgroups read x while others write y); otherwise the items' xq hold the staged codes.
+// sizes are such): the items of `b` (first_block and the tile counts are filled in here), weight layouts 0, 2 and 3.
+// qx: quantize the activations in the kernel (at most kSkinnyQuantRows rows, and no output may overlap an input, as workgroups
+// read x while others write y); otherwise the items' xq hold the staged codes.
 constexpr int kSkinnyRows = 64, kSkinnyQuantRows = 16;
-bool linear_takes_skinny(const LinBatch& b, bool int4);
+bool linear_takes_skinny(const LinBatch& b, int wmode);
 void launch_linear_skinny(LinBatch& b, sasq_dtype dt, int wmode, bool qx, int a_bits, int32_t* acc_out, hipStream_t st);
 // split_tail: hand the tiles of a sparsely filled last round out as 128x256 halves (sets b.split_first / b.split_count)
 void launch_gemm_k64_batch(LinBatch& b, int grid, sasq_dtype dt, int wmode, bool split_tail, hipStream_t st);

@@ -911,8 +911,8 @@ static void launch_mfma(const void* xin, const void* wq, const float* s, const f
 // Row-major packed int4 keeps the tiled kernel (its codes are not in operand order).
 static bool use_skinny(const LinBatch& g, sasq_wfmt wf)
 {
-    return linear_takes_skinny(g, wf == SASQ_W_INT4_BLOCKED) && wf != SASQ_W_INT4_PACKED && tuning(SASQ_TUNE_LINEAR_PATH) == 0 &&
-           tuning(SASQ_TUNE_LINEAR_TILE) == 0 && tuning(SASQ_TUNE_LINEAR_MFMA) == 0;
+    return wf != SASQ_W_INT4_PACKED && tuning(SASQ_TUNE_LINEAR_PATH) == 0 && tuning(SASQ_TUNE_LINEAR_TILE) == 0 &&
+           tuning(SASQ_TUNE_LINEAR_MFMA) == 0 && linear_takes_skinny(g, (int)wf);
 }
 
 // Whether such a call quantizes in the kernel: at most 16 rows everywhere, and no output over an input (the pre-pass has

@@ -269,11 +269,58 @@ static void launch_mt(LinBatch& b, int64_t tiles16, int a_bits, int32_t* acc_out
 //   11008 x 4096: 256 rows 56.0 | 34.6 | 40.2 | 45.7; 333 rows 57.4 | 54.6 | 42.6 | 47.4; 512 rows 57.4 | 57.0 | 71.3 | 49.0
 //   7B layer:     96 rows 93.6 | 83.3 | 66.1 | 69.7; 128 rows 94.3 | 80.2 | 103.6 | 75.0 (int4 100 | 60 | 83 | 61); 192 rows
 //                 95.1 | 107 | 106 | 121
-// So: one round of small blocks first; then blocks that take all rows at once and read the weights once, unless it is one
-// projection that fills more than half of the chip with 128 x 128 tiles (8192 x 28672, 224 of them: 96 rows 49.4 | - | 71.3); then
+// So: one round of small blocks first; then blocks that take all rows at once and read the weights once, while the GEMM's tiles
+// leave enough of the chip idle (tiles_are_better; one projection: half of it with 128 x 128 tiles); then
 // a round and a half (5056 x 5504, 227 rows: 39 | 28), with int4's shorter loads two (8192 x 1024, 2048 rows: 54.2 | 41.6; int8
 // 28672 x 8192, 256 rows, is better on the tiles: 135 | 154).  Fewer than eight runs of weight rows would leave XCDs without work.
-static int block_rows(const LinBatch& b, bool int4)
+// All rows at once in blocks of 96 comes up in batches only: one projection of at most 96 rows with more than 256 such blocks has
+// more than 128 tiles.
+
+// Share of the CUs' time that the GEMM's 256 x 256 tiles use, longest K first.
+static double tile_fill(const LinBatch& b, int64_t& tiles, int& k_max)
+{
+    double work = 0.0;
+    tiles = 0;
+    k_max = 0;
+    for (int i = 0; i < b.count; ++i) {
+        const int64_t t = ((int64_t)b.it[i].M + 255) / 256 * (((int64_t)b.it[i].N + 255) / 256);
+        tiles += t;
+        work += (double)t * b.it[i].K;
+        k_max = b.it[i].K > k_max ? b.it[i].K : k_max;
+    }
+    const double span = (double)((tiles + 255) / 256) * work / (double)tiles;
+    return work / (256.0 * (span > k_max ? span : (double)k_max));
+}
+
+// Whether the GEMM's tiles take at most 128 rows faster than the kernels here: they read the weights at a better rate once
+// enough of them run at a time, and an XCD's tiles share the activations.  Measured, us, GEMM | here, on weights that the
+// caches have not seen, a projection (or two of half the size) K -> N, with the tiles' fill:
+//   single, int8, K = 4096, 64 rows:  N = 32768 (0.50) 38 | 33, 36864 (0.56) 39 | 43, 49152 (0.75) 45 | 54, 65536 (1.0) 56 | 61,
+//     69632 (two rounds, 0.53) 79 | 72, 81920 (0.63) 79 | 79, 131072 (1.0) 100 | 114; int4 98304 (0.75) 61 | 60; 48 rows: 49152
+//     (0.75) 45 | 44, 57344 (0.88) 50 | 57, int4 131072 (1.0) 76 | 69; 32 rows: never behind by more than 5 %
+//   batch of two, int8, K = 4096, 96 rows:  (0.50) 46 | 41, (0.56) 48 | 54, two rounds (0.53) 101 | 90, (0.63) 96 | 93, (0.75) 97 |
+//     112; 128 rows: (0.38) 45 | 44, (0.50) 46 | 46, (0.56) 48 | 63, (0.53) 101 | 101; K = 1024, 128 rows: (0.25) 22 | 16, (0.31)
+//     22 | 24; int4, 96 rows: (0.75) 49 | 47, (0.88) 53 | 59; 128 rows: (0.50) 46 | 38, (0.56) 47 | 53
+//     70B gate and up, 8192 -> 28672 (0.88), int8: 96 rows 104 | 141, 128 rows 107 | 156; int4: 87 | 95, 87 | 119
+//   row-major int8 (64-byte pieces of rows), part of the GEMM's time:  single, K = 8192, 8 rows 0.98 at most, 16 rows (0.44)
+//     0.93, (0.75) 1.07, (0.88) 1.28, 32 rows (0.75) 1.04, (0.88) 1.15, (1.0) 1.19; two, 64 rows: (0.50) 0.78, (0.63) 1.05, (0.75) 1.08
+// The layers of 7B, 13B and 70B (their long down projections leave most CUs to the rest: 0.28, 0.35 and 0.46) are better here.
+static bool tiles_are_better(const LinBatch& b, int rows, int wmode)
+{
+    const bool int4 = wmode == 3, row_major = wmode == 0, single = b.count == 1;
+    int64_t tiles;
+    int k_max;
+    const double fill = tile_fill(b, tiles, k_max);
+    const bool one_round = tiles <= 256;
+    if (rows <= 12) return false;
+    if (rows <= 32) return row_major && k_max >= 4096 && (rows <= 16 ? fill > 0.7 : single && fill > 0.8);
+    if (rows <= 48) return single && fill > 0.8 && (one_round || !int4);
+    if (rows <= 64) return single ? fill > (one_round ? 0.5 : int4 ? 0.8 : 0.7) : row_major && fill > (one_round ? 0.5 : 0.8);
+    if (rows <= 96) return fill > (k_max < 2048 ? 0.5 : !one_round ? 0.7 : int4 ? 0.8 : 0.5);
+    return fill > 0.5 || (!int4 && k_max < 2048 && tiles > 64);
+}
+
+static int block_rows(const LinBatch& b, int wmode)
 {
     int64_t blocks64 = 0, blocks96 = 0, tiles128 = 0;
     int rows = 0;
@@ -287,15 +334,15 @@ static int block_rows(const LinBatch& b, bool int4)
     }
     if (blocks64 <= 256) return 64;
     if (blocks96 <= 256) return 96;
-    if (rows <= 128 && (b.count > 1 || tiles128 <= 128)) return rows <= 96 ? 96 : 128;
-    return blocks64 <= (int4 ? 512 : 384) ? 64 : 0;
+    if (rows <= 128 && (b.count > 1 ? !tiles_are_better(b, rows, wmode) : tiles128 <= 128)) return rows <= 96 ? 96 : 128;
+    return blocks64 <= (wmode == 3 ? 512 : 384) ? 64 : 0;
 }
 
-bool linear_takes_skinny(const LinBatch& b, bool int4)
+bool linear_takes_skinny(const LinBatch& b, int wmode)
 {
     int rows = 0;
     for (int i = 0; i < b.count; ++i) rows = b.it[i].M > rows ? b.it[i].M : rows;
-    return rows <= kSkinnyRows || block_rows(b, int4) != 0;
+    return rows <= kSkinnyRows ? !tiles_are_better(b, rows, wmode) : block_rows(b, wmode) != 0;
 }
 
 template <int DT, int WMODE>
@@ -308,7 +355,7 @@ static void launch_wmode(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, hip
         rows = b.it[i].M > rows ? b.it[i].M : rows;
     }
     if (rows > kSkinnyRows) {
-        switch (block_rows(b, WMODE == 3)) {
+        switch (block_rows(b, WMODE)) {
         case 64:  launch_one<DT, WMODE, 4, 4, 4, 2, false>(b, a_bits, acc_out, st); break;
         case 96:  launch_one<DT, WMODE, 6, 4, 4, 3, false>(b, a_bits, acc_out, st); break;
         default:  launch_one<DT, WMODE, 8, 4, 4, 3, false>(b, a_bits, acc_out, st); break;

@@ -80,3 +80,61 @@ def test_output_over_input_at_few_rows():
     ws = B.new_workspace(B.sasq_static_linear_workspace(*shape, B.SASQ_W_INT8_BLOCKED))
     B.sasq_static_linear(x, dev_scalar(s), wd, torch.from_numpy(s_w).cuda(), None, x, B.SASQ_W_INT8_BLOCKED, ws)
     assert_same_values(to_bits(x), ref["y"], "f16", "Y")
+
+
+def chosen_rows(rows, dims, fmt):
+    """Rows per block the dispatch takes for a batch of at most 128 and more than 64 rows (0: the GEMM's tiles), restated."""
+    cols = [-(-n // 64) for n, _ in dims]
+    if min(cols) < 8:
+        return 0
+    for block in (64, 96):
+        if sum(-(-m // block) * c for m, c in zip(rows, cols)) <= 256:
+            return block
+    tiles, work, k_max = 0, 0, max(k for _, k in dims)
+    for n, k in dims:
+        tiles, work = tiles + -(-n // 256), work + -(-n // 256) * k
+    fill = work / (256 * max(k_max, -(-tiles // 256) * work / tiles))
+    if max(rows) <= 96:
+        line = 0.5 if k_max < 2048 else 0.7 if tiles > 256 else 0.8 if fmt == "int4" else 0.5
+        return 96 if fill <= line else 0
+    return 0 if fill > 0.5 or (fmt != "int4" and k_max < 2048 and tiles > 64) else 128
+
+
+@pytest.mark.parametrize("rows,dims,want", [
+    ((96, 70), [(8200, 128), (8501, 192)], {"int8": 96, "int4": 96}),
+    ((66, 80, 96), [(6000, 128), (6500, 64), (5111, 192)], {"int8": 96, "int4": 96}),
+    ((97, 66), [(8200, 128), (8501, 192)], {"int8": 0, "int4": 128}),
+    ((100, 128), [(8200, 2048), (8501, 2112)], {"int8": 128, "int4": 128}),
+    ((70, 96), [(17000, 128), (17000, 128)], {"int8": 0, "int4": 0}),          # 134 tiles, more than half of a round
+    ((90, 65), [(20000, 2048), (20000, 2048)], {"int8": 0, "int4": 96})])
+@pytest.mark.parametrize("fmt,blocked", LAYOUTS)
+def test_batch_of_row_blocks_matches_oracle(rows, dims, want, fmt, blocked):
+    """Batches with all rows in one block of 96 or 128, unequal M and ragged N, and their neighbours on the GEMM's tiles."""
+    set_tuning()
+    assert chosen_rows(rows, dims, fmt) == want[fmt]
+    items, refs = [], []
+    for i, (m, (n, k)) in enumerate(zip(rows, dims)):
+        xb, wq, s_w, bias, s = problem(90 + i, (m, n, k), fmt, "f16")
+        b = bias if i == 1 else None
+        refs.append(oracle.static_linear(xb, s, wq, s_w, b, 8, fmt, "f16")["y"])
+        items.append((to_dev(xb, "f16"), dev_scalar(s), device_weights(wq, fmt, blocked), torch.from_numpy(s_w).cuda(),
+                      None if b is None else torch.from_numpy(b).cuda(), torch.full((m, n), float("nan"), dtype=torch.float16, device="cuda")))
+    wf = WF[(fmt, blocked)]
+    B.sasq_static_linear_batch(items, wf, B.new_workspace(B.sasq_static_linear_batch_workspace(items, wf)))
+    for it, ref in zip(items, refs):
+        assert_same_values(to_bits(it[5]), ref, "f16", "Y")
+
+
+@pytest.mark.parametrize("fmt,blocked", LAYOUTS)
+@pytest.mark.parametrize("shape", [(64, 32768, 64), (49, 32769, 64), (48, 52480, 64), (33, 52481, 64), (64, 66000, 64), (64, 93000, 64)])
+def test_few_rows_many_columns(shape, fmt, blocked):
+    """Both sides of the lines between the few-row kernels and the GEMM's tiles (half a round, four fifths, a second round)."""
+    set_tuning()
+    M, N, K = shape
+    xb, wq, s_w, bias, s = problem(95, shape, fmt, "bf16")
+    ref = oracle.static_linear(xb, s, wq, s_w, bias, 8, fmt, "bf16")
+    y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    wf = WF[(fmt, blocked)]
+    B.sasq_static_linear(to_dev(xb, "bf16"), dev_scalar(s), device_weights(wq, fmt, blocked), torch.from_numpy(s_w).cuda(),
+                         torch.from_numpy(bias).cuda(), y, wf, B.new_workspace(B.sasq_static_linear_workspace(M, N, K, wf)))
+    assert_same_values(to_bits(y), ref["y"], "bf16", "Y")
