@@ -39,13 +39,7 @@ __device__ __forceinline__ u32x4 load_codes16(const uint8_t* __restrict__ base, 
             for (int b = 0; b < 8; ++b)
                 if (k0 + 2 * b < K) q[b >> 2] |= (uint32_t)p[b] << (8 * (b & 3));
         }
-        // nibble j -> byte j, sign-extended: move it to the top of its byte, then (n ^ 8) - 8 per byte
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            const uint32_t h = q[d >> 1] >> (16 * (d & 1));
-            const uint32_t n4 = (h & 0xFu) | ((h & 0xF0u) << 4) | ((h & 0xF00u) << 8) | ((h & 0xF000u) << 12);
-            v[d] = (n4 | ((n4 & 0x08080808u) * 0x1Eu));      // 8 * 0x1E = 0xF0: the sign bit repeated in the upper nibble
-        }
+        v = widen_int4(u32x2{q[0], q[1]});
     } else {
         const uint8_t* p = base + row * K + k0;
         if (vec) {
@@ -58,9 +52,23 @@ __device__ __forceinline__ u32x4 load_codes16(const uint8_t* __restrict__ base, 
     return v;
 }
 
+// The same for the plain VALU kernel.  WHOLE: rows of whole 16-code pieces; else each piece is one unaligned load and the row's
+// end is shifted into place (byte by byte the loads were most of a call: 64 x 1000 codes by 200 rows in groups of 20 79 us, with
+// this 28; rows shorter than a piece are better off byte by byte).
+template <bool INT4, bool WHOLE>
+__device__ __forceinline__ u32x4 load_codes16_any(const uint8_t* __restrict__ base, int64_t row, bool row_ok, int k0, int K)
+{
+    if (WHOLE || K < 16) return load_codes16<INT4>(base, row, row_ok, k0, K, WHOLE);
+    if (!row_ok || k0 >= K) return u32x4{0u, 0u, 0u, 0u};
+    const int len = INT4 ? K / 2 : K;
+    const uint8_t* p = base + row * len;
+    if constexpr (INT4) return widen_int4(k0 + 16 <= K ? load_piece<u32x2>(p + k0 / 2) : load_piece_edge<u32x2>(p, k0 / 2, len));
+    else                return k0 + 16 <= K ? load_piece<u32x4>(p + k0) : load_piece_edge<u32x4>(p, k0, len);
+}
+
 __device__ __forceinline__ int sext_byte(uint32_t w, int e) { return (int)(w << (24 - 8 * e)) >> 24; }
 
-template <int DT, bool INT4, int MODE, int BM, int BN>
+template <int DT, bool INT4, int MODE, int BM, int BN, bool WHOLE>
 __global__ __launch_bounds__(256) void linear_grouped_valu_kernel(
     const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq, const float* __restrict__ s_g,
     const float* __restrict__ s_w, const float* __restrict__ bias, uint16_t* __restrict__ y,
@@ -75,7 +83,6 @@ __global__ __launch_bounds__(256) void linear_grouped_valu_kernel(
     const int tx = tid & 15, ty = tid >> 4;
     const int tm = (int)blockIdx.x % tiles_m, tn = (int)blockIdx.x / tiles_m;
     const int m0 = tm * BM, n0 = tn * BN;
-    const bool vec = (K & 15) == 0;
 
     // staging: item (row, half) = 16 codes.  W: BN x 2 items from thread 0 on; X: BM x 2 items on the last threads.
     constexpr int kWItems = 2 * BN, kXItems = 2 * BM;
@@ -85,8 +92,8 @@ __global__ __launch_bounds__(256) void linear_grouped_valu_kernel(
     const int xi = tid - (256 - kXItems), xrow = has_x ? xi % BM : 0, xhalf = has_x ? xi / BM : 0;
     u32x4 rw, rx;
     auto fetch = [&](int k0) {
-        if (has_w) rw = load_codes16<INT4>(wq, n0 + wrow, n0 + wrow < N, k0 + 16 * whalf, K, vec);
-        if (has_x) rx = load_codes16<false>(reinterpret_cast<const uint8_t*>(xq), m0 + xrow, m0 + xrow < M, k0 + 16 * xhalf, K, vec);
+        if (has_w) rw = load_codes16_any<INT4, WHOLE>(wq, n0 + wrow, n0 + wrow < N, k0 + 16 * whalf, K);
+        if (has_x) rx = load_codes16_any<false, WHOLE>(reinterpret_cast<const uint8_t*>(xq), m0 + xrow, m0 + xrow < M, k0 + 16 * xhalf, K);
     };
     auto put = [&](int buf) {
         if constexpr (MODE == GV_DOT4) {
@@ -498,8 +505,12 @@ template <int DT, bool INT4, int MODE, int BM, int BN>
 static void launch_gv(const GemmK64Args& a, int64_t group, hipStream_t st)
 {
     const int64_t tm = (a.M + BM - 1) / BM, tn = (a.N + BN - 1) / BN;
-    linear_grouped_valu_kernel<DT, INT4, MODE, BM, BN><<<(unsigned)(tm * tn), 256, 0, st>>>(
-        a.xq, a.wq, a.s, a.s_w, a.bias, a.y, reinterpret_cast<float*>(a.acc_out), (int)a.M, (int)a.N, (int)a.K, (int)group, (int)tm);
+    auto launch = [&](auto whole) {
+        linear_grouped_valu_kernel<DT, INT4, MODE, BM, BN, decltype(whole)::value><<<(unsigned)(tm * tn), 256, 0, st>>>(
+            a.xq, a.wq, a.s, a.s_w, a.bias, a.y, reinterpret_cast<float*>(a.acc_out), (int)a.M, (int)a.N, (int)a.K, (int)group, (int)tm);
+    };
+    if (a.K % 16 == 0) launch(std::true_type{});
+    else               launch(std::false_type{});
 }
 
 template <int DT, bool INT4, int MODE>

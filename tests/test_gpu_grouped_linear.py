@@ -149,6 +149,36 @@ def test_grouped_linear_group_sums_on_matrix_units(group, k, rows, fmt):
     assert_same_values(y, ref["y"], dtype, "Y")
 
 
+VALU_TILES = {(64, 128): (1100, 4200), (64, 64): (300, 4000), (32, 64): (65, 6000), (16, 64): (17, 66)}
+
+
+def valu_tile(m, n):
+    """The tile the dispatch takes for groups without a matrix-unit form, restated."""
+    for (bm, bn), least in (((64, 128), 512), ((64, 64), 256), ((32, 64), 256)):
+        if -(-m // bm) * -(-n // bn) >= least:
+            return bm, bn
+    return 16, 64
+
+
+@pytest.mark.parametrize("fmt", ["int8", "int4"])
+@pytest.mark.parametrize("tile", VALU_TILES)
+@pytest.mark.parametrize("group,k", [(12, 96), (12, 132), (20, 100), (3, 96), (7, 126), (25, 100), (7, 119)])
+def test_grouped_linear_valu_tiles(group, k, tile, fmt):
+    """Packed sums of four and single multiply-adds on each of the four tiles: several slabs of 32 channels, groups across their
+    edges, a part of the last slab over, rows of whole 16-code pieces and not, row and column remainders."""
+    if fmt == "int4" and k % 2:
+        pytest.skip("packed int4 needs an even K")
+    m, n = VALU_TILES[tile]
+    assert valu_tile(m, n) == tile
+    dtype = "f16" if fmt == "int8" else "bf16"
+    xb, wq, s_w, bias, s_g = problem(56, (m, n, k), group, dtype, fmt)
+    ref = oracle.static_linear_grouped(xb, s_g, wq, s_w, bias, group, 8, fmt, dtype)
+    y, f, xq = run_grouped(xb, s_g, wq, s_w, bias, group, fmt, dtype, False)
+    assert np.array_equal(xq, ref["xq"])
+    assert np.array_equal(f, ref["f"])
+    assert_same_values(y, ref["y"], dtype, "Y")
+
+
 def test_grouped_linear_rejects():
     x = torch.zeros((4, 128), dtype=torch.float16, device="cuda")
     y = torch.zeros((4, 4), dtype=torch.float16, device="cuda")
