@@ -120,7 +120,8 @@ __device__ __forceinline__ V load_piece(const uint8_t* __restrict__ p)
     __builtin_memcpy(&v, p, sizeof(V));
     return v;
 }
-// The piece at byte `at` of a row of `len` bytes, zeros past the row's end; nothing outside the row is read.
+// The piece at byte `at`, a multiple of the piece, of a row of `len` bytes, zeros past the row's end; nothing outside the row is
+// read.
 template <typename V>
 __device__ __forceinline__ V load_piece_edge(const uint8_t* __restrict__ row, int64_t at, int64_t len)
 {
@@ -147,16 +148,31 @@ __device__ __forceinline__ V load_piece_edge(const uint8_t* __restrict__ row, in
         }
         return v;
     }
-    V v;
-#pragma unroll
-    for (int d = 0; d < PIECE / 4; ++d) v[d] = 0u;
-#pragma unroll 1
-    for (int b = 0; b < PIECE; ++b)
-        if (at + b < len) {
-            const uint32_t t = (uint32_t)row[at + b] << (8 * (b & 3));
-#pragma unroll
-            for (int d = 0; d < PIECE / 4; ++d) v[d] |= (b >> 2) == d ? t : 0u;
+    // A row shorter than a piece: two overlapping loads of the largest power of two that fits, not a chain of byte loads
+    // (a linear of 512 x 512 outputs over 10 codes 9.6 us with that, 5.5 so).
+    uint64_t lo = 0, hi = 0;
+    if (at == 0) {
+        auto ends = [&](auto first) {
+            decltype(first) last;
+            __builtin_memcpy(&first, row, sizeof(first));
+            __builtin_memcpy(&last, row + len - sizeof(last), sizeof(last));
+            lo = first | (uint64_t)last << (8 * (len - (int64_t)sizeof(last)));
+        };
+        if (PIECE == 16 && len >= 8) {
+            __builtin_memcpy(&lo, row, 8);
+            __builtin_memcpy(&hi, row + len - 8, 8);
+            hi = len == 8 ? 0 : hi >> (8 * (16 - len));
+        } else if (len >= 4) {
+            ends(uint32_t{});
+        } else if (len >= 2) {
+            ends(uint16_t{});
+        } else {
+            lo = row[0];
         }
+    }
+    V v;
+    v[0] = (uint32_t)lo; v[1] = (uint32_t)(lo >> 32);
+    if constexpr (PIECE == 16) { v[2] = (uint32_t)hi; v[3] = (uint32_t)(hi >> 32); }
     return v;
 }
 

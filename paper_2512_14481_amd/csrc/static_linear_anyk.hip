@@ -110,6 +110,25 @@ __global__ __launch_bounds__(256, 2) void linear_anyk_kernel(
         }
     };
 
+    const int wn0 = n0 + (wave >> 1) * (BN / 2), wm0 = m0 + (wave & 1) * (BM / 2);
+    float srow[MF], sw[NF][4], bv[NF][4];
+    auto load_factors = [&]() {
+#pragma unroll
+        for (int b = 0; b < MF; ++b) srow[b] = s_ptr[ROWS ? min(wm0 + b * 16 + frow, M - 1) : 0];
+#pragma unroll
+        for (int g = 0; g < NF; ++g)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int ne = min(wn0 + g * 16 + 4 * fq + e, N - 1);
+                sw[g][e] = s_w[ne];
+                bv[g][e] = bias ? bias[ne] : 0.0f;
+            }
+    };
+    // The small tiles, whose calls are short, request the factors ahead of the operands instead of waiting for them at the end;
+    // the large ones need the registers.
+    constexpr bool kAhead = BN == 64;
+    if (kAhead) load_factors();
+
 #pragma unroll
     for (int j = 0; j < D; ++j)
         if (j < stages) fetch(ring[j], j);
@@ -133,21 +152,11 @@ __global__ __launch_bounds__(256, 2) void linear_anyk_kernel(
     }
 
     // D[i][j]: i <-> n, j <-> m; a lane holds four consecutive columns of one row per 16x16 tile
-    const int wn0 = n0 + (wave >> 1) * (BN / 2), wm0 = m0 + (wave & 1) * (BM / 2);
+    if (!kAhead) load_factors();
     const bool vec = (N & 3) == 0;
-    float srow[MF];
-#pragma unroll
-    for (int b = 0; b < MF; ++b) srow[b] = s_ptr[ROWS ? min(wm0 + b * 16 + frow, M - 1) : 0];
 #pragma unroll
     for (int g = 0; g < NF; ++g) {
         const int n = wn0 + g * 16 + 4 * fq;
-        float sw[4], bv[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int ne = min(n + e, N - 1);
-            sw[e] = s_w[ne];
-            bv[e] = bias ? bias[ne] : 0.0f;
-        }
 #pragma unroll
         for (int b = 0; b < MF; ++b) {
             const int m = wm0 + b * 16 + frow;
@@ -155,8 +164,8 @@ __global__ __launch_bounds__(256, 2) void linear_anyk_kernel(
             float yv[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                yv[e] = (float)acc[g][b][e] * (srow[b] * sw[e]);
-                if (bias) yv[e] = yv[e] + bv[e];
+                yv[e] = (float)acc[g][b][e] * (srow[b] * sw[g][e]);
+                if (bias) yv[e] = yv[e] + bv[g][e];
             }
             const int64_t o = (int64_t)m * N + n;
             if (vec) {
@@ -173,6 +182,40 @@ __global__ __launch_bounds__(256, 2) void linear_anyk_kernel(
             }
         }
     }
+}
+
+// Rows of a few codes, few outputs: one thread per output.  There is next to no work, and the kernel above is as long as its
+// instructions take to arrive.  Measured, us with the pre-pass, this | the tiles: int8, 1 x 20000 outputs, K = 1, 8, 20, 32 3.8 |
+// 5.4, 4.1 | 5.1, 4.9 | 5.4, 7.3 | 5.5; 64 x 1000, K = 20, 24 5.1 | 5.2, 5.3 | 5.1; 512 x 512, K = 4, 8, 12 4.5 | 5.2, 5.2 | 5.1, 5.7 |
+// 5.3; 2000 x 2000, K = 1 10.1 | 8.5; int4, whose rows are half as long: 64 x 1000, K = 32, 48 5.1 | 5.3, 5.8 | 5.5; 512 x 512,
+// K = 12, 20 5.1 | 5.6, 5.7 | 5.7.
+constexpr int64_t kShortRow = 20, kShortRows = 3 << 19;        // bytes of a weight row; the same times the outputs
+
+template <int DT, bool INT4, bool ROWS>
+__global__ __launch_bounds__(256) void linear_short_row_kernel(
+    const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq, const float* __restrict__ s_ptr,
+    const float* __restrict__ s_w, const float* __restrict__ bias, uint16_t* __restrict__ y,
+    int32_t* __restrict__ acc_out, int outputs, int N, int K)
+{
+    const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (i >= outputs) return;
+    const int m = i / N, n = i - m * N;
+    const int8_t* xr = xq + m * K;
+    int acc = 0;
+    if (INT4) {
+        const uint8_t* wr = wq + (int64_t)n * (K / 2);
+        for (int j = 0; j < K / 2; ++j) {
+            const int b = wr[j];
+            acc += (int)xr[2 * j] * (((b & 15) ^ 8) - 8) + (int)xr[2 * j + 1] * (((b >> 4) ^ 8) - 8);
+        }
+    } else {
+        const int8_t* wr = reinterpret_cast<const int8_t*>(wq) + (int64_t)n * K;
+        for (int k = 0; k < K; ++k) acc += (int)xr[k] * (int)wr[k];
+    }
+    float yv = (float)acc * (s_ptr[ROWS ? m : 0] * s_w[n]);
+    if (bias) yv = yv + bias[n];
+    y[i] = Store16<DT>::enc(yv);
+    if (acc_out) acc_out[i] = acc;
 }
 
 template <int DT, bool INT4, bool ROWS, int BM, int BN, int D>
@@ -192,6 +235,12 @@ static void launch_anyk_one(const GemmK64Args& a, hipStream_t st)
 template <int DT, bool INT4, bool ROWS>
 static void launch_anyk_w(const GemmK64Args& a, hipStream_t st)
 {
+    const int64_t wlen = INT4 ? a.K / 2 : a.K;
+    if (wlen <= kShortRow && a.M * a.N * wlen <= kShortRows) {
+        linear_short_row_kernel<DT, INT4, ROWS><<<(unsigned)((a.M * a.N + 255) / 256), 256, 0, st>>>(
+            a.xq, a.wq, a.s, a.s_w, a.bias, a.y, a.acc_out, (int)(a.M * a.N), (int)a.N, (int)a.K);
+        return;
+    }
     auto tiles = [&](int64_t bm, int64_t bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
     if (tiles(128, 128) >= 512)     launch_anyk_one<DT, INT4, ROWS, 128, 128, 2>(a, st);
     else if (tiles(64, 128) >= 256) launch_anyk_one<DT, INT4, ROWS, 64, 128, 2>(a, st);
