@@ -23,47 +23,18 @@ constexpr int kSlab = 32;                          // k per LDS slab
 // packed and v_dot4 sums four products exactly.  ANY: codes as 32-bit integers, one multiply-add each.
 enum { GV_DOT4 = 1, GV_ANY = 2 };
 
-// 16 consecutive codes of a row from k0 on, as bytes; zeros past K or outside the matrix
-template <bool INT4>
-__device__ __forceinline__ u32x4 load_codes16(const uint8_t* __restrict__ base, int64_t row, bool row_ok, int k0, int K, bool vec)
+// 16 consecutive codes of a row from k0 on, a multiple of 16, as bytes; zeros past K or outside the matrix.  One unaligned load,
+// at the row's end shifted into place (byte by byte the loads were most of a call: 64 x 1000 codes by 200 rows in groups of 20
+// 79 us, with this 28).  WHOLE: rows of whole pieces, where no piece has an end to look for.
+template <bool INT4, bool WHOLE = false>
+__device__ __forceinline__ u32x4 load_codes16(const uint8_t* __restrict__ base, int64_t row, bool row_ok, int k0, int K)
 {
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (!row_ok || k0 >= K) return v;
-    if constexpr (INT4) {
-        const uint8_t* p = base + row * (K / 2) + k0 / 2;
-        uint32_t q[2] = {0u, 0u};
-        if (vec) {
-            const u32x2 t = *reinterpret_cast<const u32x2*>(p);
-            q[0] = t[0]; q[1] = t[1];
-        } else {
-            for (int b = 0; b < 8; ++b)
-                if (k0 + 2 * b < K) q[b >> 2] |= (uint32_t)p[b] << (8 * (b & 3));
-        }
-        v = widen_int4(u32x2{q[0], q[1]});
-    } else {
-        const uint8_t* p = base + row * K + k0;
-        if (vec) {
-            v = *reinterpret_cast<const u32x4*>(p);
-        } else {
-            for (int b = 0; b < 16; ++b)
-                if (k0 + b < K) v[b >> 2] |= (uint32_t)p[b] << (8 * (b & 3));
-        }
-    }
-    return v;
-}
-
-// The same for the plain VALU kernel.  WHOLE: rows of whole 16-code pieces; else each piece is one unaligned load and the row's
-// end is shifted into place (byte by byte the loads were most of a call: 64 x 1000 codes by 200 rows in groups of 20 79 us, with
-// this 28; rows shorter than a piece are better off byte by byte).
-template <bool INT4, bool WHOLE>
-__device__ __forceinline__ u32x4 load_codes16_any(const uint8_t* __restrict__ base, int64_t row, bool row_ok, int k0, int K)
-{
-    if (WHOLE || K < 16) return load_codes16<INT4>(base, row, row_ok, k0, K, WHOLE);
     if (!row_ok || k0 >= K) return u32x4{0u, 0u, 0u, 0u};
+    const bool full = WHOLE || k0 + 16 <= K;
     const int len = INT4 ? K / 2 : K;
     const uint8_t* p = base + row * len;
-    if constexpr (INT4) return widen_int4(k0 + 16 <= K ? load_piece<u32x2>(p + k0 / 2) : load_piece_edge<u32x2>(p, k0 / 2, len));
-    else                return k0 + 16 <= K ? load_piece<u32x4>(p + k0) : load_piece_edge<u32x4>(p, k0, len);
+    if constexpr (INT4) return widen_int4(full ? load_piece<u32x2>(p + k0 / 2) : load_piece_edge<u32x2>(p, k0 / 2, len));
+    else                return full ? load_piece<u32x4>(p + k0) : load_piece_edge<u32x4>(p, k0, len);
 }
 
 __device__ __forceinline__ int sext_byte(uint32_t w, int e) { return (int)(w << (24 - 8 * e)) >> 24; }
@@ -92,8 +63,8 @@ __global__ __launch_bounds__(256) void linear_grouped_valu_kernel(
     const int xi = tid - (256 - kXItems), xrow = has_x ? xi % BM : 0, xhalf = has_x ? xi / BM : 0;
     u32x4 rw, rx;
     auto fetch = [&](int k0) {
-        if (has_w) rw = load_codes16_any<INT4, WHOLE>(wq, n0 + wrow, n0 + wrow < N, k0 + 16 * whalf, K);
-        if (has_x) rx = load_codes16_any<false, WHOLE>(reinterpret_cast<const uint8_t*>(xq), m0 + xrow, m0 + xrow < M, k0 + 16 * xhalf, K);
+        if (has_w) rw = load_codes16<INT4, WHOLE>(wq, n0 + wrow, n0 + wrow < N, k0 + 16 * whalf, K);
+        if (has_x) rx = load_codes16<false, WHOLE>(reinterpret_cast<const uint8_t*>(xq), m0 + xrow, m0 + xrow < M, k0 + 16 * xhalf, K);
     };
     auto put = [&](int buf) {
         if constexpr (MODE == GV_DOT4) {
@@ -258,15 +229,14 @@ __global__ __launch_bounds__(256) void linear_per_channel_kernel(
     __shared__ __attribute__((aligned(16))) float ls[2][kOneSlab];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m0 = ((int)blockIdx.x % tiles_m) * BM, n0 = ((int)blockIdx.x / tiles_m) * BN;
-    const bool vec = (K & 15) == 0;
     const int srow = tid >> 2, sch = tid & 3;           // staging: 16 codes of row srow per thread and operand
     const bool has_x = srow < BM;
     u32x4 rw, rx;
     float rs;
     auto fetch = [&](int k0) {
         rs = s_g[min(k0 + (tid & (kOneSlab - 1)), K - 1)];
-        rw = load_codes16<INT4>(wq, n0 + srow, n0 + srow < N, k0 + 16 * sch, K, vec);
-        if (has_x) rx = load_codes16<false>(reinterpret_cast<const uint8_t*>(xq), m0 + srow, m0 + srow < M, k0 + 16 * sch, K, vec);
+        rw = load_codes16<INT4>(wq, n0 + srow, n0 + srow < N, k0 + 16 * sch, K);
+        if (has_x) rx = load_codes16<false>(reinterpret_cast<const uint8_t*>(xq), m0 + srow, m0 + srow < M, k0 + 16 * sch, K);
     };
     auto put = [&](int buf) {
         *reinterpret_cast<u32x4*>(&lw[buf][srow * kOneStride + 16 * sch]) = rw;
@@ -276,6 +246,8 @@ __global__ __launch_bounds__(256) void linear_per_channel_kernel(
     float f[TM];
 #pragma unroll
     for (int i = 0; i < TM; ++i) f[i] = 0.0f;
+    const int n = n0 + lane;
+    const float sw = s_w[min(n, N - 1)], bv = bias ? bias[min(n, N - 1)] : 0.0f;      // requested ahead: a short K has little to hide them
     fetch(0);
     put(0);
     __syncthreads();
@@ -304,9 +276,7 @@ __global__ __launch_bounds__(256) void linear_per_channel_kernel(
             __syncthreads();
         }
     }
-    const int n = n0 + lane;
     if (n >= N) return;
-    const float sw = s_w[n], bv = bias ? bias[n] : 0.0f;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int m = m0 + wave * TM + i;
@@ -358,8 +328,8 @@ __device__ __forceinline__ u32x2 halves4(uint32_t codes)
     return u32x2{__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
 }
 
-template <int DT, bool INT4, int G, int F>
-__global__ __launch_bounds__(256, F == 16 ? 3 : 4) void linear_small_group_kernel(
+template <int DT, bool INT4, int G, int F, bool WHOLE>
+__global__ __launch_bounds__(256, F == 16 || G == 2 ? 3 : 4) void linear_small_group_kernel(
     const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq, const float* __restrict__ s_g,
     const float* __restrict__ s_w, const float* __restrict__ bias, uint16_t* __restrict__ y,
     float* __restrict__ f_out, int M, int N, int K, int tiles_m)
@@ -373,7 +343,6 @@ __global__ __launch_bounds__(256, F == 16 ? 3 : 4) void linear_small_group_kerne
     __shared__ __attribute__((aligned(16))) float ls[2][kSgSlab];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int m0 = ((int)blockIdx.x % tiles_m) * BM, n0 = ((int)blockIdx.x / tiles_m) * BN;
-    const bool vec = (K & 15) == 0;
     // staging: 16 codes of weight row tid/4 per thread and, on the first 4 BM threads, of activation row tid/4; two slabs ahead
     // in registers (one ahead left 64 x 4096 x 4096 waiting for memory in every slab: 133 us)
     const int irow = tid >> 2, ich = tid & 3;
@@ -383,8 +352,8 @@ __global__ __launch_bounds__(256, F == 16 ? 3 : 4) void linear_small_group_kerne
     auto fetch = [&](Slab& r, int k0) {
         const int gi = k0 / G + tid;
         if (tid < kFactors) r.s = gi < K / G ? s_g[gi] : 0.0f;            // past the end: 0 * 0 leaves every sum as it is
-        r.w = load_codes16<INT4>(wq, n0 + irow, n0 + irow < N, k0 + 16 * ich, K, vec);
-        if (has_x) r.x = load_codes16<false>(reinterpret_cast<const uint8_t*>(xq), m0 + irow, m0 + irow < M, k0 + 16 * ich, K, vec);
+        r.w = load_codes16<INT4, WHOLE>(wq, n0 + irow, n0 + irow < N, k0 + 16 * ich, K);
+        if (has_x) r.x = load_codes16<false, WHOLE>(reinterpret_cast<const uint8_t*>(xq), m0 + irow, m0 + irow < M, k0 + 16 * ich, K);
     };
     auto widen = [&](char* dst, const u32x4& v) {
 #pragma unroll
@@ -456,6 +425,13 @@ __global__ __launch_bounds__(256, F == 16 ? 3 : 4) void linear_small_group_kerne
             __builtin_amdgcn_sched_barrier(0x0100);
         }
     };
+    // Four rows: the one column's factors are requested ahead, as a short K has little to hide them behind.
+    float sw = 0.0f, bv = 0.0f;
+    if constexpr (F == 4) {
+        const int n = min(n0 + lane, N - 1);
+        sw = s_w[n];
+        bv = bias ? bias[n] : 0.0f;
+    }
     fetch(ring[0], 0);
     if (slabs > 1) fetch(ring[1], kSgSlab);
     put(ring[0], 0);
@@ -477,12 +453,44 @@ __global__ __launch_bounds__(256, F == 16 ? 3 : 4) void linear_small_group_kerne
     for (int r = 0; r < F; ++r) {
         const int m = m0 + wave * F + O::row(r, lane), n = n0 + O::col(r, lane);
         if (m >= M || n >= N) continue;
-        float yv = f[r] * s_w[n];
-        if (bias) yv = yv + bias[n];
+        float yv = f[r] * (F == 4 ? sw : s_w[n]);
+        if (bias) yv = yv + (F == 4 ? bv : bias[n]);
         const int64_t o = (int64_t)m * N + n;
         y[o] = S::enc(yv);
         if (f_out) f_out[o] = f[r];
     }
+}
+
+// Rows of a few codes, few outputs: one thread per output, as the kernels above take longer to start than there is work.
+// Measured, us with the pre-pass, this | those: 64 x 1000 outputs, K = 2, 4, 8, 12 in groups of two 4.1 | 5.3, 4.4 | 5.4, 5.2 | 5.5,
+// 5.8 | 5.7, one group of 8 4.5 | 4.9; 512 x 512, K = 4, 8 in groups of two 5.1 | 5.7, 5.9 | 5.8.
+constexpr int64_t kShortRow = 12, kShortRows = 1 << 20;        // channels; channels times outputs
+
+template <int DT, bool INT4>
+__global__ __launch_bounds__(256) void linear_grouped_short_row_kernel(
+    const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq, const float* __restrict__ s_g,
+    const float* __restrict__ s_w, const float* __restrict__ bias, uint16_t* __restrict__ y,
+    float* __restrict__ f_out, int outputs, int N, int K, int group)
+{
+    const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+    if (i >= outputs) return;
+    const int m = i / N, n = i - m * N;
+    const int8_t* xr = xq + m * K;
+    const uint8_t* wr = wq + (int64_t)n * (INT4 ? K / 2 : K);
+    float f = 0.0f;
+    for (int k = 0, g = 0; k < K; ++g) {
+        int acc = 0;
+        for (const int end = k + group; k < end; ++k) {
+            const int b = wr[INT4 ? k / 2 : k];
+            const int w = INT4 ? (((k & 1 ? b >> 4 : b & 15) ^ 8) - 8) : (int)(int8_t)b;
+            acc += (int)xr[k] * w;
+        }
+        f = __builtin_fmaf((float)acc, s_g[g], f);
+    }
+    if (f_out) f_out[i] = f;
+    float yv = f * s_w[n];
+    if (bias) yv = yv + bias[n];
+    y[i] = Store16<DT>::enc(yv);
 }
 
 template <int DT, bool INT4, int TM>
@@ -497,8 +505,12 @@ template <int DT, bool INT4, int G, int F>
 static void launch_small_group(const GemmK64Args& a, hipStream_t st)
 {
     const int64_t tm = (a.M + 4 * F - 1) / (4 * F), tn = (a.N + 63) / 64;
-    linear_small_group_kernel<DT, INT4, G, F><<<(unsigned)(tm * tn), 256, 0, st>>>(
-        a.xq, a.wq, a.s, a.s_w, a.bias, a.y, reinterpret_cast<float*>(a.acc_out), (int)a.M, (int)a.N, (int)a.K, (int)tm);
+    auto launch = [&](auto whole) {
+        linear_small_group_kernel<DT, INT4, G, F, decltype(whole)::value><<<(unsigned)(tm * tn), 256, 0, st>>>(
+            a.xq, a.wq, a.s, a.s_w, a.bias, a.y, reinterpret_cast<float*>(a.acc_out), (int)a.M, (int)a.N, (int)a.K, (int)tm);
+    };
+    if (a.K % 16 == 0) launch(std::true_type{});
+    else               launch(std::false_type{});
 }
 
 template <int DT, bool INT4, int MODE, int BM, int BN>
@@ -519,7 +531,8 @@ static void launch_gv_mode(const GemmK64Args& a, int64_t group, hipStream_t st)
     // The larger the thread's block, the fewer LDS reads per operation; the more workgroups, the more waves to issue from
     // (one wave per SIMD issues a VALU operation every 6 cycles, three every 2.8).
     auto tiles = [&](int bm, int bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
-    if (tiles(64, 128) >= 512)     launch_gv<DT, INT4, MODE, 64, 128>(a, group, st);
+    if (a.M <= 16)                 launch_gv<DT, INT4, MODE, 16, 64>(a, group, st);
+    else if (tiles(64, 128) >= 512) launch_gv<DT, INT4, MODE, 64, 128>(a, group, st);
     else if (tiles(64, 64) >= 256) launch_gv<DT, INT4, MODE, 64, 64>(a, group, st);
     else if (tiles(32, 64) >= 256) launch_gv<DT, INT4, MODE, 32, 64>(a, group, st);
     else                           launch_gv<DT, INT4, MODE, 16, 64>(a, group, st);
@@ -533,7 +546,7 @@ template <int DT, bool INT4, int G>
 static void launch_small_group_rows(const GemmK64Args& a, hipStream_t st)
 {
     const int64_t tiles = ((a.M + 63) / 64) * ((a.N + 63) / 64);
-    if (tiles > (G == 1 ? 128 : 192)) launch_small_group<DT, INT4, G, 16>(a, st);
+    if (a.M > 16 && tiles > (G == 1 ? 128 : 192)) launch_small_group<DT, INT4, G, 16>(a, st);
     else if constexpr (G == 1)        launch_per_channel<DT, INT4, 4>(a, st);
     else                              launch_small_group<DT, INT4, G, 4>(a, st);
 }
@@ -541,6 +554,11 @@ static void launch_small_group_rows(const GemmK64Args& a, hipStream_t st)
 template <int DT, bool INT4>
 static void launch_gv_w(const GemmK64Args& a, int64_t group, hipStream_t st)
 {
+    if (a.K <= kShortRow && a.M * a.N * a.K <= kShortRows) {
+        linear_grouped_short_row_kernel<DT, INT4><<<(unsigned)((a.M * a.N + 255) / 256), 256, 0, st>>>(
+            a.xq, a.wq, a.s, a.s_w, a.bias, a.y, reinterpret_cast<float*>(a.acc_out), (int)(a.M * a.N), (int)a.N, (int)a.K, (int)group);
+        return;
+    }
     switch (group) {
         case 1: launch_small_group_rows<DT, INT4, 1>(a, st); break;
         case 2: launch_small_group_rows<DT, INT4, 2>(a, st); break;

@@ -179,6 +179,24 @@ def test_grouped_linear_valu_tiles(group, k, tile, fmt):
     assert_same_values(y, ref["y"], dtype, "Y")
 
 
+@pytest.mark.parametrize("fmt", ["int8", "int4"])
+@pytest.mark.parametrize("rows", [(700, 2100), (64, 999), (7, 12300), (16, 20001), (17, 12300)])
+@pytest.mark.parametrize("group,k", [(1, 1), (1, 7), (2, 2), (3, 3), (1, 12), (2, 12), (4, 12), (6, 12), (12, 12), (1, 13), (8, 24), (3, 24), (1, 30), (2, 30)])
+def test_grouped_linear_short_rows(group, k, rows, fmt):
+    """Rows of a few channels: one thread per output while there are few outputs, the other kernels past that; at most 16 rows by
+    many columns, which take the narrow forms."""
+    if fmt == "int4" and k % 2:
+        pytest.skip("packed int4 needs an even K")
+    dtype = "bf16" if fmt == "int8" else "f16"
+    xb, wq, s_w, bias, s_g = problem(57, (*rows, k), group, dtype, fmt)
+    for b in (None, bias):
+        ref = oracle.static_linear_grouped(xb, s_g, wq, s_w, b, group, 8, fmt, dtype)
+        y, f, xq = run_grouped(xb, s_g, wq, s_w, b, group, fmt, dtype, False)
+        assert np.array_equal(xq, ref["xq"])
+        assert np.array_equal(f, ref["f"])
+        assert_same_values(y, ref["y"], dtype, "Y")
+
+
 def test_grouped_linear_rejects():
     x = torch.zeros((4, 128), dtype=torch.float16, device="cuda")
     y = torch.zeros((4, 4), dtype=torch.float16, device="cuda")
