@@ -25,27 +25,37 @@ __device__ __forceinline__ int64_t bwd_weight_offset(int64_t k, int64_t n, int64
     return ((k >> 4) * (Npad / kBwdCols) + (n >> 5)) * 1024 + ((4 * r + (c ^ swz64(r))) << 4) + ((n & 7) << 1);
 }
 
-// The transpose goes through LDS: a workgroup takes 32 rows of W (one block column) x 512 codes, 128-byte pieces of the rows
+// The transpose goes through LDS: a workgroup takes 32 rows of W (one block column) x WK codes, 128-byte pieces of the rows
 // in, whole 1 KB blocks out, lane l of a wave writing the block's 16-byte chunk l from eight byte reads.  Bound by its bytes,
 // one in and two out per weight: 11008 x 4096 and 4096 x 11008 22.7 us, 6.0 TB/s (a thread per chunk that read its eight codes
 // from memory one by one: 63 on average, 47 to 97).
-constexpr int kBwdPrepK = 512, kBwdPrepStride = kBwdPrepK + 16;
-template <int DT, bool INT4>
+// WK: 512, or 128 where workgroups of 512 would leave CUs without work or be mostly past the row's end.  Measured, us, a thread per
+// chunk | 512 | 128 codes: 16 x 64 2.6 | 2.8 | 2.4, 256 x 256 3.3 | 3.6 | 2.7, 100 x 1000 3.3 | 4.3 | 2.7, 1024 x 2048 6.0 | 4.3 | 3.7,
+// 16384 x 64 3.7 | 3.8 | 3.2.
+template <int DT, bool INT4, int WK>
 __global__ __launch_bounds__(256) void prepare_bwd_weight_kernel(
     const uint8_t* __restrict__ wq, const float* __restrict__ s_w, uint8_t* __restrict__ out,
     int64_t N, int64_t K, int64_t Npad, int64_t Kpad, uint32_t ktiles)
 {
     using S = Store16<DT>;
     using Piece = std::conditional_t<INT4, u32x2, u32x4>;
-    constexpr int kPiece = (int)sizeof(Piece), kPieces = kBwdPrepK / 16 / 8;
-    __shared__ __attribute__((aligned(16))) int8_t tile[kBwdCols][kBwdPrepStride];
-    const int64_t k0 = (int64_t)(blockIdx.x % ktiles) * kBwdPrepK, n0 = (int64_t)(blockIdx.x / ktiles) * kBwdCols;
+    constexpr int kPiece = (int)sizeof(Piece), kPieces = WK / 16 / 8;
+    __shared__ __attribute__((aligned(16))) int8_t tile[kBwdCols][WK + 16];
+    const int64_t k0 = (int64_t)(blockIdx.x % ktiles) * WK, n0 = (int64_t)(blockIdx.x / ktiles) * kBwdCols;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = lane >> 2, c = (lane & 3) ^ swz64(r);
+    float sw[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {                      // requested with the codes, not behind the barrier
+        const float f = s_w[min(n0 + 8 * c + e, N - 1)];
+        sw[e] = n0 + 8 * c + e < N ? f : 0.0f;
+    }
     {
         const int64_t row = n0 + (threadIdx.x >> 3), len = INT4 ? K / 2 : K;
         const uint8_t* src = wq + min(row, N - 1) * len;
         const int64_t at = (k0 >> 4) * kPiece + (threadIdx.x & 7) * kPiece;
         Piece v[kPieces];
-        if (k0 + kBwdPrepK <= K) {
+        if (k0 + WK <= K) {
 #pragma unroll
             for (int j = 0; j < kPieces; ++j) v[j] = load_piece<Piece>(src + at + j * 8 * kPiece);
         } else {
@@ -54,21 +64,16 @@ __global__ __launch_bounds__(256) void prepare_bwd_weight_kernel(
         }
 #pragma unroll
         for (int j = 0; j < kPieces; ++j) {
-            u32x4 c;
-            if constexpr (INT4) c = widen_int4(v[j]);
-            else                c = v[j];
-            if (row >= N) c = u32x4{0u, 0u, 0u, 0u};
-            *reinterpret_cast<u32x4*>(&tile[threadIdx.x >> 3][((threadIdx.x & 7) + 8 * j) * 16]) = c;
+            u32x4 codes;
+            if constexpr (INT4) codes = widen_int4(v[j]);
+            else                codes = v[j];
+            if (row >= N) codes = u32x4{0u, 0u, 0u, 0u};
+            *reinterpret_cast<u32x4*>(&tile[threadIdx.x >> 3][((threadIdx.x & 7) + 8 * j) * 16]) = codes;
         }
     }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int r = lane >> 2, c = (lane & 3) ^ swz64(r);
-    float sw[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) sw[e] = n0 + 8 * c + e < N ? s_w[n0 + 8 * c + e] : 0.0f;
     __syncthreads();
 #pragma unroll 2
-    for (int b = wave; b < kBwdPrepK / 16; b += 4) {
+    for (int b = wave; b < WK / 16; b += 4) {
         const int64_t k = k0 + 16 * b + r;
         if (k0 + 16 * b >= Kpad) break;
         u32x4 o;
@@ -385,19 +390,24 @@ extern "C" int sasq_prepare_bwd_weight(const void* wq, const float* s_w, void* w
     if (!aligned16(wt)) return SASQ_ERR_ALIGN;
     hipStream_t st = as_stream(stream);
     const int64_t Kpad = bwd_kpad(K), Npad = bwd_npad(N);
-    const uint32_t ktiles = (uint32_t)((Kpad + kBwdPrepK - 1) / kBwdPrepK);
-    const int64_t grid = ktiles * (Npad / kBwdCols);
+    auto tiles = [&](int64_t wk) { return (Kpad + wk - 1) / wk; };
+    const bool narrow = Kpad <= 256 || tiles(512) * (Npad / kBwdCols) < 256;
+    const int64_t ktiles = tiles(narrow ? 128 : 512), grid = ktiles * (Npad / kBwdCols);
     if (grid > 0x7FFFFFFF) return SASQ_ERR_SHAPE;
-    const auto* W = static_cast<const uint8_t*>(wq);
-    auto* O = static_cast<uint8_t*>(wt);
-    const bool i4 = wf == SASQ_W_INT4_PACKED;
-    if (dt == SASQ_F16) {
-        if (i4) prepare_bwd_weight_kernel<SASQ_F16, true><<<(unsigned)grid, 256, 0, st>>>(W, s_w, O, N, K, Npad, Kpad, ktiles);
-        else    prepare_bwd_weight_kernel<SASQ_F16, false><<<(unsigned)grid, 256, 0, st>>>(W, s_w, O, N, K, Npad, Kpad, ktiles);
-    } else {
-        if (i4) prepare_bwd_weight_kernel<SASQ_BF16, true><<<(unsigned)grid, 256, 0, st>>>(W, s_w, O, N, K, Npad, Kpad, ktiles);
-        else    prepare_bwd_weight_kernel<SASQ_BF16, false><<<(unsigned)grid, 256, 0, st>>>(W, s_w, O, N, K, Npad, Kpad, ktiles);
-    }
+    auto launch = [&](auto dt_tag, auto i4_tag, auto wk_tag) {
+        prepare_bwd_weight_kernel<decltype(dt_tag)::value, decltype(i4_tag)::value, decltype(wk_tag)::value><<<(unsigned)grid, 256, 0, st>>>(
+            static_cast<const uint8_t*>(wq), s_w, static_cast<uint8_t*>(wt), N, K, Npad, Kpad, (uint32_t)ktiles);
+    };
+    auto by_width = [&](auto dt_tag, auto i4_tag) {
+        if (narrow) launch(dt_tag, i4_tag, std::integral_constant<int, 128>{});
+        else        launch(dt_tag, i4_tag, std::integral_constant<int, 512>{});
+    };
+    auto by_format = [&](auto dt_tag) {
+        if (wf == SASQ_W_INT4_PACKED) by_width(dt_tag, std::true_type{});
+        else                          by_width(dt_tag, std::false_type{});
+    };
+    if (dt == SASQ_F16) by_format(std::integral_constant<int, SASQ_F16>{});
+    else                by_format(std::integral_constant<int, SASQ_BF16>{});
     return hipGetLastError() == hipSuccess ? SASQ_OK : SASQ_ERR_LAUNCH;
 }
 

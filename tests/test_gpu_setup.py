@@ -36,7 +36,8 @@ def test_quantize_weight_rows(k, fmt):
 
 
 @pytest.mark.parametrize("fmt,dtype", [("int8", "f16"), ("int4", "bf16")])
-@pytest.mark.parametrize("shape", [(1, 2), (31, 14), (32, 16), (33, 18), (64, 510), (40, 512), (65, 514), (7, 1376), (96, 1030)])
+@pytest.mark.parametrize("shape", [(1, 2), (31, 14), (32, 16), (33, 18), (64, 510), (40, 512), (65, 514), (7, 1376), (96, 1030),
+                                   (33, 126), (17, 128), (65, 130), (20, 258), (900, 4626), (913, 4608)])      # widths of 128 codes, and of 512 (from 256 of those)
 def test_prepared_weight(shape, fmt, dtype):
     N, K = shape
     wq, s_w = oracle.quantize_weight(wl.random_f32(33, f"pw{shape}", shape, 0.02), fmt)
