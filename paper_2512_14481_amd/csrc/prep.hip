@@ -9,6 +9,7 @@ constexpr int kPrepThreads = 256;
 constexpr int kMaxAbsmaxBlocks = 2048;       // partials the workspace has room for
 constexpr int kAbsmaxBlocks = 256;           // one per CU: every block ends with a ticket on one address
 constexpr int kAbsmaxThreads = 512, kAbsmaxUnroll = 4;   // 128-bit loads in flight per thread
+constexpr int kAbsmaxThreadsOnce = 256, kAbsmaxBlocksOnce = 128;
 
 __global__ void fill_zero_kernel(uint32_t* p, int64_t nwords)
 {
@@ -152,8 +153,11 @@ __global__ __launch_bounds__(kPrepThreads) void pack_weight_i4_kernel(
 // every block adds its ticket to one address.  45 MB 13 us, 17 MB 9 (one load at a time from 2048 blocks: 34 and 18; 256
 // threads with eight loads but no loads ahead: 19 and 6; the set-up of a 7B MLP as a whole: 270 us with 512 blocks of those,
 // 262 with 256, 260 with this).
-template <int DT>
-__global__ __launch_bounds__(kAbsmaxThreads) void absmax_kernel(
+// ONCE: every thread's loads are in flight at once and there is no loop; smaller blocks, as there is little to keep them busy.
+// Measured, us, looping | once: 8 values 4.4 | 3.7, 64 x 4096 5.0 | 4.5, 128 x 4096 5.2 | 4.8, 256 x 4096 (128 blocks) 5.8 | 5.7,
+// 512 x 4096 6.4 | 7.0.
+template <int DT, int THREADS, bool ONCE>
+__global__ __launch_bounds__(THREADS) void absmax_kernel(
     const uint16_t* __restrict__ x, float* __restrict__ s, uint32_t* __restrict__ ws_head,
     uint32_t* __restrict__ partials, int64_t n, int bits)
 {
@@ -162,26 +166,33 @@ __global__ __launch_bounds__(kAbsmaxThreads) void absmax_kernel(
     const int64_t nvec = n / 8;
     const u32x4* xv = reinterpret_cast<const u32x4*>(x);
     if (nvec > 0) {
-        const int64_t step = (int64_t)gridDim.x * kAbsmaxThreads * kAbsmaxUnroll;
-        int64_t base = (int64_t)blockIdx.x * kAbsmaxThreads * kAbsmaxUnroll + threadIdx.x;
+        const int64_t step = (int64_t)gridDim.x * THREADS * kAbsmaxUnroll;
+        int64_t base = (int64_t)blockIdx.x * THREADS * kAbsmaxUnroll + threadIdx.x;
         u32x4 cur[kAbsmaxUnroll], next[kAbsmaxUnroll];
         auto load = [&](u32x4 (&v)[kAbsmaxUnroll], int64_t from) {
 #pragma unroll
             for (int u = 0; u < kAbsmaxUnroll; ++u)      // past the end: the last vector again, which cannot change a maximum
-                v[u] = __builtin_nontemporal_load(&xv[min(from + u * kAbsmaxThreads, nvec - 1)]);
+                v[u] = __builtin_nontemporal_load(&xv[min(from + u * THREADS, nvec - 1)]);
         };
-        load(cur, base);
-        for (; base - (int64_t)threadIdx.x < nvec; base += step) {
-            load(next, base + step);
+        auto take = [&](const u32x4 (&v)[kAbsmaxUnroll]) {
 #pragma unroll
-            for (int u = 0; u < kAbsmaxUnroll; ++u) {
+            for (int u = 0; u < kAbsmaxUnroll; ++u)
 #pragma unroll
                 for (int w = 0; w < 4; ++w) {
-                    uint32_t lo = cur[u][w] & 0x7FFFu, hi = (cur[u][w] >> 16) & 0x7FFFu;
+                    uint32_t lo = v[u][w] & 0x7FFFu, hi = (v[u][w] >> 16) & 0x7FFFu;
                     m = lo > m ? lo : m;
                     m = hi > m ? hi : m;
                 }
-                cur[u] = next[u];
+        };
+        load(cur, base);
+        if (ONCE) {
+            take(cur);
+        } else {
+            for (; base - (int64_t)threadIdx.x < nvec; base += step) {
+                load(next, base + step);
+                take(cur);
+#pragma unroll
+                for (int u = 0; u < kAbsmaxUnroll; ++u) cur[u] = next[u];
             }
         }
     }
@@ -189,13 +200,13 @@ __global__ __launch_bounds__(kAbsmaxThreads) void absmax_kernel(
         uint32_t a = x[nvec * 8 + threadIdx.x] & 0x7FFFu;
         m = a > m ? a : m;
     }
-    __shared__ uint32_t sh[kAbsmaxThreads / kWave];
+    __shared__ uint32_t sh[THREADS / kWave];
     __shared__ bool is_last;
     m = wave_max(m);
     if (threadIdx.x % kWave == 0) sh[threadIdx.x / kWave] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 1; i < kAbsmaxThreads / kWave; ++i) m = sh[i] > m ? sh[i] : m;
+        for (int i = 1; i < THREADS / kWave; ++i) m = sh[i] > m ? sh[i] : m;
         const uint32_t ticket = publish_then_ticket(&partials[blockIdx.x], m, &ws_head[0]);
         is_last = (ticket == kTicketBase + gridDim.x - 1);
         if (ticket - kTicketBase >= gridDim.x) *s = __uint_as_float(0x7FC00000u);
@@ -203,14 +214,14 @@ __global__ __launch_bounds__(kAbsmaxThreads) void absmax_kernel(
     __syncthreads();
     if (!is_last) return;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    static_assert(kAbsmaxBlocks <= kAbsmaxThreads, "one partial per thread");
+    static_assert(kAbsmaxBlocks <= THREADS, "one partial per thread");
     uint32_t t = __hip_atomic_load(&partials[threadIdx.x < gridDim.x ? threadIdx.x : 0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     t = wave_max(t);                                              // a duplicate of partial 0 cannot change a max
     __syncthreads();
     if (threadIdx.x % kWave == 0) sh[threadIdx.x / kWave] = t;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 0; i < kAbsmaxThreads / kWave; ++i) t = sh[i] > t ? sh[i] : t;
+        for (int i = 0; i < THREADS / kWave; ++i) t = sh[i] > t ? sh[i] : t;
         float amax = S::one((uint16_t)t);
         *s = amax / (float)((1 << (bits - 1)) - 1);
         __hip_atomic_store(&ws_head[0], kTicketBase, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -347,14 +358,22 @@ extern "C" int sasq_absmax_scale(const void* x, float* s, int64_t rows, int64_t 
     if (!workspace || workspace_bytes < sasq_absmax_scale_workspace(rows, cols)) return SASQ_ERR_WORKSPACE;
     if (!aligned16(workspace)) return SASQ_ERR_ALIGN;
     const int64_t n = rows * cols;
-    const int64_t need = (n / 8 + kAbsmaxThreads * kAbsmaxUnroll - 1) / (kAbsmaxThreads * kAbsmaxUnroll);
-    const int grid = (int)(need < 1 ? 1 : (need > kAbsmaxBlocks ? kAbsmaxBlocks : need));
+    auto blocks = [&](int threads) { return (n / 8 + threads * kAbsmaxUnroll - 1) / (threads * kAbsmaxUnroll); };
     auto head = static_cast<uint32_t*>(workspace);
     auto parts = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + kWsHeaderBytes);
     hipStream_t st = as_stream(stream);
-    if (dt == SASQ_F16)
-        absmax_kernel<SASQ_F16><<<grid, kAbsmaxThreads, 0, st>>>(static_cast<const uint16_t*>(x), s, head, parts, n, bits);
-    else
-        absmax_kernel<SASQ_BF16><<<grid, kAbsmaxThreads, 0, st>>>(static_cast<const uint16_t*>(x), s, head, parts, n, bits);
+    auto launch = [&](auto dt_tag, auto threads_tag, auto once_tag) {
+        constexpr int T = decltype(threads_tag)::value;
+        const int64_t need = blocks(T);
+        const int grid = (int)(need < 1 ? 1 : (need > kAbsmaxBlocks ? kAbsmaxBlocks : need));
+        absmax_kernel<decltype(dt_tag)::value, T, decltype(once_tag)::value><<<grid, T, 0, st>>>(
+            static_cast<const uint16_t*>(x), s, head, parts, n, bits);
+    };
+    auto by_size = [&](auto dt_tag) {
+        if (blocks(kAbsmaxThreadsOnce) <= kAbsmaxBlocksOnce) launch(dt_tag, std::integral_constant<int, kAbsmaxThreadsOnce>{}, std::true_type{});
+        else                                             launch(dt_tag, std::integral_constant<int, kAbsmaxThreads>{}, std::false_type{});
+    };
+    if (dt == SASQ_F16) by_size(std::integral_constant<int, SASQ_F16>{});
+    else                by_size(std::integral_constant<int, SASQ_BF16>{});
     return hipGetLastError() == hipSuccess ? SASQ_OK : SASQ_ERR_LAUNCH;
 }

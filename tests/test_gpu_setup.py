@@ -58,7 +58,8 @@ def test_prepared_weight_odd_rows(k):
     assert np.array_equal(unblock(wt.cpu().numpy(), 37, k)[:k, :37], want)
 
 
-@pytest.mark.parametrize("n", [1, 7, 8, 9, 8 * 256 * 8 - 8, 8 * 256 * 8 + 11, 8 * 256 * 8 * 600 + 3])
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 8 * 256 * 8 - 8, 8 * 256 * 8 + 11, 8 * 256 * 8 * 600 + 3,
+                               8 * 1024 + 9, 8 * 1024 * 128, 8 * 1024 * 128 + 7, 8 * 1024 * 128 + 8])      # one pass of up to 128 blocks, and past it
 def test_absmax_sizes(n):
     xb = wl.random_bits(37, f"am{n}", (1, n), "bf16", gain=1.0)
     for at in {0, n - 1, n // 2}:
