@@ -228,7 +228,8 @@ __global__ __launch_bounds__(THREADS) void absmax_kernel(
     }
 }
 
-// Rows of up to 8192 weights: 256 threads, up to 32768: 1024 (eight pieces per thread at most); longer or ragged ones take the
+// Rows of up to 256 weights: one wave, which needs no barrier (20000 x 64 6.9 us, with 256 threads 12.7, as many as with the
+// general kernel), up to 8192: 256 threads, up to 32768: 1024 (eight pieces per thread at most); longer or ragged ones take the
 // general kernel.
 template <bool INT4>
 static void quantize_weight(const float* w, uint8_t* wq, float* s_w, int64_t N, int64_t K, hipStream_t st)
@@ -255,7 +256,8 @@ static void quantize_weight(const float* w, uint8_t* wq, float* s_w, int64_t N, 
             default: launch(threads_tag, std::integral_constant<int, 8>{}); break;
         }
     };
-    if (K <= 8192) by_pieces(std::integral_constant<int, 256>{});
+    if (K <= 256) launch(std::integral_constant<int, kWave>{}, std::integral_constant<int, 1>{});
+    else if (K <= 8192) by_pieces(std::integral_constant<int, 256>{});
     else           by_pieces(std::integral_constant<int, 1024>{});
 }
 

@@ -1,5 +1,5 @@
 """GPU parity of the set-up kernels at the edges of their forms: weight quantization by whole 128-bit pieces (K % 4 == 0, up to
-32768) and by the general kernel, the prepared backward weight at ragged sizes and alignments, absmax around its load batches."""
+256 in one wave, up to 32768) and by the general kernel, the prepared backward weight at ragged sizes and alignments, absmax around its load batches."""
 from __future__ import annotations
 
 import numpy as np
@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("fmt", ["int8", "int4"])
-@pytest.mark.parametrize("k", [2, 4, 6, 1020, 1024, 1028, 5120, 8188, 8192, 8196, 11008, 13824, 28672, 32768, 32772])
+@pytest.mark.parametrize("k", [2, 4, 6, 60, 252, 256, 260, 1020, 1024, 1028, 5120, 8188, 8192, 8196, 11008, 13824, 28672, 32768, 32772])
 def test_quantize_weight_rows(k, fmt):
     n = 5
     w = wl.random_f32(31, f"qw{k}", (n, k), 0.02)
