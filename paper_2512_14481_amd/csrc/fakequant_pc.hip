@@ -33,10 +33,11 @@ static int64_t pc_fwd_rows(int64_t blocks16)
 }
 // Backward, where the rows per block decide how ds is rounded: they follow from the tensor alone, never from what shares its
 // launch, so that a batch gives the bits of the single calls.  16 for a tensor of at most 64 such blocks, 64 for one that has
-// 512 of those.  Measured, us with 16 | 32 | 64 rows, one tensor, then seven in a launch: 512 x 512 (32 blocks of 16) 8.3 | 9.3 |
-// 11.8, 12.0 | 11.5 | 13.3; 128 x 4096 (64) 8.4 | 9.5 | 11.6, 12.5 | 12.4 | 14.3; 256 x 4096 (128) 9.4 | 9.7 | 12.0, 19.6 | 15.6 |
-// 16.6; 1777 x 5120 (280 of 64) 26.3 | 19.8 | 20.3, 99.5 | 74.9 | 73.5; 4096 x 4096 (512) 28.9 | 29.0 | 25.9, 138 | 138 | 139;
-// 4096 x 5120 (640) 33.0 | 33.0 | 29.7, 169 | 169 | 165.
+// more than 512 of those.  Measured, us with 16 | 32 | 64 rows, one tensor, then seven in a launch: 512 x 512 (32 blocks of 16)
+// 7.5 | 9.0 | 11.8, 10.8 | 10.2 | 13.3; 128 x 4096 (64) 7.7 | 9.1 | 11.6, 11.3 | 11.3 | 14.3; 300 x 2048 (76) 8.2 | 9.4 | -, 14.1 |
+// 13.4 | -, four 12.1 | 11.2; 256 x 4096 (128) 8.6 | 9.4 | 12.0, 17.0 | 14.7 | 16.6; 1777 x 5120 (280 of 64) 26.3 | 19.6 | 20.3, 99 |
+// 74 | 74; 4096 x 4096 (512) 28.9 | 29.2 | 28.3, 138 | 138 | 142, four - | 77 | 81; 4096 x 5120 (640) 33.0 | 32.6 | 29.7, 169 | 169 |
+// 164.
 // (The long chunks' sums are no less exact: fp64 from four rows on; ds is off by 5.2e-8 of its norm, 5.9e-8 with fp32 chunks of
 // 16 rows, 8.8e-8 with those of 32.)
 constexpr int kPcMinRowsShort = 16, kPcMinRowsLong = 64;
@@ -441,7 +442,7 @@ static void pc_geometry_bwd(int64_t rows, int64_t cols, int64_t& col_blocks, int
 {
     auto blocks = [&](int64_t n) { return (cols + kPcColsPerBlock - 1) / kPcColsPerBlock * ((rows + n - 1) / n); };
     const int64_t rows_min = blocks(kPcMinRowsShort) <= kPcShortBlocks ? kPcMinRowsShort
-                           : blocks(kPcMinRowsLong) >= kPcLongBlocks ? kPcMinRowsLong : kPcMinRows;
+                           : blocks(kPcMinRowsLong) > kPcLongBlocks ? kPcMinRowsLong : kPcMinRows;
     pc_geometry(rows, cols, rows_min, col_blocks, rpc, chunks);
 }
 

@@ -124,7 +124,7 @@ def test_per_channel_batch_with_long_chunks():
 
 
 # rows per block of 16, 32 and 64 in the backward, at the edges of the rule; launches of few and of thousands of blocks
-BATCHES = [[(2113, 4096)] * 8, [(128, 4096), (129, 4096), (1024, 512), (1025, 512), (3, 8)], [(4096, 4096), (4032, 4096), (64, 264), (700, 2048)]]
+BATCHES = [[(2113, 4096)] * 8, [(128, 4096), (129, 4096), (1024, 512), (1025, 512), (3, 8)], [(4096, 4096), (4160, 4096), (64, 264), (700, 2048)]]
 
 
 @pytest.mark.parametrize("shapes", BATCHES, ids=["many_blocks", "short", "long"])
