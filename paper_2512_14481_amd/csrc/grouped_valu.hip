@@ -43,7 +43,7 @@ template <int DT, bool INT4, int MODE, int BM, int BN, bool WHOLE>
 __global__ __launch_bounds__(256) void linear_grouped_valu_kernel(
     const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq, const float* __restrict__ s_g,
     const float* __restrict__ s_w, const float* __restrict__ bias, uint16_t* __restrict__ y,
-    float* __restrict__ f_out, int M, int N, int K, int group, int tiles_m)
+    float* __restrict__ f_out, int M, int N, int K, int group, int tiles_m, int first)
 {
     using S = Store16<DT>;
     constexpr int TM = BM / 16, TN = BN / 16, TNV = TN / 4;
@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256) void linear_grouped_valu_kernel(
     __shared__ __attribute__((aligned(16))) int lw[2][kSteps][BN];
     const int tid = threadIdx.x;
     const int tx = tid & 15, ty = tid >> 4;
-    const int tm = (int)blockIdx.x % tiles_m, tn = (int)blockIdx.x / tiles_m;
+    const int tile = first + (int)blockIdx.x, tm = tile % tiles_m, tn = tile / tiles_m;
     const int m0 = tm * BM, n0 = tn * BN;
 
     // staging: item (row, half) = 16 codes.  W: BN x 2 items from thread 0 on; X: BM x 2 items on the last threads.
@@ -220,7 +220,7 @@ template <int DT, bool INT4, int TM>
 __global__ __launch_bounds__(256) void linear_per_channel_kernel(
     const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq, const float* __restrict__ s_g,
     const float* __restrict__ s_w, const float* __restrict__ bias, uint16_t* __restrict__ y,
-    float* __restrict__ f_out, int M, int N, int K, int tiles_m)
+    float* __restrict__ f_out, int M, int N, int K, int tiles_m, int first)
 {
     using S = Store16<DT>;
     constexpr int BM = 4 * TM, BN = 64;
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(256) void linear_per_channel_kernel(
     __shared__ __attribute__((aligned(16))) uint8_t lw[2][BN * kOneStride];
     __shared__ __attribute__((aligned(16))) float ls[2][kOneSlab];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m0 = ((int)blockIdx.x % tiles_m) * BM, n0 = ((int)blockIdx.x / tiles_m) * BN;
+    const int tile = first + (int)blockIdx.x, m0 = (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
     const int srow = tid >> 2, sch = tid & 3;           // staging: 16 codes of row srow per thread and operand
     const bool has_x = srow < BM;
     u32x4 rw, rx;
@@ -332,7 +332,7 @@ template <int DT, bool INT4, int G, int F, bool WHOLE>
 __global__ __launch_bounds__(256, F == 16 || G == 2 ? 3 : 4) void linear_small_group_kernel(
     const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq, const float* __restrict__ s_g,
     const float* __restrict__ s_w, const float* __restrict__ bias, uint16_t* __restrict__ y,
-    float* __restrict__ f_out, int M, int N, int K, int tiles_m)
+    float* __restrict__ f_out, int M, int N, int K, int tiles_m, int first)
 {
     using S = Store16<DT>;
     using O = Outer<F>;
@@ -342,7 +342,7 @@ __global__ __launch_bounds__(256, F == 16 || G == 2 ? 3 : 4) void linear_small_g
     __shared__ __attribute__((aligned(16))) char lw[2][BN * kSgStride];
     __shared__ __attribute__((aligned(16))) float ls[2][kSgSlab];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int m0 = ((int)blockIdx.x % tiles_m) * BM, n0 = ((int)blockIdx.x / tiles_m) * BN;
+    const int tile = first + (int)blockIdx.x, m0 = (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
     // staging: 16 codes of weight row tid/4 per thread and, on the first 4 BM threads, of activation row tid/4; two slabs ahead
     // in registers (one ahead left 64 x 4096 x 4096 waiting for memory in every slab: 133 us)
     const int irow = tid >> 2, ich = tid & 3;
@@ -497,8 +497,10 @@ template <int DT, bool INT4, int TM>
 static void launch_per_channel(const GemmK64Args& a, hipStream_t st)
 {
     const int64_t tm = (a.M + 4 * TM - 1) / (4 * TM), tn = (a.N + 63) / 64;
-    linear_per_channel_kernel<DT, INT4, TM><<<(unsigned)(tm * tn), 256, 0, st>>>(
-        a.xq, a.wq, a.s, a.s_w, a.bias, a.y, reinterpret_cast<float*>(a.acc_out), (int)a.M, (int)a.N, (int)a.K, (int)tm);
+    launch_in_parts(tm * tn, 256, [&](unsigned blocks, int first) {
+        linear_per_channel_kernel<DT, INT4, TM><<<blocks, 256, 0, st>>>(
+            a.xq, a.wq, a.s, a.s_w, a.bias, a.y, reinterpret_cast<float*>(a.acc_out), (int)a.M, (int)a.N, (int)a.K, (int)tm, first);
+    });
 }
 
 template <int DT, bool INT4, int G, int F>
@@ -506,8 +508,10 @@ static void launch_small_group(const GemmK64Args& a, hipStream_t st)
 {
     const int64_t tm = (a.M + 4 * F - 1) / (4 * F), tn = (a.N + 63) / 64;
     auto launch = [&](auto whole) {
-        linear_small_group_kernel<DT, INT4, G, F, decltype(whole)::value><<<(unsigned)(tm * tn), 256, 0, st>>>(
-            a.xq, a.wq, a.s, a.s_w, a.bias, a.y, reinterpret_cast<float*>(a.acc_out), (int)a.M, (int)a.N, (int)a.K, (int)tm);
+        launch_in_parts(tm * tn, 256, [&](unsigned blocks, int first) {
+            linear_small_group_kernel<DT, INT4, G, F, decltype(whole)::value><<<blocks, 256, 0, st>>>(
+                a.xq, a.wq, a.s, a.s_w, a.bias, a.y, reinterpret_cast<float*>(a.acc_out), (int)a.M, (int)a.N, (int)a.K, (int)tm, first);
+        });
     };
     if (a.K % 16 == 0) launch(std::true_type{});
     else               launch(std::false_type{});
@@ -518,8 +522,10 @@ static void launch_gv(const GemmK64Args& a, int64_t group, hipStream_t st)
 {
     const int64_t tm = (a.M + BM - 1) / BM, tn = (a.N + BN - 1) / BN;
     auto launch = [&](auto whole) {
-        linear_grouped_valu_kernel<DT, INT4, MODE, BM, BN, decltype(whole)::value><<<(unsigned)(tm * tn), 256, 0, st>>>(
-            a.xq, a.wq, a.s, a.s_w, a.bias, a.y, reinterpret_cast<float*>(a.acc_out), (int)a.M, (int)a.N, (int)a.K, (int)group, (int)tm);
+        launch_in_parts(tm * tn, 256, [&](unsigned blocks, int first) {
+            linear_grouped_valu_kernel<DT, INT4, MODE, BM, BN, decltype(whole)::value><<<blocks, 256, 0, st>>>(
+                a.xq, a.wq, a.s, a.s_w, a.bias, a.y, reinterpret_cast<float*>(a.acc_out), (int)a.M, (int)a.N, (int)a.K, (int)group, (int)tm, first);
+        });
     };
     if (a.K % 16 == 0) launch(std::true_type{});
     else               launch(std::false_type{});

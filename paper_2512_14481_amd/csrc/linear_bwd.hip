@@ -35,13 +35,14 @@ __device__ __forceinline__ int64_t bwd_weight_offset(int64_t k, int64_t n, int64
 template <int DT, bool INT4, int WK>
 __global__ __launch_bounds__(256) void prepare_bwd_weight_kernel(
     const uint8_t* __restrict__ wq, const float* __restrict__ s_w, uint8_t* __restrict__ out,
-    int64_t N, int64_t K, int64_t Npad, int64_t Kpad, uint32_t ktiles)
+    int64_t N, int64_t K, int64_t Npad, int64_t Kpad, uint32_t ktiles, uint32_t first)
 {
     using S = Store16<DT>;
     using Piece = std::conditional_t<INT4, u32x2, u32x4>;
     constexpr int kPiece = (int)sizeof(Piece), kPieces = WK / 16 / 8;
     __shared__ __attribute__((aligned(16))) int8_t tile[kBwdCols][WK + 16];
-    const int64_t k0 = (int64_t)(blockIdx.x % ktiles) * WK, n0 = (int64_t)(blockIdx.x / ktiles) * kBwdCols;
+    const uint32_t id = first + blockIdx.x;
+    const int64_t k0 = (int64_t)(id % ktiles) * WK, n0 = (int64_t)(id / ktiles) * kBwdCols;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane >> 2, c = (lane & 3) ^ swz64(r);
     float sw[8];
@@ -395,8 +396,10 @@ extern "C" int sasq_prepare_bwd_weight(const void* wq, const float* s_w, void* w
     const int64_t ktiles = tiles(narrow ? 128 : 512), grid = ktiles * (Npad / kBwdCols);
     if (grid > 0x7FFFFFFF) return SASQ_ERR_SHAPE;
     auto launch = [&](auto dt_tag, auto i4_tag, auto wk_tag) {
-        prepare_bwd_weight_kernel<decltype(dt_tag)::value, decltype(i4_tag)::value, decltype(wk_tag)::value><<<(unsigned)grid, 256, 0, st>>>(
-            static_cast<const uint8_t*>(wq), s_w, static_cast<uint8_t*>(wt), N, K, Npad, Kpad, (uint32_t)ktiles);
+        launch_in_parts(grid, 256, [&](unsigned blocks, int first) {
+            prepare_bwd_weight_kernel<decltype(dt_tag)::value, decltype(i4_tag)::value, decltype(wk_tag)::value><<<blocks, 256, 0, st>>>(
+                static_cast<const uint8_t*>(wq), s_w, static_cast<uint8_t*>(wt), N, K, Npad, Kpad, (uint32_t)ktiles, (uint32_t)first);
+        });
     };
     auto by_width = [&](auto dt_tag, auto i4_tag) {
         if (narrow) launch(dt_tag, i4_tag, std::integral_constant<int, 128>{});

@@ -229,12 +229,12 @@ __global__ __launch_bounds__(THREADS) void absmax_kernel(
 }
 
 // Rows of up to 256 weights: one wave, which needs no barrier (20000 x 64 6.9 us, with 256 threads 12.7, as many as with the
-// general kernel), up to 8192: 256 threads, up to 32768: 1024 (eight pieces per thread at most); longer or ragged ones take the
-// general kernel.
+// general kernel), up to 8192: 256 threads, up to 32768: 1024 (eight pieces per thread at most); longer or ragged ones, and
+// more rows than a launch holds workgroups of 1024 threads, take the general kernel.
 template <bool INT4>
 static void quantize_weight(const float* w, uint8_t* wq, float* s_w, int64_t N, int64_t K, hipStream_t st)
 {
-    if ((K & 3) || K > 32768) {
+    if ((K & 3) || K > 32768 || (K > 8192 && N >= INT64_C(1) << 22)) {
         quantize_weight_kernel<INT4><<<(int)N, kPrepThreads, 0, st>>>(w, wq, s_w, K);
         return;
     }

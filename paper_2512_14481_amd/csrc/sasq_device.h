@@ -245,4 +245,15 @@ inline int tuning(int knob) { return g_tuning[knob]; }
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// A launch holds fewer than 2^32 work items along x; of more, HIP drops the upper bits without an error, or refuses the launch.  A
+// call of that many goes in several launches, each told the number of its first workgroup (one output row of 2^30 columns is 2^24
+// tiles of 256 threads).  launch(workgroups, first)
+template <typename Launch>
+static inline void launch_in_parts(int64_t blocks, int threads, Launch&& launch)
+{
+    const int64_t most = (INT64_C(1) << 31) / threads;                 // a multiple of the eight XCDs
+    for (int64_t first = 0; first < blocks; first += most)
+        launch((unsigned)(blocks - first < most ? blocks - first : most), (int)first);
+}
+
 }  // namespace sasq

@@ -24,7 +24,7 @@ template <int DT, bool INT4, bool ROWS, int BM, int BN, int D>
 __global__ __launch_bounds__(256, 2) void linear_anyk_kernel(
     const uint8_t* __restrict__ xq, const uint8_t* __restrict__ wq, const float* __restrict__ s_ptr,
     const float* __restrict__ s_w, const float* __restrict__ bias, uint16_t* __restrict__ y,
-    int32_t* __restrict__ acc_out, int M, int N, int K, int tiles_m, int tiles_n)
+    int32_t* __restrict__ acc_out, int M, int N, int K, int tiles_m, int tiles_n, int first)
 {
     using S = Store16<DT>;
     using WPiece = std::conditional_t<INT4, u32x2, u32x4>;
@@ -34,7 +34,7 @@ __global__ __launch_bounds__(256, 2) void linear_anyk_kernel(
     __shared__ __attribute__((aligned(128))) char lds[2 * kBufBytes];
 
     int tm, tn;
-    if (!tile_of_block((int)blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
+    if (!tile_of_block(first + (int)blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
     const int m0 = tm * BM, n0 = tn * BN;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int stages = (K + kAnyStage - 1) / kAnyStage;
@@ -222,9 +222,10 @@ template <int DT, bool INT4, bool ROWS, int BM, int BN, int D>
 static void launch_anyk_one(const GemmK64Args& a, hipStream_t st)
 {
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (int)((a.N + BN - 1) / BN);
-    const int grid = (tiles_m * tiles_n + 7) / 8 * 8;
-    linear_anyk_kernel<DT, INT4, ROWS, BM, BN, D><<<grid, 256, 0, st>>>(
-        reinterpret_cast<const uint8_t*>(a.xq), a.wq, a.s, a.s_w, a.bias, a.y, a.acc_out, (int)a.M, (int)a.N, (int)a.K, tiles_m, tiles_n);
+    launch_in_parts((tiles_m * tiles_n + 7) / 8 * 8, 256, [&](unsigned blocks, int first) {
+        linear_anyk_kernel<DT, INT4, ROWS, BM, BN, D><<<blocks, 256, 0, st>>>(
+            reinterpret_cast<const uint8_t*>(a.xq), a.wq, a.s, a.s_w, a.bias, a.y, a.acc_out, (int)a.M, (int)a.N, (int)a.K, tiles_m, tiles_n, first);
+    });
 }
 
 // Big tiles read the operands less often, small ones put more CUs to work.  Measured, int8, us on 128x128 / 64x128 / 64x64 /

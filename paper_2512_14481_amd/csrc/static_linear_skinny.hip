@@ -341,7 +341,12 @@ static int block_rows(const LinBatch& b, int wmode)
 bool linear_takes_skinny(const LinBatch& b, int wmode)
 {
     int rows = 0;
-    for (int i = 0; i < b.count; ++i) rows = b.it[i].M > rows ? b.it[i].M : rows;
+    int64_t cols = 0;
+    for (int i = 0; i < b.count; ++i) {
+        rows = b.it[i].M > rows ? b.it[i].M : rows;
+        cols += b.it[i].N;
+    }
+    if (cols > INT64_C(1) << 28) return false;         // up to 8 work items a column, and a launch holds fewer than 2^32
     return rows <= kSkinnyRows ? !tiles_are_better(b, rows, wmode) : block_rows(b, wmode) != 0;
 }
 
