@@ -33,15 +33,19 @@ static int64_t pc_fwd_rows(int64_t blocks16)
 }
 // Backward, where the rows per block decide how ds is rounded: they follow from the tensor alone, never from what shares its
 // launch, so that a batch gives the bits of the single calls.  16 for a tensor of at most 64 such blocks, 64 for one that has
-// more than 512 of those.  Measured, us with 16 | 32 | 64 rows, one tensor, then seven in a launch: 512 x 512 (32 blocks of 16)
-// 7.5 | 9.0 | 11.8, 10.8 | 10.2 | 13.3; 128 x 4096 (64) 7.7 | 9.1 | 11.6, 11.3 | 11.3 | 14.3; 300 x 2048 (76) 8.2 | 9.4 | -, 14.1 |
-// 13.4 | -, four 12.1 | 11.2; 256 x 4096 (128) 8.6 | 9.4 | 12.0, 17.0 | 14.7 | 16.6; 1777 x 5120 (280 of 64) 26.3 | 19.6 | 20.3, 99 |
-// 74 | 74; 4096 x 4096 (512) 28.9 | 29.2 | 28.3, 138 | 138 | 142, four - | 77 | 81; 4096 x 5120 (640) 33.0 | 32.6 | 29.7, 169 | 169 |
-// 164.
+// more than 512 of those, of more than 256 if it is wide and has at least 704 rows (a wide tensor's rows are long enough to keep
+// the memory busy from fewer blocks, and blocks of 32 rows compute its factors twice as often).  Measured, us with 16 | 32 | 64
+// rows, one tensor, then seven in a launch: 512 x 512 (32 blocks of 16) 7.5 | 9.0 | 11.8, 10.8 | 10.2 | 13.3; 128 x 4096 (64) 7.7 |
+// 9.1 | 11.6, 11.3 | 11.3 | 14.3; 300 x 2048 (76) 8.2 | 9.4 | -, 14.1 | 13.4 | -, four 12.1 | 11.2; 256 x 4096 (128) 8.6 | 9.4 | 12.0,
+// 17.0 | 14.7 | 16.6; with 32 | 64 rows, one tensor, two, seven (28672: four): 1777 x 5120 (280 blocks of 64) 19.6 | 19.9, 28.5 |
+// 29.4, 74.7 | 74.0, a layer of 13B 76 | 74; 2048 x 5120 (320) 19.6 | 20.2, 31.4 | 30.1, 84.5 | 83.1; 1024 x 13824 (432) 22.6 | 21.9,
+// 38.5 | 39.8, 124 | 115; 400 x 28672 (392) 18.8 | 20.2, 31.5 | 31.7, 54.5 | 57.3; 2100 x 4096 (264) 20.6 | 20.3, 30.0 | 32.3, 70 | 75;
+// 3000 x 4096 (376) 23.6 | 21.7, 36.6 | 35.8, 95 | 98; 4096 x 4096 (512) 29.1 | 30.5, 46 | 49, 139 | 147; 4096 x 5120 (640) 32.6 |
+// 29.7, -, 169 | 164.
 // (The long chunks' sums are no less exact: fp64 from four rows on; ds is off by 5.2e-8 of its norm, 5.9e-8 with fp32 chunks of
 // 16 rows, 8.8e-8 with those of 32.)
 constexpr int kPcMinRowsShort = 16, kPcMinRowsLong = 64;
-constexpr int64_t kPcShortBlocks = 64, kPcLongBlocks = 512;
+constexpr int64_t kPcShortBlocks = 64, kPcLongBlocks = 512, kPcLongBlocksWide = 256, kPcWideCols = 4608, kPcWideRows = 704;
 
 struct PcConst {
     float inv_s[8];
@@ -147,15 +151,17 @@ __global__ __launch_bounds__(kPcThreads) void fakequant_fwd_pc_kernel(
 }
 
 // SHORT: chunks of 16 rows, four a wave: a thread's sum is the fp32 sum of four rows and needs no fp64 before the waves meet, and
-// there is no loop.  The same bits; 512 x 512 8.0 us in the general form, 7.5 in this, 64 x 4096 7.8 and 7.3.
+// there is no loop.  The same bits; 512 x 512 8.0 us in the general form, 7.5 in this, 64 x 4096 7.8 and 7.3.  A kernel has one form:
+// with both the bf16 batch needs 173 registers, which leaves two waves a SIMD instead of three.
 template <int DT, bool WRITE_DX, bool SHORT>
-__device__ __forceinline__ void bwd_pc_rows(
+__device__ __forceinline__ void bwd_pc_body(
     const uint16_t* __restrict__ x, const uint16_t* dy, const float* __restrict__ s,
     uint16_t* dx, float* __restrict__ ds, uint32_t* __restrict__ tickets, float* __restrict__ partials,
     int64_t rows, int64_t cols, int64_t rows_per_chunk, int bits,
     int col_block, int row_chunk, int nchunks, double (&red)[kPcWaves][kPcColsPerBlock], bool& is_last)
 {
     using S = Store16<DT>;
+    static_assert(kPcWaves * kPcRowUnroll == 16, "a chunk of 16 rows is one group");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t cbase = (int64_t)col_block * kPcColsPerBlock;
     const int64_t col0 = cbase + lane * 8;
@@ -311,21 +317,7 @@ __device__ __forceinline__ void bwd_pc_rows(
     if (threadIdx.x == 0) __hip_atomic_store(&tickets[col_block], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int DT, bool WRITE_DX>
-__device__ __forceinline__ void bwd_pc_body(
-    const uint16_t* __restrict__ x, const uint16_t* dy, const float* __restrict__ s,
-    uint16_t* dx, float* __restrict__ ds, uint32_t* __restrict__ tickets, float* __restrict__ partials,
-    int64_t rows, int64_t cols, int64_t rows_per_chunk, int bits,
-    int col_block, int row_chunk, int nchunks, double (&red)[kPcWaves][kPcColsPerBlock], bool& is_last)
-{
-    static_assert(kPcWaves * kPcRowUnroll == 16, "a chunk of 16 rows is one group");
-    if (rows_per_chunk <= 16)
-        bwd_pc_rows<DT, WRITE_DX, true>(x, dy, s, dx, ds, tickets, partials, rows, cols, rows_per_chunk, bits, col_block, row_chunk, nchunks, red, is_last);
-    else
-        bwd_pc_rows<DT, WRITE_DX, false>(x, dy, s, dx, ds, tickets, partials, rows, cols, rows_per_chunk, bits, col_block, row_chunk, nchunks, red, is_last);
-}
-
-template <int DT, bool WRITE_DX>
+template <int DT, bool WRITE_DX, bool SHORT>
 __global__ __launch_bounds__(kPcThreads) void fakequant_bwd_pc_kernel(
     const uint16_t* __restrict__ x, const uint16_t* dy, const float* __restrict__ s,
     uint16_t* dx, float* __restrict__ ds, uint32_t* __restrict__ tickets, float* __restrict__ partials,
@@ -333,8 +325,8 @@ __global__ __launch_bounds__(kPcThreads) void fakequant_bwd_pc_kernel(
 {
     __shared__ double red[kPcWaves][kPcColsPerBlock];
     __shared__ bool is_last;
-    bwd_pc_body<DT, WRITE_DX>(x, dy, s, dx, ds, tickets, partials, rows, cols, rows_per_chunk, bits,
-                              (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.y, red, is_last);
+    bwd_pc_body<DT, WRITE_DX, SHORT>(x, dy, s, dx, ds, tickets, partials, rows, cols, rows_per_chunk, bits,
+                                     (int)blockIdx.x, (int)blockIdx.y, (int)gridDim.y, red, is_last);
 }
 
 // ---- several tensors in one launch -------------------------------------------------------------
@@ -375,7 +367,7 @@ __global__ __launch_bounds__(kPcThreads) void fakequant_fwd_pc_batch_kernel(cons
     fwd_pc_body<DT, false>(it.x, it.s, it.out, nullptr, it.rows, it.cols, it.rpc, bits, lb % it.col_blocks, lb / it.col_blocks);
 }
 
-template <int DT>
+template <int DT, bool SHORT>
 __global__ __launch_bounds__(kPcThreads) void fakequant_bwd_pc_batch_kernel(const PcBatch b, int bits)
 {
     __shared__ double red[kPcWaves][kPcColsPerBlock];
@@ -384,10 +376,10 @@ __global__ __launch_bounds__(kPcThreads) void fakequant_bwd_pc_batch_kernel(cons
     const PcItem& it = b.it[k];
     const int lb = (int)blockIdx.x - b.first_block[k];
     const int cb = lb % it.col_blocks, rc = lb / it.col_blocks;
-    if (it.out) bwd_pc_body<DT, true>(it.x, it.dy, it.s, it.out, it.ds, it.tickets, it.partials, it.rows, it.cols, it.rpc, bits,
-                                      cb, rc, it.chunks, red, is_last);
-    else        bwd_pc_body<DT, false>(it.x, it.dy, it.s, nullptr, it.ds, it.tickets, it.partials, it.rows, it.cols, it.rpc, bits,
-                                       cb, rc, it.chunks, red, is_last);
+    if (it.out) bwd_pc_body<DT, true, SHORT>(it.x, it.dy, it.s, it.out, it.ds, it.tickets, it.partials, it.rows, it.cols, it.rpc, bits,
+                                             cb, rc, it.chunks, red, is_last);
+    else        bwd_pc_body<DT, false, SHORT>(it.x, it.dy, it.s, nullptr, it.ds, it.tickets, it.partials, it.rows, it.cols, it.rpc, bits,
+                                              cb, rc, it.chunks, red, is_last);
 }
 
 // cols not a multiple of 8: one thread per column walks the rows (rarely used, kept simple)
@@ -442,7 +434,8 @@ static void pc_geometry_bwd(int64_t rows, int64_t cols, int64_t& col_blocks, int
 {
     auto blocks = [&](int64_t n) { return (cols + kPcColsPerBlock - 1) / kPcColsPerBlock * ((rows + n - 1) / n); };
     const int64_t rows_min = blocks(kPcMinRowsShort) <= kPcShortBlocks ? kPcMinRowsShort
-                           : blocks(kPcMinRowsLong) > kPcLongBlocks ? kPcMinRowsLong : kPcMinRows;
+                           : blocks(kPcMinRowsLong) > (cols > kPcWideCols && rows >= kPcWideRows ? kPcLongBlocksWide : kPcLongBlocks) ? kPcMinRowsLong
+                           : kPcMinRows;
     pc_geometry(rows, cols, rows_min, col_blocks, rpc, chunks);
 }
 
@@ -523,13 +516,20 @@ extern "C" int sasq_fakequant_bwd_pc(const void* x, const void* dy, const float*
     dim3 grid((unsigned)col_blocks, (unsigned)chunks);
     auto tickets = static_cast<uint32_t*>(workspace);
     auto parts = reinterpret_cast<float*>(static_cast<char*>(workspace) + kWsHeaderBytes);
-    if (dt == SASQ_F16) {
-        if (dx) fakequant_bwd_pc_kernel<SASQ_F16, true><<<grid, kPcThreads, 0, st>>>(X, G, s, DX, ds, tickets, parts, rows, cols, rpc, bits);
-        else    fakequant_bwd_pc_kernel<SASQ_F16, false><<<grid, kPcThreads, 0, st>>>(X, G, s, DX, ds, tickets, parts, rows, cols, rpc, bits);
-    } else {
-        if (dx) fakequant_bwd_pc_kernel<SASQ_BF16, true><<<grid, kPcThreads, 0, st>>>(X, G, s, DX, ds, tickets, parts, rows, cols, rpc, bits);
-        else    fakequant_bwd_pc_kernel<SASQ_BF16, false><<<grid, kPcThreads, 0, st>>>(X, G, s, DX, ds, tickets, parts, rows, cols, rpc, bits);
-    }
+    auto launch = [&](auto dt_tag, auto dx_tag, auto short_tag) {
+        fakequant_bwd_pc_kernel<decltype(dt_tag)::value, decltype(dx_tag)::value, decltype(short_tag)::value><<<grid, kPcThreads, 0, st>>>(
+            X, G, s, DX, ds, tickets, parts, rows, cols, rpc, bits);
+    };
+    auto by_chunk = [&](auto dt_tag, auto dx_tag) {
+        if (rpc <= 16) launch(dt_tag, dx_tag, std::true_type{});
+        else           launch(dt_tag, dx_tag, std::false_type{});
+    };
+    auto by_dx = [&](auto dt_tag) {
+        if (dx) by_chunk(dt_tag, std::true_type{});
+        else    by_chunk(dt_tag, std::false_type{});
+    };
+    if (dt == SASQ_F16) by_dx(std::integral_constant<int, SASQ_F16>{});
+    else                by_dx(std::integral_constant<int, SASQ_BF16>{});
     return hipGetLastError() == hipSuccess ? SASQ_OK : SASQ_ERR_LAUNCH;
 }
 
@@ -585,7 +585,7 @@ static int launch_pc_batch(const sasq_fq_item* items, int i0, int i1, int bits, 
 {
     PcBatch b;
     memset(&b, 0, sizeof(b));
-    int64_t blocks = 0, blocks16 = 0;
+    int64_t blocks = 0, blocks16 = 0, longest = 0;
     for (int i = i0; i < i1; ++i) blocks16 += pc_blocks16(items[i].rows, items[i].cols);
     for (int i = i0; i < i1; ++i) {
         const sasq_fq_item& src = items[i];
@@ -593,6 +593,7 @@ static int launch_pc_batch(const sasq_fq_item* items, int i0, int i1, int bits, 
         int64_t col_blocks;
         if (BACKWARD) pc_geometry_bwd(src.rows, src.cols, col_blocks, it.rpc, it.chunks);
         else          pc_geometry(src.rows, src.cols, pc_fwd_rows(blocks16), col_blocks, it.rpc, it.chunks);
+        longest = it.rpc > longest ? it.rpc : longest;
         it.col_blocks = (int)col_blocks;
         it.x = static_cast<const uint16_t*>(src.x);
         it.dy = static_cast<const uint16_t*>(src.dy);
@@ -612,8 +613,13 @@ static int launch_pc_batch(const sasq_fq_item* items, int i0, int i1, int bits, 
     b.count = i1 - i0;
     b.first_block[b.count] = (int)blocks;
     if (BACKWARD) {
-        if (dt == SASQ_F16) fakequant_bwd_pc_batch_kernel<SASQ_F16><<<(int)blocks, kPcThreads, 0, st>>>(b, bits);
-        else                fakequant_bwd_pc_batch_kernel<SASQ_BF16><<<(int)blocks, kPcThreads, 0, st>>>(b, bits);
+        auto launch = [&](auto dt_tag) {                     // chunks of 16 rows beside longer ones take the general form
+            constexpr int DT = decltype(dt_tag)::value;
+            if (longest <= 16) fakequant_bwd_pc_batch_kernel<DT, true><<<(int)blocks, kPcThreads, 0, st>>>(b, bits);
+            else               fakequant_bwd_pc_batch_kernel<DT, false><<<(int)blocks, kPcThreads, 0, st>>>(b, bits);
+        };
+        if (dt == SASQ_F16) launch(std::integral_constant<int, SASQ_F16>{});
+        else                launch(std::integral_constant<int, SASQ_BF16>{});
     } else {
         if (dt == SASQ_F16) fakequant_fwd_pc_batch_kernel<SASQ_F16><<<(int)blocks, kPcThreads, 0, st>>>(b, bits);
         else                fakequant_fwd_pc_batch_kernel<SASQ_BF16><<<(int)blocks, kPcThreads, 0, st>>>(b, bits);

@@ -124,10 +124,11 @@ def test_per_channel_batch_with_long_chunks():
 
 
 # rows per block of 16, 32 and 64 in the backward, at the edges of the rule; launches of few and of thousands of blocks
-BATCHES = [[(2113, 4096)] * 8, [(128, 4096), (129, 4096), (1024, 512), (1025, 512), (3, 8)], [(4096, 4096), (4160, 4096), (64, 264), (700, 2048)]]
+BATCHES = [[(2113, 4096)] * 8, [(128, 4096), (129, 4096), (1024, 512), (1025, 512), (3, 8)], [(4096, 4096), (4160, 4096), (64, 264), (700, 2048)],
+           [(1600, 5120), (1664, 5120), (640, 13824), (704, 13824)], [(128, 4096), (3, 8), (512, 512)]]
 
 
-@pytest.mark.parametrize("shapes", BATCHES, ids=["many_blocks", "short", "long"])
+@pytest.mark.parametrize("shapes", BATCHES, ids=["many_blocks", "short", "long", "wide", "all_short"])
 def test_per_channel_batch_equals_single_calls(shapes):
     """An item's ds (and dx) has the bits of the single-tensor call whatever else is in the launch."""
     g = torch.Generator(device="cuda").manual_seed(45)
