@@ -588,11 +588,11 @@ def main():
             grouped[f"group_{group}"] = {"achieved": round(tot_ops / (tot_ms * 1e-3) / 1e12, 1), "unit": "TOP/s",
                                          "frac": round(tot_ops / (tot_ms * 1e-3) / 1e12 / INT8_MFMA_PEAK_TOPS, 4),
                                          "us_per_call": round(1e3 * tot_ms / calls, 1), "calls": calls}
-        # the strict per-channel case (group = 1) has no MFMA form: a scalar kernel, timed once on the gate projection
+        # the strict per-channel case (group = 1): a kernel of its own, timed once on the gate projection
         p = projs[0]
         if p.wf in (B.SASQ_W_INT8, B.SASQ_W_INT4_PACKED):
             wq1, wf1 = p.wq, p.wf
-        else:                                              # the scalar kernel takes the row-major interchange format
+        else:                                              # it takes the row-major interchange format
             wf1 = B.SASQ_W_INT8 if cfg.w_fmt == wl.W_INT8 else B.SASQ_W_INT4_PACKED
             w = torch.from_numpy(wl.weight_fp32(cfg, p.name)).cuda()
             wq1 = torch.empty((p.N, p.K if wf1 == B.SASQ_W_INT8 else p.K // 2),
@@ -608,7 +608,7 @@ def main():
         torch.cuda.synchronize()
         ms1 = e0.elapsed_time(e1)
         grouped["group_1"] = {"achieved": round(p.ops / (ms1 * 1e-3) / 1e12, 2), "unit": "TOP/s", "us_per_call": round(1e3 * ms1, 1),
-                              "calls": 1, "note": "scalar kernel (one thread per output), gate projection, one timed call"}
+                              "calls": 1, "note": "group sums on the matrix units, one fp32 multiply-add per channel and output on the VALUs; gate projection, one timed call"}
         del wq1, sg1
         grouped["note"] = ("sasq_static_linear_grouped on the projections whose K the group divides "
                            "(gate, up, down for 32 and 128; gate, up for 512); warm repeat of 5.  group_32 "

@@ -308,8 +308,10 @@ int sasq_static_linear_batch(const sasq_linear_item* items, int count, int a_bit
  *   group    divides K.  The MFMA path is taken when K and group are multiples of 64 (then all
  *            four weight formats are accepted), and for group = 32 with K a multiple of 64 and
  *            any format but row-major int4 (each 64-channel K tile is then multiplied twice, one
- *            half of the channels at a time); other shapes run on the VALUs and accept the
- *            row-major weight formats only (SASQ_ERR_SHAPE for the pre-arranged ones).
+ *            half of the channels at a time); other shapes have kernels of their own (on the VALUs;
+ *            groups of 2, 4, 8 and 16, and of 1 with more than a few rows, form their sums on the
+ *            matrix units) and accept the row-major weight formats only (SASQ_ERR_SHAPE for the
+ *            pre-arranged ones).
  *   every other argument, the workspace size and the limits are those of sasq_static_linear.
  */
 int sasq_static_linear_grouped(const void* x, const float* s_g, const void* wq, const float* s_w,

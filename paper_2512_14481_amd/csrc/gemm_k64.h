@@ -23,7 +23,7 @@ void launch_gemm_k64(const GemmK64Args& a, sasq_dtype dt, int wmode, int tile, b
 // Grouped activation factors (a.s points at K / (64 group_tiles) factors, a.acc_out receives the fp32 sums):
 // tile 1 = 128x256, 2 = 128x128.  group_tiles = 0: groups of 32 channels (two per K tile; 128x128 tiles).
 void launch_gemm_k64_grouped(const GemmK64Args& a, sasq_dtype dt, int wmode, int tile, int group_tiles, hipStream_t st);
-// Group sizes without a matrix-unit form (grouped_valu.hip): row-major weights, row-major activation codes in a.xq, any
+// Every other group size (grouped_valu.hip): row-major weights, row-major activation codes in a.xq, any
 // group that divides K.
 void launch_grouped_valu(const GemmK64Args& a, sasq_dtype dt, bool int4, int64_t group, hipStream_t st);
 // K not a multiple of 64 (static_linear_anyk.hip): row-major activation codes in a.xq, row-major int8 or packed int4 weights.

@@ -68,7 +68,7 @@ __device__ __forceinline__ void lds_load16(uint32_t lds_a, uint32_t lds_b, const
 // GROUPED = 2: groups of 32 channels, two per K tile.  One MFMA contracts the whole 64-byte stage, so every K tile
 // is multiplied twice, once with the activation fragments of channels 32..63 zeroed and once with those of 0..31
 // zeroed (lanes 32..63 resp. 0..31 of a fragment), each pass into zero accumulators and folded with its own factor:
-// twice the matrix work and a fold per 32 channels, an order of magnitude faster than the scalar kernel all the same.
+// twice the matrix work and a fold per 32 channels, and faster than sums on the VALUs all the same.
 // OP 1: the same machine on v_mfma_f32_16x16x32_{f16,bf16} (DT picks the type): both operands hold 16-bit floats, 32
 // per 64-byte stage row; the "activation" operand xq is then read ROW-MAJOR (rows of K bytes, the 16-byte chunks of a
 // row gathered per lane as for row-major weights), the weight operand from 1 KB blocks; K is the contraction length in

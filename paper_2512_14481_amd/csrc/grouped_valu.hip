@@ -19,8 +19,7 @@ namespace sasq {
 
 constexpr int kSlab = 32;                          // k per LDS slab
 
-// How a group is summed.  DOT4: a multiple of four channels, codes stay
-// packed and v_dot4 sums four products exactly.  ANY: codes as 32-bit integers, one multiply-add each.
+// How a group is summed.  DOT4: a multiple of four channels, codes stay packed and v_dot4 sums four products exactly.  ANY: codes as 32-bit integers, one multiply-add each.
 enum { GV_DOT4 = 1, GV_ANY = 2 };
 
 // 16 consecutive codes of a row from k0 on, a multiple of 16, as bytes; zeros past K or outside the matrix.  One unaligned load,
@@ -290,10 +289,10 @@ __global__ __launch_bounds__(256) void linear_per_channel_kernel(
 }
 
 // Groups of 1, 2, 4, 8 or 16 channels: the matrix units form the group sums while the VALUs run the chain of fused
-// multiply-adds, one operation per output and group instead of two or more.  v_mfma_f32_{32x32x4, 16x16x4, 4x4x4}_f16 with a
-// zero accumulator operand: 32, 16 or 4 rows, the activations' block broadcast to all column blocks, by 64 columns, four
+// multiply-adds, one operation per output and group instead of two or more.  v_mfma_f32_{16x16x4, 4x4x4}_f16 with a zero
+// accumulator operand: 16 or 4 rows, the activations' block broadcast to all column blocks, by 64 columns, four
 // channels; codes are exact in f16, their products and sums (below 2^19) in fp32.  Smaller groups zero the other channels'
-// halves of the activation operand, larger ones chain.  All three forms deliver 32 outputs a cycle and SIMD.
+// halves of the activation operand, larger ones chain.  Both forms deliver 32 outputs a cycle and SIMD.
 // Measured on register loops, cycles per 16 x 64 products and adds, four | two waves per SIMD: multiply and multiply-add 72 | 85,
 // this 60 | 65 (the same with the fp32 outer product v_mfma_f32_16x16x1 70 | 73; a factor in a scalar register takes the
 // multiply-add from 2.4 cycles to 4.6, so the factors come from LDS into vector registers).

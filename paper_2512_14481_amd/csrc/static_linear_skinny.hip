@@ -12,7 +12,8 @@
 // the pre-pass's launch out of the call; each workgroup repeats that work, so it is for at most 16 rows.  Otherwise the
 // codes come from the pre-pass in their staging blocks.
 // Row blocks (more than 64 rows): what bounds them is the operands' delivery from L2, (BM + 64) K bytes per workgroup for
-// BM x 64 outputs; 333 x 4096 x 4096 takes 18.7 us with its pre-pass, 27.1 on 96 GEMM tiles of 128 x 128.
+// BM x 64 outputs; 333 x 4096 x 4096 takes 18.7 us with its pre-pass, 27.1 on 96 GEMM tiles of 128 x 128
+// (weights that the caches hold; other ones each call: 21.6).
 #include "sasq_device.h"
 #include "gemm_tile.h"
 #include "gemm_k64.h"
@@ -263,7 +264,8 @@ static void launch_mt(LinBatch& b, int64_t tiles16, int a_bits, int32_t* acc_out
 // Rows per workgroup (64 weight rows each, K over four waves) for more than kSkinnyRows rows, 0: the GEMM's tiles are better.
 // Such a call is a few dozen tiles of 128 x 128 with a long K loop; cut finer, without LDS in the loop, every CU has
 // operands in flight, until the operands' L2 reads (the smaller the block, the more of them) cost more than that.  A round is
-// 256 workgroups, one per CU.  Measured with the pre-pass, int8, us, GEMM tiles | 64 | 96 | 128 rows:
+// 256 workgroups, one per CU.  Measured with the pre-pass, int8, us, one call repeated on the same weights, GEMM tiles | 64 | 96 |
+// 128 rows:
 //   4096 x 4096:  128 rows 25.9 | 15.2 | 17.5 | 20.9; 256 rows 26.6 | 15.1 (one round) | 17.3 | 20.0;
 //                 333 rows 27.1 | 21.0 | 18.7 (one round) | 21.3; 512 rows 27.5 | 24.2 (two) | 32.7; 768 rows 28.8 | 40.6 (three)
 //   11008 x 4096: 256 rows 56.0 | 34.6 | 40.2 | 45.7; 333 rows 57.4 | 54.6 | 42.6 | 47.4; 512 rows 57.4 | 57.0 | 71.3 | 49.0

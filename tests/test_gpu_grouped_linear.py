@@ -85,7 +85,7 @@ def test_grouped_linear_mfma(shape, group, dtype, fmt, blocked, tile):
                                    (140, 150, 576), (140, 150, 704), (70, 260, 960)])   # K loop remainders of 5, 7, 7 tiles
 def test_grouped_linear_groups_of_32(shape, dtype, fmt, blocked):
     """Groups of 32 channels, two per 64-byte K tile: the matrix-unit path multiplies every K tile twice, one half
-    of the channels at a time.  Row-major int4 weights stay on the scalar kernel and are compared all the same."""
+    of the channels at a time.  Row-major int4 weights take the VALU kernel and are compared all the same."""
     xb, wq, s_w, bias, s_g = problem(53, shape, 32, dtype, fmt)
     ref = oracle.static_linear_grouped(xb, s_g, wq, s_w, bias, 32, 8, fmt, dtype)
     y, f, xq = run_grouped(xb, s_g, wq, s_w, bias, 32, fmt, dtype, blocked)
@@ -112,13 +112,13 @@ def test_grouped_linear_scalar_path(shape, group, dtype, fmt):
 @pytest.mark.parametrize("fmt", ["int8", "int4"])
 @pytest.mark.parametrize("shape,group", [
     ((5, 70, 1), 1), ((9, 65, 130), 1), ((33, 130, 64), 1),      # four rows per wave: row, column and slab remainders
-    ((200, 3600, 66), 1),                                        # eight rows per wave
-    ((390, 4100, 70), 1), ((780, 4101, 34), 1), ((1500, 4200, 36), 1),   # 32x64, 64x64 and 64x128 tiles
-    ((7, 90, 36), 4), ((70, 3000, 40), 8), ((300, 4090, 52), 4), ((1025, 4100, 24), 12),   # packed sums of four, every tile
-    ((17, 66, 54), 6), ((65, 4099, 50), 10), ((300, 4000, 42), 3), ((900, 4200, 14), 7)])  # any other group, every tile
+    ((200, 3600, 66), 1),                                        # sixteen rows per wave, sums on the matrix units
+    ((390, 4100, 70), 1), ((780, 4101, 34), 1), ((1500, 4200, 36), 1),   # the same with more rows
+    ((7, 90, 36), 4), ((70, 3000, 40), 8), ((300, 4090, 52), 4), ((1025, 4100, 24), 12),   # groups of 4 and 8; packed sums of four, less than a slab
+    ((17, 66, 54), 6), ((65, 4099, 50), 10), ((300, 4000, 42), 3), ((900, 4200, 14), 7)])  # any other group
 def test_grouped_linear_small_groups_every_kernel(shape, group, fmt):
-    """Group sizes without a matrix-unit form: each kernel and tile the dispatch can choose, at sizes that leave rows,
-    columns and part of a K slab over.  Bit for bit: the chain of fused multiply-adds is part of the contract."""
+    """Groups that the int8 GEMM does not take, on each kind of kernel, at sizes that leave rows, columns and part of a K slab
+    over (test_grouped_linear_valu_tiles has every tile of the VALU kernel).  Bit for bit: the chain of fused multiply-adds is part of the contract."""
     if fmt == "int4" and shape[2] % 2:
         pytest.skip("packed int4 needs an even K")
     dtype = "f16" if fmt == "int8" else "bf16"

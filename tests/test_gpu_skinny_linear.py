@@ -18,8 +18,8 @@ pytestmark = pytest.mark.gpu
 LAYOUTS = [("int8", False), ("int8", True), ("int4", True)]
 SHAPES = [(1, 1, 64), (3, 47, 576), (15, 130, 128), (16, 512, 1088), (17, 33, 64), (32, 96, 704), (33, 72, 2112), (48, 250, 640),
           (49, 31, 192), (64, 264, 1024), (65, 64, 128), (16, 8200, 192), (2, 8185, 320), (30, 8192, 128), (64, 8189, 192),
-          # row blocks of 64 (one round, one and a half, int4's two), 96 (one round, all rows at once) and 128
-          (333, 1000, 704), (270, 4090, 128), (450, 4090, 128), (300, 3500, 192), (96, 16500, 64), (97, 9001, 128), (128, 8200, 320)]
+          # row blocks of 64 (one round, one and a half, int4's two), 96 (one round) and 128; (96, 16500) and int8 (450, 4090) go to the tiles
+          (333, 1000, 704), (227, 5504, 128), (270, 4090, 128), (450, 4090, 128), (300, 3500, 192), (96, 16500, 64), (97, 9001, 128), (128, 8200, 320)]
 
 
 def problem(seed, shape, fmt, dtype):
