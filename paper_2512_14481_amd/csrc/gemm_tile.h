@@ -73,6 +73,7 @@ struct LinBatch {
     int first_block[kMaxLinearBatch + 1];
     int count;
     int split_first, split_count;   // 16x16x64 kernel: workgroup ids from split_first on are half tiles (see gemm_k64_batch_kernel)
+    int trim_rows;                  // and so are tiles of at most so many rows
 };
 
 __device__ __forceinline__ int lin_item_of(const LinBatch& b, int block)
