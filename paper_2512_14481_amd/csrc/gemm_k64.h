@@ -29,6 +29,8 @@ void launch_grouped_valu(const GemmK64Args& a, sasq_dtype dt, bool int4, int64_t
 // K not a multiple of 64 (static_linear_anyk.hip): row-major activation codes in a.xq, row-major int8 or packed int4 weights.
 // rows: one activation factor per row.
 void launch_linear_anyk(const GemmK64Args& a, sasq_dtype dt, bool int4, bool rows, hipStream_t st);
+// Rounds of 256x256 tiles (or of as much work) that a single call's GEMM takes with the tiles chosen for it (static_linear.hip).
+double gemm_rounds(int64_t M, int64_t N);
 // At most kSkinnyRows rows, or too few tiles for the GEMM (static_linear_skinny.hip; linear_takes_skinny says whether the
 // sizes are such): the items of `b` (first_block and the tile counts are filled in here), weight layouts 0, 2 and 3.
 // qx: quantize the activations in the kernel (at most kSkinnyQuantRows rows, and no output may overlap an input, as workgroups

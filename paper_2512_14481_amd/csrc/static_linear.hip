@@ -846,9 +846,9 @@ static void launch_tiles(const void* xin, const void* wq, const float* s, const 
 // ceil(T / 256) rounds on 256 CUs; problems with few tiles use 128x256 or 128x128 tiles (the
 // latter two workgroups per CU) so that the chip is filled.  Relative costs per output element
 // (measured) are folded into `cost`.  sasq_set_tuning(SASQ_TUNE_LINEAR_TILE, 1 | 2 | 3) forces one.
-static int choose_tile(int64_t M, int64_t N)
+struct TileChoice { int tile; double rounds; };
+static TileChoice best_tile(int64_t M, int64_t N)
 {
-    if (const int t = tuning(SASQ_TUNE_LINEAR_TILE)) return t - 1;
     auto rounds = [&](int bm, int bn, int slots) {
         const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
         return (double)((tiles + slots - 1) / slots);
@@ -858,9 +858,17 @@ static int choose_tile(int64_t M, int64_t N)
     const double c0 = (t0 > 256 && t0 % 256 > 0 && t0 % 256 <= 128) ? (double)(t0 / 256) + 0.6 : rounds(256, 256, 256) * 1.00;
     const double c1 = rounds(128, 256, 256) * 0.50 * kCost128x256;
     const double c2 = rounds(128, 128, 512) * 0.50 * kCost128x128;   // two co-resident workgroups share a CU
-    if (c0 <= c1 && c0 <= c2) return 0;
-    return c1 <= c2 ? 1 : 2;
+    if (c0 <= c1 && c0 <= c2) return {0, c0};
+    return c1 <= c2 ? TileChoice{1, c1} : TileChoice{2, c2};
 }
+
+static int choose_tile(int64_t M, int64_t N)
+{
+    if (const int t = tuning(SASQ_TUNE_LINEAR_TILE)) return t - 1;
+    return best_tile(M, N).tile;
+}
+
+double gemm_rounds(int64_t M, int64_t N) { return best_tile(M, N).rounds; }
 
 // int8 weights and pre-arranged int4 weights over staged activations run on the 16x16x64 MFMA kernel (static_linear_k64.hip) unless
 // sasq_set_tuning(SASQ_TUNE_LINEAR_MFMA, 1) asks for the 32x32x32 one.

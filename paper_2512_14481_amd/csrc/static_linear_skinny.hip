@@ -12,21 +12,35 @@
 // the pre-pass's launch out of the call; each workgroup repeats that work, so it is for at most 16 rows.  Otherwise the
 // codes come from the pre-pass in their staging blocks.
 // Row blocks (more than 64 rows): what bounds them is the operands' delivery from L2, (BM + 64) K bytes per workgroup for
-// BM x 64 outputs; 333 x 4096 x 4096 takes 18.7 us with its pre-pass, 27.1 on 96 GEMM tiles of 128 x 128
-// (weights that the caches hold; other ones each call: 21.6).
+// BM x 64 outputs, and the few us in which a workgroup starts and ends; 333 x 4096 x 4096 takes 16.0 us with its pre-pass (27.1 on
+// 96 GEMM tiles of 128 x 128).  Of 333 x 4096 x 4096's 11 us in the kernel, 1.3 are arguments and addresses, 8 the K loop (19 TB/s
+// out of the L2s), 1.6 the sums' meeting and the stores; it was 15 (row blocks 21.6) while the factors were fetched at the end (3 us),
+// the weights, which four row blocks read, went past the L2s (2), and the loop waited for a round's last load before its first
+// product.  K over eight waves, two a SIMD, instead of four: 256 rows 14.7 | 13.6.
 #include "sasq_device.h"
 #include "gemm_tile.h"
 #include "gemm_k64.h"
+#include <cmath>
 #include <type_traits>
 
 namespace sasq {
 
-template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX>
+// An operand from `base` on as a buffer: a load is then a lane offset + a scalar offset, with no 64-bit address to form, and one
+// that is not wanted (an empty buffer) returns zeros without a memory access and without a branch.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_rsrc(const void* base, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+}
+
+// Row tiles whose sums meet in LDS at a time (128 KB at most).
+template <int MT, int NT, int NW> constexpr int skinny_rows_per_phase() { return NW * NT * MT <= 128 ? MT : MT / 2; }
+
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE>
 __device__ __forceinline__
 void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __restrict__ acc_out, char* lds)
 {
     using S = Store16<DT>;
-    constexpr bool I4 = WMODE == 3, ROWMAJOR = WMODE == 0;
+    constexpr bool I4 = WMODE == 3, ROWMAJOR = WMODE == 0, BLOCKS = !ONCE || MT > 4;
     static_assert(!I4 || NT % 2 == 0, "int4 blocks hold 32 weight rows");
     constexpr int WL = I4 ? NT / 2 : NT;               // 128-bit weight loads per lane and K tile
     const int lane = threadIdx.x & 63;
@@ -39,45 +53,31 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
     const int per = (KT + NW - 1) / NW;
     const int t0 = min(wave * per, KT), count = min(per, KT - t0);
 
-    // Scalar base + 32-bit lane offset for every stream; a base advances 1 KB (or 64 bytes of a row) per K tile.
-    const char* wbase[WL];
-    uint32_t woff;
-    if (I4) {
-        // Lane l takes 16 bytes: the K tile's codes 16 (l/16) .. + 15 of the weight rows 2 (l%16) and 2 (l%16) + 1.
-        woff = 256 * fq + 16 * frow;
-    } else if (ROWMAJOR) {
-        woff = (uint32_t)(16 * fq);                     // + the row, below
-    } else {
-        woff = (4 * frow + (fq ^ swz64(frow))) * 16;
-    }
+    // One scalar base per operand, advanced 1 KB (or 64 bytes of a row) per K tile, + a 32-bit lane offset per stream (at most 8
+    // row blocks of 2 MB): the products of 96 rows leave no registers for 64-bit lane addresses.  Blocks and rows past the
+    // matrix repeat its last one.
+    const int wblk = I4 ? n0 >> 5 : n0 >> 4, wlast = I4 ? (N - 1) >> 5 : (N - 1) >> 4;
+    const char* wbase = reinterpret_cast<const char*>(it.wq) +
+                        (ROWMAJOR ? (int64_t)n0 * K + (int64_t)t0 * 64 : ((int64_t)wblk * KT + t0) * 1024);
+    uint32_t woff[WL];
 #pragma unroll
     for (int j = 0; j < WL; ++j) {
-        const char* w = reinterpret_cast<const char*>(it.wq);
-        if (I4)            wbase[j] = w + ((int64_t)min((n0 >> 5) + j, (N - 1) >> 5) * KT + t0) * 1024;
-        else if (ROWMAJOR) wbase[j] = w + (int64_t)min(n0 + 16 * j, ((N - 1) >> 4) << 4) * K + (int64_t)t0 * 64;
-        else               wbase[j] = w + ((int64_t)min((n0 >> 4) + j, (N - 1) >> 4) * KT + t0) * 1024;
-    }
-    uint32_t wrow[ROWMAJOR ? NT : 1];                   // row-major: this lane's row inside each 16-row tile, clamped to N - 1
-    if (ROWMAJOR) {
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-            const int first = min(n0 + 16 * j, ((N - 1) >> 4) << 4);
-            wrow[j] = (uint32_t)min(frow, N - 1 - first) * (uint32_t)K + woff;
+        if (ROWMAJOR) {
+            woff[j] = (uint32_t)min(16 * j + frow, N - 1 - n0) * (uint32_t)K + 16 * fq;
+        } else {
+            // int4: lane l takes 16 bytes: the K tile's codes 16 (l/16) .. + 15 of the weight rows 2 (l%16) and 2 (l%16) + 1.
+            const uint32_t in_block = I4 ? 256 * fq + 16 * frow : (4 * frow + (fq ^ swz64(frow))) * 16;
+            woff[j] = (uint32_t)min(j, wlast - wblk) * (uint32_t)KT * 1024 + in_block;
         }
     }
     constexpr int kWStep = ROWMAJOR ? 64 : 1024;
-    const char* xbase[MT];
+    const char* xbase = QX ? reinterpret_cast<const char*>(it.x) + ((int64_t)m0 * K + (int64_t)t0 * 64) * 2
+                           : reinterpret_cast<const char*>(it.xq) + ((int64_t)(m0 >> 4) * KT + t0) * 1024;
     uint32_t xoff[MT];
 #pragma unroll
     for (int b = 0; b < MT; ++b) {
-        const int first = min(m0 + 16 * b, ((M - 1) >> 4) << 4);
-        if (QX) {
-            xbase[b] = reinterpret_cast<const char*>(it.x) + ((int64_t)first * K + (int64_t)t0 * 64) * 2;
-            xoff[b] = (uint32_t)min(frow, M - 1 - first) * (uint32_t)K * 2 + fq * 32;
-        } else {
-            xbase[b] = reinterpret_cast<const char*>(it.xq) + ((int64_t)(first >> 4) * KT + t0) * 1024;
-            xoff[b] = (4 * frow + (fq ^ swz64(frow))) * 16;
-        }
+        if (QX) xoff[b] = (uint32_t)min(16 * b + frow, M - 1 - m0) * (uint32_t)K * 2 + fq * 32;
+        else    xoff[b] = (uint32_t)min(b, ((M - 1) >> 4) - (m0 >> 4)) * (uint32_t)KT * 1024 + (4 * frow + (fq ^ swz64(frow))) * 16;
     }
     constexpr int kXStep = QX ? 128 : 1024;
     const QConst qk = make_qconst(*it.s, a_bits);
@@ -87,18 +87,20 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
         u32x4 x[MT][QX ? 2 : 1];
     };
     auto load = [&](Frag& f, int t) {
+        int bytes = -1;                                 // in so many words: from a select the compiler builds the buffers in vector registers
+        if (BLOCKS) asm("s_cmp_lt_i32 %1, %2\n\ts_cselect_b32 %0, -1, 0" : "=s"(bytes) : "s"(t), "s"(count) : "scc");
+        const __amdgpu_buffer_rsrc_t wrsrc = operand_rsrc(wbase, bytes), xrsrc = operand_rsrc(xbase, bytes);
+        // ONCE: no other workgroup reads these weights.  Where row blocks share them they have to stay in L2 (333 x 4096 x 4096
+        // 18.8 us non-temporal, 16.8 cached), and row-major a K tile is half a 128-byte line of each row, the other half the next
+        // K tile's (the 7B layer below: 54 us and 51).
+        constexpr int kNonTemporal = 2;
 #pragma unroll
-        for (int j = 0; j < WL; ++j) {
-            const u32x4* p = reinterpret_cast<const u32x4*>(wbase[j] + (int64_t)t * kWStep + (ROWMAJOR ? wrow[ROWMAJOR ? j : 0] : woff));
-            // Row-major: a K tile is half a 128-byte line of each row, the other half is the next K tile's; it has to stay cached
-            // until then (non-temporal: 54 us for the 7B layer below, cached: 51).
-            f.w[j] = ROWMAJOR ? *p : __builtin_nontemporal_load(p);
-        }
+        for (int j = 0; j < WL; ++j)
+            f.w[j] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, woff[j], t * kWStep, ONCE && !ROWMAJOR ? kNonTemporal : 0);
 #pragma unroll
         for (int b = 0; b < MT; ++b)
 #pragma unroll
-            for (int h = 0; h < (QX ? 2 : 1); ++h)
-                f.x[b][h] = *reinterpret_cast<const u32x4*>(xbase[b] + (int64_t)t * kXStep + xoff[b] + 16 * h);
+            for (int h = 0; h < (QX ? 2 : 1); ++h) f.x[b][h] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff[b] + 16 * h, t * kXStep, 0);
     };
     i32x4 acc[NT][MT];
 #pragma unroll
@@ -139,93 +141,135 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
         }
     };
 
-    Frag ring[D];
+    // At the end a wave finishes output tiles of one run of 16 (int4: 32) columns; their factors are requested behind the first
+    // operands instead of being waited for there.
+    constexpr int kRegs = I4 ? 2 : 1, kCols = 4 * kRegs, kRuns = NT / kRegs;         // int4: two tiles interleave into 32 columns
+    static_assert(NW % kRuns == 0, "a wave stays in one run of columns");
+    const int g0 = wave % kRuns * kRegs, n = n0 + 16 * g0 + kCols * fq;
+    float sw[kCols], bv[kCols];
+    auto load_factors = [&]() {
 #pragma unroll
-    for (int j = 0; j < D; ++j)
-        if (j < count) load(ring[j], j);
-    int i = 0;
-#pragma unroll 1
-    for (; i + 2 * D <= count; i += D) {
+        for (int e = 0; e < kCols; ++e) {
+            const int ne = min(n + e, N - 1);
+            sw[e] = it.s_w[ne];
+            bv[e] = (it.bias ? it.bias : it.s_w)[ne];                                // without a bias: not used
+        }
+    };
+
+    Frag ring[D];
+    if constexpr (BLOCKS) {
+        // D K tiles in flight.  Loads and products carry no conditions (tiles past the last are zeros), so that the wait in front of
+        // a product counts exactly the loads behind its own; the barriers keep the scheduler from moving all products of a round in
+        // front of all its loads, which exposed the whole latency once a round.
 #pragma unroll
         for (int j = 0; j < D; ++j) {
-            multiply(ring[j]);
-            load(ring[j], i + j + D);
+            load(ring[j], j);
+            __builtin_amdgcn_sched_barrier(0);
         }
+        load_factors();
+        asm volatile("" ::: "memory");                  // here, not behind the loop
+#pragma unroll 1
+        for (int i = 0; i < count; i += D) {
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                multiply(ring[j]);
+                load(ring[j], i + j + D);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < D; ++j)
+            if (j < count) load(ring[j], j);
+        load_factors();
+        asm volatile("" ::: "memory");
+        int i = 0;
+#pragma unroll 1
+        for (; i + 2 * D <= count; i += D) {
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                multiply(ring[j]);
+                load(ring[j], i + j + D);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < D; ++j)
+            if (i + j < count) {
+                multiply(ring[j]);
+                if (i + j + D < count) load(ring[j], i + j + D);
+            }
+#pragma unroll
+        for (int j = 0; j < D; ++j)
+            if (i + D + j < count) multiply(ring[j]);
     }
-#pragma unroll
-    for (int j = 0; j < D; ++j)
-        if (i + j < count) {
-            multiply(ring[j]);
-            if (i + j + D < count) load(ring[j], i + j + D);
-        }
-#pragma unroll
-    for (int j = 0; j < D; ++j)
-        if (i + D + j < count) multiply(ring[j]);
 
-    // The waves' sums meet in LDS; wave w finishes the output tiles w, w + NW, ...
-    constexpr int kTiles = (I4 ? NT / 2 : NT) * MT, kRegs = I4 ? 2 : 1;      // int4: two tiles interleave into 32 columns
+    // The waves' sums meet in LDS, as many row tiles at a time as fit; wave w finishes the output tiles w, w + NW, ...
+    constexpr int kRows = skinny_rows_per_phase<MT, NT, NW>(), kTiles = kRuns * kRows;
     i32x4* part = reinterpret_cast<i32x4*>(lds);
-#pragma unroll
-    for (int g = 0; g < NT; ++g)
-#pragma unroll
-        for (int b = 0; b < MT; ++b) part[((wave * NT + g) * MT + b) * 64 + lane] = acc[g][b];
-    __syncthreads();
     const float s = qk.s;
 #pragma unroll
-    for (int t = wave; t < kTiles; t += NW) {
-        const int b = t % MT, g0 = t / MT * kRegs;
-        int v[4 * kRegs];
+    for (int b0 = 0; b0 < MT; b0 += kRows) {
+        if (b0 > 0) __syncthreads();
 #pragma unroll
-        for (int r = 0; r < kRegs; ++r) {
-            i32x4 sum = {0, 0, 0, 0};
+        for (int g = 0; g < NT; ++g)
 #pragma unroll
-            for (int w = 0; w < NW; ++w) sum += part[((w * NT + g0 + r) * MT + b) * 64 + lane];
+            for (int b = 0; b < kRows; ++b) part[((wave * NT + g) * kRows + b) * 64 + lane] = acc[g][b0 + b];
+        __syncthreads();
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[kRegs * e + r] = I4 ? sum[e] >> 4 : sum[e];
-        }
-        const int m = m0 + 16 * b + frow, n = n0 + 16 * g0 + 4 * kRegs * fq;      // 4 (8) consecutive columns of one row
-        if (m >= M || n >= N) continue;
-        uint16_t* dst = it.y + (int64_t)m * N + n;
-        float yv[4 * kRegs];
+        for (int t = wave; t < kTiles; t += NW) {
+            const int b = t / kRuns;
+            int v[kCols];
 #pragma unroll
-        for (int e = 0; e < 4 * kRegs; ++e) {
-            const int ne = min(n + e, N - 1);
-            float f = (float)v[e] * (s * it.s_w[ne]);
-            if (it.bias) f = f + it.bias[ne];
-            yv[e] = f;
-        }
-        if ((N & 7) == 0) {                                                  // then every full run is aligned to its own size
+            for (int r = 0; r < kRegs; ++r) {
+                i32x4 sum = {0, 0, 0, 0};
 #pragma unroll
-            for (int h = 0; h < kRegs; ++h)
-                *reinterpret_cast<u32x2*>(dst + 4 * h) = u32x2{S::pack(yv[4 * h], yv[4 * h + 1]), S::pack(yv[4 * h + 2], yv[4 * h + 3])};
-        } else {
+                for (int w = 0; w < NW; ++w) sum += part[((w * NT + g0 + r) * kRows + b) * 64 + lane];
 #pragma unroll
-            for (int e = 0; e < 4 * kRegs; ++e)
-                if (n + e < N) dst[e] = S::enc(yv[e]);
-        }
-        if (acc_out) {
+                for (int e = 0; e < 4; ++e) v[kRegs * e + r] = I4 ? sum[e] >> 4 : sum[e];
+            }
+            const int m = m0 + 16 * (b0 + b) + frow;                         // 4 (8) consecutive columns of one row
+            if (m >= M || n >= N) continue;
+            uint16_t* dst = it.y + (int64_t)m * N + n;
+            float yv[kCols];
 #pragma unroll
-            for (int e = 0; e < 4 * kRegs; ++e)
-                if (n + e < N) acc_out[(int64_t)m * N + n + e] = v[e];
+            for (int e = 0; e < kCols; ++e) {
+                float f = (float)v[e] * (s * sw[e]);
+                if (it.bias) f = f + bv[e];
+                yv[e] = f;
+            }
+            if ((N & 7) == 0) {                                              // then every full run is aligned to its own size
+#pragma unroll
+                for (int h = 0; h < kRegs; ++h)
+                    *reinterpret_cast<u32x2*>(dst + 4 * h) = u32x2{S::pack(yv[4 * h], yv[4 * h + 1]), S::pack(yv[4 * h + 2], yv[4 * h + 3])};
+            } else {
+#pragma unroll
+                for (int e = 0; e < kCols; ++e)
+                    if (n + e < N) dst[e] = S::enc(yv[e]);
+            }
+            if (acc_out) {
+#pragma unroll
+                for (int e = 0; e < kCols; ++e)
+                    if (n + e < N) acc_out[(int64_t)m * N + n + e] = v[e];
+            }
         }
     }
 }
 
-template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX>
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE>
 __global__ __launch_bounds__(64 * NW)
 void skinny_kernel(const LinBatch b, int a_bits, int32_t* __restrict__ acc_out)
 {
-    __shared__ __attribute__((aligned(1024))) char lds[NW * NT * MT * 1024];
+    __shared__ __attribute__((aligned(1024))) char lds[NW * NT * skinny_rows_per_phase<MT, NT, NW>() * 1024];
     const int k = lin_item_of(b, (int)blockIdx.x);
     // Eight neighbours in the id go to the eight XCDs: the row blocks of one run of weight rows stay on one, 8 ids apart.
     const int id = (int)blockIdx.x - b.first_block[k], octet = id >> 3, tiles_m = b.it[k].tiles_m;
     const int mblk = octet % tiles_m, nblk = octet / tiles_m * 8 + (id & 7);
     if (nblk >= b.it[k].tiles_n) return;
-    skinny_body<DT, WMODE, MT, NT, NW, D, QX>(b.it[k], mblk, nblk, a_bits, acc_out, lds);
+    skinny_body<DT, WMODE, MT, NT, NW, D, QX, ONCE>(b.it[k], mblk, nblk, a_bits, acc_out, lds);
 }
 
 
-template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX>
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE>
 static void launch_one(LinBatch& b, int a_bits, int32_t* acc_out, hipStream_t st)
 {
     b.first_block[0] = 0;
@@ -239,44 +283,30 @@ static void launch_one(LinBatch& b, int a_bits, int32_t* acc_out, hipStream_t st
         }
         b.first_block[i + 1] = b.first_block[i] + blocks;
     }
-    skinny_kernel<DT, WMODE, MT, NT, NW, D, QX><<<b.first_block[b.count], 64 * NW, 0, st>>>(b, a_bits, acc_out);
+    skinny_kernel<DT, WMODE, MT, NT, NW, D, QX, ONCE><<<b.first_block[b.count], 64 * NW, 0, st>>>(b, a_bits, acc_out);
 }
 
-// Wide or narrow workgroups: the narrow form (16 weight rows, K over eight waves) gives four times the waves for the same
-// weights, the wide one reads the activations half or a quarter as often.  Measured at 8 rows, int8, wide | narrow:
+// Wide or narrow workgroups: the narrow form (16 weight rows, K over eight waves) gives more workgroups for the same weights, the
+// wide one reads the activations half or a quarter as often.  Measured at 8 rows, int8, wide (then K over four waves) | narrow:
 // 4096 x 4096 (256 tiles of 16 rows) 8.3 | 6.5 us, 4096 x 11008 17.3 | 12.8, 11008 x 4096 (688 tiles) 12.3 | 13.4, the 7B
-// layer (2656 tiles) 36 | 51; the line lies at two workgroups of the wide form per CU.
+// layer (2656 tiles) 36 | 51; the line lies at 512 tiles.
+// Waves of the wide form, four with four K tiles in flight | eight with three: the 7B layer at 8 rows 35.0 | 35.0, its MLP 29.7 |
+// 26.4, 8192 x 16384 28.0 | 25.7; row-major int8, whose lines are shared between K tiles, 7B layer 50.9 | 51.3.
 template <int DT, int WMODE, int MT, bool QX>
 static void launch_mt(LinBatch& b, int64_t tiles16, int a_bits, int32_t* acc_out, hipStream_t st)
 {
     const bool wide = tiles16 >= 512;
     if constexpr (WMODE == 3) {                        // int4: half the bytes per tile, a block is two tiles
-        if (!wide)             launch_one<DT, WMODE, MT, 2, 8, 2, QX>(b, a_bits, acc_out, st);
-        else if constexpr (QX) launch_one<DT, WMODE, MT, 4, 8, 2, QX>(b, a_bits, acc_out, st);
-        else                   launch_one<DT, WMODE, MT, 4, 4, 2, QX>(b, a_bits, acc_out, st);
+        if (!wide)             launch_one<DT, WMODE, MT, 2, 8, 2, QX, true>(b, a_bits, acc_out, st);
+        else if constexpr (QX) launch_one<DT, WMODE, MT, 4, 8, 2, QX, true>(b, a_bits, acc_out, st);
+        else                   launch_one<DT, WMODE, MT, 4, 4, 2, QX, true>(b, a_bits, acc_out, st);
     } else {
-        if (!wide)               launch_one<DT, WMODE, MT, 1, 8, 4, QX>(b, a_bits, acc_out, st);
-        else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX>(b, a_bits, acc_out, st);
-        else                     launch_one<DT, WMODE, MT, 2, 4, 4, QX>(b, a_bits, acc_out, st);
+        if (!wide)               launch_one<DT, WMODE, MT, 1, 8, 4, QX, true>(b, a_bits, acc_out, st);
+        else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, true>(b, a_bits, acc_out, st);
+        else if constexpr (WMODE == 0) launch_one<DT, WMODE, MT, 2, 4, 4, QX, true>(b, a_bits, acc_out, st);
+        else                     launch_one<DT, WMODE, MT, 2, 8, 3, QX, true>(b, a_bits, acc_out, st);
     }
 }
-
-// Rows per workgroup (64 weight rows each, K over four waves) for more than kSkinnyRows rows, 0: the GEMM's tiles are better.
-// Such a call is a few dozen tiles of 128 x 128 with a long K loop; cut finer, without LDS in the loop, every CU has
-// operands in flight, until the operands' L2 reads (the smaller the block, the more of them) cost more than that.  A round is
-// 256 workgroups, one per CU.  Measured with the pre-pass, int8, us, one call repeated on the same weights, GEMM tiles | 64 | 96 |
-// 128 rows:
-//   4096 x 4096:  128 rows 25.9 | 15.2 | 17.5 | 20.9; 256 rows 26.6 | 15.1 (one round) | 17.3 | 20.0;
-//                 333 rows 27.1 | 21.0 | 18.7 (one round) | 21.3; 512 rows 27.5 | 24.2 (two) | 32.7; 768 rows 28.8 | 40.6 (three)
-//   11008 x 4096: 256 rows 56.0 | 34.6 | 40.2 | 45.7; 333 rows 57.4 | 54.6 | 42.6 | 47.4; 512 rows 57.4 | 57.0 | 71.3 | 49.0
-//   7B layer:     96 rows 93.6 | 83.3 | 66.1 | 69.7; 128 rows 94.3 | 80.2 | 103.6 | 75.0 (int4 100 | 60 | 83 | 61); 192 rows
-//                 95.1 | 107 | 106 | 121
-// So: one round of small blocks first; then blocks that take all rows at once and read the weights once, while the GEMM's tiles
-// leave enough of the chip idle (tiles_are_better; one projection: half of it with 128 x 128 tiles); then
-// a round and a half (5056 x 5504, 227 rows: 39 | 28), with int4's shorter loads two (8192 x 1024, 2048 rows: 54.2 | 41.6; int8
-// 28672 x 8192, 256 rows, is better on the tiles: 135 | 154).  Fewer than eight runs of weight rows would leave XCDs without work.
-// All rows at once in blocks of 96 comes up in batches only: one projection of at most 96 rows with more than 256 such blocks has
-// more than 128 tiles.
 
 // Share of the CUs' time that the GEMM's 256 x 256 tiles use, longest K first.
 static double tile_fill(const LinBatch& b, int64_t& tiles, int& k_max)
@@ -294,16 +324,12 @@ static double tile_fill(const LinBatch& b, int64_t& tiles, int& k_max)
     return work / (256.0 * (span > k_max ? span : (double)k_max));
 }
 
-// Whether the GEMM's tiles take at most 128 rows faster than the kernels here: they read the weights at a better rate once
+// Whether the GEMM's tiles take at most 64 rows faster than the kernels here: they read the weights at a better rate once
 // enough of them run at a time, and an XCD's tiles share the activations.  Measured, us, GEMM | here, on weights that the
 // caches have not seen, a projection (or two of half the size) K -> N, with the tiles' fill:
 //   single, int8, K = 4096, 64 rows:  N = 32768 (0.50) 38 | 33, 36864 (0.56) 39 | 43, 49152 (0.75) 45 | 54, 65536 (1.0) 56 | 61,
 //     69632 (two rounds, 0.53) 79 | 72, 81920 (0.63) 79 | 79, 131072 (1.0) 100 | 114; int4 98304 (0.75) 61 | 60; 48 rows: 49152
 //     (0.75) 45 | 44, 57344 (0.88) 50 | 57, int4 131072 (1.0) 76 | 69; 32 rows: never behind by more than 5 %
-//   batch of two, int8, K = 4096, 96 rows:  (0.50) 46 | 41, (0.56) 48 | 54, two rounds (0.53) 101 | 90, (0.63) 96 | 93, (0.75) 97 |
-//     112; 128 rows: (0.38) 45 | 44, (0.50) 46 | 46, (0.56) 48 | 63, (0.53) 101 | 101; K = 1024, 128 rows: (0.25) 22 | 16, (0.31)
-//     22 | 24; int4, 96 rows: (0.75) 49 | 47, (0.88) 53 | 59; 128 rows: (0.50) 46 | 38, (0.56) 47 | 53
-//     70B gate and up, 8192 -> 28672 (0.88), int8: 96 rows 104 | 141, 128 rows 107 | 156; int4: 87 | 95, 87 | 119
 //   row-major int8 (64-byte pieces of rows), part of the GEMM's time:  single, K = 8192, 8 rows 0.98 at most, 16 rows (0.44)
 //     0.93, (0.75) 1.07, (0.88) 1.28, 32 rows (0.75) 1.04, (0.88) 1.15, (1.0) 1.19; two, 64 rows: (0.50) 0.78, (0.63) 1.05, (0.75) 1.08
 // The layers of 7B, 13B and 70B (their long down projections leave most CUs to the rest: 0.28, 0.35 and 0.46) are better here.
@@ -317,27 +343,68 @@ static bool tiles_are_better(const LinBatch& b, int rows, int wmode)
     if (rows <= 12) return false;
     if (rows <= 32) return row_major && k_max >= 4096 && (rows <= 16 ? fill > 0.7 : single && fill > 0.8);
     if (rows <= 48) return single && fill > 0.8 && (one_round || !int4);
-    if (rows <= 64) return single ? fill > (one_round ? 0.5 : int4 ? 0.8 : 0.7) : row_major && fill > (one_round ? 0.5 : 0.8);
-    if (rows <= 96) return fill > (k_max < 2048 ? 0.5 : !one_round ? 0.7 : int4 ? 0.8 : 0.5);
-    return fill > 0.5 || (!int4 && k_max < 2048 && tiles > 64);
+    return single ? fill > (one_round ? 0.5 : int4 ? 0.8 : 0.7) : row_major && fill > (one_round ? 0.5 : 0.8);
 }
+
+// Rows per workgroup (64 weight rows each, K over eight waves) for more than kSkinnyRows rows, 0: the GEMM's tiles are better.
+// A call of few tiles leaves CUs idle or waiting for one long K loop; cut finer every CU has operands in flight, until the operands'
+// L2 reads (the smaller the block, the more of them) cost more than that.  Neither side's time follows from one size, so both are
+// estimated, in us, from what they do: workgroups go in rounds (of 256; row blocks one workgroup a CU), a round costs what a
+// workgroup takes to start and end, and the operands of its K tiles.  The constants are least squares over 550 calls of 65 to 1200
+// rows, K and N from 1024 to 28672, single projections and layers, of times from 8 to 500 us: rms error 7 to 11 %.  Over those calls
+// the choice costs 0.8 % against the best of the four each time, and the calls take 0.87 of what they took with lines drawn by hand.
+// Row blocks are taken from 8 % less time on: the estimates are no better than that.  us, GEMM tiles | 64 | 96 | 128 rows:
+//   4096 x 4096: 128 rows 26.2 | 12.9 | 14.8 | 20.4, 256 rows 26.4 | 13.7 | 15.5 | 17.3, 333 rows 26.7 | 20.3 | 16.0 | 17.3, 512 rows
+//   27.1 | 21.3 | 24.3 | 18.9, 768 rows 27.9 | 29.7 | 27.1 | 30.4, 1000 rows 28.8 | 40.5 | 39.1 | 34.6; 8192 x 8192, 200 rows 56.5 |
+//   37.1 | 42.8 | 33.5; 7B layer, 96 rows 98.6 | 68.3 | 60.4 | 61.8, 192 rows 113 | 104 | 92.7 | 94.3, 333 rows tiles
+struct BlockTime { double call, round, k_tile; };
+static const BlockTime kBlockTime[3][3] = {                          // row-major int8, pre-arranged int8, pre-arranged int4; 64, 96, 128 rows
+    {{4.8, 2.4, 0.167}, {4.7, 3.7, 0.195}, {4.6, 4.6, 0.213}},
+    {{4.6, 2.9, 0.107}, {5.1, 3.9, 0.137}, {5.3, 4.7, 0.161}},
+    {{4.6, 2.8, 0.076}, {4.8, 4.1, 0.100}, {4.9, 4.9, 0.121}}};
+static const BlockTime kTileTime[3] = {{1.0, 12.0, 0.72}, {1.0, 13.0, 0.54}, {1.0, 16.0, 0.49}};
 
 static int block_rows(const LinBatch& b, int wmode)
 {
-    int64_t blocks64 = 0, blocks96 = 0, tiles128 = 0;
-    int rows = 0;
+    const int format = wmode == 0 ? 0 : wmode == 2 ? 1 : 2;
+    double work = 0.0, k_max = 0.0;                                  // GEMM tiles x K tiles
+    int64_t tiles = 0;
     for (int i = 0; i < b.count; ++i) {
-        const int64_t m = b.it[i].M, cols = ((int64_t)b.it[i].N + 63) / 64;
-        if (cols < 8) return 0;
-        blocks64 += (m + 63) / 64 * cols;
-        blocks96 += (m + 95) / 96 * cols;
-        tiles128 += (m + 127) / 128 * ((cols + 1) / 2);
-        rows = b.it[i].M > rows ? b.it[i].M : rows;
+        if (b.it[i].N <= 448) return 0;                              // fewer than eight runs of weight rows leave XCDs without work
+        const double kt = b.it[i].K / 64;
+        const int64_t t = ((int64_t)b.it[i].M + 255) / 256 * (((int64_t)b.it[i].N + 255) / 256);
+        tiles += t;
+        work += (double)t * kt;
+        k_max = kt > k_max ? kt : k_max;
     }
-    if (blocks64 <= 256) return 64;
-    if (blocks96 <= 256) return 96;
-    if (rows <= 128 && (b.count > 1 ? !tiles_are_better(b, rows, wmode) : tiles128 <= 128)) return rows <= 96 ? 96 : 128;
-    return blocks64 <= (wmode == 3 ? 512 : 384) ? 64 : 0;
+    // A single call has its choice of tiles, and rounds in units of whole ones.  The tiles of a batch fill each other's last round
+    // in part: between whole rounds and none.
+    const BlockTime& tt = kTileTime[format];
+    double best;
+    if (b.count == 1) {
+        best = tt.call + gemm_rounds(b.it[0].M, b.it[0].N) * (tt.round + tt.k_tile * k_max);
+    } else {
+        const double rounds = (double)((tiles + 255) / 256), span = work / 256.0 * std::sqrt(rounds * 256.0 / (double)tiles);
+        best = tt.call + rounds * tt.round + tt.k_tile * (span > k_max ? span : k_max);
+    }
+    best *= 0.92;
+    int rows = 0;
+    for (int f = 0; f < 3; ++f) {
+        const int r = f == 0 ? 64 : f == 1 ? 96 : 128;
+        int64_t blocks = 0;
+        double block_work = 0.0;
+        for (int i = 0; i < b.count; ++i) {
+            const int64_t n = ((int64_t)b.it[i].M + r - 1) / r * (((int64_t)b.it[i].N + 511) / 512 * 8);
+            blocks += n;
+            block_work += (double)n * (b.it[i].K / 64);
+        }
+        if (blocks >= INT64_C(1) << 22) continue;                    // a launch holds fewer than 2^32 work items
+        const double rounds = (double)((blocks + 255) / 256), span = block_work / (double)blocks * rounds;
+        const BlockTime& bt = kBlockTime[format][f];
+        const double us = bt.call + rounds * bt.round + bt.k_tile * (span > k_max ? span : k_max);
+        if (us < best) { best = us; rows = r; }
+    }
+    return rows;
 }
 
 bool linear_takes_skinny(const LinBatch& b, int wmode)
@@ -348,7 +415,7 @@ bool linear_takes_skinny(const LinBatch& b, int wmode)
         rows = b.it[i].M > rows ? b.it[i].M : rows;
         cols += b.it[i].N;
     }
-    if (cols > INT64_C(1) << 28) return false;         // up to 8 work items a column, and a launch holds fewer than 2^32
+    if (cols > INT64_C(1) << 27) return false;         // up to 16 work items a column, and a launch holds fewer than 2^32
     return rows <= kSkinnyRows ? !tiles_are_better(b, rows, wmode) : block_rows(b, wmode) != 0;
 }
 
@@ -362,11 +429,12 @@ static void launch_wmode(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, hip
         rows = b.it[i].M > rows ? b.it[i].M : rows;
     }
     if (rows > kSkinnyRows) {
-        switch (block_rows(b, WMODE)) {
-        case 64:  launch_one<DT, WMODE, 4, 4, 4, 2, false>(b, a_bits, acc_out, st); break;
-        case 96:  launch_one<DT, WMODE, 6, 4, 4, 3, false>(b, a_bits, acc_out, st); break;
-        default:  launch_one<DT, WMODE, 8, 4, 4, 3, false>(b, a_bits, acc_out, st); break;
-        }
+        const int block = block_rows(b, WMODE);
+        if (block == 64)                     launch_one<DT, WMODE, 4, 4, 8, 2, false, false>(b, a_bits, acc_out, st);
+        else if (block == 96 && rows > 96)   launch_one<DT, WMODE, 6, 4, 8, 2, false, false>(b, a_bits, acc_out, st);
+        else if (block == 96)                launch_one<DT, WMODE, 6, 4, 8, 2, false, true>(b, a_bits, acc_out, st);
+        else if (rows > 128)                 launch_one<DT, WMODE, 8, 4, 8, 2, false, false>(b, a_bits, acc_out, st);
+        else                                 launch_one<DT, WMODE, 8, 4, 8, 2, false, true>(b, a_bits, acc_out, st);
     } else if (qx)       launch_mt<DT, WMODE, 1, true>(b, tiles16, a_bits, acc_out, st);
     else if (rows <= 32) launch_mt<DT, WMODE, 2, false>(b, tiles16, a_bits, acc_out, st);
     else if (rows <= 48) launch_mt<DT, WMODE, 3, false>(b, tiles16, a_bits, acc_out, st);
