@@ -1,12 +1,17 @@
-"""ctypes binding of libsasq.so: one Python function per C entry point of include/sasq.h.
+"""Binding of libsasq.so: one Python function per C entry point of include/sasq.h.
 
 Only argument marshalling happens here (device pointers, sizes, the current HIP stream taken
 from PyTorch); every step of the path runs in the library's kernels.  Tensors must be device
 tensors, contiguous, of the dtypes the header states.  A non-zero status raises SasqError.
+
+The calls of a training or serving loop are marshalled by a native module (host/marshal.cpp), which
+makes the same checks and returns None where one of them fails; the checks written out here then run
+and raise.  The others go through ctypes.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Optional
 
@@ -14,6 +19,7 @@ import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libsasq.so")
+MARSHAL_PATH = os.path.join(_PKG, "_marshal.so")
 
 SASQ_F16, SASQ_BF16 = 0, 1
 SASQ_W_INT8, SASQ_W_INT4_PACKED, SASQ_W_INT8_BLOCKED, SASQ_W_INT4_BLOCKED = 0, 1, 2, 3
@@ -43,9 +49,36 @@ class SasqError(RuntimeError):
 
 _LIB = None
 
+# The entry points that the native module marshals.
+_NATIVE = ("sasq_fakequant_fwd", "sasq_fakequant_bwd", "sasq_fakequant_fwd_batch", "sasq_fakequant_bwd_batch",
+           "sasq_fakequant_fwd_pc_batch", "sasq_fakequant_bwd_pc_batch", "sasq_scale_sgd", "sasq_scale_sgd_vec", "sasq_scale_adamw",
+           "sasq_static_linear", "sasq_static_linear_batch", "sasq_static_linear_grouped", "sasq_linear_bwd_input",
+           "sasq_absmax_scale", "sasq_quantize_weight", "sasq_pack_weight", "sasq_prepare_bwd_weight")
+
+
+class _Unbound:
+    """Stands for the native module until the library is loaded: takes no call."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+_native = _Unbound()
+
+
+def _load_native(lib: ctypes.CDLL):
+    if not os.path.exists(MARSHAL_PATH):
+        raise RuntimeError(f"{MARSHAL_PATH} is missing: build it with `python -m paper_2512_14481_amd.build`")
+    spec = importlib.util.spec_from_file_location("paper_2512_14481_amd._marshal", MARSHAL_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    module.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+                 for name in _NATIVE + ("sasq_packed_weight_bytes", "sasq_bwd_weight_bytes")})
+    return module
+
 
 def _lib() -> ctypes.CDLL:
-    global _LIB
+    global _LIB, _native
     if _LIB is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(
@@ -99,6 +132,7 @@ def _lib() -> ctypes.CDLL:
         L.sasq_absmax_scale_workspace.restype = sz
         L.sasq_absmax_scale_workspace.argtypes = [i64, i64]
         L.sasq_absmax_scale.argtypes = [vp, vp, i64, i64, i32, i32, vp, sz, vp]
+        _native = _load_native(L)
         _LIB = L
     return _LIB
 
@@ -158,6 +192,9 @@ def new_workspace(nbytes: int, device="cuda") -> torch.Tensor:
 
 def sasq_fakequant_fwd(x: torch.Tensor, s: torch.Tensor, y: torch.Tensor,
                        codes: Optional[torch.Tensor] = None, bits: int = 8) -> None:
+    rc = _native.sasq_fakequant_fwd(x, s, y, codes, bits)
+    if rc is not None:
+        return _check(rc, "sasq_fakequant_fwd")
     _want(s, torch.float32, "s"); _want(codes, torch.int8, "codes")
     if y.dtype != x.dtype or y.shape != x.shape:
         raise ValueError("y must match x")
@@ -172,6 +209,9 @@ def sasq_fakequant_bwd_workspace(rows: int, cols: int) -> int:
 
 def sasq_fakequant_bwd(x: torch.Tensor, dy: torch.Tensor, s: torch.Tensor, dx: Optional[torch.Tensor],
                        ds: torch.Tensor, workspace: torch.Tensor, bits: int = 8) -> None:
+    rc = _native.sasq_fakequant_bwd(x, dy, s, dx, ds, workspace, bits)
+    if rc is not None:
+        return _check(rc, "sasq_fakequant_bwd")
     _want(s, torch.float32, "s"); _want(ds, torch.float32, "ds")
     if dy.dtype != x.dtype or dy.shape != x.shape or (dx is not None and (dx.dtype != x.dtype or dx.shape != x.shape)):
         raise ValueError("dy and dx must match x")
@@ -247,6 +287,9 @@ def _fq_items(items, backward: bool):
 
 
 def sasq_fakequant_fwd_batch(items, bits: int = 8) -> None:
+    rc = _native.sasq_fakequant_fwd_batch(items, bits)
+    if rc is not None:
+        return _check(rc, "sasq_fakequant_fwd_batch")
     arr, dt = _fq_items(items, False)
     _check(_lib().sasq_fakequant_fwd_batch(arr, len(items), bits, dt, _stream()), "sasq_fakequant_fwd_batch")
 
@@ -256,6 +299,9 @@ def sasq_fakequant_bwd_batch_workspace(count: int) -> int:
 
 
 def sasq_fakequant_bwd_batch(items, workspace: torch.Tensor, bits: int = 8) -> None:
+    rc = _native.sasq_fakequant_bwd_batch(items, workspace, bits)
+    if rc is not None:
+        return _check(rc, "sasq_fakequant_bwd_batch")
     arr, dt = _fq_items(items, True)
     _check(_lib().sasq_fakequant_bwd_batch(arr, len(items), bits, dt, _ptr(workspace),
                                            workspace.numel() * workspace.element_size(), _stream()),
@@ -271,6 +317,9 @@ def _pc_check(items, backward: bool) -> None:
 
 def sasq_fakequant_fwd_pc_batch(items, bits: int = 8) -> None:
     """items: sequence of (x, s[cols], y)."""
+    rc = _native.sasq_fakequant_fwd_pc_batch(items, bits)
+    if rc is not None:
+        return _check(rc, "sasq_fakequant_fwd_pc_batch")
     _pc_check(items, False)
     arr, dt = _fq_items(items, False)
     _check(_lib().sasq_fakequant_fwd_pc_batch(arr, len(items), bits, dt, _stream()), "sasq_fakequant_fwd_pc_batch")
@@ -284,6 +333,9 @@ def sasq_fakequant_bwd_pc_batch_workspace(items) -> int:
 
 def sasq_fakequant_bwd_pc_batch(items, workspace: torch.Tensor, bits: int = 8) -> None:
     """items: sequence of (x, dy, s[cols], dx_or_None, ds[cols])."""
+    rc = _native.sasq_fakequant_bwd_pc_batch(items, workspace, bits)
+    if rc is not None:
+        return _check(rc, "sasq_fakequant_bwd_pc_batch")
     _pc_check(items, True)
     arr, dt = _fq_items(items, True)
     _check(_lib().sasq_fakequant_bwd_pc_batch(arr, len(items), bits, dt, _ptr(workspace),
@@ -292,6 +344,9 @@ def sasq_fakequant_bwd_pc_batch(items, workspace: torch.Tensor, bits: int = 8) -
 
 
 def sasq_scale_sgd_vec(s: torch.Tensor, ds: torch.Tensor, lr: float) -> None:
+    rc = _native.sasq_scale_sgd_vec(s, ds, lr)
+    if rc is not None:
+        return _check(rc, "sasq_scale_sgd_vec")
     _want(s, torch.float32, "s"); _want(ds, torch.float32, "ds")
     if s.numel() != ds.numel():
         raise ValueError("s and ds must have the same length")
@@ -299,12 +354,18 @@ def sasq_scale_sgd_vec(s: torch.Tensor, ds: torch.Tensor, lr: float) -> None:
 
 
 def sasq_scale_sgd(s: torch.Tensor, ds: torch.Tensor, lr: float) -> None:
+    rc = _native.sasq_scale_sgd(s, ds, lr)
+    if rc is not None:
+        return _check(rc, "sasq_scale_sgd")
     _want(s, torch.float32, "s"); _want(ds, torch.float32, "ds")
     _check(_lib().sasq_scale_sgd(_ptr(s), _ptr(ds), ctypes.c_float(lr), _stream()), "sasq_scale_sgd")
 
 
 def sasq_scale_adamw(s: torch.Tensor, ds: torch.Tensor, m: torch.Tensor, v: torch.Tensor, step: int, lr: float,
                      beta1: float = 0.9, beta2: float = 0.999, eps: float = 1e-8, weight_decay: float = 0.01) -> None:
+    rc = _native.sasq_scale_adamw(s, ds, m, v, step, lr, beta1, beta2, eps, weight_decay)
+    if rc is not None:
+        return _check(rc, "sasq_scale_adamw")
     for t_, n_ in ((s, "s"), (ds, "ds"), (m, "m"), (v, "v")):
         _want(t_, torch.float32, n_)
     if not (s.numel() == ds.numel() == m.numel() == v.numel()):
@@ -322,6 +383,9 @@ def sasq_static_linear(x: torch.Tensor, s: torch.Tensor, wq: torch.Tensor, s_w: 
                        bias: Optional[torch.Tensor], y: torch.Tensor, wf: int = SASQ_W_INT8,
                        workspace: Optional[torch.Tensor] = None, acc_out: Optional[torch.Tensor] = None,
                        xq_out: Optional[torch.Tensor] = None, a_bits: int = 8) -> None:
+    rc = _native.sasq_static_linear(x, s, wq, s_w, bias, y, wf, workspace, acc_out, xq_out, a_bits)
+    if rc is not None:
+        return _check(rc, "sasq_static_linear")
     _want(s, torch.float32, "s"); _want(s_w, torch.float32, "s_w"); _want(bias, torch.float32, "bias")
     _want(acc_out, torch.int32, "acc_out"); _want(xq_out, torch.int8, "xq_out")
     if wq.dtype not in (torch.int8, torch.uint8):
@@ -347,6 +411,9 @@ def sasq_static_linear_grouped(x: torch.Tensor, s_g: torch.Tensor, wq: torch.Ten
                                bias: Optional[torch.Tensor], y: torch.Tensor, group: int, wf: int = SASQ_W_INT8,
                                workspace: Optional[torch.Tensor] = None, f_out: Optional[torch.Tensor] = None,
                                xq_out: Optional[torch.Tensor] = None, a_bits: int = 8) -> None:
+    rc = _native.sasq_static_linear_grouped(x, s_g, wq, s_w, bias, y, group, wf, workspace, f_out, xq_out, a_bits)
+    if rc is not None:
+        return _check(rc, "sasq_static_linear_grouped")
     _want(s_g, torch.float32, "s_g"); _want(s_w, torch.float32, "s_w"); _want(bias, torch.float32, "bias")
     _want(f_out, torch.float32, "f_out"); _want(xq_out, torch.int8, "xq_out")
     if wq.dtype not in (torch.int8, torch.uint8):
@@ -429,6 +496,9 @@ def sasq_static_linear_batch_workspace(items, wf: int = SASQ_W_INT8) -> int:
 
 
 def sasq_static_linear_batch(items, wf: int, workspace: torch.Tensor, a_bits: int = 8) -> None:
+    rc = _native.sasq_static_linear_batch(items, wf, workspace, a_bits)
+    if rc is not None:
+        return _check(rc, "sasq_static_linear_batch")
     arr, dt = _lin_items(items, wf)
     _check(_lib().sasq_static_linear_batch(arr, len(items), a_bits, wf, dt, _ptr(workspace),
                                            workspace.numel() * workspace.element_size(), _stream()),
@@ -436,6 +506,9 @@ def sasq_static_linear_batch(items, wf: int, workspace: torch.Tensor, a_bits: in
 
 
 def sasq_quantize_weight(w: torch.Tensor, wq: torch.Tensor, s_w: torch.Tensor, wf: int = SASQ_W_INT8) -> None:
+    rc = _native.sasq_quantize_weight(w, wq, s_w, wf)
+    if rc is not None:
+        return _check(rc, "sasq_quantize_weight")
     _want(w, torch.float32, "w"); _want(s_w, torch.float32, "s_w")
     N, K = w.shape
     _check(_lib().sasq_quantize_weight(_ptr(w), _ptr(wq), _ptr(s_w), N, K, wf, _stream()), "sasq_quantize_weight")
@@ -446,6 +519,9 @@ def sasq_packed_weight_bytes(N: int, K: int, wf: int) -> int:
 
 
 def sasq_pack_weight(wq: torch.Tensor, packed: torch.Tensor, N: int, K: int, wf_src: int = SASQ_W_INT8) -> None:
+    rc = _native.sasq_pack_weight(wq, packed, N, K, wf_src)
+    if rc is not None:
+        return _check(rc, "sasq_pack_weight")
     blocked = SASQ_W_INT8_BLOCKED if wf_src == SASQ_W_INT8 else SASQ_W_INT4_BLOCKED
     if wq.numel() != (N * K if wf_src == SASQ_W_INT8 else N * (K // 2)):
         raise ValueError("wq does not hold N x K codes in the source format")
@@ -460,6 +536,9 @@ def sasq_bwd_weight_bytes(N: int, K: int) -> int:
 
 def sasq_prepare_bwd_weight(wq: torch.Tensor, s_w: torch.Tensor, wt: torch.Tensor, N: int, K: int,
                             wf: int, dtype: torch.dtype) -> None:
+    rc = _native.sasq_prepare_bwd_weight(wq, s_w, wt, N, K, wf, _DT.get(dtype))
+    if rc is not None:
+        return _check(rc, "sasq_prepare_bwd_weight")
     _want(s_w, torch.float32, "s_w")
     if dtype not in _DT:
         raise TypeError("dtype must be float16 or bfloat16")
@@ -475,6 +554,9 @@ def sasq_prepare_bwd_weight(wq: torch.Tensor, s_w: torch.Tensor, wt: torch.Tenso
 
 def sasq_linear_bwd_input(dy: torch.Tensor, wt: torch.Tensor, dx: torch.Tensor, K: int,
                           acc_out: Optional[torch.Tensor] = None) -> None:
+    rc = _native.sasq_linear_bwd_input(dy, wt, dx, K, acc_out)
+    if rc is not None:
+        return _check(rc, "sasq_linear_bwd_input")
     M, N = dy.shape
     _want(acc_out, torch.float32, "acc_out")
     if acc_out is not None and tuple(acc_out.shape) != (M, K):
@@ -492,6 +574,9 @@ def sasq_absmax_scale_workspace(rows: int, cols: int) -> int:
 
 
 def sasq_absmax_scale(x: torch.Tensor, s: torch.Tensor, workspace: torch.Tensor, bits: int = 8) -> None:
+    rc = _native.sasq_absmax_scale(x, s, workspace, bits)
+    if rc is not None:
+        return _check(rc, "sasq_absmax_scale")
     _want(s, torch.float32, "s")
     rows, cols = x.shape[0], x.numel() // max(x.shape[0], 1)
     _check(_lib().sasq_absmax_scale(_ptr(x), _ptr(s), rows, cols, bits, _dt(x), _ptr(workspace),

@@ -10,6 +10,8 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libsasq.so")
+HOST_SOURCE = os.path.join(PKG, "host", "marshal.cpp")
+MARSHAL_LIB = os.path.join(PKG, "_marshal.so")       # the Python binding's argument marshalling
 BENCH_CSRC = os.path.join(PKG, "bench_csrc")
 BENCH_LIB = os.path.join(PKG, "libsasq_bench.so")    # benchmark tooling (register-only MFMA probe), not part of the C ABI
 TS_LIB = os.path.join(PKG, "libsasq_ts.so")          # benchmark tooling: the library with per-tile timestamps in the batched GEMM
@@ -35,6 +37,24 @@ def stale() -> bool:
     t = os.path.getmtime(LIB)
     deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + [os.path.join(ROOT, "include", "sasq.h")]
     return any(os.path.getmtime(d) > t for d in deps)
+
+
+def build_marshal(verbose: bool = True) -> None:
+    """Compile the binding's native module against the installed torch (host code only)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    for inc in cpp_extension.include_paths() + ["/opt/rocm/include", sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", inc]
+    cmd += ["-I", os.path.join(ROOT, "include"), HOST_SOURCE, "-o", MARSHAL_LIB, "-L", torch_lib]
+    cmd += ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
 
 
 def build(verbose: bool = True, incremental: bool = False) -> str:
@@ -80,8 +100,13 @@ def build(verbose: bool = True, incremental: bool = False) -> str:
         workers = max(1, min(len(srcs) + 1, int(os.environ.get("MAX_JOBS", "0")) or os.cpu_count() or 1))
         with concurrent.futures.ThreadPoolExecutor(max_workers=workers) as pool:
             ts_future = pool.submit(compile_ts, os.path.join(CSRC, TS_SOURCE))
+            host_deps = [HOST_SOURCE, os.path.join(ROOT, "include", "sasq.h")]
+            host_built = incremental and os.path.exists(MARSHAL_LIB) and all(os.path.getmtime(f) <= os.path.getmtime(MARSHAL_LIB) for f in host_deps)
+            host_future = None if host_built else pool.submit(build_marshal, verbose)
             objs = list(pool.map(compile_one, srcs))
             ts_obj = ts_future.result()
+            if host_future:
+                host_future.result()
         link = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
         if verbose:
             print(" ".join(link), flush=True)
