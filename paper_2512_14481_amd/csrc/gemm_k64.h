@@ -33,11 +33,16 @@ void launch_linear_anyk(const GemmK64Args& a, sasq_dtype dt, bool int4, bool row
 double gemm_rounds(int64_t M, int64_t N);
 // At most kSkinnyRows rows, or too few tiles for the GEMM (static_linear_skinny.hip; linear_takes_skinny says whether the
 // sizes are such): the items of `b` (first_block and the tile counts are filled in here), weight layouts 0, 2 and 3.
-// qx: quantize the activations in the kernel (at most kSkinnyQuantRows rows, and no output may overlap an input, as workgroups
-// read x while others write y); otherwise the items' xq hold the staged codes.
+// qx: quantize the activations in the kernel (where linear_quantizes_in_kernel allows it and no output overlaps an input, as
+// workgroups read x while others write y); otherwise the items' xq hold the staged codes.
 constexpr int kSkinnyRows = 64, kSkinnyQuantRows = 16;
 bool linear_takes_skinny(const LinBatch& b, int wmode);
+bool linear_quantizes_in_kernel(const LinBatch& b);
 void launch_linear_skinny(LinBatch& b, sasq_dtype dt, int wmode, bool qx, int a_bits, int32_t* acc_out, hipStream_t st);
+// The backward GEMM dX[M, K] = dY[M, N] . B^T over the prepared weight (linear_bwd.hip), for few rows or too few tiles; N a multiple
+// of 32.  bwd_takes_skinny: rows per workgroup, 0: the tiles are better.
+int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_rounds);
+void launch_bwd_skinny(const void* dy, const void* wt, void* dx, float* acc_out, int64_t M, int64_t N, int64_t K, sasq_dtype dt, int rows, hipStream_t st);
 // split_tail: hand the tiles of a sparsely filled last round out as 128x256 halves (sets b.split_first / b.split_count)
 void launch_gemm_k64_batch(LinBatch& b, int grid, sasq_dtype dt, int wmode, bool split_tail, hipStream_t st);
 

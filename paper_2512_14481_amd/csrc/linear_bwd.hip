@@ -6,6 +6,7 @@
 // runs along operand rows.
 #include "sasq_device.h"
 #include "gemm_tile.h"
+#include "gemm_k64.h"
 #include "gemm_k64_body.h"
 #include <cstdlib>
 #include <cstring>
@@ -357,14 +358,15 @@ static void launch_bwd_k32(const void* dy, const void* wt, void* dx, float* acc_
 
 // 256x256 tiles unless they would leave most of the 256 CUs idle for a round; then 128x128
 // (two workgroups per CU).  sasq_set_tuning(SASQ_TUNE_BWD_TILE, 1 | 2) forces one of them.
+static double rounds256(int64_t M, int64_t K) { return (double)((((M + 255) / 256) * ((K + 255) / 256) + 255) / 256); }
+static double rounds128(int64_t M, int64_t K) { return (double)((((M + 127) / 128) * ((K + 127) / 128) + 511) / 512) * 0.5 * 1.42; }
 static bool bwd_small_tiles(int64_t M, int64_t K)
 {
     if (tuning(SASQ_TUNE_BWD_TILE) == 1) return false;
     if (tuning(SASQ_TUNE_BWD_TILE) == 2) return true;
-    const int64_t t256 = ((M + 255) / 256) * ((K + 255) / 256), t128 = ((M + 127) / 128) * ((K + 127) / 128);
-    const double c256 = (double)((t256 + 255) / 256), c128 = (double)((t128 + 511) / 512) * 0.5 * 1.42;
-    return c128 < c256;
+    return rounds128(M, K) < rounds256(M, K);
 }
+static double bwd_tile_rounds(int64_t M, int64_t K) { return rounds128(M, K) < rounds256(M, K) ? rounds128(M, K) : rounds256(M, K); }
 
 static int64_t bwd_kpad(int64_t K) { return (K + 15) / 16 * 16; }
 static int64_t bwd_npad(int64_t N) { return (N + kBwdCols - 1) / kBwdCols * kBwdCols; }
@@ -435,6 +437,11 @@ extern "C" int sasq_linear_bwd_input(const void* dy, const void* wt, void* dx, f
         else                linear_bwd_scalar_kernel<SASQ_BF16><<<(int)grid, 256, 0, st>>>(DY, WT, DX, acc_out, M, N, K, bwd_npad(N));
         return hipGetLastError() == hipSuccess ? SASQ_OK : SASQ_ERR_LAUNCH;
     }
+    if (tuning(SASQ_TUNE_LINEAR_MFMA) == 0 && tuning(SASQ_TUNE_BWD_TILE) == 0)
+        if (const int rows = bwd_takes_skinny(M, N, K, bwd_tile_rounds(M, K))) {
+            launch_bwd_skinny(dy, wt, dx, acc_out, M, N, K, dt, rows, st);
+            return hipGetLastError() == hipSuccess ? SASQ_OK : SASQ_ERR_LAUNCH;
+        }
     const bool small = bwd_small_tiles(M, K);
     // the 16x16x32 kernel addresses dY rows with 32-bit byte offsets inside a 256-row tile
     if (tuning(SASQ_TUNE_LINEAR_MFMA) != 1 && N <= (INT64_C(1) << 22)) {

@@ -923,17 +923,17 @@ static bool use_skinny(const LinBatch& g, sasq_wfmt wf)
            tuning(SASQ_TUNE_LINEAR_MFMA) == 0 && linear_takes_skinny(g, (int)wf);
 }
 
-// Whether such a call quantizes in the kernel: at most 16 rows everywhere, and no output over an input (the pre-pass has
-// read every x before the first y is written; workgroups that quantize for themselves have not).
+// Whether such a call quantizes in the kernel: few codes, and no output over an input (the pre-pass has read every x before the
+// first y is written; workgroups that quantize for themselves have not).
 static bool skinny_quantizes(const LinBatch& g, const int32_t* acc_out)
 {
     auto overlap = [](const void* a, size_t an, const void* b, size_t bn) {
         const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
         return pa < pb + bn && pb < pa + an;
     };
+    if (!linear_quantizes_in_kernel(g)) return false;
     for (int i = 0; i < g.count; ++i) {
         const LinItem& in = g.it[i];
-        if (in.M > kSkinnyQuantRows) return false;
         const size_t xbytes = (size_t)in.M * in.K * 2;
         for (int j = 0; j < g.count; ++j) {
             const LinItem& out = g.it[j];

@@ -9,8 +9,8 @@
 // 1 KB block IS one operand read of a wave), D K tiles ahead, with no LDS and no barrier until the waves' int32 sums are
 // added up at the end, so that some thousand waves each keep several KB in flight.  Integer sums make the split exact.
 // QX: the activations are quantized on the way into the operand registers, 16 elements per lane and K tile, which takes
-// the pre-pass's launch out of the call; each workgroup repeats that work, so it is for at most 16 rows.  Otherwise the
-// codes come from the pre-pass in their staging blocks.
+// the pre-pass's launch out of the call; each workgroup repeats that work, so it is for at most 16 rows, or for few codes
+// (linear_quantizes_in_kernel).  Otherwise the codes come from the pre-pass in their staging blocks.
 // Row blocks (more than 64 rows): what bounds them is the operands' delivery from L2, (BM + 64) K bytes per workgroup for
 // BM x 64 outputs, and the few us in which a workgroup starts and ends; 333 x 4096 x 4096 takes 16.0 us with its pre-pass (27.1 on
 // 96 GEMM tiles of 128 x 128).  Of 333 x 4096 x 4096's 11 us in the kernel, 1.3 are arguments and addresses, 8 the K loop (19 TB/s
@@ -20,6 +20,7 @@
 #include "sasq_device.h"
 #include "gemm_tile.h"
 #include "gemm_k64.h"
+#include "gemm_k64_body.h"
 #include <cmath>
 #include <type_traits>
 
@@ -35,13 +36,17 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_rsrc(const void* base,
 // Row tiles whose sums meet in LDS at a time (128 KB at most).
 template <int MT, int NT, int NW> constexpr int skinny_rows_per_phase() { return NW * NT * MT <= 128 ? MT : MT / 2; }
 
-template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE>
+// FLT: the backward GEMM of the frozen linear.  x is dY, 16-bit and row-major, K the contraction's bytes per row, the weight blocks
+// hold 16 rows x 32 numbers, the sums are fp32 (the waves' parts added in their order) and go out rounded, without factors.
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool FLT = false>
 __device__ __forceinline__
 void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __restrict__ acc_out, char* lds)
 {
     using S = Store16<DT>;
     constexpr bool I4 = WMODE == 3, ROWMAJOR = WMODE == 0, BLOCKS = !ONCE || MT > 4;
     static_assert(!I4 || NT % 2 == 0, "int4 blocks hold 32 weight rows");
+    static_assert(!FLT || (WMODE == 2 && !QX), "float contraction: weight blocks, no codes");
+    using AccT = std::conditional_t<FLT, f32x4, i32x4>;
     constexpr int WL = I4 ? NT / 2 : NT;               // 128-bit weight loads per lane and K tile
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -71,16 +76,18 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
         }
     }
     constexpr int kWStep = ROWMAJOR ? 64 : 1024;
-    const char* xbase = QX ? reinterpret_cast<const char*>(it.x) + ((int64_t)m0 * K + (int64_t)t0 * 64) * 2
+    const char* xbase = FLT ? reinterpret_cast<const char*>(it.x) + (int64_t)m0 * K + (int64_t)t0 * 64
+                      : QX ? reinterpret_cast<const char*>(it.x) + ((int64_t)m0 * K + (int64_t)t0 * 64) * 2
                            : reinterpret_cast<const char*>(it.xq) + ((int64_t)(m0 >> 4) * KT + t0) * 1024;
     uint32_t xoff[MT];
 #pragma unroll
     for (int b = 0; b < MT; ++b) {
-        if (QX) xoff[b] = (uint32_t)min(16 * b + frow, M - 1 - m0) * (uint32_t)K * 2 + fq * 32;
-        else    xoff[b] = (uint32_t)min(b, ((M - 1) >> 4) - (m0 >> 4)) * (uint32_t)KT * 1024 + (4 * frow + (fq ^ swz64(frow))) * 16;
+        if (FLT)     xoff[b] = (uint32_t)min(16 * b + frow, M - 1 - m0) * (uint32_t)K + 16 * fq;
+        else if (QX) xoff[b] = (uint32_t)min(16 * b + frow, M - 1 - m0) * (uint32_t)K * 2 + fq * 32;
+        else         xoff[b] = (uint32_t)min(b, ((M - 1) >> 4) - (m0 >> 4)) * (uint32_t)KT * 1024 + (4 * frow + (fq ^ swz64(frow))) * 16;
     }
-    constexpr int kXStep = QX ? 128 : 1024;
-    const QConst qk = make_qconst(*it.s, a_bits);
+    constexpr int kXStep = FLT ? 64 : QX ? 128 : 1024;
+    const QConst qk = FLT ? QConst{} : make_qconst(*it.s, a_bits);
 
     struct Frag {
         u32x4 w[WL];
@@ -102,11 +109,11 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
 #pragma unroll
             for (int h = 0; h < (QX ? 2 : 1); ++h) f.x[b][h] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff[b] + 16 * h, t * kXStep, 0);
     };
-    i32x4 acc[NT][MT];
+    AccT acc[NT][MT];
 #pragma unroll
     for (int g = 0; g < NT; ++g)
 #pragma unroll
-        for (int b = 0; b < MT; ++b) acc[g][b] = i32x4{0, 0, 0, 0};
+        for (int b = 0; b < MT; ++b) acc[g][b] = AccT{0, 0, 0, 0};
     auto multiply = [&](const Frag& f) {
         i32x4 xv[MT];
 #pragma unroll
@@ -137,7 +144,10 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
                 wv = __builtin_bit_cast(i32x4, f.w[g]);
             }
 #pragma unroll
-            for (int b = 0; b < MT; ++b) acc[g][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wv, xv[b], acc[g][b], 0, 0, 0);
+            for (int b = 0; b < MT; ++b) {
+                if constexpr (FLT) acc[g][b] = Mfma16x16<DT>::mma(wv, xv[b], acc[g][b]);
+                else               acc[g][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wv, xv[b], acc[g][b], 0, 0, 0);
+            }
         }
     };
 
@@ -148,6 +158,7 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
     const int g0 = wave % kRuns * kRegs, n = n0 + 16 * g0 + kCols * fq;
     float sw[kCols], bv[kCols];
     auto load_factors = [&]() {
+        if (FLT) return;
 #pragma unroll
         for (int e = 0; e < kCols; ++e) {
             const int ne = min(n + e, N - 1);
@@ -205,7 +216,7 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
 
     // The waves' sums meet in LDS, as many row tiles at a time as fit; wave w finishes the output tiles w, w + NW, ...
     constexpr int kRows = skinny_rows_per_phase<MT, NT, NW>(), kTiles = kRuns * kRows;
-    i32x4* part = reinterpret_cast<i32x4*>(lds);
+    AccT* part = reinterpret_cast<AccT*>(lds);
     const float s = qk.s;
 #pragma unroll
     for (int b0 = 0; b0 < MT; b0 += kRows) {
@@ -218,14 +229,17 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
 #pragma unroll
         for (int t = wave; t < kTiles; t += NW) {
             const int b = t / kRuns;
-            int v[kCols];
+            std::conditional_t<FLT, float, int> v[kCols];
 #pragma unroll
             for (int r = 0; r < kRegs; ++r) {
-                i32x4 sum = {0, 0, 0, 0};
+                AccT sum = {0, 0, 0, 0};
 #pragma unroll
                 for (int w = 0; w < NW; ++w) sum += part[((w * NT + g0 + r) * kRows + b) * 64 + lane];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[kRegs * e + r] = I4 ? sum[e] >> 4 : sum[e];
+                for (int e = 0; e < 4; ++e) {
+                    if constexpr (I4) v[kRegs * e + r] = sum[e] >> 4;
+                    else              v[kRegs * e + r] = sum[e];
+                }
             }
             const int m = m0 + 16 * (b0 + b) + frow;                         // 4 (8) consecutive columns of one row
             if (m >= M || n >= N) continue;
@@ -233,8 +247,9 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
             float yv[kCols];
 #pragma unroll
             for (int e = 0; e < kCols; ++e) {
-                float f = (float)v[e] * (s * sw[e]);
-                if (it.bias) f = f + bv[e];
+                float f = (float)v[e];
+                if (!FLT) f = f * (s * sw[e]);
+                if (!FLT && it.bias) f = f + bv[e];
                 yv[e] = f;
             }
             if ((N & 7) == 0) {                                              // then every full run is aligned to its own size
@@ -249,7 +264,7 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
             if (acc_out) {
 #pragma unroll
                 for (int e = 0; e < kCols; ++e)
-                    if (n + e < N) acc_out[(int64_t)m * N + n + e] = v[e];
+                    if (n + e < N) acc_out[(int64_t)m * N + n + e] = __builtin_bit_cast(int32_t, v[e]);
             }
         }
     }
@@ -419,6 +434,21 @@ bool linear_takes_skinny(const LinBatch& b, int wmode)
     return rows <= kSkinnyRows ? !tiles_are_better(b, rows, wmode) : block_rows(b, wmode) != 0;
 }
 
+// Whether such a call, of at most kSkinnyRows rows, quantizes in the kernel: at most 16 rows, or so few codes in an item's row tiles
+// (of 32 or 64 rows) that repeating them costs a workgroup less than a launch.  Measured, us, pre-pass | in the kernel: 32 rows, K =
+// 256 4.8 | 3.3, 1024 5.4 | 4.9, 2048 6.8 | 7.0, 4096 8.5 | 10.6; 64 rows, K = 256 5.1 | 3.7, 512 5.3 | 4.7, 1024 6.0 | 7.1.
+bool linear_quantizes_in_kernel(const LinBatch& b)
+{
+    int rows = 0, k_max = 0;
+    int64_t tiles16 = 0;
+    for (int i = 0; i < b.count; ++i) {
+        rows = b.it[i].M > rows ? b.it[i].M : rows;
+        k_max = b.it[i].K > k_max ? b.it[i].K : k_max;
+        tiles16 += (b.it[i].N + 15) / 16;
+    }
+    return rows <= kSkinnyQuantRows || (rows <= kSkinnyRows && (int64_t)(rows <= 32 ? 32 : 64) * k_max <= 32768 && tiles16 < 512);
+}
+
 template <int DT, int WMODE>
 static void launch_wmode(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, hipStream_t st)
 {
@@ -435,7 +465,9 @@ static void launch_wmode(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, hip
         else if (block == 96)                launch_one<DT, WMODE, 6, 4, 8, 2, false, true>(b, a_bits, acc_out, st);
         else if (rows > 128)                 launch_one<DT, WMODE, 8, 4, 8, 2, false, false>(b, a_bits, acc_out, st);
         else                                 launch_one<DT, WMODE, 8, 4, 8, 2, false, true>(b, a_bits, acc_out, st);
-    } else if (qx)       launch_mt<DT, WMODE, 1, true>(b, tiles16, a_bits, acc_out, st);
+    } else if (qx && rows > 32)               launch_one<DT, WMODE, 4, WMODE == 3 ? 2 : 1, 8, 2, true, true>(b, a_bits, acc_out, st);
+    else if (qx && rows > kSkinnyQuantRows) launch_one<DT, WMODE, 2, WMODE == 3 ? 2 : 1, 8, 2, true, true>(b, a_bits, acc_out, st);
+    else if (qx)       launch_mt<DT, WMODE, 1, true>(b, tiles16, a_bits, acc_out, st);
     else if (rows <= 32) launch_mt<DT, WMODE, 2, false>(b, tiles16, a_bits, acc_out, st);
     else if (rows <= 48) launch_mt<DT, WMODE, 3, false>(b, tiles16, a_bits, acc_out, st);
     else                 launch_mt<DT, WMODE, 4, false>(b, tiles16, a_bits, acc_out, st);
@@ -451,6 +483,83 @@ void launch_linear_skinny(LinBatch& b, sasq_dtype dt, int wmode, bool qx, int a_
     };
     if (dt == SASQ_F16) by_wmode(std::integral_constant<int, SASQ_F16>{});
     else                by_wmode(std::integral_constant<int, SASQ_BF16>{});
+}
+
+// ---- the backward GEMM ----------------------------------------------------------------------
+template <int DT, int MT, int NT, int NW, int D, bool ONCE>
+__global__ __launch_bounds__(64 * NW)
+void bwd_skinny_kernel(const LinItem it, float* __restrict__ acc_out)
+{
+    __shared__ __attribute__((aligned(1024))) char lds[NW * NT * skinny_rows_per_phase<MT, NT, NW>() * 1024];
+    const int id = (int)blockIdx.x, octet = id >> 3;                 // as in skinny_kernel
+    const int mblk = octet % it.tiles_m, nblk = octet / it.tiles_m * 8 + (id & 7);
+    if (nblk >= it.tiles_n) return;
+    skinny_body<DT, 2, MT, NT, NW, D, false, ONCE, true>(it, mblk, nblk, 8, reinterpret_cast<int32_t*>(acc_out), lds);
+}
+
+template <int DT, int MT, int NT, int NW, int D, bool ONCE>
+static void launch_bwd_one(LinItem& it, float* acc_out, hipStream_t st)
+{
+    it.tiles_m = (it.M + 16 * MT - 1) / (16 * MT);
+    it.tiles_n = (it.N + 16 * NT - 1) / (16 * NT);
+    bwd_skinny_kernel<DT, MT, NT, NW, D, ONCE><<<(it.tiles_n + 7) / 8 * 8 * it.tiles_m, 64 * NW, 0, st>>>(it, acc_out);
+}
+
+// Rows per workgroup, from estimates in us as in block_rows above: at most 64 rows 64 (in row tiles of 16, 32 or 64); more rows 64 or
+// 96 by 64 columns, where that takes 15 % less time than the GEMM's tiles (128 never do).  260 calls of 8 to 1500 rows, contractions and outputs
+// of 256 to 13824: at most 16 rows take 0.41 of their time on the tiles, 17 to 32 0.56, 33 to 64 0.69, more 0.89 (those on row
+// blocks 0.76), and none 2 % more.  us, tiles | here: 1 x 4096 x 4096 25.3 | 8.0, 64 x 256 x 256 4.8 | 3.4, 131 x 2816 x 1344 23.4 |
+// 17.3, 334 x 11072 x 1536 76.2 | 52.5.
+int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_rounds)
+{
+    if (M <= 32 || (M <= 64 && K <= 4096)) return K <= INT64_C(1) << 26 ? 64 : 0;     // up to 32 work items a column
+    if (K <= 448) return 0;                                          // fewer than eight runs of weight rows leave XCDs without work
+    static const BlockTime block[2] = {{1.8, 2.1, 0.155}, {1.5, 3.4, 0.205}};
+    const double kt = (double)(N / 32);
+    double best = 0.85 * tile_rounds * (3.7 + 0.396 * kt);
+    int rows = 0;
+    for (int f = 0; f < (M <= 64 ? 1 : 2); ++f) {
+        const int r = f == 0 ? 64 : 96;
+        const int64_t blocks = (M + r - 1) / r * ((K + 511) / 512 * 8);
+        if (blocks >= INT64_C(1) << 22) continue;                    // a launch holds fewer than 2^32 work items
+        const double us = block[f].call + (double)((blocks + 255) / 256) * (block[f].round + block[f].k_tile * kt);
+        if (us < best) { best = us; rows = r; }
+    }
+    return rows;
+}
+
+// Few rows: narrow workgroups (16 columns) while they make one round of at most 256, wide ones from then on (over calls of 17 to 64
+// rows a line at 4096 columns takes 0.96 of the time of one at 8192).
+template <int DT>
+static void launch_bwd_dt(LinItem& it, float* acc_out, int rows, hipStream_t st)
+{
+    const bool wide = it.N > 4096;
+    if (it.M > 64) {
+        if (rows == 64) launch_bwd_one<DT, 4, 4, 8, 2, false>(it, acc_out, st);
+        else            launch_bwd_one<DT, 6, 4, 8, 2, false>(it, acc_out, st);
+    } else if (it.M <= 16) {
+        if (wide) launch_bwd_one<DT, 1, 2, 8, 3, true>(it, acc_out, st);
+        else      launch_bwd_one<DT, 1, 1, 8, 4, true>(it, acc_out, st);
+    } else if (it.M <= 32) {
+        if (wide) launch_bwd_one<DT, 2, 2, 8, 3, true>(it, acc_out, st);
+        else      launch_bwd_one<DT, 2, 1, 8, 4, true>(it, acc_out, st);
+    } else {
+        if (wide) launch_bwd_one<DT, 4, 4, 8, 2, true>(it, acc_out, st);
+        else      launch_bwd_one<DT, 4, 1, 8, 4, true>(it, acc_out, st);
+    }
+}
+
+void launch_bwd_skinny(const void* dy, const void* wt, void* dx, float* acc_out, int64_t M, int64_t N, int64_t K, sasq_dtype dt, int rows, hipStream_t st)
+{
+    LinItem it{};
+    it.x = dy;
+    it.wq = static_cast<const uint8_t*>(wt);
+    it.y = static_cast<uint16_t*>(dx);
+    it.M = (int)M;
+    it.N = (int)K;                                                   // the body's columns and contraction bytes
+    it.K = (int)(2 * N);
+    if (dt == SASQ_F16) launch_bwd_dt<SASQ_F16>(it, acc_out, rows, st);
+    else                launch_bwd_dt<SASQ_BF16>(it, acc_out, rows, st);
 }
 
 }  // namespace sasq

@@ -1,0 +1,50 @@
+"""GPU parity of the backward linear's kernels for few rows and row blocks (contraction split over the waves, no tiles) against the CPU
+oracle: the row-tile forms (16, 32, 64 rows; narrow and wide), blocks of 64 and 96 rows, waves without a contraction tile, ragged
+rows and columns.  Bounds as for the tiled kernels: fp32 sums in any order, one rounding."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2512_14481_amd import workloads as wl
+from tests.test_gpu_linear_bwd import check_dx, prepare, problem, run_bwd
+
+pytestmark = pytest.mark.gpu
+
+
+def up(a, b):
+    return -(-a // b)
+
+
+def chosen(M, N, K):
+    """Rows per workgroup the dispatch takes (bwd_takes_skinny), 0: the GEMM's tiles."""
+    if M <= 32 or (M <= 64 and K <= 4096):
+        return 64
+    if K <= 448:
+        return 0
+    rounds = min(up(up(M, 256) * up(K, 256), 256), up(up(M, 128) * up(K, 128), 512) * 0.71)
+    best, rows = 0.85 * rounds * (3.7 + 0.396 * (N // 32)), 0
+    for r, (call, per_round, per_tile) in list(zip((64, 96), [(1.8, 2.1, 0.155), (1.5, 3.4, 0.205)]))[:1 if M <= 64 else 2]:
+        us = call + up(up(M, r) * up(K, 512) * 8, 256) * (per_round + per_tile * (N // 32))
+        if us < best:
+            best, rows = us, r
+    return rows
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("shape,want", [
+    ((1, 32, 2), 64), ((16, 576, 4096), 64), ((15, 96, 4104), 64), ((17, 64, 70), 64), ((32, 1088, 5001), 64), ((33, 96, 48), 64),
+    ((64, 1056, 4096), 64), ((64, 2048, 4200), 64), ((50, 1024, 5003), 64), ((40, 32, 20000), 0),
+    ((65, 1024, 1000), 64), ((130, 1024, 520), 64), ((129, 1600, 449), 64), ((130, 1024, 448), 0), ((380, 4096, 4000), 96)])
+def test_few_rows_and_row_blocks_match_oracle(shape, want, dtype):
+    assert chosen(*shape) == want
+    dyb, wq, s_w = problem(83, shape, dtype, "int8")
+    wt, K = prepare(wq, s_w, "int8", dtype)
+    ref = oracle.linear_bwd_input(dyb, wq, s_w, "int8", dtype)
+    got, acc = run_bwd(dyb, wt, K, dtype, want_acc=True)
+    check_dx(got, ref, dtype, shape[1], f"{shape} {dtype}")
+    err = np.abs(acc.astype(np.float64) - ref["exact"])
+    assert (err <= shape[1] * 2.0 ** -24 * ref["sum_abs"] + 1e-45).all(), err.max()
+    assert np.array_equal(got, wl.f32_to_storage_bits(acc, dtype))
+    assert np.array_equal(run_bwd(dyb, wt, K, dtype), got)

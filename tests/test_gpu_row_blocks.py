@@ -88,3 +88,30 @@ def test_row_blocks_match_oracle(items, want, fmt, blocked):
         B.sasq_static_linear_batch(batch, wf, B.new_workspace(B.sasq_static_linear_batch_workspace(batch, wf)))
     for it, ref in zip(batch, refs):
         assert_same_values(to_bits(it[5]), ref["y"], "bf16", "Y")
+
+
+@pytest.mark.parametrize("fmt,blocked", LAYOUTS)
+@pytest.mark.parametrize("shape", [(17, 47, 64), (32, 700, 1024), (32, 700, 1088), (33, 701, 512), (64, 700, 512), (64, 700, 576), (20, 8200, 192)])
+def test_rows_quantized_in_the_kernel_match_oracle(shape, fmt, blocked):
+    """17 to 64 rows around the line up to which each workgroup quantizes for itself (rows in tiles of 32 or 64, times K: 32768)."""
+    set_tuning()
+    M, N, K = shape
+    xb, wq, s_w, bias, s = problem(110, shape, fmt, "f16")
+    ref = oracle.static_linear(xb, s, wq, s_w, bias, 8, fmt, "f16")
+    wf = WF[(fmt, blocked)]
+    y, acc = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda"), torch.zeros((M, N), dtype=torch.int32, device="cuda")
+    B.sasq_static_linear(to_dev(xb, "f16"), dev_scalar(s), device_weights(wq, fmt, blocked), torch.from_numpy(s_w).cuda(),
+                         torch.from_numpy(bias).cuda(), y, wf, B.new_workspace(B.sasq_static_linear_workspace(M, N, K, wf)), acc, None)
+    assert np.array_equal(acc.cpu().numpy(), ref["acc"])
+    assert_same_values(to_bits(y), ref["y"], "f16", "Y")
+
+
+def test_output_over_input_at_thirty_rows():
+    set_tuning()
+    shape = (30, 1024, 1024)
+    xb, wq, s_w, _, s = problem(111, shape, "int8", "f16")
+    ref = oracle.static_linear(xb, s, wq, s_w, None, 8, "int8", "f16")
+    x = to_dev(xb, "f16")
+    B.sasq_static_linear(x, dev_scalar(s), device_weights(wq, "int8", True), torch.from_numpy(s_w).cuda(), None, x, B.SASQ_W_INT8_BLOCKED,
+                         B.new_workspace(B.sasq_static_linear_workspace(*shape, B.SASQ_W_INT8_BLOCKED)))
+    assert_same_values(to_bits(x), ref["y"], "f16", "Y")
