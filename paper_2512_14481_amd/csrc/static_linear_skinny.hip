@@ -101,13 +101,19 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
         // 18.8 us non-temporal, 16.8 cached), and row-major a K tile is half a 128-byte line of each row, the other half the next
         // K tile's (the 7B layer below: 54 us and 51).
         constexpr int kNonTemporal = 2;
+        // Few row-major rows: plain loads (7B layer, 8 rows 50.6 us through buffers, 49.8 so; 12 x 2368 x 28544's MLP 72.9, 70.0).
+        constexpr bool kPlain = ROWMAJOR && !BLOCKS;
 #pragma unroll
         for (int j = 0; j < WL; ++j)
-            f.w[j] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, woff[j], t * kWStep, ONCE && !ROWMAJOR ? kNonTemporal : 0);
+            if constexpr (kPlain) f.w[j] = *reinterpret_cast<const u32x4*>(wbase + (int64_t)t * kWStep + woff[j]);
+            else                  f.w[j] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, woff[j], t * kWStep, ONCE && !ROWMAJOR ? kNonTemporal : 0);
 #pragma unroll
         for (int b = 0; b < MT; ++b)
 #pragma unroll
-            for (int h = 0; h < (QX ? 2 : 1); ++h) f.x[b][h] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff[b] + 16 * h, t * kXStep, 0);
+            for (int h = 0; h < (QX ? 2 : 1); ++h) {
+                if constexpr (kPlain) f.x[b][h] = *reinterpret_cast<const u32x4*>(xbase + (int64_t)t * kXStep + xoff[b] + 16 * h);
+                else                  f.x[b][h] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff[b] + 16 * h, t * kXStep, 0);
+            }
     };
     AccT acc[NT][MT];
 #pragma unroll
