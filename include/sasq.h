@@ -142,7 +142,8 @@ int sasq_fakequant_bwd(const void* x, const void* dy, const float* s, void* dx, 
  *   - rows * cols above SASQ_FAKEQUANT_BWD_STATIC_MAX_ELEMENTS is rejected with SASQ_ERR_SHAPE.
  *   - The first call on a device looks the array's address up (no allocation); make that call
  *     outside graph capture.  A failed lookup returns SASQ_ERR_WORKSPACE.
- *   - Two kernels are enqueued: a one-thread clear of the ticket word, then the backward kernel.
+ *   - Two kernels are enqueued: a one-thread clear of the ticket word, then the backward kernel (a small tensor's,
+ *     up to 24583 elements, needs no ticket: one kernel, and the array is not touched).
  */
 #define SASQ_FAKEQUANT_BWD_STATIC_MAX_ELEMENTS (INT64_C(1) << 40)
 int sasq_fakequant_bwd_static(const void* x, const void* dy, const float* s, void* dx, float* ds,

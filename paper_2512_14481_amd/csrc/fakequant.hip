@@ -333,6 +333,76 @@ __global__ __launch_bounds__(kThreads) void fakequant_bwd_kernel(
     bwd_body<DT, WRITE_DX>(x, dy, s_ptr, dx, ds, ws_head, partials, nvec, n, bits, (int)blockIdx.x, (int)gridDim.x);
 }
 
+// Backward of a small tensor by one workgroup: all of a thread's accesses are requested before the first is used, and the sum needs no
+// ticket, whose round trips to the level that the XCDs share (publish, ticket, partials) are a third of such a call.  One CU's
+// bandwidth ends it.  Measured, us, blocks with a ticket 4.9 to 5.2 at all these sizes | one workgroup: 2048 elements 3.3, 8192 3.3,
+// 16384 3.7, 24576 4.5, 32768 5.3.
+// The ticket word is only looked at, so that a workspace that was never initialised still shows (head: NULL without a workspace).
+constexpr int kSmallThreads = 1024, kSmallWaves = kSmallThreads / kWave;
+constexpr int64_t kSmallVec = 3 * kSmallThreads;
+
+template <int DT, bool WRITE_DX, int U>
+__global__ __launch_bounds__(kSmallThreads) void fakequant_bwd_small_kernel(
+    const u32x4* x, const u32x4* dy, const float* __restrict__ s_ptr, u32x4* dx, float* __restrict__ ds, const uint32_t* __restrict__ head,
+    int nvec, int n, int bits)
+{
+    using S = Store16<DT>;
+    const int t = (int)threadIdx.x;
+    const uint32_t ticket = head ? *head : kTicketBase;
+    u32x4 xin[U], gin[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = u * kSmallThreads + t;
+        xin[u] = gin[u] = u32x4{0u, 0u, 0u, 0u};
+        if (i < nvec) { xin[u] = x[i]; gin[u] = dy[i]; }
+    }
+    // the n % 8 elements behind the last vector, one a thread
+    const uint16_t* xs = reinterpret_cast<const uint16_t*>(x);
+    const uint16_t* gs = reinterpret_cast<const uint16_t*>(dy);
+    const int e = nvec * 8 + t;
+    uint16_t xe = 0, ge = 0;
+    if (e < n) { xe = xs[e]; ge = gs[e]; }
+    const QConst k = make_qconst(*s_ptr, bits);
+    double acc = 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = u * kSmallThreads + t;
+        u32x4 out;
+        const double part = (double)bwd_vec<DT>(xin[u], gin[u], k, out);
+        if (i < nvec) {
+            acc += part;
+            if (WRITE_DX) dx[i] = out;
+        }
+    }
+    if (e < n) {
+        bool keep;
+        acc += (double)ds_term(S::one(xe), S::one(ge), k, keep);
+        if (WRITE_DX) reinterpret_cast<uint16_t*>(dx)[e] = keep ? ge : (uint16_t)0;
+    }
+    __shared__ double wave_part[kSmallWaves];
+    const double w = wave_sum(acc);
+    if (t % kWave == 0) wave_part[t / kWave] = w;
+    __syncthreads();
+    if (t < kWave) {                                       // one wave adds the sixteen: a tree instead of a chain of LDS reads
+        const double sum = wave_sum(t < kSmallWaves ? wave_part[t] : 0.0);
+        if (t == 0) *ds = ticket == kTicketBase ? (float)sum : __uint_as_float(0x7FC00000u);
+    }
+}
+
+template <int DT, bool WRITE_DX>
+static void launch_bwd(const u32x4* x, const u32x4* dy, const float* s, u32x4* dx, float* ds, uint32_t* head, double* parts,
+                       int64_t nvec, int64_t n, int bits, bool small, int grid, hipStream_t st)
+{
+    if (!small)
+        fakequant_bwd_kernel<DT, WRITE_DX><<<grid, kThreads, 0, st>>>(x, dy, s, dx, ds, head, parts, nvec, n, bits);
+    else if (nvec <= kSmallThreads)
+        fakequant_bwd_small_kernel<DT, WRITE_DX, 1><<<1, kSmallThreads, 0, st>>>(x, dy, s, dx, ds, head, (int)nvec, (int)n, bits);
+    else if (nvec <= 2 * kSmallThreads)
+        fakequant_bwd_small_kernel<DT, WRITE_DX, 2><<<1, kSmallThreads, 0, st>>>(x, dy, s, dx, ds, head, (int)nvec, (int)n, bits);
+    else
+        fakequant_bwd_small_kernel<DT, WRITE_DX, 3><<<1, kSmallThreads, 0, st>>>(x, dy, s, dx, ds, head, (int)nvec, (int)n, bits);
+}
+
 // Batched backward: every entry is one operator (sharing the read of x did not pay here: the
 // fused body needs 200 registers and ran 2 % slower than the operators apart); it uses the ticket
 // word and the run of kMaxReduceBlocks partials of its index in the caller's batch.
@@ -444,6 +514,7 @@ extern "C" int sasq_fakequant_bwd(const void* x, const void* dy, const float* s,
     if (!workspace || workspace_bytes < sasq_fakequant_bwd_workspace(rows, cols)) return SASQ_ERR_WORKSPACE;
     if (!aligned16(workspace)) return SASQ_ERR_ALIGN;
     const int64_t n = rows * cols, nvec = n / 8;
+    const bool small = nvec <= kSmallVec;
     const int grid = grid_for(nvec, kMaxReduceBlocks);
     hipStream_t st = as_stream(stream);
     auto X = static_cast<const u32x4*>(x);
@@ -452,11 +523,11 @@ extern "C" int sasq_fakequant_bwd(const void* x, const void* dy, const float* s,
     auto head = static_cast<uint32_t*>(workspace);
     auto parts = reinterpret_cast<double*>(static_cast<char*>(workspace) + kWsHeaderBytes);
     if (dt == SASQ_F16) {
-        if (dx) fakequant_bwd_kernel<SASQ_F16, true><<<grid, kThreads, 0, st>>>(X, G, s, DX, ds, head, parts, nvec, n, bits);
-        else    fakequant_bwd_kernel<SASQ_F16, false><<<grid, kThreads, 0, st>>>(X, G, s, DX, ds, head, parts, nvec, n, bits);
+        if (dx) launch_bwd<SASQ_F16, true>(X, G, s, DX, ds, head, parts, nvec, n, bits, small, grid, st);
+        else    launch_bwd<SASQ_F16, false>(X, G, s, DX, ds, head, parts, nvec, n, bits, small, grid, st);
     } else {
-        if (dx) fakequant_bwd_kernel<SASQ_BF16, true><<<grid, kThreads, 0, st>>>(X, G, s, DX, ds, head, parts, nvec, n, bits);
-        else    fakequant_bwd_kernel<SASQ_BF16, false><<<grid, kThreads, 0, st>>>(X, G, s, DX, ds, head, parts, nvec, n, bits);
+        if (dx) launch_bwd<SASQ_BF16, true>(X, G, s, DX, ds, head, parts, nvec, n, bits, small, grid, st);
+        else    launch_bwd<SASQ_BF16, false>(X, G, s, DX, ds, head, parts, nvec, n, bits, small, grid, st);
     }
     return hipGetLastError() == hipSuccess ? SASQ_OK : SASQ_ERR_LAUNCH;
 }
@@ -510,20 +581,21 @@ extern "C" int sasq_fakequant_bwd_static(const void* x, const void* dy, const fl
     void* base = scratch_of_current_device();
     if (!base) return SASQ_ERR_WORKSPACE;
     const int64_t n = rows * cols, nvec = n / 8;
+    const bool small = nvec <= kSmallVec;
     const int grid = grid_for(nvec, kMaxReduceBlocks);
     hipStream_t st = as_stream(stream);
     auto X = static_cast<const u32x4*>(x);
     auto G = static_cast<const u32x4*>(dy);
     auto DX = static_cast<u32x4*>(dx);
-    auto head = static_cast<uint32_t*>(base);
+    auto head = small ? nullptr : static_cast<uint32_t*>(base);
     auto parts = reinterpret_cast<double*>(static_cast<char*>(base) + kWsHeaderBytes);
-    clear_ticket_kernel<<<1, 64, 0, st>>>(head);
+    if (!small) clear_ticket_kernel<<<1, 64, 0, st>>>(head);
     if (dt == SASQ_F16) {
-        if (dx) fakequant_bwd_kernel<SASQ_F16, true><<<grid, kThreads, 0, st>>>(X, G, s, DX, ds, head, parts, nvec, n, bits);
-        else    fakequant_bwd_kernel<SASQ_F16, false><<<grid, kThreads, 0, st>>>(X, G, s, DX, ds, head, parts, nvec, n, bits);
+        if (dx) launch_bwd<SASQ_F16, true>(X, G, s, DX, ds, head, parts, nvec, n, bits, small, grid, st);
+        else    launch_bwd<SASQ_F16, false>(X, G, s, DX, ds, head, parts, nvec, n, bits, small, grid, st);
     } else {
-        if (dx) fakequant_bwd_kernel<SASQ_BF16, true><<<grid, kThreads, 0, st>>>(X, G, s, DX, ds, head, parts, nvec, n, bits);
-        else    fakequant_bwd_kernel<SASQ_BF16, false><<<grid, kThreads, 0, st>>>(X, G, s, DX, ds, head, parts, nvec, n, bits);
+        if (dx) launch_bwd<SASQ_BF16, true>(X, G, s, DX, ds, head, parts, nvec, n, bits, small, grid, st);
+        else    launch_bwd<SASQ_BF16, false>(X, G, s, DX, ds, head, parts, nvec, n, bits, small, grid, st);
     }
     return hipGetLastError() == hipSuccess ? SASQ_OK : SASQ_ERR_LAUNCH;
 }
