@@ -26,6 +26,10 @@ void launch_gemm_k64_grouped(const GemmK64Args& a, sasq_dtype dt, int wmode, int
 // Every other group size (grouped_valu.hip): row-major weights, row-major activation codes in a.xq, any
 // group that divides K.
 void launch_grouped_valu(const GemmK64Args& a, sasq_dtype dt, bool int4, int64_t group, hipStream_t st);
+// Few output tiles (grouped_split.hip), K a multiple of 64: int8 weights, row-major or pre-arranged, row-major activation codes in a.xq.
+// grouped_takes_split: the form to take, 0: the other kernels are better or the group is none of its own.
+int grouped_takes_split(int64_t M, int64_t N, int64_t K, int64_t group, bool blocked);
+void launch_grouped_split(const GemmK64Args& a, sasq_dtype dt, bool blocked, int64_t group, int form, hipStream_t st);
 // K not a multiple of 64 (static_linear_anyk.hip): row-major activation codes in a.xq, row-major int8 or packed int4 weights.
 // rows: one activation factor per row.
 void launch_linear_anyk(const GemmK64Args& a, sasq_dtype dt, bool int4, bool rows, hipStream_t st);

@@ -204,6 +204,21 @@ __device__ __forceinline__ void products(float (&p)[TM], float a, float b)
     }
 }
 
+// One or two rows: a row's products and adds are a chain, so the products of several k are made ahead of their adds.
+template <int TM, int KS>
+__device__ __forceinline__ void few_row_steps(float (&f)[TM], const float (&a)[KS], const float (&b)[KS], const float (&s)[KS])
+{
+    float p[KS][TM];
+#pragma unroll
+    for (int k = 0; k < KS; ++k) products<TM>(p[k], a[k], b[k]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) f[i] = __builtin_fmaf(p[k][i], s[k], f[i]);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 template <int TM>
 __device__ __forceinline__ void one_step(float (&f)[TM], float a, float b, float s)
 {
@@ -263,6 +278,16 @@ __global__ __launch_bounds__(256) void linear_per_channel_kernel(
                 f32x4 sv[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) sv[q] = *reinterpret_cast<const f32x4*>(&ls[buf][16 * c + 4 * q]);
+                if constexpr (TM <= 2) {
+                    float a[16], b[16], s[16];
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        a[e] = (float)sext_byte(av[e >> 2], e & 3);
+                        b[e] = (float)sext_byte(bv[e >> 2], e & 3);
+                        s[e] = sv[e >> 2][e & 3];
+                    }
+                    few_row_steps<TM, 16>(f, a, b, s);
+                } else
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
                     one_step<TM>(f, (float)sext_byte(av[e >> 2], e & 3), (float)sext_byte(bv[e >> 2], e & 3), sv[e >> 2][e & 3]);
@@ -552,7 +577,16 @@ static void launch_small_group_rows(const GemmK64Args& a, hipStream_t st)
 {
     const int64_t tiles = ((a.M + 63) / 64) * ((a.N + 63) / 64);
     if (a.M > 16 && tiles > (G == 1 ? 128 : 192)) launch_small_group<DT, INT4, G, 16>(a, st);
-    else if constexpr (G == 1)        launch_per_channel<DT, INT4, 4>(a, st);
+    else if constexpr (G == 1) {
+        // Rows of a wave: fewer give more waves, and a wave alone on its SIMD takes as long as it has operations.  Measured, us, four |
+        // one | two: 16 x 1024 x 1024 (256 rows of 64 outputs) 33.6 | 20.5 | 26.3, 16 x 2048 x 4096 (1024) 63.4 | 37.5 | 48.5, 200 x
+        // 1024 x 1024 (3200) 34.0 | 41.6 | 32.5, 64 x 2048 x 4096 (4096) 63.6 | 78 | 61, 200 x 4096 x 1500 (4800) 175 | 183 | 159,
+        // 512 x 1024 x 1024 (8192) 48 | 71 | 54.
+        const int64_t rows64 = a.M * ((a.N + 63) / 64);              // rows of 64 outputs: waves of the one-row form
+        if (rows64 <= 1024)      launch_per_channel<DT, INT4, 1>(a, st);
+        else if (rows64 <= 4800) launch_per_channel<DT, INT4, 2>(a, st);
+        else                     launch_per_channel<DT, INT4, 4>(a, st);
+    }
     else                              launch_small_group<DT, INT4, G, 4>(a, st);
 }
 

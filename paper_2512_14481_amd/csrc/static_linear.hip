@@ -1051,7 +1051,14 @@ static void run_linear_grouped(const void* x, const float* s_g, const void* wq, 
     // groups of 32 channels run on the matrix units too (16x16x64 kernel, int8 and pre-arranged int4 weights)
     const bool half_ok = group == 32 && (K % kBK) == 0 && wf != SASQ_W_INT4_PACKED;
     const bool mfma_ok = ((K % kBK) == 0 && (group % kBK) == 0) || half_ok;
-    if (mfma_ok) {
+    const bool split_ok = (wf == SASQ_W_INT8 || wf == SASQ_W_INT8_BLOCKED) && tuning(SASQ_TUNE_LINEAR_PATH) == 0 &&
+                          tuning(SASQ_TUNE_LINEAR_TILE) == 0 && tuning(SASQ_TUNE_LINEAR_MFMA) == 0;
+    if (const int form = split_ok ? grouped_takes_split(M, N, K, group, wf == SASQ_W_INT8_BLOCKED) : 0) {
+        quantize_rowmajor(xq_ws);
+        GemmK64Args a{xq_ws, static_cast<const uint8_t*>(wq), s_g, s_w, bias, static_cast<uint16_t*>(y),
+                      reinterpret_cast<int32_t*>(f_out), M, N, K};
+        launch_grouped_split(a, (sasq_dtype)DT, wf == SASQ_W_INT8_BLOCKED, group, form, st);
+    } else if (mfma_ok) {
         // row-major packed int4 unpacks in (0,2,4,6,1,3,5,7) order: the activation bytes are stored to match
         if (wf == SASQ_W_INT4_PACKED)
             quantize_act_grouped_kernel<DT, true, true><<<grid_of(nvec), 256, 0, st>>>(X, s_g, reinterpret_cast<u32x2*>(xq_ws), nvec, (int)K, (int)group, a_bits);
