@@ -43,6 +43,9 @@ constexpr int kSkinnyRows = 64, kSkinnyQuantRows = 16;
 bool linear_takes_skinny(const LinBatch& b, int wmode);
 bool linear_quantizes_in_kernel(const LinBatch& b);
 void launch_linear_skinny(LinBatch& b, sasq_dtype dt, int wmode, bool qx, int a_bits, int32_t* acc_out, hipStream_t st);
+// The same for K that is not a multiple of 64, a single call with row-major int8 weights (row-major codes in xq).
+bool linear_anyk_takes_skinny(int64_t M, int64_t N, int64_t K);
+void launch_linear_anyk_skinny(LinBatch& b, sasq_dtype dt, bool qx, int a_bits, int32_t* acc_out, hipStream_t st);
 // The backward GEMM dX[M, K] = dY[M, N] . B^T over the prepared weight (linear_bwd.hip), for few rows or too few tiles; N a multiple
 // of 32.  bwd_takes_skinny: rows per workgroup, 0: the tiles are better.
 int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_rounds);

@@ -915,12 +915,17 @@ static void launch_mfma(const void* xin, const void* wq, const float* s, const f
     }
 }
 
+// A knob asks for a variant of the tiled kernels.
+static bool variant_asked_for()
+{
+    return tuning(SASQ_TUNE_LINEAR_PATH) != 0 || tuning(SASQ_TUNE_LINEAR_TILE) != 0 || tuning(SASQ_TUNE_LINEAR_MFMA) != 0;
+}
+
 // Few rows, or few tiles: the kernels of static_linear_skinny.hip, unless a knob asks for a variant of the tiled ones.
 // Row-major packed int4 keeps the tiled kernel (its codes are not in operand order).
 static bool use_skinny(const LinBatch& g, sasq_wfmt wf)
 {
-    return wf != SASQ_W_INT4_PACKED && tuning(SASQ_TUNE_LINEAR_PATH) == 0 && tuning(SASQ_TUNE_LINEAR_TILE) == 0 &&
-           tuning(SASQ_TUNE_LINEAR_MFMA) == 0 && linear_takes_skinny(g, (int)wf);
+    return wf != SASQ_W_INT4_PACKED && !variant_asked_for() && linear_takes_skinny(g, (int)wf);
 }
 
 // Whether such a call quantizes in the kernel: few codes, and no output over an input (the pre-pass has read every x before the
@@ -1005,6 +1010,10 @@ static void run_linear(const void* x, const float* s, const void* wq, const floa
                 launch_mfma<DT, X_PREQ, W_I8>(xq_ws, wq, s, s_w, bias, y, acc_out, M, N, K, a_bits, st);
             }
         }
+    } else if (!int4 && !variant_asked_for() && linear_anyk_takes_skinny(M, N, K)) {
+        const bool qx = skinny_quantizes(g, acc_out);
+        if (!qx) quantize_act_kernel<DT, false, false><<<qgrid, 256, 0, st>>>(X, s, reinterpret_cast<u32x2*>(xq_ws), nvec, n, (int)K, a_bits);
+        launch_linear_anyk_skinny(g, (sasq_dtype)DT, qx, a_bits, acc_out, st);
     } else {
         quantize_act_kernel<DT, false, false><<<qgrid, 256, 0, st>>>(X, s, reinterpret_cast<u32x2*>(xq_ws), nvec, n, (int)K, a_bits);
         GemmK64Args a{xq_ws, static_cast<const uint8_t*>(wq), s, s_w, bias, static_cast<uint16_t*>(y), acc_out, M, N, K};
@@ -1051,8 +1060,7 @@ static void run_linear_grouped(const void* x, const float* s_g, const void* wq, 
     // groups of 32 channels run on the matrix units too (16x16x64 kernel, int8 and pre-arranged int4 weights)
     const bool half_ok = group == 32 && (K % kBK) == 0 && wf != SASQ_W_INT4_PACKED;
     const bool mfma_ok = ((K % kBK) == 0 && (group % kBK) == 0) || half_ok;
-    const bool split_ok = (wf == SASQ_W_INT8 || wf == SASQ_W_INT8_BLOCKED) && tuning(SASQ_TUNE_LINEAR_PATH) == 0 &&
-                          tuning(SASQ_TUNE_LINEAR_TILE) == 0 && tuning(SASQ_TUNE_LINEAR_MFMA) == 0;
+    const bool split_ok = (wf == SASQ_W_INT8 || wf == SASQ_W_INT8_BLOCKED) && !variant_asked_for();
     if (const int form = split_ok ? grouped_takes_split(M, N, K, group, wf == SASQ_W_INT8_BLOCKED) : 0) {
         quantize_rowmajor(xq_ws);
         GemmK64Args a{xq_ws, static_cast<const uint8_t*>(wq), s_g, s_w, bias, static_cast<uint16_t*>(y),

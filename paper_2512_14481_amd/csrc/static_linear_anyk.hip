@@ -1,5 +1,5 @@
 // int8 linear for contraction lengths that are not whole 64-channel tiles (a projection sharded over GPUs: 11008 / 8 =
-// 1376), row-major weights with any row alignment, over row-major activation codes.
+// 1376), row-major weights with any row alignment, over row-major activation codes.  (Few rows of int8: static_linear_skinny.hip.)
 //
 // What bounds it: at 1000 x 4096 x 1376 the 17 MB of operands and output take 3 us and the 11.3 G operations as much; the
 // rest is the latency of a short K loop.  One thread per output walking its row and column byte by byte took 10.65 ms

@@ -38,7 +38,9 @@ template <int MT, int NT, int NW> constexpr int skinny_rows_per_phase() { return
 
 // FLT: the backward GEMM of the frozen linear.  x is dY, 16-bit and row-major, K the contraction's bytes per row, the weight blocks
 // hold 16 rows x 32 numbers, the sums are fp32 (the waves' parts added in their order) and go out rounded, without factors.
-template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool FLT = false>
+// ANYK: K not a multiple of 64, few rows of row-major int8; the activation codes are row-major too.  Rows then start at any byte, and
+// the last wave multiplies the rest of the row, with zeros behind, after its whole K tiles.
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool FLT = false, bool ANYK = false>
 __device__ __forceinline__
 void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __restrict__ acc_out, char* lds)
 {
@@ -46,6 +48,7 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
     constexpr bool I4 = WMODE == 3, ROWMAJOR = WMODE == 0, BLOCKS = !ONCE || MT > 4;
     static_assert(!I4 || NT % 2 == 0, "int4 blocks hold 32 weight rows");
     static_assert(!FLT || (WMODE == 2 && !QX), "float contraction: weight blocks, no codes");
+    static_assert(!ANYK || (ROWMAJOR && !BLOCKS), "rows at any byte: plain loads");
     using AccT = std::conditional_t<FLT, f32x4, i32x4>;
     constexpr int WL = I4 ? NT / 2 : NT;               // 128-bit weight loads per lane and K tile
     const int lane = threadIdx.x & 63;
@@ -78,15 +81,16 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
     constexpr int kWStep = ROWMAJOR ? 64 : 1024;
     const char* xbase = FLT ? reinterpret_cast<const char*>(it.x) + (int64_t)m0 * K + (int64_t)t0 * 64
                       : QX ? reinterpret_cast<const char*>(it.x) + ((int64_t)m0 * K + (int64_t)t0 * 64) * 2
+                      : ANYK ? reinterpret_cast<const char*>(it.xq) + (int64_t)m0 * K + (int64_t)t0 * 64
                            : reinterpret_cast<const char*>(it.xq) + ((int64_t)(m0 >> 4) * KT + t0) * 1024;
     uint32_t xoff[MT];
 #pragma unroll
     for (int b = 0; b < MT; ++b) {
-        if (FLT)     xoff[b] = (uint32_t)min(16 * b + frow, M - 1 - m0) * (uint32_t)K + 16 * fq;
+        if (FLT || (ANYK && !QX)) xoff[b] = (uint32_t)min(16 * b + frow, M - 1 - m0) * (uint32_t)K + 16 * fq;
         else if (QX) xoff[b] = (uint32_t)min(16 * b + frow, M - 1 - m0) * (uint32_t)K * 2 + fq * 32;
         else         xoff[b] = (uint32_t)min(b, ((M - 1) >> 4) - (m0 >> 4)) * (uint32_t)KT * 1024 + (4 * frow + (fq ^ swz64(frow))) * 16;
     }
-    constexpr int kXStep = FLT ? 64 : QX ? 128 : 1024;
+    constexpr int kXStep = FLT || (ANYK && !QX) ? 64 : QX ? 128 : 1024;
     const QConst qk = FLT ? QConst{} : make_qconst(*it.s, a_bits);
 
     struct Frag {
@@ -105,13 +109,15 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
         constexpr bool kPlain = ROWMAJOR && !BLOCKS;
 #pragma unroll
         for (int j = 0; j < WL; ++j)
-            if constexpr (kPlain) f.w[j] = *reinterpret_cast<const u32x4*>(wbase + (int64_t)t * kWStep + woff[j]);
+            if constexpr (ANYK)        f.w[j] = load_piece<u32x4>(reinterpret_cast<const uint8_t*>(wbase) + (int64_t)t * kWStep + woff[j]);
+            else if constexpr (kPlain) f.w[j] = *reinterpret_cast<const u32x4*>(wbase + (int64_t)t * kWStep + woff[j]);
             else                  f.w[j] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, woff[j], t * kWStep, ONCE && !ROWMAJOR ? kNonTemporal : 0);
 #pragma unroll
         for (int b = 0; b < MT; ++b)
 #pragma unroll
             for (int h = 0; h < (QX ? 2 : 1); ++h) {
-                if constexpr (kPlain) f.x[b][h] = *reinterpret_cast<const u32x4*>(xbase + (int64_t)t * kXStep + xoff[b] + 16 * h);
+                if constexpr (ANYK)        f.x[b][h] = load_piece<u32x4>(reinterpret_cast<const uint8_t*>(xbase) + (int64_t)t * kXStep + xoff[b] + 16 * h);
+                else if constexpr (kPlain) f.x[b][h] = *reinterpret_cast<const u32x4*>(xbase + (int64_t)t * kXStep + xoff[b] + 16 * h);
                 else                  f.x[b][h] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff[b] + 16 * h, t * kXStep, 0);
             }
     };
@@ -173,6 +179,22 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
         }
     };
 
+    Frag rest;                                          // ANYK: the channels behind the last whole K tile
+    const bool has_rest = ANYK && wave == NW - 1;
+    if constexpr (ANYK) {
+        if (has_rest) {
+            const uint8_t* w = reinterpret_cast<const uint8_t*>(it.wq);
+            const uint8_t* x = QX ? static_cast<const uint8_t*>(it.x) : reinterpret_cast<const uint8_t*>(it.xq);
+            constexpr int kBytes = QX ? 2 : 1;
+#pragma unroll
+            for (int j = 0; j < WL; ++j) rest.w[j] = load_piece_edge<u32x4>(w + (int64_t)min(n0 + 16 * j + frow, N - 1) * K, KT * 64 + 16 * fq, K);
+#pragma unroll
+            for (int b = 0; b < MT; ++b)
+#pragma unroll
+                for (int h = 0; h < kBytes; ++h)
+                    rest.x[b][h] = load_piece_edge<u32x4>(x + (int64_t)min(m0 + 16 * b + frow, M - 1) * K * kBytes, (KT * 64 + 16 * fq) * kBytes + 16 * h, K * kBytes);
+        }
+    }
     Frag ring[D];
     if constexpr (BLOCKS) {
         // D K tiles in flight.  Loads and products carry no conditions (tiles past the last are zeros), so that the wait in front of
@@ -218,6 +240,9 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
 #pragma unroll
         for (int j = 0; j < D; ++j)
             if (i + D + j < count) multiply(ring[j]);
+    }
+    if constexpr (ANYK) {
+        if (has_rest) multiply(rest);
     }
 
     // The waves' sums meet in LDS, as many row tiles at a time as fit; wave w finishes the output tiles w, w + NW, ...
@@ -276,7 +301,7 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
     }
 }
 
-template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE>
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool ANYK>
 __global__ __launch_bounds__(64 * NW)
 void skinny_kernel(const LinBatch b, int a_bits, int32_t* __restrict__ acc_out)
 {
@@ -286,11 +311,10 @@ void skinny_kernel(const LinBatch b, int a_bits, int32_t* __restrict__ acc_out)
     const int id = (int)blockIdx.x - b.first_block[k], octet = id >> 3, tiles_m = b.it[k].tiles_m;
     const int mblk = octet % tiles_m, nblk = octet / tiles_m * 8 + (id & 7);
     if (nblk >= b.it[k].tiles_n) return;
-    skinny_body<DT, WMODE, MT, NT, NW, D, QX, ONCE>(b.it[k], mblk, nblk, a_bits, acc_out, lds);
+    skinny_body<DT, WMODE, MT, NT, NW, D, QX, ONCE, false, ANYK>(b.it[k], mblk, nblk, a_bits, acc_out, lds);
 }
 
-
-template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE>
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool ANYK = false>
 static void launch_one(LinBatch& b, int a_bits, int32_t* acc_out, hipStream_t st)
 {
     b.first_block[0] = 0;
@@ -304,7 +328,7 @@ static void launch_one(LinBatch& b, int a_bits, int32_t* acc_out, hipStream_t st
         }
         b.first_block[i + 1] = b.first_block[i] + blocks;
     }
-    skinny_kernel<DT, WMODE, MT, NT, NW, D, QX, ONCE><<<b.first_block[b.count], 64 * NW, 0, st>>>(b, a_bits, acc_out);
+    skinny_kernel<DT, WMODE, MT, NT, NW, D, QX, ONCE, ANYK><<<b.first_block[b.count], 64 * NW, 0, st>>>(b, a_bits, acc_out);
 }
 
 // Wide or narrow workgroups: the narrow form (16 weight rows, K over eight waves) gives more workgroups for the same weights, the
@@ -313,10 +337,15 @@ static void launch_one(LinBatch& b, int a_bits, int32_t* acc_out, hipStream_t st
 // layer (2656 tiles) 36 | 51; the line lies at 512 tiles.
 // Waves of the wide form, four with four K tiles in flight | eight with three: the 7B layer at 8 rows 35.0 | 35.0, its MLP 29.7 |
 // 26.4, 8192 x 16384 28.0 | 25.7; row-major int8, whose lines are shared between K tiles, 7B layer 50.9 | 51.3.
-template <int DT, int WMODE, int MT, bool QX>
+template <int DT, int WMODE, int MT, bool QX, bool ANYK = false>
 static void launch_mt(LinBatch& b, int64_t tiles16, int a_bits, int32_t* acc_out, hipStream_t st)
 {
     const bool wide = tiles16 >= 512;
+    if constexpr (ANYK) {                              // as row-major int8 below
+        if (!wide)                 launch_one<DT, WMODE, MT, 1, 8, 4, QX, true, true>(b, a_bits, acc_out, st);
+        else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, true>(b, a_bits, acc_out, st);
+        else                       launch_one<DT, WMODE, MT, 2, 4, 4, QX, true, true>(b, a_bits, acc_out, st);
+    } else
     if constexpr (WMODE == 3) {                        // int4: half the bytes per tile, a block is two tiles
         if (!wide)             launch_one<DT, WMODE, MT, 2, 8, 2, QX, true>(b, a_bits, acc_out, st);
         else if constexpr (QX) launch_one<DT, WMODE, MT, 4, 8, 2, QX, true>(b, a_bits, acc_out, st);
@@ -489,6 +518,35 @@ void launch_linear_skinny(LinBatch& b, sasq_dtype dt, int wmode, bool qx, int a_
     };
     if (dt == SASQ_F16) by_wmode(std::integral_constant<int, SASQ_F16>{});
     else                by_wmode(std::integral_constant<int, SASQ_BF16>{});
+}
+
+// K not a multiple of 64, at most kSkinnyRows rows of a single call; row-major codes in it.xq unless qx.  Rows that do not start on a
+// whole dword cost each load several accesses, and every workgroup reads all activation rows: more than 32 of those stay with the
+// tiles.  Measured, us, tiles (static_linear_anyk.hip) | here: 8 x 3000, K = 1000 8.1 | 4.1, 16 x 4096, 2500 11.8 | 6.5, 1 x 1000, 4000
+// 14.6 | 5.5, 32 x 4096, 1376 9.1 | 7.1, 64 x 4096, 1376 9.2 | 8.4, 64 x 1000, 4000 15.9 | 12.2; odd K: 1 x 4000, 3001 14.3 | 7.4, 16
+// rows 15.0 | 13.7, 32 rows 14.9 | 15.0, 40 rows 15.0 | 17.4, 64 rows 15.1 | 21.5; 32 x 900, 777 8.3 | 7.6, 64 rows 8.5 | 9.7.
+bool linear_anyk_takes_skinny(int64_t M, int64_t N, int64_t K)
+{
+    return M <= (K % 4 == 0 ? kSkinnyRows : 32) && K > 64 && N <= INT64_C(1) << 27;
+}
+
+template <int DT>
+static void launch_anyk_dt(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, hipStream_t st)
+{
+    const int rows = b.it[0].M;
+    const int64_t tiles16 = ((int64_t)b.it[0].N + 15) / 16;
+    if (qx && rows > 32)                    launch_one<DT, 0, 4, 1, 8, 2, true, true, true>(b, a_bits, acc_out, st);
+    else if (qx && rows > kSkinnyQuantRows) launch_one<DT, 0, 2, 1, 8, 2, true, true, true>(b, a_bits, acc_out, st);
+    else if (qx)         launch_mt<DT, 0, 1, true, true>(b, tiles16, a_bits, acc_out, st);
+    else if (rows <= 32) launch_mt<DT, 0, 2, false, true>(b, tiles16, a_bits, acc_out, st);
+    else if (rows <= 48) launch_mt<DT, 0, 3, false, true>(b, tiles16, a_bits, acc_out, st);
+    else                 launch_mt<DT, 0, 4, false, true>(b, tiles16, a_bits, acc_out, st);
+}
+
+void launch_linear_anyk_skinny(LinBatch& b, sasq_dtype dt, bool qx, int a_bits, int32_t* acc_out, hipStream_t st)
+{
+    if (dt == SASQ_F16) launch_anyk_dt<SASQ_F16>(b, qx, a_bits, acc_out, st);
+    else                launch_anyk_dt<SASQ_BF16>(b, qx, a_bits, acc_out, st);
 }
 
 // ---- the backward GEMM ----------------------------------------------------------------------

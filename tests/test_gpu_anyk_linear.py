@@ -78,3 +78,26 @@ def test_any_contraction_length(mn, k, fmt):
     yd, accd, _, _ = run_dynamic(xb, wq, s_w, b, fmt, dtype, False)
     assert np.array_equal(accd, ref["acc"])
     assert_same_values(yd, ref["y"], dtype, "Y, one factor per row")
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("mn", [(1, 1), (1, 8200), (15, 130), (16, 250), (16, 8195), (17, 33), (32, 96), (32, 8200), (33, 72), (48, 250), (49, 31), (64, 264), (64, 8189)])
+@pytest.mark.parametrize("k", [65, 79, 100, 127, 200, 333, 516, 1000, 1031, 2095, 2108])
+def test_few_rows(mn, k, dtype):
+    """At most 64 rows: K over the waves, whole K tiles and the rest of a row; quantized in the kernel (at most 16 rows, or few codes)
+    and before it; the tiled kernel, asked for by a knob, gives the same."""
+    if mn[1] > 8000 and k not in (79, 200, 1031):
+        pytest.skip("the narrow outputs cover the other lengths")
+    (M, N) = mn
+    xb, wq, s_w, bias, s = problem(92, (M, N, k), "int8", dtype)
+    wd, swd, x, bd = torch.from_numpy(wq).cuda(), torch.from_numpy(s_w).cuda(), to_dev(xb, dtype), torch.from_numpy(bias).cuda()
+    ws = B.new_workspace(B.sasq_static_linear_workspace(M, N, k, B.SASQ_W_INT8))
+    ref = oracle.static_linear(xb, s, wq, s_w, bias, 8, "int8", dtype)
+    for path in (None, "twopass"):
+        set_tuning(path=path)
+        y = torch.full((M, N), float("nan"), dtype=TDT[dtype], device="cuda")
+        acc = torch.zeros((M, N), dtype=torch.int32, device="cuda")
+        B.sasq_static_linear(x, dev_scalar(s), wd, swd, bd, y, B.SASQ_W_INT8, ws, acc, None)
+        set_tuning()
+        assert np.array_equal(acc.cpu().numpy(), ref["acc"]), path
+        assert_same_values(to_bits(y), ref["y"], dtype, "Y")
