@@ -396,6 +396,27 @@ static bool tiles_are_better(const LinBatch& b, int rows, int wmode)
     return single ? fill > (one_round ? 0.5 : int4 ? 0.8 : 0.7) : row_major && fill > (one_round ? 0.5 : 0.8);
 }
 
+// Blocks of 32 rows by 32 or 64 columns (returned in units of 16, 0: neither), for more than kSkinnyRows rows: where they all run at
+// once, one a CU, the call takes as long as one block, and these are the shortest; from a second round on the larger ones read less.
+// The runs of columns go round the eight XCDs, so a round is 32 blocks on the XCD with the most of them.  Measured, us, pre-arranged
+// int8, before | 32 x 32 | 32 x 64: 80 x 1024 x 1024 8.6 | 7.2 | 7.8, 143 x 2816 x 2816 11.0 | 11.8 | 9.5, 128 x 5248 -> 2048 14.1 |
+// 10.5, 224 x 11008 -> 1792 21.4 | - | 18.4, 1000 x 11008 -> 250 66.8 | 23.7; row-major 96 x 11008 -> 1024 31.2 | 18.9.  The backward: 80
+// x 1024 x 1024 7.9 | 5.0 | 6.4, 143 x 2816 x 2816 16.5 | 16.4 | 11.3, 128 x 5248 -> 2048 26.8 | 15.4, 224 x 5248 -> 1792 26.9 | - |
+// 17.7, 1000 x 512 -> 250 8.2 | 4.9.  Beyond a round: 171 x 1344 -> 1344 (36 blocks of 32 x 32 on one XCD) 9.4 | 10.4, 224 x 2240 ->
+// 2240 (35 of 32 x 64) 14.2 | - | 16.2, forward 10.7 | - | 12.4.
+static int small_block_cols(const LinItem* items, int count)
+{
+    for (int i = 0; i < count; ++i)
+        if (count > 1 && items[i].N <= 448) return 0;                // as block_rows: the other items' blocks share the XCDs unevenly
+    for (int nt = 2; nt <= 4; nt += 2) {
+        int64_t blocks = 0;
+        for (int i = 0; i < count; ++i)
+            blocks += ((int64_t)items[i].M + 31) / 32 * (((int64_t)items[i].N + 128 * nt - 1) / (128 * nt) * 8);
+        if (blocks <= 256) return nt;
+    }
+    return 0;
+}
+
 // Rows per workgroup (64 weight rows each, K over eight waves) for more than kSkinnyRows rows, 0: the GEMM's tiles are better.
 // A call of few tiles leaves CUs idle or waiting for one long K loop; cut finer every CU has operands in flight, until the operands'
 // L2 reads (the smaller the block, the more of them) cost more than that.  Neither side's time follows from one size, so both are
@@ -466,7 +487,7 @@ bool linear_takes_skinny(const LinBatch& b, int wmode)
         cols += b.it[i].N;
     }
     if (cols > INT64_C(1) << 27) return false;         // up to 16 work items a column, and a launch holds fewer than 2^32
-    return rows <= kSkinnyRows ? !tiles_are_better(b, rows, wmode) : block_rows(b, wmode) != 0;
+    return rows <= kSkinnyRows ? !tiles_are_better(b, rows, wmode) : small_block_cols(b.it, b.count) != 0 || block_rows(b, wmode) != 0;
 }
 
 // Whether such a call, of at most kSkinnyRows rows, quantizes in the kernel: at most 16 rows, or so few codes in an item's row tiles
@@ -494,8 +515,10 @@ static void launch_wmode(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, hip
         rows = b.it[i].M > rows ? b.it[i].M : rows;
     }
     if (rows > kSkinnyRows) {
-        const int block = block_rows(b, WMODE);
-        if (block == 64)                     launch_one<DT, WMODE, 4, 4, 8, 2, false, false>(b, a_bits, acc_out, st);
+        const int small = small_block_cols(b.it, b.count), block = small ? 32 : block_rows(b, WMODE);
+        if (small == 2)                      launch_one<DT, WMODE, 2, 2, 8, 4, false, false>(b, a_bits, acc_out, st);
+        else if (small == 4)                 launch_one<DT, WMODE, 2, 4, 8, 3, false, false>(b, a_bits, acc_out, st);
+        else if (block == 64)                     launch_one<DT, WMODE, 4, 4, 8, 2, false, false>(b, a_bits, acc_out, st);
         else if (block == 96 && rows > 96)   launch_one<DT, WMODE, 6, 4, 8, 2, false, false>(b, a_bits, acc_out, st);
         else if (block == 96)                launch_one<DT, WMODE, 6, 4, 8, 2, false, true>(b, a_bits, acc_out, st);
         else if (rows > 128)                 launch_one<DT, WMODE, 8, 4, 8, 2, false, false>(b, a_bits, acc_out, st);
@@ -569,14 +592,28 @@ static void launch_bwd_one(LinItem& it, float* acc_out, hipStream_t st)
     bwd_skinny_kernel<DT, MT, NT, NW, D, ONCE><<<(it.tiles_n + 7) / 8 * 8 * it.tiles_m, 64 * NW, 0, st>>>(it, acc_out);
 }
 
-// Rows per workgroup, from estimates in us as in block_rows above: at most 64 rows 64 (in row tiles of 16, 32 or 64); more rows 64 or
-// 96 by 64 columns, where that takes 15 % less time than the GEMM's tiles (128 never do).  260 calls of 8 to 1500 rows, contractions and outputs
+static LinItem bwd_item(const void* dy, const void* wt, void* dx, int64_t M, int64_t N, int64_t K)
+{
+    LinItem it{};
+    it.x = dy;
+    it.wq = static_cast<const uint8_t*>(wt);
+    it.y = static_cast<uint16_t*>(dx);
+    it.M = (int)M;
+    it.N = (int)K;                                                   // the body's columns and contraction bytes
+    it.K = (int)(2 * N);
+    return it;
+}
+
+// Rows per workgroup, from estimates in us as in block_rows above: at most 64 rows 64 (in row tiles of 16, 32 or 64); more rows 32
+// where such blocks all run at once (small_block_cols), or 64 or 96 by 64 columns, where that takes 15 % less time than the GEMM's tiles (128 never do).  260 calls of 8 to 1500 rows, contractions and outputs
 // of 256 to 13824: at most 16 rows take 0.41 of their time on the tiles, 17 to 32 0.56, 33 to 64 0.69, more 0.89 (those on row
 // blocks 0.76), and none 2 % more.  us, tiles | here: 1 x 4096 x 4096 25.3 | 8.0, 64 x 256 x 256 4.8 | 3.4, 131 x 2816 x 1344 23.4 |
 // 17.3, 334 x 11072 x 1536 76.2 | 52.5.
 int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_rounds)
 {
     if (M <= 32 || (M <= 64 && K <= 4096)) return K <= INT64_C(1) << 26 ? 64 : 0;     // up to 32 work items a column
+    const LinItem it = bwd_item(nullptr, nullptr, nullptr, M, N, K);
+    if (M > 64 && small_block_cols(&it, 1)) return 32;
     if (K <= 448) return 0;                                          // fewer than eight runs of weight rows leave XCDs without work
     static const BlockTime block[2] = {{1.8, 2.1, 0.155}, {1.5, 3.4, 0.205}};
     const double kt = (double)(N / 32);
@@ -599,7 +636,9 @@ static void launch_bwd_dt(LinItem& it, float* acc_out, int rows, hipStream_t st)
 {
     const bool wide = it.N > 4096;
     if (it.M > 64) {
-        if (rows == 64) launch_bwd_one<DT, 4, 4, 8, 2, false>(it, acc_out, st);
+        if (rows == 32 && small_block_cols(&it, 1) == 2) launch_bwd_one<DT, 2, 2, 8, 4, false>(it, acc_out, st);
+        else if (rows == 32) launch_bwd_one<DT, 2, 4, 8, 3, false>(it, acc_out, st);
+        else if (rows == 64) launch_bwd_one<DT, 4, 4, 8, 2, false>(it, acc_out, st);
         else            launch_bwd_one<DT, 6, 4, 8, 2, false>(it, acc_out, st);
     } else if (it.M <= 16) {
         if (wide) launch_bwd_one<DT, 1, 2, 8, 3, true>(it, acc_out, st);
@@ -615,13 +654,7 @@ static void launch_bwd_dt(LinItem& it, float* acc_out, int rows, hipStream_t st)
 
 void launch_bwd_skinny(const void* dy, const void* wt, void* dx, float* acc_out, int64_t M, int64_t N, int64_t K, sasq_dtype dt, int rows, hipStream_t st)
 {
-    LinItem it{};
-    it.x = dy;
-    it.wq = static_cast<const uint8_t*>(wt);
-    it.y = static_cast<uint16_t*>(dx);
-    it.M = (int)M;
-    it.N = (int)K;                                                   // the body's columns and contraction bytes
-    it.K = (int)(2 * N);
+    LinItem it = bwd_item(dy, wt, dx, M, N, K);
     if (dt == SASQ_F16) launch_bwd_dt<SASQ_F16>(it, acc_out, rows, st);
     else                launch_bwd_dt<SASQ_BF16>(it, acc_out, rows, st);
 }

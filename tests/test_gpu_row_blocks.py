@@ -1,4 +1,4 @@
-"""GPU parity of the linear's row blocks (more than 64 rows in workgroups of 64, 96 or 128 rows by 64 columns, K over eight waves)
+"""GPU parity of the linear's row blocks (more than 64 rows in workgroups of 32 rows by 32 or 64 columns, or 64, 96 or 128 by 64, K over eight waves)
 against the CPU oracle: each block form and weight layout, alone and in batches, with waves that have no K tile at all (K = 64),
 uneven shares of them, and rows and columns that end inside a block."""
 from __future__ import annotations
@@ -30,6 +30,8 @@ def up(a, b):
 
 def chosen(items, layout):
     """Rows per block the dispatch takes for (rows, columns, K) items of more than 64 rows, 0: the GEMM's tiles."""
+    if (len(items) == 1 or min(n for _, n, _ in items) > 448) and min(sum(up(m, 32) * up(n, 8 * w) * 8 for m, n, _ in items) for w in (32, 64)) <= 256:
+        return 32
     if min(n for _, n, _ in items) <= 448:
         return 0
     k_max = max(k // 64 for _, _, k in items)
@@ -57,8 +59,14 @@ def chosen(items, layout):
 
 @pytest.mark.parametrize("fmt,blocked", LAYOUTS)
 @pytest.mark.parametrize("items,want", [
-    ([(65, 1000, 64)], (64, 64, 64)),
-    ([(130, 1003, 704)], (64, 64, 64)),
+    ([(65, 1000, 64)], (32, 32, 32)),                                           # 32 x 32: 96 blocks, waves without a K tile
+    ([(130, 1003, 704)], (32, 32, 32)),
+    ([(1024, 256, 576)], (32, 32, 32)),                                         # exactly 256
+    ([(500, 700, 576)], (32, 32, 32)),                                          # 384, so 32 x 64
+    ([(70, 5120, 640)], (32, 32, 32)),                                          # 240 of 32 x 64
+    ([(96, 1000, 1088), (70, 1201, 192), (20, 500, 64)], (32, 32, 32)),
+    ([(70, 5121, 64)], (64, 64, 64)),
+    ([(190, 2900, 704)], (64, 64, 64)),
     ([(383, 4090, 192)], (96, 96, 96)),
     ([(1500, 1000, 576)], (96, 96, 96)),
     ([(500, 4090, 1088)], (128, 128, 128)),
