@@ -45,6 +45,14 @@ __device__ __forceinline__ void fwd_vec(const u32x4& in, const QConst& k, u32x4&
 }
 
 // Forward over one tensor by block `block` of the `nblocks` that share it.
+// The block that takes what is left behind the last full chunk: the one whose turn it would be, so that it is nobody's second piece while
+// blocks are without any, with all loads in flight.  Taken by block 0, one access at a time: 33000 elements forward 3.7 us, now 3.2,
+// 40000 backward 6.2, now 5.2, 171264 6.0, now 5.5.
+__device__ __forceinline__ int rest_block(int64_t nvec, int nblocks)
+{
+    return (int)((uint64_t)(nvec / ((int64_t)kThreads * kUnroll)) % (uint32_t)nblocks);
+}
+
 template <int DT, bool CODES>
 // (y may alias x: neither is restrict-qualified.)
 __device__ __forceinline__ void fwd_body(
@@ -69,14 +77,24 @@ __device__ __forceinline__ void fwd_body(
             if (CODES) codes[base + u * kThreads + threadIdx.x] = cw;
         }
     }
-    if (block != 0) return;
+    if (block != rest_block(nvec, nblocks)) return;
     // remainder: fewer than kChunk vectors, then fewer than 8 scalars
-    for (int64_t i = full_end + threadIdx.x; i < nvec; i += kThreads) {
-        u32x4 out;
-        u32x2 cw;
-        fwd_vec<DT, CODES>(x[i], k, out, cw);
-        y[i] = out;
-        if (CODES) codes[i] = cw;
+    u32x4 in[kUnroll];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+        const int64_t i = full_end + u * kThreads + threadIdx.x;
+        if (i < nvec) in[u] = x[i];
+    }
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+        const int64_t i = full_end + u * kThreads + threadIdx.x;
+        if (i < nvec) {
+            u32x4 out;
+            u32x2 cw;
+            fwd_vec<DT, CODES>(in[u], k, out, cw);
+            y[i] = out;
+            if (CODES) codes[i] = cw;
+        }
     }
     if (threadIdx.x < (unsigned)(n - nvec * 8)) {
         int64_t i = nvec * 8 + threadIdx.x;
@@ -153,7 +171,7 @@ __device__ __forceinline__ void fwd_body_shared(const FqBatchItem& it, int bits,
                 __builtin_nontemporal_store(out, &it.out[j][base + u * kThreads + threadIdx.x]);
             }
     }
-    if (block != 0) return;
+    if (block != rest_block(it.nvec, nblocks)) return;
     for (int64_t i = full_end + threadIdx.x; i < nvec; i += kThreads) {
         const u32x4 in = x[i];
 #pragma unroll
@@ -303,11 +321,21 @@ __device__ __forceinline__ void bwd_body(
             if (WRITE_DX) __builtin_nontemporal_store(out, &dx[base + u * kThreads + threadIdx.x]);
         }
     }
-    if (block == 0) {
-        for (int64_t i = full_end + threadIdx.x; i < nvec; i += kThreads) {
-            u32x4 out;
-            acc += (double)bwd_vec<DT>(x[i], dy[i], k, out);
-            if (WRITE_DX) dx[i] = out;
+    if (block == rest_block(nvec, nblocks)) {
+        u32x4 xin[kUnroll], gin[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int64_t i = full_end + u * kThreads + threadIdx.x;
+            if (i < nvec) { xin[u] = x[i]; gin[u] = dy[i]; }
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int64_t i = full_end + u * kThreads + threadIdx.x;
+            if (i < nvec) {
+                u32x4 out;
+                acc += (double)bwd_vec<DT>(xin[u], gin[u], k, out);
+                if (WRITE_DX) dx[i] = out;
+            }
         }
         if (threadIdx.x < (unsigned)(n - nvec * 8)) {
             int64_t i = nvec * 8 + threadIdx.x;
