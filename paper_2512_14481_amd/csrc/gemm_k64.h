@@ -50,6 +50,8 @@ void launch_linear_anyk_skinny(LinBatch& b, sasq_dtype dt, bool qx, int a_bits, 
 // of 32.  bwd_takes_skinny: rows per workgroup, 0: the tiles are better.
 int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_rounds);
 void launch_bwd_skinny(const void* dy, const void* wt, void* dx, float* acc_out, int64_t M, int64_t N, int64_t K, sasq_dtype dt, int rows, hipStream_t st);
+// Batches of at least so many workgroup ids, and at most 128, go as half tiles throughout.
+constexpr int kHalvesFrom = 32;
 // split_tail: hand the tiles of a sparsely filled last round out as 128x256 halves (sets b.split_first / b.split_count)
 void launch_gemm_k64_batch(LinBatch& b, int grid, sasq_dtype dt, int wmode, bool split_tail, hipStream_t st);
 

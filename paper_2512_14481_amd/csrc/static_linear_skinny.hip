@@ -439,24 +439,25 @@ static int block_rows(const LinBatch& b, int wmode)
 {
     const int format = wmode == 0 ? 0 : wmode == 2 ? 1 : 2;
     double work = 0.0, k_max = 0.0;                                  // GEMM tiles x K tiles
-    int64_t tiles = 0;
+    int64_t tiles = 0, ids = 0;
     for (int i = 0; i < b.count; ++i) {
         if (b.it[i].N <= 448) return 0;                              // fewer than eight runs of weight rows leave XCDs without work
         const double kt = b.it[i].K / 64;
         const int64_t t = ((int64_t)b.it[i].M + 255) / 256 * (((int64_t)b.it[i].N + 255) / 256);
         tiles += t;
+        ids += (t + 7) / 8 * 8;
         work += (double)t * kt;
         k_max = kt > k_max ? kt : k_max;
     }
     // A single call has its choice of tiles, and rounds in units of whole ones.  The tiles of a batch fill each other's last round
-    // in part: between whole rounds and none.
+    // in part: between whole rounds and none; where they go as halves throughout (launch_gemm_k64_batch), a round is 0.7 of one.
     const BlockTime& tt = kTileTime[format];
     double best;
     if (b.count == 1) {
         best = tt.call + gemm_rounds(b.it[0].M, b.it[0].N) * (tt.round + tt.k_tile * k_max);
     } else {
         const double rounds = (double)((tiles + 255) / 256), span = work / 256.0 * std::sqrt(rounds * 256.0 / (double)tiles);
-        best = tt.call + rounds * tt.round + tt.k_tile * (span > k_max ? span : k_max);
+        best = tt.call + (ids >= kHalvesFrom && ids <= 128 ? 0.7 : 1.0) * (rounds * tt.round + tt.k_tile * (span > k_max ? span : k_max));
     }
     best *= 0.92;
     int rows = 0;

@@ -46,7 +46,8 @@ def chosen(items, layout):
         tiles = [up(m, 256) * up(n, 256) for m, n, _ in items]
         work = sum(t * (k // 64) for t, (_, _, k) in zip(tiles, items))
         rounds = up(sum(tiles), 256)
-        best = call + rounds * per_round + per_tile * max(k_max, work / 256 * math.sqrt(rounds * 256 / sum(tiles)))
+        halves = 32 <= sum(up(t, 8) * 8 for t in tiles) <= 128
+        best = call + (0.7 if halves else 1.0) * (rounds * per_round + per_tile * max(k_max, work / 256 * math.sqrt(rounds * 256 / sum(tiles))))
     best, rows = 0.92 * best, 0
     for r, (call, per_round, per_tile) in zip((64, 96, 128), BLOCK[layout]):
         blocks = [up(m, r) * up(n, 512) * 8 for m, n, _ in items]
@@ -71,10 +72,12 @@ def chosen(items, layout):
     ([(1500, 1000, 576)], (96, 96, 96)),
     ([(500, 4090, 1088)], (128, 128, 128)),
     ([(500, 4090, 192)], (0, 0, 128)),
-    ([(96, 5000, 1088), (70, 8201, 192), (96, 6000, 64)], (64, 64, 64)),
-    ([(96, 9000, 1088), (70, 8201, 192)], (96, 96, 96)),                       # all rows in one block: weights read once
-    ([(400, 2000, 64), (400, 3001, 64)], (96, 96, 96)),
-    ([(128, 9001, 2112), (100, 8200, 2112)], (128, 64, 64)),                   # the same at 128 rows
+    ([(96, 5000, 1088), (70, 8201, 192), (96, 6000, 64)], (64, 0, 64)),        # 0: the GEMM's half tiles
+    ([(96, 9000, 1088), (70, 8201, 192)], (96, 0, 96)),
+    ([(96, 4000, 1088), (70, 4201, 192)], (96, 96, 96)),                       # all rows in one block: weights read once
+    ([(400, 2000, 64), (400, 3001, 64)], (0, 0, 0)),
+    ([(128, 9001, 2112), (100, 8200, 2112)], (0, 0, 64)),
+    ([(128, 4001, 1024), (100, 4200, 1024)], (128, 128, 128)),                 # the same at 128 rows
     ([(300, 2000, 1088), (257, 3001, 576)], (128, 128, 128))])
 def test_row_blocks_match_oracle(items, want, fmt, blocked):
     set_tuning()
