@@ -356,7 +356,7 @@ static void launch_bwd_k32(const void* dy, const void* wt, void* dx, float* acc_
         (int)M, (int)N, (int)K, tiles_m, tiles_n);
 }
 
-// 256x256 tiles unless they would leave most of the 256 CUs idle for a round; then 128x128
+// The 32x32x16 kernel: 256x256 tiles unless they would leave most of the 256 CUs idle for a round; then 128x128
 // (two workgroups per CU).  sasq_set_tuning(SASQ_TUNE_BWD_TILE, 1 | 2) forces one of them.
 static double rounds256(int64_t M, int64_t K) { return (double)((((M + 255) / 256) * ((K + 255) / 256) + 255) / 256); }
 static double rounds128(int64_t M, int64_t K) { return (double)((((M + 127) / 128) * ((K + 127) / 128) + 511) / 512) * 0.5 * 1.42; }
@@ -365,6 +365,20 @@ static bool bwd_small_tiles(int64_t M, int64_t K)
     if (tuning(SASQ_TUNE_BWD_TILE) == 1) return false;
     if (tuning(SASQ_TUNE_BWD_TILE) == 2) return true;
     return rounds128(M, K) < rounds256(M, K);
+}
+// The tile of the 16x16x32 kernel: 0: 256x256, 1: 128x256, 2: 128x128, by the rounds of a 256x256 tile's time that a launch takes.  A
+// 128x256 tile alone on its CU takes 0.65 of it, a 128x128 tile 0.44, two of them on a CU 0.8: of 257 to 512 tiles of 128x128 some CUs
+// hold two, and as 128x256 they all run at once.  Measured, us, M x N -> K, 256x256 | 128x256 | 128x128: 1834 x 2304 -> 2304 (270 tiles
+// of 128x128) 42.6 | 28.0 | 32.6, 900 x 5504 -> 4992 (312) 92 | 63 | 85, 2048 x 4096 -> 2304 (512) 48 | 35 | 40, 1000 x 2304 -> 2816
+// (176) 42.5 | 27.3 | 19.8, 4096 x 2304 -> 5120 (1280) 95.7 | 92.0 | 94.7, 3000 x 2304 -> 3328 (624) 45.4 | 57.9 | 52.1.
+static int bwd_tile(int64_t M, int64_t K)
+{
+    if (const int t = tuning(SASQ_TUNE_BWD_TILE)) return t == 1 ? 0 : 2;
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((K + bn - 1) / bn); };
+    const int64_t t128 = tiles(128, 128), rest = t128 % 512;
+    const double c0 = rounds256(M, K), c1 = 0.65 * (double)((tiles(128, 256) + 255) / 256);
+    const double c2 = 0.8 * (double)(t128 / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 0.44 : 0.8);
+    return c0 <= c1 && c0 <= c2 ? 0 : c1 < c2 ? 1 : 2;
 }
 static double bwd_tile_rounds(int64_t M, int64_t K) { return rounds128(M, K) < rounds256(M, K) ? rounds128(M, K) : rounds256(M, K); }
 
@@ -445,13 +459,16 @@ extern "C" int sasq_linear_bwd_input(const void* dy, const void* wt, void* dx, f
     const bool small = bwd_small_tiles(M, K);
     // the 16x16x32 kernel addresses dY rows with 32-bit byte offsets inside a 256-row tile
     if (tuning(SASQ_TUNE_LINEAR_MFMA) != 1 && N <= (INT64_C(1) << 22)) {
-        if (dt == SASQ_F16) {
-            if (small) launch_bwd_k32<SASQ_F16, 128, 128>(dy, wt, dx, acc_out, M, N, K, st);
-            else       launch_bwd_k32<SASQ_F16, 256, 256>(dy, wt, dx, acc_out, M, N, K, st);
-        } else {
-            if (small) launch_bwd_k32<SASQ_BF16, 128, 128>(dy, wt, dx, acc_out, M, N, K, st);
-            else       launch_bwd_k32<SASQ_BF16, 256, 256>(dy, wt, dx, acc_out, M, N, K, st);
-        }
+        auto by_tile = [&](auto dt_tag) {
+            constexpr int DT = decltype(dt_tag)::value;
+            switch (bwd_tile(M, K)) {
+                case 0:  launch_bwd_k32<DT, 256, 256>(dy, wt, dx, acc_out, M, N, K, st); break;
+                case 1:  launch_bwd_k32<DT, 128, 256>(dy, wt, dx, acc_out, M, N, K, st); break;
+                default: launch_bwd_k32<DT, 128, 128>(dy, wt, dx, acc_out, M, N, K, st); break;
+            }
+        };
+        if (dt == SASQ_F16) by_tile(std::integral_constant<int, SASQ_F16>{});
+        else                by_tile(std::integral_constant<int, SASQ_BF16>{});
         return hipGetLastError() == hipSuccess ? SASQ_OK : SASQ_ERR_LAUNCH;
     }
     if (dt == SASQ_F16) {

@@ -52,3 +52,18 @@ def test_few_rows_and_row_blocks_match_oracle(shape, want, dtype):
     assert (err <= shape[1] * 2.0 ** -24 * ref["sum_abs"] + 1e-45).all(), err.max()
     assert np.array_equal(got, wl.f32_to_storage_bits(acc, dtype))
     assert np.array_equal(run_bwd(dyb, wt, K, dtype), got)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("shape", [(1830, 32, 2310), (1793, 160, 2241), (1000, 576, 5001), (2048, 288, 4096)])
+def test_tiles_of_128_by_256(shape, dtype):
+    """257 to 512 tiles of 128x128: they go as 128x256, ragged and whole; the 256x256 tiles sum in the same order."""
+    M, N, K = shape
+    assert chosen(*shape) == 0 and 256 < up(M, 128) * up(K, 128) <= 512
+    dyb, wq, s_w = problem(84, shape, dtype, "int8")
+    wt, K = prepare(wq, s_w, "int8", dtype)
+    ref = oracle.linear_bwd_input(dyb, wq, s_w, "int8", dtype)
+    got, acc = run_bwd(dyb, wt, K, dtype, want_acc=True)
+    check_dx(got, ref, dtype, N, f"{shape} {dtype}")
+    assert np.array_equal(got, wl.f32_to_storage_bits(acc, dtype))
+    assert np.array_equal(run_bwd(dyb, wt, K, dtype, tile="256"), got)
