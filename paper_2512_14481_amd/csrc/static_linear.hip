@@ -930,13 +930,13 @@ static bool use_skinny(const LinBatch& g, sasq_wfmt wf)
 
 // Whether such a call quantizes in the kernel: few codes, and no output over an input (the pre-pass has read every x before the
 // first y is written; workgroups that quantize for themselves have not).
-static bool skinny_quantizes(const LinBatch& g, const int32_t* acc_out)
+static bool skinny_quantizes(const LinBatch& g, sasq_wfmt wf, const int32_t* acc_out, bool any_k = false)
 {
     auto overlap = [](const void* a, size_t an, const void* b, size_t bn) {
         const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
         return pa < pb + bn && pb < pa + an;
     };
-    if (!linear_quantizes_in_kernel(g)) return false;
+    if (!linear_quantizes_in_kernel(g, (int)wf, any_k)) return false;
     for (int i = 0; i < g.count; ++i) {
         const LinItem& in = g.it[i];
         const size_t xbytes = (size_t)in.M * in.K * 2;
@@ -986,7 +986,7 @@ static void run_linear(const void* x, const float* s, const void* wq, const floa
     li.y = static_cast<uint16_t*>(y);
     li.M = (int)M; li.N = (int)N; li.K = (int)K;
     if (mfma_ok && use_skinny(g, wf)) {
-        const bool qx = skinny_quantizes(g, acc_out);
+        const bool qx = skinny_quantizes(g, wf, acc_out);
         if (!qx) launch_quantize_blocks<DT, false>(x, s, xq_ws, M, K, a_bits, st);
         launch_linear_skinny(g, (sasq_dtype)DT, (int)wf, qx, a_bits, acc_out, st);
     } else if (wf == SASQ_W_INT8_BLOCKED || wf == SASQ_W_INT4_BLOCKED) {
@@ -1011,7 +1011,7 @@ static void run_linear(const void* x, const float* s, const void* wq, const floa
             }
         }
     } else if (!int4 && !variant_asked_for() && linear_anyk_takes_skinny(M, N, K)) {
-        const bool qx = skinny_quantizes(g, acc_out);
+        const bool qx = skinny_quantizes(g, wf, acc_out, true);
         if (!qx) quantize_act_kernel<DT, false, false><<<qgrid, 256, 0, st>>>(X, s, reinterpret_cast<u32x2*>(xq_ws), nvec, n, (int)K, a_bits);
         launch_linear_anyk_skinny(g, (sasq_dtype)DT, qx, a_bits, acc_out, st);
     } else {
@@ -1300,7 +1300,7 @@ extern "C" int sasq_static_linear_batch(const sasq_linear_item* items, int count
 
     hipStream_t st = as_stream(stream);
     const bool skinny = use_skinny(g, wf);
-    if (skinny && skinny_quantizes(g, nullptr)) {
+    if (skinny && skinny_quantizes(g, wf, nullptr)) {
         launch_linear_skinny(g, dt, (int)wf, true, a_bits, nullptr, st);
         return hipGetLastError() == hipSuccess ? SASQ_OK : SASQ_ERR_LAUNCH;
     }

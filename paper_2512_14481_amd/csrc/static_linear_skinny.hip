@@ -396,25 +396,39 @@ static bool tiles_are_better(const LinBatch& b, int rows, int wmode)
     return single ? fill > (one_round ? 0.5 : int4 ? 0.8 : 0.7) : row_major && fill > (one_round ? 0.5 : 0.8);
 }
 
-// Blocks of 32 rows by 32 or 64 columns (returned in units of 16, 0: neither), for more than kSkinnyRows rows: where they all run at
-// once, one a CU, the call takes as long as one block, and these are the shortest; from a second round on the larger ones read less.
-// The runs of columns go round the eight XCDs, so a round is 32 blocks on the XCD with the most of them.  Measured, us, pre-arranged
-// int8, before | 32 x 32 | 32 x 64: 80 x 1024 x 1024 8.6 | 7.2 | 7.8, 143 x 2816 x 2816 11.0 | 11.8 | 9.5, 128 x 5248 -> 2048 14.1 |
-// 10.5, 224 x 11008 -> 1792 21.4 | - | 18.4, 1000 x 11008 -> 250 66.8 | 23.7; row-major 96 x 11008 -> 1024 31.2 | 18.9.  The backward: 80
-// x 1024 x 1024 7.9 | 5.0 | 6.4, 143 x 2816 x 2816 16.5 | 16.4 | 11.3, 128 x 5248 -> 2048 26.8 | 15.4, 224 x 5248 -> 1792 26.9 | - |
-// 17.7, 1000 x 512 -> 250 8.2 | 4.9.  Beyond a round: 171 x 1344 -> 1344 (36 blocks of 32 x 32 on one XCD) 9.4 | 10.4, 224 x 2240 ->
-// 2240 (35 of 32 x 64) 14.2 | - | 16.2, forward 10.7 | - | 12.4.
-static int small_block_cols(const LinItem* items, int count)
+// Small blocks, for more than 16 rows: the smallest of 16 x 16 outputs (int4 16 x 32), 32 x 16 (32 x 32), 32 x 32 and 32 x 64 that
+// the call has no more than a round of, one a CU.  All run at once, so the call takes as long as one of them, and the smallest are the
+// shortest; from a second round on the larger ones of the other rules read less.  The runs of columns go round the eight XCDs, so a
+// round is 32 blocks on the XCD with the most of them.  Measured, us, before | 16 x 16 | 32 x 16: pre-arranged 64 x 4096 -> 512 10.2 |
+// 7.0 | 7.6, 20 x 4096 -> 2048 9.2 | 7.4 | 8.3, row-major 64 x 1024 -> 256 7.2 | 4.8 | 6.5, backward 64 x 4096 -> 1024 19.8 | 7.3 |
+// 10.7, 64 x 1024 -> 2048 6.2 | 5.2 (two rounds) | 4.7, 32 x 4096 -> 512 11.2 | 6.9 | 10.2; | 32 x 32 | 32 x 64: pre-arranged 80 x 1024 x
+// 1024 8.6 | 7.2 | 7.8, 143 x 2816 x 2816 11.0 | 11.8 | 9.5, 1000 x 11008 -> 250 66.8 | 23.7, row-major 96 x 11008 -> 1024 31.2 | 18.9;
+// backward 143 x 1280 x 1280 9.4 | 6.4 | 6.8, 143 x 2816 x 2816 16.5 | 16.4 | 11.3, 128 x 5248 -> 2048 26.8 | 15.4, 224 x 5248 -> 1792
+// 26.9 | - | 17.7.  Beyond a round: backward 171 x 1344 -> 1344 (36 blocks of 32 x 32 on one XCD) 9.4 | 10.4, 224 x 2240 -> 2240 (35 of
+// 32 x 64) 14.2 | - | 16.2, 64 x 4096 x 1024 (128 of 16 x 16) 7.0 | 8.4 | 7.5.
+// Row-major int8, whose few-row kernel has the better loads (plain ones), leaves it for blocks of 16 columns only, and of those for at least two
+// row blocks: 40 x 2048 -> 3000 7.4 | 9.0 as 32 x 32, 50 x 8192 -> 3500 14.3 | 15.9, 24 x 2048 -> 3000 6.8 | 7.8 as 32 x 16.
+struct SmallBlock { int mt, nt; };                                       // in units of 16; 0: none
+static SmallBlock small_block(const LinItem* items, int count, int wmode)
 {
-    for (int i = 0; i < count; ++i)
-        if (count > 1 && items[i].N <= 448) return 0;                // as block_rows: the other items' blocks share the XCDs unevenly
-    for (int nt = 2; nt <= 4; nt += 2) {
+    const bool int4 = wmode == 3, row_major = wmode == 0;
+    int rows = 0;
+    for (int i = 0; i < count; ++i) {
+        rows = items[i].M > rows ? items[i].M : rows;
+        if (count > 1 && items[i].N <= 448) return {0, 0};           // as block_rows: the other items' blocks share the XCDs unevenly
+    }
+    if (rows <= 16) return {0, 0};
+    static const SmallBlock forms[] = {{1, 1}, {1, 2}, {2, 1}, {2, 2}, {2, 4}};
+    for (const SmallBlock& f : forms) {
+        if (int4 ? f.nt == 1 : f.mt == 1 && f.nt == 2) continue;     // int4 blocks hold 32 weight rows
+        if (rows <= 32 && (f.nt == 4 || (f.nt == 2 && !int4))) continue;
+        if (row_major && rows <= kSkinnyRows && (f.nt > 1 || (f.mt == 2 && rows <= 32))) continue;
         int64_t blocks = 0;
         for (int i = 0; i < count; ++i)
-            blocks += ((int64_t)items[i].M + 31) / 32 * (((int64_t)items[i].N + 128 * nt - 1) / (128 * nt) * 8);
-        if (blocks <= 256) return nt;
+            blocks += ((int64_t)items[i].M + 16 * f.mt - 1) / (16 * f.mt) * (((int64_t)items[i].N + 128 * f.nt - 1) / (128 * f.nt) * 8);
+        if (blocks <= 256) return f;
     }
-    return 0;
+    return {0, 0};
 }
 
 // Rows per workgroup (64 weight rows each, K over eight waves) for more than kSkinnyRows rows, 0: the GEMM's tiles are better.
@@ -488,13 +502,14 @@ bool linear_takes_skinny(const LinBatch& b, int wmode)
         cols += b.it[i].N;
     }
     if (cols > INT64_C(1) << 27) return false;         // up to 16 work items a column, and a launch holds fewer than 2^32
-    return rows <= kSkinnyRows ? !tiles_are_better(b, rows, wmode) : small_block_cols(b.it, b.count) != 0 || block_rows(b, wmode) != 0;
+    return rows <= kSkinnyRows ? !tiles_are_better(b, rows, wmode) : small_block(b.it, b.count, wmode).mt != 0 || block_rows(b, wmode) != 0;
 }
 
-// Whether such a call, of at most kSkinnyRows rows, quantizes in the kernel: at most 16 rows, or so few codes in an item's row tiles
-// (of 32 or 64 rows) that repeating them costs a workgroup less than a launch.  Measured, us, pre-pass | in the kernel: 32 rows, K =
-// 256 4.8 | 3.3, 1024 5.4 | 4.9, 2048 6.8 | 7.0, 4096 8.5 | 10.6; 64 rows, K = 256 5.1 | 3.7, 512 5.3 | 4.7, 1024 6.0 | 7.1.
-bool linear_quantizes_in_kernel(const LinBatch& b)
+// Whether such a call quantizes in the kernel: at most 16 rows, or so few codes in a workgroup's rows (of row tiles of 32 or 64, or of a
+// small block) that repeating them costs it less than a launch.  Measured, us, pre-pass | in the kernel: 32 rows, K = 256 4.8 | 3.3,
+// 1024 5.4 | 4.9, 2048 6.8 | 7.0, 4096 8.5 | 10.6; 64 rows, K = 256 5.1 | 3.7, 512 5.3 | 4.7, 1024 6.0 | 7.1; small blocks of 16 rows, K =
+// 1024 6.8 | 4.8, 4096 7.8 | 8.2.  any_k: K not a multiple of 64, where there are no small blocks.
+bool linear_quantizes_in_kernel(const LinBatch& b, int wmode, bool any_k)
 {
     int rows = 0, k_max = 0;
     int64_t tiles16 = 0;
@@ -503,7 +518,19 @@ bool linear_quantizes_in_kernel(const LinBatch& b)
         k_max = b.it[i].K > k_max ? b.it[i].K : k_max;
         tiles16 += (b.it[i].N + 15) / 16;
     }
-    return rows <= kSkinnyQuantRows || (rows <= kSkinnyRows && (int64_t)(rows <= 32 ? 32 : 64) * k_max <= 32768 && tiles16 < 512);
+    if (rows <= kSkinnyQuantRows) return true;
+    if (const int mt = any_k ? 0 : small_block(b.it, b.count, wmode).mt) return k_max <= (mt == 1 ? 3072 : 1024);
+    return rows <= kSkinnyRows && (int64_t)(rows <= 32 ? 32 : 64) * k_max <= 32768 && tiles16 < 512;
+}
+
+template <int DT, int WMODE, bool QX>
+static void launch_small(LinBatch& b, SmallBlock f, int a_bits, int32_t* acc_out, hipStream_t st)
+{
+    if (f.nt == 4)                launch_one<DT, WMODE, 2, 4, 8, 3, QX, false>(b, a_bits, acc_out, st);
+    else if (f.mt == 2 && f.nt == 2) launch_one<DT, WMODE, 2, 2, 8, 4, QX, false>(b, a_bits, acc_out, st);
+    else if constexpr (WMODE == 3)   launch_one<DT, WMODE, 1, 2, 8, 4, QX, false>(b, a_bits, acc_out, st);
+    else if (f.mt == 2)              launch_one<DT, WMODE, 2, 1, 8, 3, QX, false>(b, a_bits, acc_out, st);
+    else                             launch_one<DT, WMODE, 1, 1, 8, 4, QX, false>(b, a_bits, acc_out, st);
 }
 
 template <int DT, int WMODE>
@@ -515,11 +542,13 @@ static void launch_wmode(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, hip
         tiles16 += (b.it[i].N + 15) / 16;
         rows = b.it[i].M > rows ? b.it[i].M : rows;
     }
-    if (rows > kSkinnyRows) {
-        const int small = small_block_cols(b.it, b.count), block = small ? 32 : block_rows(b, WMODE);
-        if (small == 2)                      launch_one<DT, WMODE, 2, 2, 8, 4, false, false>(b, a_bits, acc_out, st);
-        else if (small == 4)                 launch_one<DT, WMODE, 2, 4, 8, 3, false, false>(b, a_bits, acc_out, st);
-        else if (block == 64)                     launch_one<DT, WMODE, 4, 4, 8, 2, false, false>(b, a_bits, acc_out, st);
+    const SmallBlock small = small_block(b.it, b.count, WMODE);
+    if (small.mt) {
+        if (qx) launch_small<DT, WMODE, true>(b, small, a_bits, acc_out, st);
+        else    launch_small<DT, WMODE, false>(b, small, a_bits, acc_out, st);
+    } else if (rows > kSkinnyRows) {
+        const int block = block_rows(b, WMODE);
+        if (block == 64)                     launch_one<DT, WMODE, 4, 4, 8, 2, false, false>(b, a_bits, acc_out, st);
         else if (block == 96 && rows > 96)   launch_one<DT, WMODE, 6, 4, 8, 2, false, false>(b, a_bits, acc_out, st);
         else if (block == 96)                launch_one<DT, WMODE, 6, 4, 8, 2, false, true>(b, a_bits, acc_out, st);
         else if (rows > 128)                 launch_one<DT, WMODE, 8, 4, 8, 2, false, false>(b, a_bits, acc_out, st);
@@ -605,16 +634,16 @@ static LinItem bwd_item(const void* dy, const void* wt, void* dx, int64_t M, int
     return it;
 }
 
-// Rows per workgroup, from estimates in us as in block_rows above: at most 64 rows 64 (in row tiles of 16, 32 or 64); more rows 32
-// where such blocks all run at once (small_block_cols), or 64 or 96 by 64 columns, where that takes 15 % less time than the GEMM's tiles (128 never do).  260 calls of 8 to 1500 rows, contractions and outputs
+// Rows per workgroup, from estimates in us as in block_rows above: 32, small blocks, where small_block has some; at most 64 rows 64 (in
+// row tiles of 16, 32 or 64); more rows 64 or 96 by 64 columns, where that takes 15 % less time than the GEMM's tiles (128 never do).  260 calls of 8 to 1500 rows, contractions and outputs
 // of 256 to 13824: at most 16 rows take 0.41 of their time on the tiles, 17 to 32 0.56, 33 to 64 0.69, more 0.89 (those on row
 // blocks 0.76), and none 2 % more.  us, tiles | here: 1 x 4096 x 4096 25.3 | 8.0, 64 x 256 x 256 4.8 | 3.4, 131 x 2816 x 1344 23.4 |
 // 17.3, 334 x 11072 x 1536 76.2 | 52.5.
 int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_rounds)
 {
-    if (M <= 32 || (M <= 64 && K <= 4096)) return K <= INT64_C(1) << 26 ? 64 : 0;     // up to 32 work items a column
     const LinItem it = bwd_item(nullptr, nullptr, nullptr, M, N, K);
-    if (M > 64 && small_block_cols(&it, 1)) return 32;
+    if (small_block(&it, 1, 2).mt) return 32;
+    if (M <= 32) return K <= INT64_C(1) << 26 ? 64 : 0;     // up to 32 work items a column
     if (K <= 448) return 0;                                          // fewer than eight runs of weight rows leave XCDs without work
     static const BlockTime block[2] = {{1.8, 2.1, 0.155}, {1.5, 3.4, 0.205}};
     const double kt = (double)(N / 32);
@@ -630,26 +659,26 @@ int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_rounds)
     return rows;
 }
 
-// Few rows: narrow workgroups (16 columns) while they make one round of at most 256, wide ones from then on (over calls of 17 to 64
-// rows a line at 4096 columns takes 0.96 of the time of one at 8192).
+// At most 16 rows: narrow workgroups (16 columns) while they make one round of at most 256, wide ones from then on.
 template <int DT>
 static void launch_bwd_dt(LinItem& it, float* acc_out, int rows, hipStream_t st)
 {
-    const bool wide = it.N > 4096;
-    if (it.M > 64) {
-        if (rows == 32 && small_block_cols(&it, 1) == 2) launch_bwd_one<DT, 2, 2, 8, 4, false>(it, acc_out, st);
-        else if (rows == 32) launch_bwd_one<DT, 2, 4, 8, 3, false>(it, acc_out, st);
-        else if (rows == 64) launch_bwd_one<DT, 4, 4, 8, 2, false>(it, acc_out, st);
+    if (rows == 32) {
+        const SmallBlock f = small_block(&it, 1, 2);
+        if (f.nt == 4)      launch_bwd_one<DT, 2, 4, 8, 3, false>(it, acc_out, st);
+        else if (f.nt == 2) launch_bwd_one<DT, 2, 2, 8, 4, false>(it, acc_out, st);
+        else if (f.mt == 2) launch_bwd_one<DT, 2, 1, 8, 4, false>(it, acc_out, st);
+        else                launch_bwd_one<DT, 1, 1, 8, 4, false>(it, acc_out, st);
+    } else if (it.M > 64) {
+        if (rows == 64) launch_bwd_one<DT, 4, 4, 8, 2, false>(it, acc_out, st);
         else            launch_bwd_one<DT, 6, 4, 8, 2, false>(it, acc_out, st);
     } else if (it.M <= 16) {
-        if (wide) launch_bwd_one<DT, 1, 2, 8, 3, true>(it, acc_out, st);
-        else      launch_bwd_one<DT, 1, 1, 8, 4, true>(it, acc_out, st);
+        if (it.N > 4096) launch_bwd_one<DT, 1, 2, 8, 3, true>(it, acc_out, st);
+        else             launch_bwd_one<DT, 1, 1, 8, 4, true>(it, acc_out, st);
     } else if (it.M <= 32) {
-        if (wide) launch_bwd_one<DT, 2, 2, 8, 3, true>(it, acc_out, st);
-        else      launch_bwd_one<DT, 2, 1, 8, 4, true>(it, acc_out, st);
+        launch_bwd_one<DT, 2, 2, 8, 3, true>(it, acc_out, st);
     } else {
-        if (wide) launch_bwd_one<DT, 4, 4, 8, 2, true>(it, acc_out, st);
-        else      launch_bwd_one<DT, 4, 1, 8, 4, true>(it, acc_out, st);
+        launch_bwd_one<DT, 4, 4, 8, 2, true>(it, acc_out, st);
     }
 }
 

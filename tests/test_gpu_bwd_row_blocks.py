@@ -1,5 +1,5 @@
 """GPU parity of the backward linear's kernels for few rows and row blocks (contraction split over the waves, no tiles) against the CPU
-oracle: the row-tile forms (16, 32, 64 rows; narrow and wide), blocks of 32, 64 and 96 rows, waves without a contraction tile, ragged
+oracle: the row-tile forms (16, 32, 64 rows; narrow and wide), small blocks, blocks of 64 and 96 rows, waves without a contraction tile, ragged
 rows and columns.  Bounds as for the tiled kernels: fp32 sums in any order, one rounding."""
 from __future__ import annotations
 
@@ -19,10 +19,10 @@ def up(a, b):
 
 def chosen(M, N, K):
     """Rows per workgroup the dispatch takes (bwd_takes_skinny), 0: the GEMM's tiles."""
-    if M <= 32 or (M <= 64 and K <= 4096):
-        return 64
-    if M > 64 and up(M, 32) * min(up(K, 256), up(K, 512)) * 8 <= 256:
+    if M > 16 and min(up(M, 16 * mt) * up(K, 128 * nt) * 8 for mt, nt in ((1, 1), (2, 1), (2, 2), (2, 4)) if M > 32 or nt == 1) <= 256:
         return 32
+    if M <= 32:
+        return 64
     if K <= 448:
         return 0
     rounds = min(up(up(M, 256) * up(K, 256), 256), up(up(M, 128) * up(K, 128), 512) * 0.71)
@@ -36,8 +36,10 @@ def chosen(M, N, K):
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("shape,want", [
-    ((1, 32, 2), 64), ((16, 576, 4096), 64), ((15, 96, 4104), 64), ((17, 64, 70), 64), ((32, 1088, 5001), 64), ((33, 96, 48), 64),
-    ((64, 1056, 4096), 64), ((64, 2048, 4200), 64), ((50, 1024, 5003), 64), ((40, 32, 20000), 0),
+    ((1, 32, 2), 64), ((16, 576, 4096), 64), ((15, 96, 4104), 64), ((32, 1088, 5001), 64), ((64, 2048, 8300), 64), ((50, 1024, 9003), 64), ((40, 32, 20000), 0),
+    ((17, 64, 70), 32), ((33, 96, 48), 32), ((64, 576, 1024), 32), ((130, 160, 130), 32),                                 # 16 x 16
+    ((32, 1088, 4090), 32), ((33, 96, 1300), 32), ((300, 320, 256), 32),                                                  # 32 x 16
+    ((64, 1056, 4096), 32), ((64, 2048, 4200), 32), ((50, 1024, 5003), 32),
     ((65, 32, 2), 32), ((65, 1024, 1000), 32), ((130, 1024, 520), 32), ((129, 1600, 449), 32), ((1024, 96, 256), 32),    # 32 x 32
     ((500, 288, 700), 32), ((70, 1056, 5120), 32), ((222, 544, 1530), 32),                                                # 32 x 64
     ((70, 1056, 5121), 64), ((300, 1024, 1700), 64), ((1000, 1024, 520), 64), ((2000, 1024, 448), 0), ((380, 4096, 4000), 96)])

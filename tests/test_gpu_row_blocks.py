@@ -1,4 +1,4 @@
-"""GPU parity of the linear's row blocks (more than 64 rows in workgroups of 32 rows by 32 or 64 columns, or 64, 96 or 128 by 64, K over eight waves)
+"""GPU parity of the linear's row blocks (more than 64 rows in small blocks of 16 or 32 rows, or 64, 96 or 128 by 64, K over eight waves)
 against the CPU oracle: each block form and weight layout, alone and in batches, with waves that have no K tile at all (K = 64),
 uneven shares of them, and rows and columns that end inside a block."""
 from __future__ import annotations
@@ -62,6 +62,9 @@ def chosen(items, layout):
 @pytest.mark.parametrize("items,want", [
     ([(65, 1000, 64)], (32, 32, 32)),                                           # 32 x 32: 96 blocks, waves without a K tile
     ([(130, 1003, 704)], (32, 32, 32)),
+    ([(130, 100, 576)], (32, 32, 32)),                                          # 16 x 16, quantized in the kernel
+    ([(130, 100, 3136)], (32, 32, 32)),                                         # and before it
+    ([(300, 250, 1024)], (32, 32, 32)),                                         # 32 x 16, quantized in the kernel
     ([(1024, 256, 576)], (32, 32, 32)),                                         # exactly 256
     ([(500, 700, 576)], (32, 32, 32)),                                          # 384, so 32 x 64
     ([(70, 5120, 640)], (32, 32, 32)),                                          # 240 of 32 x 64
