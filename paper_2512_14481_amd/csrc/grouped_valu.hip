@@ -579,7 +579,7 @@ static void launch_small_group_rows(const GemmK64Args& a, hipStream_t st)
     if (a.M > 16 && tiles > (G == 1 ? 128 : 192)) launch_small_group<DT, INT4, G, 16>(a, st);
     else if constexpr (G == 1) {
         // Rows of a wave: fewer give more waves, and a wave alone on its SIMD takes as long as it has operations.  Measured, us, four |
-        // one | two: 16 x 1024 x 1024 (256 rows of 64 outputs) 33.6 | 20.5 | 26.3, 16 x 2048 x 4096 (1024) 63.4 | 37.5 | 48.5, 200 x
+        // one | two: 16 x 1024 x 1024 (256 rows of 64 outputs) 33.6 | 20.5 | 26.3, 16 x 2048 x 4096 (1024) 63.4 | 37.5 | 48.5, 72 x 1024 x 1024 (1152) - | 25.7 | 23.2, 200 x
         // 1024 x 1024 (3200) 34.0 | 41.6 | 32.5, 64 x 2048 x 4096 (4096) 63.6 | 78 | 61, 200 x 4096 x 1500 (4800) 175 | 183 | 159,
         // 512 x 1024 x 1024 (8192) 48 | 71 | 54.
         const int64_t rows64 = a.M * ((a.N + 63) / 64);              // rows of 64 outputs: waves of the one-row form
