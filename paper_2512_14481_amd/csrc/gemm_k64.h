@@ -47,7 +47,9 @@ void launch_linear_skinny(LinBatch& b, sasq_dtype dt, int wmode, bool qx, int a_
 bool linear_anyk_takes_skinny(int64_t M, int64_t N, int64_t K);
 void launch_linear_anyk_skinny(LinBatch& b, sasq_dtype dt, bool qx, int a_bits, int32_t* acc_out, hipStream_t st);
 // The backward GEMM dX[M, K] = dY[M, N] . B^T over the prepared weight (linear_bwd.hip), for few rows or too few tiles; N a multiple
-// of 32.  bwd_takes_skinny: rows per workgroup, 0: the tiles are better.
+// of 32.  bwd_takes_skinny: rows per workgroup, 0: the tiles are better, or the contraction is too long.
+// Longest contraction of the kernels that reach a block's rows by 32-bit byte offsets (256 rows of dY, 2 GB; 64 columns' weight blocks).
+constexpr int64_t kBwdOffsetCols = INT64_C(1) << 22;
 int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_rounds);
 void launch_bwd_skinny(const void* dy, const void* wt, void* dx, float* acc_out, int64_t M, int64_t N, int64_t K, sasq_dtype dt, int rows, hipStream_t st);
 // Batches of at least so many workgroup ids, and at most 128, go as half tiles throughout.

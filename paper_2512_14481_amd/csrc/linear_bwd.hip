@@ -458,7 +458,7 @@ extern "C" int sasq_linear_bwd_input(const void* dy, const void* wt, void* dx, f
         }
     const bool small = bwd_small_tiles(M, K);
     // the 16x16x32 kernel addresses dY rows with 32-bit byte offsets inside a 256-row tile
-    if (tuning(SASQ_TUNE_LINEAR_MFMA) != 1 && N <= (INT64_C(1) << 22)) {
+    if (tuning(SASQ_TUNE_LINEAR_MFMA) != 1 && N <= kBwdOffsetCols) {
         auto by_tile = [&](auto dt_tag) {
             constexpr int DT = decltype(dt_tag)::value;
             switch (bwd_tile(M, K)) {

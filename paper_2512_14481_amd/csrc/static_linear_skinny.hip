@@ -61,8 +61,9 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
     const int per = (KT + NW - 1) / NW;
     const int t0 = min(wave * per, KT), count = min(per, KT - t0);
 
-    // One scalar base per operand, advanced 1 KB (or 64 bytes of a row) per K tile, + a 32-bit lane offset per stream (at most 8
-    // row blocks of 2 MB): the products of 96 rows leave no registers for 64-bit lane addresses.  Blocks and rows past the
+    // One scalar base per operand, advanced 1 KB (or 64 bytes of a row) per K tile, + a 32-bit lane offset per stream: the products of 96
+    // rows leave no registers for 64-bit lane addresses.  At K <= 131071 the codes are at most 8 row blocks of 2 MB; FLT's 96 rows stay
+    // under 0.8 GB and its four weight blocks under 0.4 GB as no contraction here is longer than kBwdOffsetCols.  Blocks and rows past the
     // matrix repeat its last one.
     const int wblk = I4 ? n0 >> 5 : n0 >> 4, wlast = I4 ? (N - 1) >> 5 : (N - 1) >> 4;
     const char* wbase = reinterpret_cast<const char*>(it.wq) +
@@ -641,6 +642,7 @@ static LinItem bwd_item(const void* dy, const void* wt, void* dx, int64_t M, int
 // 17.3, 334 x 11072 x 1536 76.2 | 52.5.
 int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_rounds)
 {
+    if (N > kBwdOffsetCols) return 0;                                // the body's lane offsets are 32-bit
     const LinItem it = bwd_item(nullptr, nullptr, nullptr, M, N, K);
     if (small_block(&it, 1, 2).mt) return 32;
     if (M <= 32) return K <= INT64_C(1) << 26 ? 64 : 0;     // up to 32 work items a column

@@ -1,0 +1,19 @@
+"""The library's own answers to which kernel a call takes: host functions of libsasq.so, no device needed."""
+from __future__ import annotations
+
+import ctypes
+
+from paper_2512_14481_amd import binding as B
+
+
+def _function(symbol, *argtypes):
+    f = getattr(B._lib(), symbol)
+    f.restype, f.argtypes = ctypes.c_int, argtypes
+    return f
+
+
+def bwd_rows(M, N, K):
+    """Rows per workgroup of the backward linear's few-row and row-block kernels, 0: the GEMM's tiles (sasq::bwd_takes_skinny)."""
+    rounds = min(-(-(-(-M // 256) * -(-K // 256)) // 256), -(-(-(-M // 128) * -(-K // 128)) // 512) * 0.71)
+    i64 = ctypes.c_int64
+    return _function("_ZN4sasq16bwd_takes_skinnyEllld", i64, i64, i64, ctypes.c_double)(M, N, K, rounds)

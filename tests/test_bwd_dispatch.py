@@ -1,0 +1,28 @@
+"""The backward linear's choice of kernels, a host function: calls that take the few-row and row-block kernels stay inside the range of
+their 32-bit lane offsets, whatever contraction the entry point accepts."""
+from __future__ import annotations
+
+import random
+
+from tests.dispatch import bwd_rows
+
+MOST = 2 ** 40                                              # the entry point's limit on each product of two sizes
+
+
+def largest_offset(rows, N):
+    """Largest lane offset in bytes: the last row of a block in dY, the last of its 64 columns' weight blocks, the last K tile."""
+    return max((max(rows, 64) - 1) * 2 * N, 3 * (N // 32) * 1024) + N // 32 * 1024 + 1024
+
+
+def test_no_call_wraps_its_offsets():
+    rng = random.Random(11)
+    shapes = [(1025, 23068672, 1024), (1025, 34603008, 512), (600, 45088768, 512), (1056, 36 << 20, 512), (16, 1 << 27, 16), (32, 1 << 26, 4096)]
+    for _ in range(20000):
+        M, N, K = (int(2 ** rng.uniform(0, top)) for top in (14, 29.9, 16))
+        N = max(N // 32, 1) * 32
+        if max(M * N, M * K, N * K) <= MOST:
+            shapes.append((M, N, K))
+    taken = [(s, bwd_rows(*s)) for s in shapes]
+    wrapped = [(s, rows) for s, rows in taken if rows and largest_offset(rows, s[1]) >= 2 ** 32]
+    assert not wrapped, wrapped[:5]
+    assert sum(rows != 0 for _, rows in taken) > 1000

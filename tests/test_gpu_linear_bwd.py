@@ -11,6 +11,7 @@ import torch
 import oracle
 from paper_2512_14481_amd import binding as B
 from paper_2512_14481_amd import workloads as wl
+from tests.dispatch import bwd_rows
 from tests.gpu_util import TDT, set_tuning, to_bits, to_dev, val
 
 pytestmark = pytest.mark.gpu
@@ -164,3 +165,23 @@ def test_linear_bwd_output_beyond_2_31_elements():
     rows = np.array([0, 1, edge - 1, edge, edge + 1, M - 2, M - 1])
     ref = oracle.linear_bwd_input(dyb[rows], wq, s_w, fmt, dtype)
     check_dx(to_bits(dx[torch.from_numpy(rows).cuda()]), ref, dtype, N, "rows across the boundary")
+
+
+@pytest.mark.parametrize("cols", [2 ** 22, 2 ** 22 + 32])
+def test_contractions_around_the_longest_of_the_32_bit_offsets(cols):
+    """Either side of the longest contraction of the few-row kernel.  Integers, so that every partial sum is exact in fp32 (the
+    largest possible one is 7 * cols = 2^24.9, those of random signs stay under 2^20)."""
+    M, N, K = 17, cols, 18
+    assert (bwd_rows(M, N, K) != 0) == (N <= 2 ** 22)
+    gen = torch.Generator(device="cuda").manual_seed(84)
+    dy = torch.randint(-1, 2, (M, N), generator=gen, device="cuda", dtype=torch.int8).to(torch.bfloat16)
+    wq = torch.randint(-7, 8, (N, K), generator=gen, device="cuda", dtype=torch.int8)
+    wt = torch.empty(B.sasq_bwd_weight_bytes(N, K), dtype=torch.uint8, device="cuda")
+    B.sasq_prepare_bwd_weight(wq, torch.ones(N, device="cuda"), wt, N, K, WF["int8"], torch.bfloat16)
+    dx, acc = torch.empty((M, K), dtype=torch.bfloat16, device="cuda"), torch.empty((M, K), dtype=torch.float32, device="cuda")
+    set_tuning()
+    B.sasq_linear_bwd_input(dy, wt, dx, K, acc)
+    ref = torch.zeros((M, K), dtype=torch.float64, device="cuda")
+    for a in range(0, N, 1 << 20):
+        ref += dy[:, a:a + (1 << 20)].double() @ wq[a:a + (1 << 20)].double()
+    assert torch.equal(acc.double(), ref) and torch.equal(dx, acc.to(torch.bfloat16))
