@@ -174,11 +174,11 @@ void linear_bwd_mfma_kernel(const uint8_t* __restrict__ dy, const uint8_t* __res
     for (int j = 0; j < WS; ++j)
         gw[j] = wt + (int64_t)min((k0 >> 4) + 4 * j + wave, (K - 1) >> 4) * KT * 1024 + lane * 16;
     auto dma_x = [&](int Tk, int j) {
-        __builtin_amdgcn_global_load_lds((glb_ptr_t)(gx[j] + eff_tile(Tk) * kBK),
+        __builtin_amdgcn_global_load_lds((glb_ptr_t)(gx[j] + (int64_t)eff_tile(Tk) * kBK),
                                          (lds_ptr_t)(stage_ptr(stage_of(Tk), 0) + (4 * j + wave) * 1024), 16, 0, 0);
     };
     auto dma_w = [&](int Tk, int j) {
-        __builtin_amdgcn_global_load_lds((glb_ptr_t)(gw[j] + eff_tile(Tk) * 1024),
+        __builtin_amdgcn_global_load_lds((glb_ptr_t)(gw[j] + (int64_t)eff_tile(Tk) * 1024),
                                          (lds_ptr_t)(stage_ptr(stage_of(Tk), 1) + (4 * j + wave) * 1024), 16, 0, 0);
     };
 

@@ -167,10 +167,10 @@ def test_linear_bwd_output_beyond_2_31_elements():
     check_dx(to_bits(dx[torch.from_numpy(rows).cuda()]), ref, dtype, N, "rows across the boundary")
 
 
-@pytest.mark.parametrize("cols", [2 ** 22, 2 ** 22 + 32])
-def test_contractions_around_the_longest_of_the_32_bit_offsets(cols):
-    """Either side of the longest contraction of the few-row kernel.  Integers, so that every partial sum is exact in fp32 (the
-    largest possible one is 7 * cols = 2^24.9, those of random signs stay under 2^20)."""
+@pytest.mark.parametrize("cols", [2 ** 22, 2 ** 22 + 32, 2 ** 26 + 64])
+def test_contractions_around_the_limits_of_32_bit_offsets(cols):
+    """Either side of the longest contraction of the few-row kernel, and one whose weight blocks lie more than 2^31 bytes apart in a row
+    of blocks.  Integers, so that the partial sums, of random signs and under 2^20, are exact in fp32."""
     M, N, K = 17, cols, 18
     assert (bwd_rows(M, N, K) != 0) == (N <= 2 ** 22)
     gen = torch.Generator(device="cuda").manual_seed(84)
@@ -184,4 +184,4 @@ def test_contractions_around_the_longest_of_the_32_bit_offsets(cols):
     ref = torch.zeros((M, K), dtype=torch.float64, device="cuda")
     for a in range(0, N, 1 << 20):
         ref += dy[:, a:a + (1 << 20)].double() @ wq[a:a + (1 << 20)].double()
-    assert torch.equal(acc.double(), ref) and torch.equal(dx, acc.to(torch.bfloat16))
+    assert ref.abs().max() < 2 ** 20 and torch.equal(acc.double(), ref) and torch.equal(dx, acc.to(torch.bfloat16))
