@@ -6,13 +6,16 @@ tensors, contiguous, of the dtypes the header states.  A non-zero status raises 
 
 The calls of a training or serving loop are marshalled by a native module (host/marshal.cpp), which
 makes the same checks and returns None where one of them fails; the checks written out here then run
-and raise.  The others go through ctypes.
+and raise.  The others go through ctypes, and so do all of them where that module is missing or was
+built for another torch or Python (with a warning: a call costs 5 to 8 us more of the host's time).
 """
 from __future__ import annotations
 
 import ctypes
 import importlib.util
 import os
+import sysconfig
+import warnings
 from typing import Optional
 
 import torch
@@ -57,7 +60,7 @@ _NATIVE = ("sasq_fakequant_fwd", "sasq_fakequant_bwd", "sasq_fakequant_fwd_batch
 
 
 class _Unbound:
-    """Stands for the native module until the library is loaded: takes no call."""
+    """Stands for the native module until the library is loaded, or where it cannot be: takes no call."""
 
     def __getattr__(self, name):
         return lambda *args: None
@@ -66,14 +69,25 @@ class _Unbound:
 _native = _Unbound()
 
 
+def marshal_abi() -> str:
+    """What the native module depends on beside its source: torch's C++ headers and Python's."""
+    return f"torch {torch.__version__}, {sysconfig.get_config_var('SOABI')}"
+
+
 def _load_native(lib: ctypes.CDLL):
-    if not os.path.exists(MARSHAL_PATH):
-        raise RuntimeError(f"{MARSHAL_PATH} is missing: build it with `python -m paper_2512_14481_amd.build`")
-    spec = importlib.util.spec_from_file_location("paper_2512_14481_amd._marshal", MARSHAL_PATH)
-    module = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(module)
-    module.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
-                 for name in _NATIVE + ("sasq_packed_weight_bytes", "sasq_bwd_weight_bytes")})
+    """The native module, bound to the library's entry points; the stand-in, where it is missing or does not fit."""
+    try:
+        spec = importlib.util.spec_from_file_location("paper_2512_14481_amd._marshal", MARSHAL_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        if module.ABI != marshal_abi():
+            raise ImportError(f"built for {module.ABI}, this is {marshal_abi()}")
+        module.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+                     for name in _NATIVE + ("sasq_packed_weight_bytes", "sasq_bwd_weight_bytes")})
+    except (ImportError, OSError, AttributeError) as e:
+        warnings.warn(f"{MARSHAL_PATH} is not used, calls go through ctypes ({e}); "
+                      "build it with `python -m paper_2512_14481_amd.build`", RuntimeWarning, stacklevel=3)
+        return _Unbound()
     return module
 
 

@@ -31,30 +31,38 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
-def stale() -> bool:
-    if not os.path.exists(LIB):
-        return True
-    t = os.path.getmtime(LIB)
-    deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + [os.path.join(ROOT, "include", "sasq.h")]
-    return any(os.path.getmtime(d) > t for d in deps)
-
-
-def build_marshal(verbose: bool = True) -> None:
-    """Compile the binding's native module against the installed torch (host code only)."""
+def marshal_command() -> list[str]:
+    """The command that compiles the binding's native module against the installed torch (host code only)."""
     import sysconfig
 
     import torch
     from torch.utils import cpp_extension
+
+    from .binding import marshal_abi
     torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DSASQ_MARSHAL_ABI="{marshal_abi()}"']
     for inc in cpp_extension.include_paths() + ["/opt/rocm/include", sysconfig.get_paths()["include"]]:
         cmd += ["-isystem", inc]
     cmd += ["-I", os.path.join(ROOT, "include"), HOST_SOURCE, "-o", MARSHAL_LIB, "-L", torch_lib]
-    cmd += ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    return cmd + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+
+
+def build_marshal(verbose: bool = True, stamp: str | None = None) -> None:
+    """stamp: a file that keeps the command; the module is compiled again only if the command, its source or the C ABI changed."""
+    cmd = marshal_command()
+    if stamp and os.path.exists(stamp) and os.path.exists(MARSHAL_LIB):
+        deps = [HOST_SOURCE, os.path.join(ROOT, "include", "sasq.h")]
+        with open(stamp) as f:
+            same = f.read() == "\n".join(cmd)
+        if same and all(os.path.getmtime(d) <= os.path.getmtime(MARSHAL_LIB) for d in deps):
+            return
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    if stamp:
+        with open(stamp, "w") as f:
+            f.write("\n".join(cmd))
 
 
 def build(verbose: bool = True, incremental: bool = False) -> str:
@@ -100,13 +108,10 @@ def build(verbose: bool = True, incremental: bool = False) -> str:
         workers = max(1, min(len(srcs) + 1, int(os.environ.get("MAX_JOBS", "0")) or os.cpu_count() or 1))
         with concurrent.futures.ThreadPoolExecutor(max_workers=workers) as pool:
             ts_future = pool.submit(compile_ts, os.path.join(CSRC, TS_SOURCE))
-            host_deps = [HOST_SOURCE, os.path.join(ROOT, "include", "sasq.h")]
-            host_built = incremental and os.path.exists(MARSHAL_LIB) and all(os.path.getmtime(f) <= os.path.getmtime(MARSHAL_LIB) for f in host_deps)
-            host_future = None if host_built else pool.submit(build_marshal, verbose)
+            host_future = pool.submit(build_marshal, verbose, os.path.join(tmp, "marshal.cmd") if incremental else None)
             objs = list(pool.map(compile_one, srcs))
             ts_obj = ts_future.result()
-            if host_future:
-                host_future.result()
+            host_future.result()
         link = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
         if verbose:
             print(" ".join(link), flush=True)

@@ -462,4 +462,10 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }
+// ABI: what the module was compiled against, which the binding compares with what it runs on.
+PyMODINIT_FUNC PyInit__marshal()
+{
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "ABI", SASQ_MARSHAL_ABI) < 0) Py_CLEAR(m);
+    return m;
+}

@@ -125,3 +125,22 @@ def test_same_bits_and_same_errors_as_through_ctypes(name, monkeypatch):
         with monkeypatch.context() as m:
             m.setattr(B, "_native", fast)
             assert error(args) == by_ctypes
+
+
+@pytest.mark.parametrize("how", ["missing", "not a module", "built for another torch"])
+def test_without_the_native_module_the_calls_go_through_ctypes(how, monkeypatch, tmp_path):
+    if how == "built for another torch":
+        monkeypatch.setattr(B, "marshal_abi", lambda: "torch 0.0")
+    else:
+        monkeypatch.setattr(B, "MARSHAL_PATH", str(tmp_path / "_marshal.so"))
+        if how == "not a module":
+            (tmp_path / "_marshal.so").write_text("no library")
+    monkeypatch.setattr(B, "_LIB", None)
+    monkeypatch.setattr(B, "_native", B._Unbound())
+    with pytest.warns(RuntimeWarning, match="go through ctypes"):
+        assert B.sasq_version() >= 100
+    for name in CALLS:
+        args, _ = arguments(name, "cpu")
+        assert native(name, args) is None
+        with pytest.raises(ValueError, match="device tensors"):                # the checks written out in Python
+            getattr(B, name)(*args)
