@@ -46,6 +46,8 @@ void launch_linear_skinny(LinBatch& b, sasq_dtype dt, int wmode, bool qx, int a_
 // The same for K that is not a multiple of 64, a single call with row-major int8 weights (row-major codes in xq).
 bool linear_anyk_takes_skinny(int64_t M, int64_t N, int64_t K);
 void launch_linear_anyk_skinny(LinBatch& b, sasq_dtype dt, bool qx, int a_bits, int32_t* acc_out, hipStream_t st);
+// The backward GEMM's tile (linear_bwd.hip): 0: 256x256, 1: 128x256, 2: 128x128.
+int bwd_tile(int64_t M, int64_t N, int64_t K);
 // The backward GEMM dX[M, K] = dY[M, N] . B^T over the prepared weight (linear_bwd.hip), for few rows or too few tiles; N a multiple
 // of 32.  bwd_takes_skinny: rows per workgroup, 0: the tiles are better, or the contraction is too long.
 // Longest contraction of the kernels that reach a block's rows by 32-bit byte offsets (256 rows of dY, 2 GB; 64 columns' weight blocks).

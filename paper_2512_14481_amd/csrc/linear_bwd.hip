@@ -367,17 +367,23 @@ static bool bwd_small_tiles(int64_t M, int64_t K)
     return rounds128(M, K) < rounds256(M, K);
 }
 // The tile of the 16x16x32 kernel: 0: 256x256, 1: 128x256, 2: 128x128, by the rounds of a 256x256 tile's time that a launch takes.  A
-// 128x256 tile alone on its CU takes 0.65 of it, a 128x128 tile 0.44, two of them on a CU 0.8: of 257 to 512 tiles of 128x128 some CUs
-// hold two, and as 128x256 they all run at once.  Measured, us, M x N -> K, 256x256 | 128x256 | 128x128: 1834 x 2304 -> 2304 (270 tiles
-// of 128x128) 42.6 | 28.0 | 32.6, 900 x 5504 -> 4992 (312) 92 | 63 | 85, 2048 x 4096 -> 2304 (512) 48 | 35 | 40, 1000 x 2304 -> 2816
-// (176) 42.5 | 27.3 | 19.8, 4096 x 2304 -> 5120 (1280) 95.7 | 92.0 | 94.7, 3000 x 2304 -> 3328 (624) 45.4 | 57.9 | 52.1.
-static int bwd_tile(int64_t M, int64_t K)
+// 128x256 tile alone on its CU takes 0.65 of it (several rounds of them 0.68 each), a 128x128 tile 0.44, two of them on a CU 0.8: of 257
+// to 512 tiles of 128x128 some CUs hold two, and as 128x256 they all run at once.  But the one wave a SIMD of a 128x256 tile has nothing
+// beside it while it fills its pipeline and stores, and under 12 contraction tiles that is most of it: there 128x128 tiles are the better ones
+// by the old measure already, 0.71 for every two a CU.  Measured, us, M x N -> K,
+// 256x256 | 128x256 | 128x128: 1834 x 2304 -> 2304 (270 tiles of 128x128) 42.6 | 28.0 | 32.6, 900 x 5504 -> 4992 (312) 92 | 63 | 85, 2048 x
+// 4096 -> 2304 (512) 48 | 35 | 40, 1000 x 2304 -> 2816 (176) 42.5 | 27.3 | 19.8, 3000 x 2304 -> 3328 (624) 45.4 | 57.9 | 52.1; several
+// rounds: 4096 x 2304 -> 5120 95.7 | 92.0 | 94.7, 2920 x 3904 -> 8448 175 | 204 | 216, 1926 x 4288 -> 11008 183 | 207 | 232; short: 537 x
+// 128 -> 6720 10.7 | 7.4 | 6.1, 1647 x 96 -> 19008 28.5 | 24.5 | 19.3, means of 21 to 31 calls of 8 to 11 contraction tiles - | 9.8 | 9.9, of 12 to
+// 19 - | 12.2 | 12.4.
+int bwd_tile(int64_t M, int64_t N, int64_t K)
 {
     if (const int t = tuning(SASQ_TUNE_BWD_TILE)) return t == 1 ? 0 : 2;
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((K + bn - 1) / bn); };
-    const int64_t t128 = tiles(128, 128), rest = t128 % 512;
-    const double c0 = rounds256(M, K), c1 = 0.65 * (double)((tiles(128, 256) + 255) / 256);
-    const double c2 = 0.8 * (double)(t128 / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 0.44 : 0.8);
+    const int64_t t128 = tiles(128, 128), rest = t128 % 512, r1 = (tiles(128, 256) + 255) / 256;
+    const double c0 = rounds256(M, K), c2 = 0.8 * (double)(t128 / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 0.44 : 0.8);
+    const double c1 = r1 == 1 ? 0.65 : 0.68 * (double)r1;
+    if (N < 12 * kBwdCols) return rounds128(M, K) < c0 ? 2 : 0;
     return c0 <= c1 && c0 <= c2 ? 0 : c1 < c2 ? 1 : 2;
 }
 static double bwd_tile_rounds(int64_t M, int64_t K) { return rounds128(M, K) < rounds256(M, K) ? rounds128(M, K) : rounds256(M, K); }
@@ -461,7 +467,7 @@ extern "C" int sasq_linear_bwd_input(const void* dy, const void* wt, void* dx, f
     if (tuning(SASQ_TUNE_LINEAR_MFMA) != 1 && N <= kBwdOffsetCols) {
         auto by_tile = [&](auto dt_tag) {
             constexpr int DT = decltype(dt_tag)::value;
-            switch (bwd_tile(M, K)) {
+            switch (bwd_tile(M, N, K)) {
                 case 0:  launch_bwd_k32<DT, 256, 256>(dy, wt, dx, acc_out, M, N, K, st); break;
                 case 1:  launch_bwd_k32<DT, 128, 256>(dy, wt, dx, acc_out, M, N, K, st); break;
                 default: launch_bwd_k32<DT, 128, 128>(dy, wt, dx, acc_out, M, N, K, st); break;

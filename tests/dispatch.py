@@ -17,3 +17,9 @@ def bwd_rows(M, N, K):
     rounds = min(-(-(-(-M // 256) * -(-K // 256)) // 256), -(-(-(-M // 128) * -(-K // 128)) // 512) * 0.71)
     i64 = ctypes.c_int64
     return _function("_ZN4sasq16bwd_takes_skinnyEllld", i64, i64, i64, ctypes.c_double)(M, N, K, rounds)
+
+
+def bwd_tile(M, N, K):
+    """The backward GEMM's tile, rows and columns (sasq::bwd_tile)."""
+    i64 = ctypes.c_int64
+    return ((256, 256), (128, 256), (128, 128))[_function("_ZN4sasq8bwd_tileElll", i64, i64, i64)(M, N, K)]

@@ -4,7 +4,7 @@ from __future__ import annotations
 
 import random
 
-from tests.dispatch import bwd_rows
+from tests.dispatch import bwd_rows, bwd_tile
 
 MOST = 2 ** 40                                              # the entry point's limit on each product of two sizes
 
@@ -26,3 +26,12 @@ def test_no_call_wraps_its_offsets():
     wrapped = [(s, rows) for s, rows in taken if rows and largest_offset(rows, s[1]) >= 2 ** 32]
     assert not wrapped, wrapped[:5]
     assert sum(rows != 0 for _, rows in taken) > 1000
+
+
+def test_tiles_where_each_was_measured_fastest():
+    for shape in ((2920, 3904, 8448), (1926, 4288, 11008), (3000, 2304, 3328)):
+        assert bwd_tile(*shape) == (256, 256), shape
+    for shape in ((1834, 2304, 2304), (900, 5504, 4992), (2048, 4096, 2304), (1834, 384, 2304)):
+        assert bwd_tile(*shape) == (128, 256), shape
+    for shape in ((537, 128, 6720), (376, 96, 10944), (1647, 96, 19008), (3379, 320, 9280), (2218, 160, 2112), (1834, 352, 2304), (1000, 2304, 2816)):
+        assert bwd_tile(*shape) == (128, 128), shape
