@@ -46,13 +46,25 @@ void launch_linear_skinny(LinBatch& b, sasq_dtype dt, int wmode, bool qx, int a_
 // The same for K that is not a multiple of 64, a single call with row-major int8 weights (row-major codes in xq).
 bool linear_anyk_takes_skinny(int64_t M, int64_t N, int64_t K);
 void launch_linear_anyk_skinny(LinBatch& b, sasq_dtype dt, bool qx, int a_bits, int32_t* acc_out, hipStream_t st);
-// The backward GEMM's tile (linear_bwd.hip): 0: 256x256, 1: 128x256, 2: 128x128.
+// The choice of kernels in linear_bwd.hip: rows per workgroup without tiles, 0: tiles; the tile, 0: 256x256, 1: 128x256, 2: 128x128.
+int bwd_rows(int64_t M, int64_t N, int64_t K);
 int bwd_tile(int64_t M, int64_t N, int64_t K);
 // The backward GEMM dX[M, K] = dY[M, N] . B^T over the prepared weight (linear_bwd.hip), for few rows or too few tiles; N a multiple
-// of 32.  bwd_takes_skinny: rows per workgroup, 0: the tiles are better, or the contraction is too long.
+// of 32.  bwd_takes_skinny: rows per workgroup, 0: the tiles, which take tile_us, are better, or the contraction is too long.
+// An estimate of a launch's time in us: its workgroups go in rounds of 256, one a CU; a round costs what a workgroup takes to start and end,
+// and its K tiles, each the longer the more CUs are at work beside it (the clock comes down, the operands come later).
+struct RoundTime {
+    double call, round, k_tile, k_fill;
+    double of(int64_t blocks, double k_tiles) const { return round + k_tiles * (k_tile + k_fill * (double)blocks / 256.0); }
+    double launch(int64_t blocks, double k_tiles) const
+    {
+        const int64_t rest = blocks % 256;
+        return call + (double)(blocks / 256) * of(256, k_tiles) + (rest ? of(rest, k_tiles) : 0.0);
+    }
+};
 // Longest contraction of the kernels that reach a block's rows by 32-bit byte offsets (256 rows of dY, 2 GB; 64 columns' weight blocks).
 constexpr int64_t kBwdOffsetCols = INT64_C(1) << 22;
-int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_rounds);
+int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_us);
 void launch_bwd_skinny(const void* dy, const void* wt, void* dx, float* acc_out, int64_t M, int64_t N, int64_t K, sasq_dtype dt, int rows, hipStream_t st);
 // Batches of at least so many workgroup ids, and at most 128, go as half tiles throughout.
 constexpr int kHalvesFrom = 32;

@@ -386,7 +386,23 @@ int bwd_tile(int64_t M, int64_t N, int64_t K)
     if (N < 12 * kBwdCols) return rounds128(M, K) < c0 ? 2 : 0;
     return c0 <= c1 && c0 <= c2 ? 0 : c1 < c2 ? 1 : 2;
 }
-static double bwd_tile_rounds(int64_t M, int64_t K) { return rounds128(M, K) < rounds256(M, K) ? rounds128(M, K) : rounds256(M, K); }
+// The time of those tiles, us, for the choice between them and the few-row and row-block kernels: least squares over 3900 calls of 1 to 4000
+// rows, contractions of 64 to 14000 and outputs of 128 to 28000, each tile timed in all of them (rms error 7 %, 8 % and 10 %).  Of 128x128
+// tiles a CU holds two in rounds of more than 256.
+static double bwd_tile_us(int64_t M, int64_t N, int64_t K)
+{
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((K + bn - 1) / bn); };
+    const double kt = (double)(N / kBwdCols);
+    const int tile = bwd_tile(M, N, K);
+    if (tile == 0) return RoundTime{0.0, 7.8, 0.466, 0.311}.launch(tiles(256, 256), kt);
+    if (tile == 1) return RoundTime{0.65, 4.4, 0.284, 0.207}.launch(tiles(128, 256), kt);
+    const RoundTime one{2.0, 1.5, 0.163, 0.175}, two{2.0, 2.9, 0.354, 0.088};
+    const int64_t t = tiles(128, 128), rest = t % 512;
+    return two.call + (double)(t / 512) * two.of(512, kt) + (rest == 0 ? 0.0 : rest <= 256 ? one.of(rest, kt) : two.of(rest, kt));
+}
+
+// Rows per workgroup of the kernels without tiles, 0: tiles.
+int bwd_rows(int64_t M, int64_t N, int64_t K) { return N % kBwdCols ? 0 : bwd_takes_skinny(M, N, K, bwd_tile_us(M, N, K)); }
 
 static int64_t bwd_kpad(int64_t K) { return (K + 15) / 16 * 16; }
 static int64_t bwd_npad(int64_t N) { return (N + kBwdCols - 1) / kBwdCols * kBwdCols; }
@@ -458,7 +474,7 @@ extern "C" int sasq_linear_bwd_input(const void* dy, const void* wt, void* dx, f
         return hipGetLastError() == hipSuccess ? SASQ_OK : SASQ_ERR_LAUNCH;
     }
     if (tuning(SASQ_TUNE_LINEAR_MFMA) == 0 && tuning(SASQ_TUNE_BWD_TILE) == 0)
-        if (const int rows = bwd_takes_skinny(M, N, K, bwd_tile_rounds(M, K))) {
+        if (const int rows = bwd_rows(M, N, K)) {
             launch_bwd_skinny(dy, wt, dx, acc_out, M, N, K, dt, rows, st);
             return hipGetLastError() == hipSuccess ? SASQ_OK : SASQ_ERR_LAUNCH;
         }

@@ -635,28 +635,35 @@ static LinItem bwd_item(const void* dy, const void* wt, void* dx, int64_t M, int
     return it;
 }
 
-// Rows per workgroup, from estimates in us as in block_rows above: 32, small blocks, where small_block has some; at most 64 rows 64 (in
-// row tiles of 16, 32 or 64); more rows 64 or 96 by 64 columns, where that takes 15 % less time than the GEMM's tiles (128 never do).  260 calls of 8 to 1500 rows, contractions and outputs
-// of 256 to 13824: at most 16 rows take 0.41 of their time on the tiles, 17 to 32 0.56, 33 to 64 0.69, more 0.89 (those on row
-// blocks 0.76), and none 2 % more.  us, tiles | here: 1 x 4096 x 4096 25.3 | 8.0, 64 x 256 x 256 4.8 | 3.4, 131 x 2816 x 1344 23.4 |
-// 17.3, 334 x 11072 x 1536 76.2 | 52.5.
-int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_rounds)
+// Rows per workgroup: 32, small blocks, where small_block has some; at most 64 rows 64 (in row tiles of 16, 32 or 64); more rows 64 or
+// 96 by 64 columns (128 never pay).  At most 16 rows are never behind the tiles, which read the weight as often: of 540 calls 15 x 1696 ->
+// 20160 is the worst, 14.3 us on the tiles | 15.4 here.  More rows read dY once in 32 or 64 columns, so that with many columns they end up
+// waiting for it, while one round of 128x128 tiles holds them all: weights that the caches hold, us, 30 x 4480 -> 24768 33.5 | 57.6, 28 x
+// 2400 -> 25216 20.2 | 31.3; that they have not seen, 40 x 4224 -> 17792 42.9 | 50.1, 51 x 960 -> 24960 11.7 | 17.7, but 17 x 9696 -> 9728 79 |
+// 49, 25 x 13248 -> 8896 107 | 77.  And 64 x 256 x 256 4.8 | 3.4, 131 x 2816 x 1344 23.4 | 17.3, 334 x 11072 x 1536 76.2 | 52.5.
+// So both sides are estimated, here from the same 3900 calls as the tiles, on weights that the caches have not seen (rms error 8 to 9 %), and
+// the tiles left from 10 % less time on: the calls then take 0.71 of what the tiles alone take, 2 % more than the best form of each.
+int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_us)
 {
     if (N > kBwdOffsetCols) return 0;                                // the body's lane offsets are 32-bit
     const LinItem it = bwd_item(nullptr, nullptr, nullptr, M, N, K);
-    if (small_block(&it, 1, 2).mt) return 32;
-    if (M <= 32) return K <= INT64_C(1) << 26 ? 64 : 0;     // up to 32 work items a column
-    if (K <= 448) return 0;                                          // fewer than eight runs of weight rows leave XCDs without work
-    static const BlockTime block[2] = {{1.8, 2.1, 0.155}, {1.5, 3.4, 0.205}};
-    const double kt = (double)(N / 32);
-    double best = 0.85 * tile_rounds * (3.7 + 0.396 * kt);
+    const SmallBlock small = small_block(&it, 1, 2);
+    // blocks of 32 x 64 leave most of their eight waves idle under four contraction tiles: 198 x 64 -> 1984 3.6 | 4.1, 65 x 96 -> 4928 4.1 | 4.3
+    if (small.mt && (small.nt < 4 || N >= 128)) return 32;
+    if (M <= 16) return K <= INT64_C(1) << 26 ? 64 : 0;              // up to 32 work items a column
+    if (M > 32 && K <= 448) return 0;                                // fewer than eight runs of weight rows leave XCDs without work
+    struct Form { int rows, block_rows, block_cols; RoundTime time; };
+    static const Form forms[] = {{64, 32, 32, {2.5, 0.05, 0.065, 0.039}}, {64, 64, 64, {1.3, 1.8, 0.131, 0.094}},
+                                 {64, 64, 64, {1.5, 2.5, 0.120, 0.032}}, {96, 96, 64, {1.5, 3.7, 0.160, 0.046}}};
+    const int first = M <= 32 ? 0 : M <= 64 ? 1 : 2, last = M <= 64 ? first : 3;
+    double best = 0.9 * tile_us;
     int rows = 0;
-    for (int f = 0; f < (M <= 64 ? 1 : 2); ++f) {
-        const int r = f == 0 ? 64 : 96;
-        const int64_t blocks = (M + r - 1) / r * ((K + 511) / 512 * 8);
+    for (int i = first; i <= last; ++i) {
+        const Form& f = forms[i];
+        const int64_t blocks = (M + f.block_rows - 1) / f.block_rows * ((K + 8 * f.block_cols - 1) / (8 * f.block_cols) * 8);
         if (blocks >= INT64_C(1) << 22) continue;                    // a launch holds fewer than 2^32 work items
-        const double us = block[f].call + (double)((blocks + 255) / 256) * (block[f].round + block[f].k_tile * kt);
-        if (us < best) { best = us; rows = r; }
+        const double us = f.time.launch(blocks, (double)(N / 32));
+        if (us < best) { best = us; rows = f.rows; }
     }
     return rows;
 }

@@ -13,10 +13,9 @@ def _function(symbol, *argtypes):
 
 
 def bwd_rows(M, N, K):
-    """Rows per workgroup of the backward linear's few-row and row-block kernels, 0: the GEMM's tiles (sasq::bwd_takes_skinny)."""
-    rounds = min(-(-(-(-M // 256) * -(-K // 256)) // 256), -(-(-(-M // 128) * -(-K // 128)) // 512) * 0.71)
+    """Rows per workgroup of the backward linear's few-row and row-block kernels, 0: the GEMM's tiles (sasq::bwd_rows)."""
     i64 = ctypes.c_int64
-    return _function("_ZN4sasq16bwd_takes_skinnyEllld", i64, i64, i64, ctypes.c_double)(M, N, K, rounds)
+    return _function("_ZN4sasq8bwd_rowsElll", i64, i64, i64)(M, N, K)
 
 
 def bwd_tile(M, N, K):

@@ -35,3 +35,13 @@ def test_tiles_where_each_was_measured_fastest():
         assert bwd_tile(*shape) == (128, 256), shape
     for shape in ((537, 128, 6720), (376, 96, 10944), (1647, 96, 19008), (3379, 320, 9280), (2218, 160, 2112), (1834, 352, 2304), (1000, 2304, 2816)):
         assert bwd_tile(*shape) == (128, 128), shape
+
+
+def test_few_rows_and_row_blocks_where_each_was_measured_fastest():
+    """On the tiles: many columns of 17 to 64 rows, short contractions of large small blocks; off them: fewer columns, long contractions."""
+    for shape in ((30, 4480, 24768), (28, 2400, 25216), (40, 4224, 17792), (51, 960, 24960), (53, 160, 16392), (198, 64, 1984),
+                  (643, 2688, 1216), (342, 3200, 3968), (838, 544, 9168)):
+        assert bwd_rows(*shape) == 0, shape
+    for shape, rows in (((1, 4096, 4096), 64), ((16, 4096, 27456), 64), ((17, 9696, 9728), 64), ((25, 13248, 8896), 64), ((64, 256, 256), 32),
+                        ((334, 11072, 1536), 64), ((198, 128, 1984), 32)):
+        assert bwd_rows(*shape) == rows, shape

@@ -8,31 +8,10 @@ import pytest
 
 import oracle
 from paper_2512_14481_amd import workloads as wl
-from tests.dispatch import bwd_tile
+from tests.dispatch import bwd_rows, bwd_tile
 from tests.test_gpu_linear_bwd import check_dx, prepare, problem, run_bwd
 
 pytestmark = pytest.mark.gpu
-
-
-def up(a, b):
-    return -(-a // b)
-
-
-def chosen(M, N, K):
-    """Rows per workgroup the dispatch takes (bwd_takes_skinny), 0: the GEMM's tiles."""
-    if M > 16 and min(up(M, 16 * mt) * up(K, 128 * nt) * 8 for mt, nt in ((1, 1), (2, 1), (2, 2), (2, 4)) if M > 32 or nt == 1) <= 256:
-        return 32
-    if M <= 32:
-        return 64
-    if K <= 448:
-        return 0
-    rounds = min(up(up(M, 256) * up(K, 256), 256), up(up(M, 128) * up(K, 128), 512) * 0.71)
-    best, rows = 0.85 * rounds * (3.7 + 0.396 * (N // 32)), 0
-    for r, (call, per_round, per_tile) in list(zip((64, 96), [(1.8, 2.1, 0.155), (1.5, 3.4, 0.205)]))[:1 if M <= 64 else 2]:
-        us = call + up(up(M, r) * up(K, 512) * 8, 256) * (per_round + per_tile * (N // 32))
-        if us < best:
-            best, rows = us, r
-    return rows
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
@@ -43,9 +22,11 @@ def chosen(M, N, K):
     ((64, 1056, 4096), 32), ((64, 2048, 4200), 32), ((50, 1024, 5003), 32),
     ((65, 32, 2), 32), ((65, 1024, 1000), 32), ((130, 1024, 520), 32), ((129, 1600, 449), 32), ((1024, 96, 256), 32),    # 32 x 32
     ((500, 288, 700), 32), ((70, 1056, 5120), 32), ((222, 544, 1530), 32),                                                # 32 x 64
-    ((70, 1056, 5121), 64), ((300, 1024, 1700), 64), ((1000, 1024, 520), 64), ((2000, 1024, 448), 0), ((380, 4096, 4000), 96)])
+    ((70, 1056, 5121), 64), ((300, 1024, 1700), 64), ((500, 4096, 2000), 64), ((1000, 1024, 520), 0), ((2000, 1024, 448), 0), ((198, 64, 1984), 0),
+    ((18, 544, 27456), 0), ((53, 160, 16392), 0), ((380, 4096, 4000), 0),
+    ((130, 4096, 7500), 96)])
 def test_few_rows_and_row_blocks_match_oracle(shape, want, dtype):
-    assert chosen(*shape) == want
+    assert bwd_rows(*shape) == want
     dyb, wq, s_w = problem(83, shape, dtype, "int8")
     wt, K = prepare(wq, s_w, "int8", dtype)
     ref = oracle.linear_bwd_input(dyb, wq, s_w, "int8", dtype)
@@ -62,7 +43,7 @@ def test_few_rows_and_row_blocks_match_oracle(shape, want, dtype):
 def test_tiles_of_128_by_256(shape, dtype):
     """257 to 512 tiles of 128x128: they go as 128x256, ragged and whole; the 256x256 tiles sum in the same order."""
     M, N, K = shape
-    assert chosen(*shape) == 0 and bwd_tile(*shape) == (128, 256)
+    assert bwd_rows(*shape) == 0 and bwd_tile(*shape) == (128, 256)
     dyb, wq, s_w = problem(84, shape, dtype, "int8")
     wt, K = prepare(wq, s_w, "int8", dtype)
     ref = oracle.linear_bwd_input(dyb, wq, s_w, "int8", dtype)
