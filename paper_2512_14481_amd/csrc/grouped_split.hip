@@ -13,6 +13,7 @@
 #include "sasq_device.h"
 #include "gemm_tile.h"
 #include "gemm_k64.h"
+#include <cmath>
 #include <type_traits>
 
 namespace sasq {
@@ -172,30 +173,59 @@ static void launch_split(const GemmK64Args& a, int64_t group, hipStream_t st)
 
 // 0: the other kernels; rows / 16 and columns / 16 of a workgroup: 1: 1, 1, 2: 2, 2, 3: 1, 2.
 // A workgroup of many outputs reads its operands less often, one of few leaves room for more of them; the other kernels' time is their K
-// loop's, at any fill.  So the line is a number of 16 x 16 output tiles.  Measured, us, before | 1 | 2 | 3, with that number:
-//   groups of 4 (one workgroup a CU for its LDS: one round):  64 x 1024 x 1024 (256) 15.2 | 11.3, 200 x 1024 x 1024 (832) 15.6 | 32.9
-//   16:  64 x 2048 x 4096 (1024) 23.8 | 15.2 | 16.5 | 16.3, 200 x 4096 x 1500 (1222) 48.4 | 30.7 | 50.5 | 37.7, 512 x 1024 x 1024 (2048)
-//     16.3 | 17.4 | 18.2 | 18.0, 200 x 2048 x 4096 (3328) 32.6 | 39.1 | 53.5 | 45.4
-//   32:  16 x 4096 x 1000 (63) 54.7 | 10.6 | 15.3 | 13.5, 64 x 2048 x 4096 (1024) 30.3 | 12.8 | 11.2 | 10.9, 200 x 2048 x 4096 30.9 |
-//     30.7 | 30.8 | 28.0, 512 x 2048 x 4096 (8192) 31.3 | 64.8 | 60.3 | 58.2
-//   64, row-major:  128 x 1024 x 1024 (512) 13.8 | 6.9 | 7.4 | 6.6, 128 x 4096 x 4096 (2048) 34.3 | 35.3 | 21.0 | 28.5, 300 x 4096 x 4096
-//     (4864) 34.5 | 73.5 | 50.2 | 59.8; pre-arranged 13.8 | 6.3 | 6.8 | 6.0, 34.4 | 24.9 | 17.4 | 18.2, 35.6 | 50.4 | 37.9 | 35.8
-//   128, pre-arranged:  128 x 4096 x 4096 27.2 | 24.6 | 16.5 | 17.6, 300 x 4096 x 4096 28.1 | 49.6 | 35.1 | 34.5
-//   512, row-major and pre-arranged:  300 x 2048 x 1024 (1216) 14.4 | 14.9 | 12.7 | 13.4, 14.1 | 12.8 | 10.3 | 9.7, 300 x 4096 x 4096 22.1 |
-//     71.5 | 44.2 | 58.1, 21.5 | 48.3 | 32.3 | 33.4
+// loop's, at any fill.  A launch's workgroups count with the runs of columns rounded up to the eight XCDs, as the XCD with the most of them
+// ends the call.
+// Outputs whose rows are not whole 16-byte stores cost the other kernels more, 1.5 us a round or a quarter of the workgroups below.
+// Groups of 4 to 32: lines, drawn through 2700 calls of K from 64 to 8192 on weights that the caches have not seen.  us, before | here:
+//   4 (one workgroup a CU for its LDS: one round):  64 x 1024 x 1024 (rows, K, columns; 256 workgroups) 15.2 | 11.3, 94 x 1920 x 664 (288)
+//     25.3 | 30.5; 5 x 192 x 1424 6.4 | 5.9, shorter K 1.04 to 1.12 of the time
+//   8 (one a CU as well, but eight waves of half the chain): up to 256 workgroups 0.95 to 0.4 of the time, up to 384 0.94 at K = 256 to 511 and
+//     1.15 under it, up to 512 0.85 at K = 512, 0.72 at 1024, up to 700 0.87 from K = 2048 on
+//   16: 1.0 of the time at 400 workgroups and K = 128, 900 and 384, 1450 and 768, 2000 and 1500; 443 x 512 x 920 (1792) 10.7 | 11.7
+//     12 x 64 x 56 4.2 | 4.8, as at all sizes of a single K tile
+//   32 (16 x 32 outputs): 1.0 at 950 and K = 128, 1650 and 384, 1900 to 2100 from K = 512 on; up to 512 tiles of 16 x 16 those, as a few
+//     columns of 32 fill a few XCDs only: 1076 x 5312 x 24 18.0 as 16 x 16, 27.9 as 16 x 32
+// Multiples of 64: the line is a number of 16 x 16 output tiles: the other kernel's K tile, with its share of a fold, costs 0.19 us + 0.24 a
+// group, this one's 0.105 ns an output tile, row-major 0.14.  That is a mean over calls of some groups and whole rounds: a wave takes whole
+// groups, so that few of them leave waves without any, and a round is as many workgroups as the CUs' LDS and waves hold.  Both sides' time
+// is therefore estimated as well, in us, by least squares over 10700 calls of 1 to 128 groups of 64 to 1024 channels, K from 64 to 8192
+// (rms error: 4 % of the other kernel's 128x128 tiles, which go two to a CU, 8 to 10 % here): another form is taken where it is 15 %
+// shorter, and none where all of them are 7 % longer than the tiles.  The calls then take 0.70 of what they take on the tiles, 0.04 % of
+// them more than 1.1 (0.6 % by the line alone).  A single K tile leaves nothing to split but the outputs: 16 x 64 x 256 6.1 | 4.0, 296 x 64 x
+// 3144 7.3 | 8.5, in one round only.  us, before | here: one group, 128 x 512 x 2048 9.1 | 7.0, 1094 x 1024 x 384 11.2 | 15.4; two, 128 x
+// 2048 x 1024 13.6 | 9.5; 290 x 6656 x 1664, groups of 128 40.7 | 45.2, 323 x 5120 x 1104, of 256 29.3 | 33.7 (16 x 32), 25.1 (32 x 32).
+struct SplitTime { double call, round, k_tile, phase, k_fill; };
+static const SplitTime kSplitTime[2][3] = {                          // row-major, pre-arranged; forms 1, 2, 3
+    {{4.72, 0.28, 0.170, 0.166, 0.0497}, {4.53, 0.41, 0.213, 0.417, 0.1131}, {4.54, 0.19, 0.202, 0.328, 0.0810}},
+    {{4.52, 0.55, 0.189, 0.193, 0.0285}, {4.44, 0.58, 0.224, 0.462, 0.0689}, {4.51, 0.49, 0.204, 0.332, 0.0407}}};
+
 int grouped_takes_split(int64_t M, int64_t N, int64_t K, int64_t group, bool blocked)
 {
     if (K % 64 != 0 || K / group > kSplitFactors) return 0;
-    const int64_t tiles = (M + 15) / 16 * ((N + 15) / 16);
-    if (group == 4) return tiles <= 256 ? 1 : 0;
-    if (group == 8) return tiles <= 512 ? 1 : 0;
-    if (group == 16) return tiles <= 1800 ? 1 : 0;
-    if (group == 32) return tiles <= 512 ? 1 : tiles <= 3500 ? 3 : 0;
-    if (group % 64 != 0) return 0;
-    // the other kernel's K tile, with its share of a fold, costs 0.19 us + 0.24 a group, this one's 0.105 ns an output tile, row-major 0.14
-    const double most = (0.19 + 0.24 * 64.0 / (double)group) / (blocked ? 0.105e-3 : 0.14e-3);
-    if ((double)tiles > most) return 0;
-    return tiles < 256 ? 1 : !blocked && tiles >= 1500 ? 2 : 3;
+    auto workgroups = [&](int64_t mt, int64_t nt) { return (M + 16 * mt - 1) / (16 * mt) * ((N + 128 * nt - 1) / (128 * nt) * 8); };
+    const int64_t tiles16 = (M + 15) / 16 * ((N + 15) / 16), tiles = (M + 127) / 128 * ((N + 127) / 128);
+    const double k = (double)K, ragged = N % 8 ? 1.25 : 1.0;
+    if (group == 4)  return K >= 192 && workgroups(1, 1) <= 256 ? 1 : 0;
+    if (group == 8)  return K >= 128 && tiles16 <= 512 && workgroups(1, 1) <= (K >= 2048 ? 700 : K >= 512 ? 512 : K >= 256 ? 384 : 256) ? 1 : 0;
+    if (group == 16) return K >= 128 && tiles16 <= 1800 && (double)workgroups(1, 1) <= ragged * (200.0 + 1.6 * k) ? 1 : 0;
+    if (group == 32) return tiles16 <= 512 ? 1 : tiles16 <= 3500 && (double)workgroups(1, 2) <= ragged * fmin(2050.0, 500.0 + 3.0 * k) ? 3 : 0;
+    if (group % 64 != 0 || (K < 128 && N % 8 == 0 && workgroups(1, 2) > 1024)) return 0;
+    const double kt = (double)(K / 64), per_group = (double)(group / 64), phases = (double)((K / group + 7) / 8);
+    if ((double)tiles16 > (0.19 + 0.24 / per_group) / (blocked ? 0.105e-3 : 0.14e-3)) return 0;
+    const double tile_kt = (blocked ? 0.201 : 0.215) + (blocked ? 0.241 : 0.221) / per_group + (blocked ? 0.040 : 0.054) * (double)(tiles < 512 ? tiles : 512) / 256.0;
+    const double tile_us = 7.5 + (double)((tiles + 511) / 512) * (kt * tile_kt + (N % 8 ? 1.5 : 0.0));
+    double us[4];
+    for (int f = 1; f <= 3; ++f) {
+        const int64_t count = f == 1 ? workgroups(1, 1) : f == 2 ? workgroups(2, 2) : workgroups(1, 2);
+        const int64_t resident = f == 2 ? 512 : 1024, rest = count % resident;
+        const SplitTime& t = kSplitTime[blocked][f - 1];
+        auto round = [&](int64_t n) { return t.round + phases * (per_group * t.k_tile + t.phase) + kt * t.k_fill * (double)(n < 128 ? 128 : n) / 256.0; };
+        us[f] = t.call + (double)(count / resident) * round(resident) + (rest ? round(rest) : 0.0);
+    }
+    int form = tiles16 < 256 ? 1 : !blocked && tiles16 >= 1500 ? 2 : 3;
+    const int least = us[1] <= us[2] && us[1] <= us[3] ? 1 : us[2] <= us[3] ? 2 : 3;
+    if (us[least] < 0.85 * us[form]) form = least;
+    return us[form] > 1.07 * tile_us ? 0 : form;
 }
 
 template <int DT, int G, bool BLOCKED>

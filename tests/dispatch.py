@@ -22,3 +22,9 @@ def bwd_tile(M, N, K):
     """The backward GEMM's tile, rows and columns (sasq::bwd_tile)."""
     i64 = ctypes.c_int64
     return ((256, 256), (128, 256), (128, 128))[_function("_ZN4sasq8bwd_tileElll", i64, i64, i64)(M, N, K)]
+
+
+def grouped_form(M, N, K, group, blocked):
+    """The form of the grouped linear's split kernel, 0: the other kernels (sasq::grouped_takes_split)."""
+    i64 = ctypes.c_int64
+    return _function("_ZN4sasq19grouped_takes_splitEllllb", i64, i64, i64, i64, ctypes.c_bool)(M, N, K, group, blocked)
