@@ -579,9 +579,17 @@ void launch_linear_skinny(LinBatch& b, sasq_dtype dt, int wmode, bool qx, int a_
 // tiles.  Measured, us, tiles (static_linear_anyk.hip) | here: 8 x 3000, K = 1000 8.1 | 4.1, 16 x 4096, 2500 11.8 | 6.5, 1 x 1000, 4000
 // 14.6 | 5.5, 32 x 4096, 1376 9.1 | 7.1, 64 x 4096, 1376 9.2 | 8.4, 64 x 1000, 4000 15.9 | 12.2; odd K: 1 x 4000, 3001 14.3 | 7.4, 16
 // rows 15.0 | 13.7, 32 rows 14.9 | 15.0, 40 rows 15.0 | 17.4, 64 rows 15.1 | 21.5; 32 x 900, 777 8.3 | 7.6, 64 rows 8.5 | 9.7.
+// Rows a few bytes longer or shorter than whole 128-byte lines begin at about the same place of a line, so that the sixteen rows of a load
+// contend for the same part of the L1 cache: at most 3 bytes and K over 600 the tiles are ahead from 17 rows on, 32 x 540, K = 2561 13.9 |
+// 18.8, 30 x 1732, 1026 8.6 | 10.5 (1024 + 2), 32 x 540, 2569 13.9 | 11.9; 3 bytes from 25 rows, one byte and long rows from 14, 16 x 975, 3841
+// 18.4 | 22.0; 4 bytes from 49, 62 x 3224, 516 6.9 | 7.5.
 bool linear_anyk_takes_skinny(int64_t M, int64_t N, int64_t K)
 {
-    return M <= (K % 4 == 0 ? kSkinnyRows : 32) && K > 64 && N <= INT64_C(1) << 27;
+    const int64_t over = K % 128, off = over < 64 ? over : 128 - over;
+    int64_t most = K % 4 == 0 ? kSkinnyRows : 32;
+    if (K % 4 == 0 && off == 4 && K < 1200) most = 48;
+    if (off <= 3 && K > 600) most = off == 3 ? 24 : off == 1 && K > 1600 ? 13 : 16;
+    return M <= most && K > 64 && N <= INT64_C(1) << 27;
 }
 
 template <int DT>

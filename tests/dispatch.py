@@ -28,3 +28,9 @@ def grouped_form(M, N, K, group, blocked):
     """The form of the grouped linear's split kernel, 0: the other kernels (sasq::grouped_takes_split)."""
     i64 = ctypes.c_int64
     return _function("_ZN4sasq19grouped_takes_splitEllllb", i64, i64, i64, i64, ctypes.c_bool)(M, N, K, group, blocked)
+
+
+def anyk_few_rows(M, N, K):
+    """Whether a static linear with K not a multiple of 64 takes the few-row kernel (sasq::linear_anyk_takes_skinny)."""
+    i64 = ctypes.c_int64
+    return bool(_function("_ZN4sasq24linear_anyk_takes_skinnyElll", i64, i64, i64)(M, N, K) & 1)

@@ -80,14 +80,16 @@ def test_any_contraction_length(mn, k, fmt):
     assert_same_values(yd, ref["y"], dtype, "Y, one factor per row")
 
 
+FEW_K = [65, 79, 100, 127, 200, 333, 516, 1000, 1031, 2095, 2108]
+FEW_ROWS = [(1, 1), (15, 130), (16, 250), (17, 33), (32, 96), (33, 72), (48, 250), (49, 31), (64, 264)]
+FEW_ROWS_WIDE = [(1, 8200), (16, 8195), (32, 8200), (64, 8189)]             # wide workgroups
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
-@pytest.mark.parametrize("mn", [(1, 1), (1, 8200), (15, 130), (16, 250), (16, 8195), (17, 33), (32, 96), (32, 8200), (33, 72), (48, 250), (49, 31), (64, 264), (64, 8189)])
-@pytest.mark.parametrize("k", [65, 79, 100, 127, 200, 333, 516, 1000, 1031, 2095, 2108])
+@pytest.mark.parametrize("mn,k", [(mn, k) for k in FEW_K for mn in FEW_ROWS] + [(mn, k) for k in (79, 200, 1031) for mn in FEW_ROWS_WIDE])
 def test_few_rows(mn, k, dtype):
     """At most 64 rows: K over the waves, whole K tiles and the rest of a row; quantized in the kernel (at most 16 rows, or few codes)
     and before it; the tiled kernel, asked for by a knob, gives the same."""
-    if mn[1] > 8000 and k not in (79, 200, 1031):
-        pytest.skip("the narrow outputs cover the other lengths")
     (M, N) = mn
     xb, wq, s_w, bias, s = problem(92, (M, N, k), "int8", dtype)
     wd, swd, x, bd = torch.from_numpy(wq).cuda(), torch.from_numpy(s_w).cuda(), to_dev(xb, dtype), torch.from_numpy(bias).cuda()
