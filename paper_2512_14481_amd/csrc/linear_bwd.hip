@@ -369,21 +369,24 @@ static bool bwd_small_tiles(int64_t M, int64_t K)
 // The tile of the 16x16x32 kernel: 0: 256x256, 1: 128x256, 2: 128x128, by the rounds of a 256x256 tile's time that a launch takes.  A
 // 128x256 tile alone on its CU takes 0.65 of it (several rounds of them 0.68 each), a 128x128 tile 0.44, two of them on a CU 0.8: of 257
 // to 512 tiles of 128x128 some CUs hold two, and as 128x256 they all run at once.  But the one wave a SIMD of a 128x256 tile has nothing
-// beside it while it fills its pipeline and stores, and under 12 contraction tiles that is most of it: there 128x128 tiles are the better ones
-// by the old measure already, 0.71 for every two a CU.  Measured, us, M x N -> K,
-// 256x256 | 128x256 | 128x128: 1834 x 2304 -> 2304 (270 tiles of 128x128) 42.6 | 28.0 | 32.6, 900 x 5504 -> 4992 (312) 92 | 63 | 85, 2048 x
-// 4096 -> 2304 (512) 48 | 35 | 40, 1000 x 2304 -> 2816 (176) 42.5 | 27.3 | 19.8, 3000 x 2304 -> 3328 (624) 45.4 | 57.9 | 52.1; several
-// rounds: 4096 x 2304 -> 5120 95.7 | 92.0 | 94.7, 2920 x 3904 -> 8448 175 | 204 | 216, 1926 x 4288 -> 11008 183 | 207 | 232; short: 537 x
-// 128 -> 6720 10.7 | 7.4 | 6.1, 1647 x 96 -> 19008 28.5 | 24.5 | 19.3, means of 21 to 31 calls of 8 to 11 contraction tiles - | 9.8 | 9.9, of 12 to
-// 19 - | 12.2 | 12.4.
+// beside it while it fills its pipeline, stores, or waits for weights that the caches have not seen, as those of a training step: it pays from
+// about 390 tiles of 128x128 and 32 contraction tiles on.  128x256 | 128x128, on such weights and on ones that the caches hold, part of the
+// other's time: 257 to 350 tiles 0.95 to 1.04 and 0.82 to 1.02, 350 to 512 0.87 to 0.97 and 0.81 to 0.94, under 32 contraction tiles 0.97 to
+// 1.04 and 1.01.  us, M x N -> K, 256x256 | 128x256 | 128x128, weights not in the caches: 409 x 8576 -> 15808 (496 tiles of 128x128) 189 |
+// 129 | 184, 674 x 6016 -> 10560 (498) 138 | 91 | 131, 2176 x 4000 -> 3136 (425) 92 | 78 | 74, 1144 x 1568 -> 4928 (351) 43 | 34 | 30; a
+// layer's four in a training step, 128x256 | 128x128, 1023 x 4416 -> 4416 (280) 320 | 280, 1400 rows (385) 1.11 of the time, 1500 rows (420) 1.02, 2000
+// x 3904 (496) 0.86, 3500 x 1920 (420) 0.81, 1100 x 5120 (360) 0.95.  In the caches: 900 x 5504 -> 4992 (312) 92 | 63 | 85, 2048 x
+// 4096 -> 2304 (288) 48 | 35 | 40, 1000 x 2304 -> 2816 (176) 42.5 | 27.3 | 19.8, 3000 x 2304 -> 3328 (624) 45.4 | 57.9 | 52.1; several rounds: 4096 x
+// 2304 -> 5120 95.7 | 92.0 | 94.7, 2920 x 3904 -> 8448 175 | 204 | 216; short: 537 x 128 -> 6720 10.7 | 7.4 | 6.1, 1647 x 96 -> 19008 28.5 | 24.5 | 19.3.
 int bwd_tile(int64_t M, int64_t N, int64_t K)
 {
     if (const int t = tuning(SASQ_TUNE_BWD_TILE)) return t == 1 ? 0 : 2;
+    const double c0 = rounds256(M, K);
+    if (N < 32 * kBwdCols) return rounds128(M, K) < c0 ? 2 : 0;
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((K + bn - 1) / bn); };
     const int64_t t128 = tiles(128, 128), rest = t128 % 512, r1 = (tiles(128, 256) + 255) / 256;
-    const double c0 = rounds256(M, K), c2 = 0.8 * (double)(t128 / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 0.44 : 0.8);
-    const double c1 = r1 == 1 ? 0.65 : 0.68 * (double)r1;
-    if (N < 12 * kBwdCols) return rounds128(M, K) < c0 ? 2 : 0;
+    const double c2 = 0.8 * (double)(t128 / 512) + (rest == 0 ? 0.0 : rest <= 256 ? 0.44 : 0.8);
+    const double c1 = r1 > 1 ? 0.68 * (double)r1 : t128 >= 390 ? 0.65 : c2;
     return c0 <= c1 && c0 <= c2 ? 0 : c1 < c2 ? 1 : 2;
 }
 // The time of those tiles, us, for the choice between them and the few-row and row-block kernels: least squares over 3900 calls of 1 to 4000

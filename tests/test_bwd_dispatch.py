@@ -29,11 +29,12 @@ def test_no_call_wraps_its_offsets():
 
 
 def test_tiles_where_each_was_measured_fastest():
-    for shape in ((2920, 3904, 8448), (1926, 4288, 11008), (3000, 2304, 3328)):
+    for shape in ((2920, 3904, 8448), (1926, 4288, 11008), (3000, 2304, 3328), (4096, 4096, 11008)):
         assert bwd_tile(*shape) == (256, 256), shape
-    for shape in ((1834, 2304, 2304), (900, 5504, 4992), (2048, 4096, 2304), (1834, 384, 2304)):
+    for shape in ((409, 8576, 15808), (674, 6016, 10560), (2439, 10272, 2753), (2000, 3904, 3904), (3500, 1920, 1920)):
         assert bwd_tile(*shape) == (128, 256), shape
-    for shape in ((537, 128, 6720), (376, 96, 10944), (1647, 96, 19008), (3379, 320, 9280), (2218, 160, 2112), (1834, 352, 2304), (1000, 2304, 2816)):
+    for shape in ((537, 128, 6720), (376, 96, 10944), (1647, 96, 19008), (3379, 320, 9280), (2218, 160, 2112), (1000, 2304, 2816),
+                  (1023, 4416, 4416), (895, 4800, 4800), (2429, 8640, 2176), (1007, 12928, 4224), (1400, 4416, 4416), (1144, 1568, 4928)):
         assert bwd_tile(*shape) == (128, 128), shape
 
 
