@@ -40,15 +40,15 @@ template <int MT, int NT, int NW> constexpr int skinny_rows_per_phase() { return
 // hold 16 rows x 32 numbers, the sums are fp32 (the waves' parts added in their order) and go out rounded, without factors.
 // ANYK: K not a multiple of 64, few rows of row-major int8; the activation codes are row-major too.  Rows then start at any byte, and
 // the last wave multiplies the rest of the row, with zeros behind, after its whole K tiles.
-template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool FLT = false, bool ANYK = false>
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool EVEN, bool FLT = false, bool ANYK = false>
 __device__ __forceinline__
 void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __restrict__ acc_out, char* lds)
 {
     using S = Store16<DT>;
-    constexpr bool I4 = WMODE == 3, ROWMAJOR = WMODE == 0, BLOCKS = !ONCE || MT > 4;
+    constexpr bool I4 = WMODE == 3, ROWMAJOR = WMODE == 0;
     static_assert(!I4 || NT % 2 == 0, "int4 blocks hold 32 weight rows");
     static_assert(!FLT || (WMODE == 2 && !QX), "float contraction: weight blocks, no codes");
-    static_assert(!ANYK || (ROWMAJOR && !BLOCKS), "rows at any byte: plain loads");
+    static_assert(!ANYK || (ROWMAJOR && !EVEN), "rows at any byte: plain loads");
     using AccT = std::conditional_t<FLT, f32x4, i32x4>;
     constexpr int WL = I4 ? NT / 2 : NT;               // 128-bit weight loads per lane and K tile
     const int lane = threadIdx.x & 63;
@@ -100,14 +100,14 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
     };
     auto load = [&](Frag& f, int t) {
         int bytes = -1;                                 // in so many words: from a select the compiler builds the buffers in vector registers
-        if (BLOCKS) asm("s_cmp_lt_i32 %1, %2\n\ts_cselect_b32 %0, -1, 0" : "=s"(bytes) : "s"(t), "s"(count) : "scc");
+        if (EVEN) asm("s_cmp_lt_i32 %1, %2\n\ts_cselect_b32 %0, -1, 0" : "=s"(bytes) : "s"(t), "s"(count) : "scc");
         const __amdgpu_buffer_rsrc_t wrsrc = operand_rsrc(wbase, bytes), xrsrc = operand_rsrc(xbase, bytes);
         // ONCE: no other workgroup reads these weights.  Where row blocks share them they have to stay in L2 (333 x 4096 x 4096
         // 18.8 us non-temporal, 16.8 cached), and row-major a K tile is half a 128-byte line of each row, the other half the next
         // K tile's (the 7B layer below: 54 us and 51).
         constexpr int kNonTemporal = 2;
         // Few row-major rows: plain loads (7B layer, 8 rows 50.6 us through buffers, 49.8 so; 12 x 2368 x 28544's MLP 72.9, 70.0).
-        constexpr bool kPlain = ROWMAJOR && !BLOCKS;
+        constexpr bool kPlain = ROWMAJOR && !EVEN;
 #pragma unroll
         for (int j = 0; j < WL; ++j)
             if constexpr (ANYK)        f.w[j] = load_piece<u32x4>(reinterpret_cast<const uint8_t*>(wbase) + (int64_t)t * kWStep + woff[j]);
@@ -197,7 +197,7 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
         }
     }
     Frag ring[D];
-    if constexpr (BLOCKS) {
+    if constexpr (EVEN) {
         // D K tiles in flight.  Loads and products carry no conditions (tiles past the last are zeros), so that the wait in front of
         // a product counts exactly the loads behind its own; the barriers keep the scheduler from moving all products of a round in
         // front of all its loads, which exposed the whole latency once a round.
@@ -302,7 +302,7 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
     }
 }
 
-template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool ANYK>
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool EVEN, bool ANYK>
 __global__ __launch_bounds__(64 * NW)
 void skinny_kernel(const LinBatch b, int a_bits, int32_t* __restrict__ acc_out)
 {
@@ -312,10 +312,10 @@ void skinny_kernel(const LinBatch b, int a_bits, int32_t* __restrict__ acc_out)
     const int id = (int)blockIdx.x - b.first_block[k], octet = id >> 3, tiles_m = b.it[k].tiles_m;
     const int mblk = octet % tiles_m, nblk = octet / tiles_m * 8 + (id & 7);
     if (nblk >= b.it[k].tiles_n) return;
-    skinny_body<DT, WMODE, MT, NT, NW, D, QX, ONCE, false, ANYK>(b.it[k], mblk, nblk, a_bits, acc_out, lds);
+    skinny_body<DT, WMODE, MT, NT, NW, D, QX, ONCE, EVEN, false, ANYK>(b.it[k], mblk, nblk, a_bits, acc_out, lds);
 }
 
-template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool ANYK = false>
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool EVEN, bool ANYK = false>
 static void launch_one(LinBatch& b, int a_bits, int32_t* acc_out, hipStream_t st)
 {
     b.first_block[0] = 0;
@@ -329,7 +329,7 @@ static void launch_one(LinBatch& b, int a_bits, int32_t* acc_out, hipStream_t st
         }
         b.first_block[i + 1] = b.first_block[i] + blocks;
     }
-    skinny_kernel<DT, WMODE, MT, NT, NW, D, QX, ONCE, ANYK><<<b.first_block[b.count], 64 * NW, 0, st>>>(b, a_bits, acc_out);
+    skinny_kernel<DT, WMODE, MT, NT, NW, D, QX, ONCE, EVEN, ANYK><<<b.first_block[b.count], 64 * NW, 0, st>>>(b, a_bits, acc_out);
 }
 
 // Wide or narrow workgroups: the narrow form (16 weight rows, K over eight waves) gives more workgroups for the same weights, the
@@ -343,19 +343,19 @@ static void launch_mt(LinBatch& b, int64_t tiles16, int a_bits, int32_t* acc_out
 {
     const bool wide = tiles16 >= 512;
     if constexpr (ANYK) {                              // as row-major int8 below
-        if (!wide)                 launch_one<DT, WMODE, MT, 1, 8, 4, QX, true, true>(b, a_bits, acc_out, st);
-        else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, true>(b, a_bits, acc_out, st);
-        else                       launch_one<DT, WMODE, MT, 2, 4, 4, QX, true, true>(b, a_bits, acc_out, st);
+        if (!wide)                 launch_one<DT, WMODE, MT, 1, 8, 4, QX, true, false, true>(b, a_bits, acc_out, st);
+        else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, false, true>(b, a_bits, acc_out, st);
+        else                       launch_one<DT, WMODE, MT, 2, 4, 4, QX, true, false, true>(b, a_bits, acc_out, st);
     } else
     if constexpr (WMODE == 3) {                        // int4: half the bytes per tile, a block is two tiles
-        if (!wide)             launch_one<DT, WMODE, MT, 2, 8, 2, QX, true>(b, a_bits, acc_out, st);
-        else if constexpr (QX) launch_one<DT, WMODE, MT, 4, 8, 2, QX, true>(b, a_bits, acc_out, st);
-        else                   launch_one<DT, WMODE, MT, 4, 4, 2, QX, true>(b, a_bits, acc_out, st);
+        if (!wide)             launch_one<DT, WMODE, MT, 2, 8, 2, QX, true, false>(b, a_bits, acc_out, st);
+        else if constexpr (QX) launch_one<DT, WMODE, MT, 4, 8, 2, QX, true, false>(b, a_bits, acc_out, st);
+        else                   launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, false>(b, a_bits, acc_out, st);
     } else {
-        if (!wide)               launch_one<DT, WMODE, MT, 1, 8, 4, QX, true>(b, a_bits, acc_out, st);
-        else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, true>(b, a_bits, acc_out, st);
-        else if constexpr (WMODE == 0) launch_one<DT, WMODE, MT, 2, 4, 4, QX, true>(b, a_bits, acc_out, st);
-        else                     launch_one<DT, WMODE, MT, 2, 8, 3, QX, true>(b, a_bits, acc_out, st);
+        if (!wide)               launch_one<DT, WMODE, MT, 1, 8, 4, QX, true, false>(b, a_bits, acc_out, st);
+        else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, false>(b, a_bits, acc_out, st);
+        else if constexpr (WMODE == 0) launch_one<DT, WMODE, MT, 2, 4, 4, QX, true, false>(b, a_bits, acc_out, st);
+        else                     launch_one<DT, WMODE, MT, 2, 8, 3, QX, true, false>(b, a_bits, acc_out, st);
     }
 }
 
@@ -397,6 +397,10 @@ static bool tiles_are_better(const LinBatch& b, int rows, int wmode)
     return single ? fill > (one_round ? 0.5 : int4 ? 0.8 : 0.7) : row_major && fill > (one_round ? 0.5 : 0.8);
 }
 
+// They take the loop that loads only K tiles there are: a wave has few of them, and the loop without conditions (EVEN) requests tiles past
+// the last and multiplies their zeros.  Parts of that loop's time, weights not in the caches | in them: forward 16 x 16 0.94 | 0.93, 32 x 16
+// 0.96 | 0.95, 32 x 32 0.92 | 0.91, 32 x 64 0.94 | 0.92, row-major 0.85 to 0.91, backward 0.94 | 0.92, 0.91 | 0.88, 0.87 | 0.85, 0.90 | 0.87.
+// The weights keep the ordinary cache policy: non-temporal, another 0.95 | 1.13.
 // Small blocks, for more than 16 rows: the smallest of 16 x 16 outputs (int4 16 x 32), 32 x 16 (32 x 32), 32 x 32 and 32 x 64 that
 // the call has no more than a round of, one a CU.  All run at once, so the call takes as long as one of them, and the smallest are the
 // shortest; from a second round on the larger ones of the other rules read less.  The runs of columns go round the eight XCDs, so a
@@ -527,11 +531,11 @@ bool linear_quantizes_in_kernel(const LinBatch& b, int wmode, bool any_k)
 template <int DT, int WMODE, bool QX>
 static void launch_small(LinBatch& b, SmallBlock f, int a_bits, int32_t* acc_out, hipStream_t st)
 {
-    if (f.nt == 4)                launch_one<DT, WMODE, 2, 4, 8, 3, QX, false>(b, a_bits, acc_out, st);
-    else if (f.mt == 2 && f.nt == 2) launch_one<DT, WMODE, 2, 2, 8, 4, QX, false>(b, a_bits, acc_out, st);
-    else if constexpr (WMODE == 3)   launch_one<DT, WMODE, 1, 2, 8, 4, QX, false>(b, a_bits, acc_out, st);
-    else if (f.mt == 2)              launch_one<DT, WMODE, 2, 1, 8, 3, QX, false>(b, a_bits, acc_out, st);
-    else                             launch_one<DT, WMODE, 1, 1, 8, 4, QX, false>(b, a_bits, acc_out, st);
+    if (f.nt == 4)                launch_one<DT, WMODE, 2, 4, 8, 2, QX, false, false>(b, a_bits, acc_out, st);
+    else if (f.mt == 2 && f.nt == 2) launch_one<DT, WMODE, 2, 2, 8, 3, QX, false, false>(b, a_bits, acc_out, st);
+    else if constexpr (WMODE == 3)   launch_one<DT, WMODE, 1, 2, 8, 3, QX, false, false>(b, a_bits, acc_out, st);
+    else if (f.mt == 2)              launch_one<DT, WMODE, 2, 1, 8, 3, QX, false, false>(b, a_bits, acc_out, st);
+    else                             launch_one<DT, WMODE, 1, 1, 8, 3, QX, false, false>(b, a_bits, acc_out, st);
 }
 
 template <int DT, int WMODE>
@@ -549,13 +553,13 @@ static void launch_wmode(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, hip
         else    launch_small<DT, WMODE, false>(b, small, a_bits, acc_out, st);
     } else if (rows > kSkinnyRows) {
         const int block = block_rows(b, WMODE);
-        if (block == 64)                     launch_one<DT, WMODE, 4, 4, 8, 2, false, false>(b, a_bits, acc_out, st);
-        else if (block == 96 && rows > 96)   launch_one<DT, WMODE, 6, 4, 8, 2, false, false>(b, a_bits, acc_out, st);
-        else if (block == 96)                launch_one<DT, WMODE, 6, 4, 8, 2, false, true>(b, a_bits, acc_out, st);
-        else if (rows > 128)                 launch_one<DT, WMODE, 8, 4, 8, 2, false, false>(b, a_bits, acc_out, st);
-        else                                 launch_one<DT, WMODE, 8, 4, 8, 2, false, true>(b, a_bits, acc_out, st);
-    } else if (qx && rows > 32)               launch_one<DT, WMODE, 4, WMODE == 3 ? 2 : 1, 8, 2, true, true>(b, a_bits, acc_out, st);
-    else if (qx && rows > kSkinnyQuantRows) launch_one<DT, WMODE, 2, WMODE == 3 ? 2 : 1, 8, 2, true, true>(b, a_bits, acc_out, st);
+        if (block == 64)                     launch_one<DT, WMODE, 4, 4, 8, 2, false, false, true>(b, a_bits, acc_out, st);
+        else if (block == 96 && rows > 96)   launch_one<DT, WMODE, 6, 4, 8, 2, false, false, true>(b, a_bits, acc_out, st);
+        else if (block == 96)                launch_one<DT, WMODE, 6, 4, 8, 2, false, true, true>(b, a_bits, acc_out, st);
+        else if (rows > 128)                 launch_one<DT, WMODE, 8, 4, 8, 2, false, false, true>(b, a_bits, acc_out, st);
+        else                                 launch_one<DT, WMODE, 8, 4, 8, 2, false, true, true>(b, a_bits, acc_out, st);
+    } else if (qx && rows > 32)               launch_one<DT, WMODE, 4, WMODE == 3 ? 2 : 1, 8, 2, true, true, false>(b, a_bits, acc_out, st);
+    else if (qx && rows > kSkinnyQuantRows) launch_one<DT, WMODE, 2, WMODE == 3 ? 2 : 1, 8, 2, true, true, false>(b, a_bits, acc_out, st);
     else if (qx)       launch_mt<DT, WMODE, 1, true>(b, tiles16, a_bits, acc_out, st);
     else if (rows <= 32) launch_mt<DT, WMODE, 2, false>(b, tiles16, a_bits, acc_out, st);
     else if (rows <= 48) launch_mt<DT, WMODE, 3, false>(b, tiles16, a_bits, acc_out, st);
@@ -597,8 +601,8 @@ static void launch_anyk_dt(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, h
 {
     const int rows = b.it[0].M;
     const int64_t tiles16 = ((int64_t)b.it[0].N + 15) / 16;
-    if (qx && rows > 32)                    launch_one<DT, 0, 4, 1, 8, 2, true, true, true>(b, a_bits, acc_out, st);
-    else if (qx && rows > kSkinnyQuantRows) launch_one<DT, 0, 2, 1, 8, 2, true, true, true>(b, a_bits, acc_out, st);
+    if (qx && rows > 32)                    launch_one<DT, 0, 4, 1, 8, 2, true, true, false, true>(b, a_bits, acc_out, st);
+    else if (qx && rows > kSkinnyQuantRows) launch_one<DT, 0, 2, 1, 8, 2, true, true, false, true>(b, a_bits, acc_out, st);
     else if (qx)         launch_mt<DT, 0, 1, true, true>(b, tiles16, a_bits, acc_out, st);
     else if (rows <= 32) launch_mt<DT, 0, 2, false, true>(b, tiles16, a_bits, acc_out, st);
     else if (rows <= 48) launch_mt<DT, 0, 3, false, true>(b, tiles16, a_bits, acc_out, st);
@@ -612,7 +616,7 @@ void launch_linear_anyk_skinny(LinBatch& b, sasq_dtype dt, bool qx, int a_bits, 
 }
 
 // ---- the backward GEMM ----------------------------------------------------------------------
-template <int DT, int MT, int NT, int NW, int D, bool ONCE>
+template <int DT, int MT, int NT, int NW, int D, bool ONCE, bool EVEN>
 __global__ __launch_bounds__(64 * NW)
 void bwd_skinny_kernel(const LinItem it, float* __restrict__ acc_out)
 {
@@ -620,15 +624,15 @@ void bwd_skinny_kernel(const LinItem it, float* __restrict__ acc_out)
     const int id = (int)blockIdx.x, octet = id >> 3;                 // as in skinny_kernel
     const int mblk = octet % it.tiles_m, nblk = octet / it.tiles_m * 8 + (id & 7);
     if (nblk >= it.tiles_n) return;
-    skinny_body<DT, 2, MT, NT, NW, D, false, ONCE, true>(it, mblk, nblk, 8, reinterpret_cast<int32_t*>(acc_out), lds);
+    skinny_body<DT, 2, MT, NT, NW, D, false, ONCE, EVEN, true>(it, mblk, nblk, 8, reinterpret_cast<int32_t*>(acc_out), lds);
 }
 
-template <int DT, int MT, int NT, int NW, int D, bool ONCE>
+template <int DT, int MT, int NT, int NW, int D, bool ONCE, bool EVEN>
 static void launch_bwd_one(LinItem& it, float* acc_out, hipStream_t st)
 {
     it.tiles_m = (it.M + 16 * MT - 1) / (16 * MT);
     it.tiles_n = (it.N + 16 * NT - 1) / (16 * NT);
-    bwd_skinny_kernel<DT, MT, NT, NW, D, ONCE><<<(it.tiles_n + 7) / 8 * 8 * it.tiles_m, 64 * NW, 0, st>>>(it, acc_out);
+    bwd_skinny_kernel<DT, MT, NT, NW, D, ONCE, EVEN><<<(it.tiles_n + 7) / 8 * 8 * it.tiles_m, 64 * NW, 0, st>>>(it, acc_out);
 }
 
 static LinItem bwd_item(const void* dy, const void* wt, void* dx, int64_t M, int64_t N, int64_t K)
@@ -682,20 +686,20 @@ static void launch_bwd_dt(LinItem& it, float* acc_out, int rows, hipStream_t st)
 {
     if (rows == 32) {
         const SmallBlock f = small_block(&it, 1, 2);
-        if (f.nt == 4)      launch_bwd_one<DT, 2, 4, 8, 3, false>(it, acc_out, st);
-        else if (f.nt == 2) launch_bwd_one<DT, 2, 2, 8, 4, false>(it, acc_out, st);
-        else if (f.mt == 2) launch_bwd_one<DT, 2, 1, 8, 4, false>(it, acc_out, st);
-        else                launch_bwd_one<DT, 1, 1, 8, 4, false>(it, acc_out, st);
+        if (f.nt == 4)      launch_bwd_one<DT, 2, 4, 8, 2, false, false>(it, acc_out, st);
+        else if (f.nt == 2) launch_bwd_one<DT, 2, 2, 8, 3, false, false>(it, acc_out, st);
+        else if (f.mt == 2) launch_bwd_one<DT, 2, 1, 8, 3, false, false>(it, acc_out, st);
+        else                launch_bwd_one<DT, 1, 1, 8, 3, false, false>(it, acc_out, st);
     } else if (it.M > 64) {
-        if (rows == 64) launch_bwd_one<DT, 4, 4, 8, 2, false>(it, acc_out, st);
-        else            launch_bwd_one<DT, 6, 4, 8, 2, false>(it, acc_out, st);
+        if (rows == 64) launch_bwd_one<DT, 4, 4, 8, 2, false, true>(it, acc_out, st);
+        else            launch_bwd_one<DT, 6, 4, 8, 2, false, true>(it, acc_out, st);
     } else if (it.M <= 16) {
-        if (it.N > 4096) launch_bwd_one<DT, 1, 2, 8, 3, true>(it, acc_out, st);
-        else             launch_bwd_one<DT, 1, 1, 8, 4, true>(it, acc_out, st);
+        if (it.N > 4096) launch_bwd_one<DT, 1, 2, 8, 3, true, false>(it, acc_out, st);
+        else             launch_bwd_one<DT, 1, 1, 8, 4, true, false>(it, acc_out, st);
     } else if (it.M <= 32) {
-        launch_bwd_one<DT, 2, 2, 8, 3, true>(it, acc_out, st);
+        launch_bwd_one<DT, 2, 2, 8, 3, true, false>(it, acc_out, st);
     } else {
-        launch_bwd_one<DT, 4, 4, 8, 2, true>(it, acc_out, st);
+        launch_bwd_one<DT, 4, 4, 8, 2, true, false>(it, acc_out, st);
     }
 }
 
