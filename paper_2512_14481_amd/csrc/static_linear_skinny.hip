@@ -436,14 +436,16 @@ static SmallBlock small_block(const LinItem* items, int count, int wmode)
     return {0, 0};
 }
 
-// Rows per workgroup (64 weight rows each, K over eight waves) for more than kSkinnyRows rows, 0: the GEMM's tiles are better.
+// Rows per workgroup (64 weight rows each, K over eight waves or four) for more than kSkinnyRows rows, 0: the GEMM's tiles are better.
 // A call of few tiles leaves CUs idle or waiting for one long K loop; cut finer every CU has operands in flight, until the operands'
 // L2 reads (the smaller the block, the more of them) cost more than that.  Neither side's time follows from one size, so both are
 // estimated, in us, from what they do: workgroups go in rounds (of 256; row blocks one workgroup a CU), a round costs what a
 // workgroup takes to start and end, and the operands of its K tiles.  The constants are least squares over 550 calls of 65 to 1200
 // rows, K and N from 1024 to 28672, single projections and layers, of times from 8 to 500 us: rms error 7 to 11 %.  Over those calls
 // the choice costs 0.8 % against the best of the four each time, and the calls take 0.87 of what they took with lines drawn by hand.
-// Row blocks are taken from 8 % less time on: the estimates are no better than that.  us, GEMM tiles | 64 | 96 | 128 rows:
+// Row blocks are taken from 10 % less time on: the estimates are no better than that.  Blocks of 64 rows take four waves instead of eight from
+// a second round on: their sums then meet in 64 KB of LDS and two of them share a CU, 0.91 of the time at 257 to 768 blocks, 0.87 to 1536, 0.84
+// beyond, weights in the caches or not (eight waves are 1.00 to 1.04 of four in a single round).  us, GEMM tiles | 64 | 96 | 128 rows:
 //   4096 x 4096: 128 rows 26.2 | 12.9 | 14.8 | 20.4, 256 rows 26.4 | 13.7 | 15.5 | 17.3, 333 rows 26.7 | 20.3 | 16.0 | 17.3, 512 rows
 //   27.1 | 21.3 | 24.3 | 18.9, 768 rows 27.9 | 29.7 | 27.1 | 30.4, 1000 rows 28.8 | 40.5 | 39.1 | 34.6; 8192 x 8192, 200 rows 56.5 |
 //   37.1 | 42.8 | 33.5; 7B layer, 96 rows 98.6 | 68.3 | 60.4 | 61.8, 192 rows 113 | 104 | 92.7 | 94.3, 333 rows tiles
@@ -453,6 +455,14 @@ static const BlockTime kBlockTime[3][3] = {                          // row-majo
     {{4.6, 2.9, 0.107}, {5.1, 3.9, 0.137}, {5.3, 4.7, 0.161}},
     {{4.6, 2.8, 0.076}, {4.8, 4.1, 0.100}, {4.9, 4.9, 0.121}}};
 static const BlockTime kTileTime[3] = {{1.0, 12.0, 0.72}, {1.0, 13.0, 0.54}, {1.0, 16.0, 0.49}};
+
+// Row blocks of r rows, the runs of columns filled up to the eight XCDs.
+static int64_t blocks_of(const LinBatch& b, int r)
+{
+    int64_t blocks = 0;
+    for (int i = 0; i < b.count; ++i) blocks += ((int64_t)b.it[i].M + r - 1) / r * (((int64_t)b.it[i].N + 511) / 512 * 8);
+    return blocks;
+}
 
 static int block_rows(const LinBatch& b, int wmode)
 {
@@ -478,21 +488,18 @@ static int block_rows(const LinBatch& b, int wmode)
         const double rounds = (double)((tiles + 255) / 256), span = work / 256.0 * std::sqrt(rounds * 256.0 / (double)tiles);
         best = tt.call + (ids >= kHalvesFrom && ids <= 128 ? 0.7 : 1.0) * (rounds * tt.round + tt.k_tile * (span > k_max ? span : k_max));
     }
-    best *= 0.92;
+    best *= 0.9;
     int rows = 0;
     for (int f = 0; f < 3; ++f) {
         const int r = f == 0 ? 64 : f == 1 ? 96 : 128;
-        int64_t blocks = 0;
+        const int64_t blocks = blocks_of(b, r);
         double block_work = 0.0;
-        for (int i = 0; i < b.count; ++i) {
-            const int64_t n = ((int64_t)b.it[i].M + r - 1) / r * (((int64_t)b.it[i].N + 511) / 512 * 8);
-            blocks += n;
-            block_work += (double)n * (b.it[i].K / 64);
-        }
+        for (int i = 0; i < b.count; ++i)
+            block_work += (double)(((int64_t)b.it[i].M + r - 1) / r * (((int64_t)b.it[i].N + 511) / 512 * 8)) * (b.it[i].K / 64);
         if (blocks >= INT64_C(1) << 22) continue;                    // a launch holds fewer than 2^32 work items
         const double rounds = (double)((blocks + 255) / 256), span = block_work / (double)blocks * rounds;
         const BlockTime& bt = kBlockTime[format][f];
-        const double us = bt.call + rounds * bt.round + bt.k_tile * (span > k_max ? span : k_max);
+        const double us = bt.call + (r == 64 && blocks > 256 ? 0.87 : 1.0) * (rounds * bt.round + bt.k_tile * (span > k_max ? span : k_max));
         if (us < best) { best = us; rows = r; }
     }
     return rows;
@@ -553,7 +560,8 @@ static void launch_wmode(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, hip
         else    launch_small<DT, WMODE, false>(b, small, a_bits, acc_out, st);
     } else if (rows > kSkinnyRows) {
         const int block = block_rows(b, WMODE);
-        if (block == 64)                     launch_one<DT, WMODE, 4, 4, 8, 2, false, false, true>(b, a_bits, acc_out, st);
+        if (block == 64 && blocks_of(b, 64) > 256) launch_one<DT, WMODE, 4, 4, 4, 2, false, false, true>(b, a_bits, acc_out, st);
+        else if (block == 64)                launch_one<DT, WMODE, 4, 4, 8, 2, false, false, true>(b, a_bits, acc_out, st);
         else if (block == 96 && rows > 96)   launch_one<DT, WMODE, 6, 4, 8, 2, false, false, true>(b, a_bits, acc_out, st);
         else if (block == 96)                launch_one<DT, WMODE, 6, 4, 8, 2, false, true, true>(b, a_bits, acc_out, st);
         else if (rows > 128)                 launch_one<DT, WMODE, 8, 4, 8, 2, false, false, true>(b, a_bits, acc_out, st);

@@ -48,11 +48,11 @@ def chosen(items, layout):
         rounds = up(sum(tiles), 256)
         halves = 32 <= sum(up(t, 8) * 8 for t in tiles) <= 128
         best = call + (0.7 if halves else 1.0) * (rounds * per_round + per_tile * max(k_max, work / 256 * math.sqrt(rounds * 256 / sum(tiles))))
-    best, rows = 0.92 * best, 0
+    best, rows = 0.9 * best, 0
     for r, (call, per_round, per_tile) in zip((64, 96, 128), BLOCK[layout]):
         blocks = [up(m, r) * up(n, 512) * 8 for m, n, _ in items]
         work, rounds = sum(b * (k // 64) for b, (_, _, k) in zip(blocks, items)), up(sum(blocks), 256)
-        us = call + rounds * per_round + per_tile * max(k_max, work / sum(blocks) * rounds)
+        us = call + (0.87 if r == 64 and sum(blocks) > 256 else 1.0) * (rounds * per_round + per_tile * max(k_max, work / sum(blocks) * rounds))
         if us < best:
             best, rows = us, r
     return rows
@@ -71,17 +71,20 @@ def chosen(items, layout):
     ([(96, 1000, 1088), (70, 1201, 192), (20, 500, 64)], (32, 32, 32)),
     ([(70, 5121, 64)], (64, 64, 64)),
     ([(190, 2900, 704)], (64, 64, 64)),
-    ([(383, 4090, 192)], (96, 96, 96)),
+    ([(383, 4090, 192)], (96, 0, 96)),
     ([(1500, 1000, 576)], (96, 96, 96)),
-    ([(500, 4090, 1088)], (128, 128, 128)),
-    ([(500, 4090, 192)], (0, 0, 128)),
-    ([(96, 5000, 1088), (70, 8201, 192), (96, 6000, 64)], (64, 0, 64)),        # 0: the GEMM's half tiles
-    ([(96, 9000, 1088), (70, 8201, 192)], (96, 0, 96)),
+    ([(500, 4090, 1088)], (128, 128, 64)),
+    ([(500, 4090, 192)], (0, 0, 64)),
+    ([(250, 5000, 576)], (96, 96, 96)),
+    ([(250, 6000, 2112)], (128, 128, 128)),
+    ([(100, 5500, 2112), (80, 5600, 2112)], (128, 128, 128)),
+    ([(96, 5000, 1088), (70, 8201, 192), (96, 6000, 64)], (64, 64, 64)),
+    ([(96, 9000, 1088), (70, 8201, 192)], (64, 0, 64)),
     ([(96, 4000, 1088), (70, 4201, 192)], (96, 96, 96)),                       # all rows in one block: weights read once
     ([(400, 2000, 64), (400, 3001, 64)], (0, 0, 0)),
     ([(128, 9001, 2112), (100, 8200, 2112)], (0, 0, 64)),
-    ([(128, 4001, 1024), (100, 4200, 1024)], (128, 128, 128)),                 # the same at 128 rows
-    ([(300, 2000, 1088), (257, 3001, 576)], (128, 128, 128))])
+    ([(128, 4001, 1024), (100, 4200, 1024)], (128, 128, 64)),                 # the same at 128 rows
+    ([(300, 2000, 1088), (257, 3001, 576)], (64, 64, 64))])
 def test_row_blocks_match_oracle(items, want, fmt, blocked):
     set_tuning()
     assert chosen(items, (fmt, blocked)) == want[LAYOUTS.index((fmt, blocked))]
