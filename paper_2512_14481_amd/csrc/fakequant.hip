@@ -7,7 +7,7 @@
 // access, a block covers kUnroll such accesses per lane back to back so enough bytes are in
 // flight to cover HBM latency, and a scalar tail handles the last (n mod 8) elements.
 // x is loaded with the ordinary policy: other operators of the layer, the linear's pre-pass and the backward read it again, and
-// up to 256 MB of it stay in the Infinity Cache.  dy, y and dx pass by once and go non-temporal.  Measured, us, x non-temporal |
+// up to 256 MB of it stay in the Infinity Cache (the pre-pass's own loads are non-temporal; the other policy is untimed there).  dy, y and dx pass by once and go non-temporal.  Measured, us, x non-temporal |
 // not: forward of four 2048 x 4096 on one x 24.4 | 19.5, of a 13B layer at 1777 rows 58.4 | 50.1, of 7B's MLP 51.5 | 45.6;
 // backward 38.1 | 35.2, 102 | 89.7, 84.1 | 69.0; 8192 x 8192, four, 179 | 172 and 265 | 237.
 #include "sasq_device.h"
@@ -46,7 +46,8 @@ __device__ __forceinline__ void fwd_vec(const u32x4& in, const QConst& k, u32x4&
 
 // Forward over one tensor by block `block` of the `nblocks` that share it.
 // The block that takes what is left behind the last full chunk: the one whose turn it would be, so that it is nobody's second piece while
-// blocks are without any, with all loads in flight.  Taken by block 0, one access at a time: 33000 elements forward 3.7 us, now 3.2,
+// blocks are without any; one tensor's forward and backward have all of its loads in flight, operators that share a read take them in
+// turn.  Taken by block 0, one access at a time: 33000 elements forward 3.7 us, now 3.2,
 // 40000 backward 6.2, now 5.2, 171264 6.0, now 5.5.
 __device__ __forceinline__ int rest_block(int64_t nvec, int nblocks)
 {

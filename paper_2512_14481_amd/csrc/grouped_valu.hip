@@ -287,10 +287,11 @@ __global__ __launch_bounds__(256) void linear_per_channel_kernel(
                         s[e] = sv[e >> 2][e & 3];
                     }
                     few_row_steps<TM, 16>(f, a, b, s);
-                } else
+                } else {
 #pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    one_step<TM>(f, (float)sext_byte(av[e >> 2], e & 3), (float)sext_byte(bv[e >> 2], e & 3), sv[e >> 2][e & 3]);
+                    for (int e = 0; e < 16; ++e)
+                        one_step<TM>(f, (float)sext_byte(av[e >> 2], e & 3), (float)sext_byte(bv[e >> 2], e & 3), sv[e >> 2][e & 3]);
+                }
             }
         } else {
             for (int k = 0; k < K - k0; ++k) one_step<TM>(f, (float)(int8_t)pa[k], (float)(int8_t)pb[k], ls[buf][k]);

@@ -2,7 +2,7 @@
 // and for some hundred rows where the GEMM's tiles are too few to fill the chip (a chunk of a prefill), in row blocks.
 //
 // What bounds it: the weight bytes (a 7B layer's seven projections at 8 rows, int8: 202 MB in 36 us = 5.6 TB/s, the GEMM's
-// tiles took 93; a 13B layer's at one row, int4: 159 MB in 30 us, from 128; row-major int8, whose rows are gathered in
+// tiles took 93; a 13B layer's at one row, int4: 159 MB in 27.5 us, from 128; row-major int8, whose rows are gathered in
 // 64-byte pieces: 51 us).  The tiled GEMM hands out 256 (or 128) weight rows per workgroup, which at small M is
 // a few dozen workgroups with a K loop that nothing overlaps.  Here a workgroup owns 16 NT weight rows and its NW waves
 // share out K: a wave streams its part of the weights straight from memory into MFMA operand registers (a pre-arranged
@@ -346,8 +346,7 @@ static void launch_mt(LinBatch& b, int64_t tiles16, int a_bits, int32_t* acc_out
         if (!wide)                 launch_one<DT, WMODE, MT, 1, 8, 4, QX, true, false, true>(b, a_bits, acc_out, st);
         else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, false, true>(b, a_bits, acc_out, st);
         else                       launch_one<DT, WMODE, MT, 2, 4, 4, QX, true, false, true>(b, a_bits, acc_out, st);
-    } else
-    if constexpr (WMODE == 3) {                        // int4: half the bytes per tile, a block is two tiles
+    } else if constexpr (WMODE == 3) {                 // int4: half the bytes per tile, a block is two tiles
         if (!wide)             launch_one<DT, WMODE, MT, 2, 8, 2, QX, true, false>(b, a_bits, acc_out, st);
         else if constexpr (QX) launch_one<DT, WMODE, MT, 4, 8, 2, QX, true, false>(b, a_bits, acc_out, st);
         else                   launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, false>(b, a_bits, acc_out, st);
