@@ -504,6 +504,8 @@ static int block_rows(const LinBatch& b, int wmode)
     return rows;
 }
 
+int linear_block_rows(const LinBatch& b, int wmode) { return small_block(b.it, b.count, wmode).mt ? 32 : block_rows(b, wmode); }
+
 bool linear_takes_skinny(const LinBatch& b, int wmode)
 {
     int rows = 0;
@@ -513,7 +515,7 @@ bool linear_takes_skinny(const LinBatch& b, int wmode)
         cols += b.it[i].N;
     }
     if (cols > INT64_C(1) << 27) return false;         // up to 16 work items a column, and a launch holds fewer than 2^32
-    return rows <= kSkinnyRows ? !tiles_are_better(b, rows, wmode) : small_block(b.it, b.count, wmode).mt != 0 || block_rows(b, wmode) != 0;
+    return rows <= kSkinnyRows ? !tiles_are_better(b, rows, wmode) : linear_block_rows(b, wmode) != 0;
 }
 
 // Whether such a call quantizes in the kernel: at most 16 rows, or so few codes in a workgroup's rows (of row tiles of 32 or 64, or of a

@@ -34,3 +34,20 @@ def anyk_few_rows(M, N, K):
     """Whether a static linear with K not a multiple of 64 takes the few-row kernel (sasq::linear_anyk_takes_skinny)."""
     i64 = ctypes.c_int64
     return bool(_function("_ZN4sasq24linear_anyk_takes_skinnyElll", i64, i64, i64)(M, N, K) & 1)
+
+
+class _LinItem(ctypes.Structure):
+    _fields_ = [(f, ctypes.c_void_p) for f in ("x", "xq", "s", "wq", "s_w", "bias", "y")] + [(f, ctypes.c_int) for f in ("M", "N", "K", "tiles_m", "tiles_n")]
+
+
+class _LinBatch(ctypes.Structure):
+    _fields_ = [("it", _LinItem * 8), ("first_block", ctypes.c_int * 9)] + [(f, ctypes.c_int) for f in ("count", "split_first", "split_count", "trim_rows")]
+
+
+def linear_block_rows(items, wf):
+    """Rows per workgroup of the linear's row blocks for (rows, columns, K) items of more than 64 rows, 32: small blocks, 0: the GEMM's
+    tiles (sasq::linear_block_rows)."""
+    batch = _LinBatch(count=len(items))
+    for i, (m, n, k) in enumerate(items):
+        batch.it[i].M, batch.it[i].N, batch.it[i].K = m, n, k
+    return _function("_ZN4sasq17linear_block_rowsERKNS_8LinBatchEi", ctypes.POINTER(_LinBatch), ctypes.c_int)(ctypes.byref(batch), wf)

@@ -3,59 +3,18 @@ against the CPU oracle: each block form and weight layout, alone and in batches,
 uneven shares of them, and rows and columns that end inside a block."""
 from __future__ import annotations
 
-import math
-
 import numpy as np
 import pytest
 import torch
 
 import oracle
 from paper_2512_14481_amd import binding as B
+from tests.dispatch import linear_block_rows
 from tests.gpu_util import assert_same_values, dev_scalar, set_tuning, to_bits, to_dev
 from tests.test_gpu_grouped_linear import WF, device_weights
 from tests.test_gpu_skinny_linear import LAYOUTS, problem
 
 pytestmark = pytest.mark.gpu
-
-# us per call, round and K tile, by layout: blocks of 64, 96 and 128 rows; the GEMM's tiles (block_rows in static_linear_skinny.hip)
-BLOCK = {("int8", False): [(4.8, 2.4, .167), (4.7, 3.7, .195), (4.6, 4.6, .213)],
-         ("int8", True): [(4.6, 2.9, .107), (5.1, 3.9, .137), (5.3, 4.7, .161)],
-         ("int4", True): [(4.6, 2.8, .076), (4.8, 4.1, .100), (4.9, 4.9, .121)]}
-TILE = {("int8", False): (1.0, 12.0, .72), ("int8", True): (1.0, 13.0, .54), ("int4", True): (1.0, 16.0, .49)}
-
-
-def up(a, b):
-    return -(-a // b)
-
-
-def chosen(items, layout):
-    """Rows per block the dispatch takes for (rows, columns, K) items of more than 64 rows, 0: the GEMM's tiles."""
-    if (len(items) == 1 or min(n for _, n, _ in items) > 448) and min(sum(up(m, 32) * up(n, 8 * w) * 8 for m, n, _ in items) for w in (32, 64)) <= 256:
-        return 32
-    if min(n for _, n, _ in items) <= 448:
-        return 0
-    k_max = max(k // 64 for _, _, k in items)
-    call, per_round, per_tile = TILE[layout]
-    if len(items) == 1:
-        m, n, _ = items[0]
-        t = up(m, 256) * up(n, 256)
-        rounds = min(t // 256 + 0.6 if t > 256 and 0 < t % 256 <= 128 else up(t, 256),
-                     up(up(m, 128) * up(n, 256), 256) * 0.64, up(up(m, 128) * up(n, 128), 512) * 0.71)
-        best = call + rounds * (per_round + per_tile * k_max)
-    else:
-        tiles = [up(m, 256) * up(n, 256) for m, n, _ in items]
-        work = sum(t * (k // 64) for t, (_, _, k) in zip(tiles, items))
-        rounds = up(sum(tiles), 256)
-        halves = 32 <= sum(up(t, 8) * 8 for t in tiles) <= 128
-        best = call + (0.7 if halves else 1.0) * (rounds * per_round + per_tile * max(k_max, work / 256 * math.sqrt(rounds * 256 / sum(tiles))))
-    best, rows = 0.9 * best, 0
-    for r, (call, per_round, per_tile) in zip((64, 96, 128), BLOCK[layout]):
-        blocks = [up(m, r) * up(n, 512) * 8 for m, n, _ in items]
-        work, rounds = sum(b * (k // 64) for b, (_, _, k) in zip(blocks, items)), up(sum(blocks), 256)
-        us = call + (0.87 if r == 64 and sum(blocks) > 256 else 1.0) * (rounds * per_round + per_tile * max(k_max, work / sum(blocks) * rounds))
-        if us < best:
-            best, rows = us, r
-    return rows
 
 
 @pytest.mark.parametrize("fmt,blocked", LAYOUTS)
@@ -87,7 +46,7 @@ def chosen(items, layout):
     ([(300, 2000, 1088), (257, 3001, 576)], (64, 64, 64))])
 def test_row_blocks_match_oracle(items, want, fmt, blocked):
     set_tuning()
-    assert chosen(items, (fmt, blocked)) == want[LAYOUTS.index((fmt, blocked))]
+    assert linear_block_rows(items, WF[(fmt, blocked)]) == want[LAYOUTS.index((fmt, blocked))]
     batch, refs = [], []
     for i, (m, n, k) in enumerate(items):
         xb, wq, s_w, bias, s = problem(101 + i, (m, n, k), fmt, "bf16")
