@@ -7,9 +7,14 @@
 // access, a block covers kUnroll such accesses per lane back to back so enough bytes are in
 // flight to cover HBM latency, and a scalar tail handles the last (n mod 8) elements.
 // x is loaded with the ordinary policy: other operators of the layer, the linear's pre-pass and the backward read it again, and
-// up to 256 MB of it stay in the Infinity Cache (the pre-pass's own loads are non-temporal; the other policy is untimed there).  dy, y and dx pass by once and go non-temporal.  Measured, us, x non-temporal |
-// not: forward of four 2048 x 4096 on one x 24.4 | 19.5, of a 13B layer at 1777 rows 58.4 | 50.1, of 7B's MLP 51.5 | 45.6;
-// backward 38.1 | 35.2, 102 | 89.7, 84.1 | 69.0; 8192 x 8192, four, 179 | 172 and 265 | 237.
+// up to 256 MB of it stay in the Infinity Cache (the pre-pass's own loads are non-temporal; the other policy is untimed there).
+// dy, y and dx pass by once and go non-temporal.  Measured, us, x non-temporal | not: forward of four 2048 x 4096 on one x 24.4 |
+// 19.5, of a 13B layer at 1777 rows 58.4 | 50.1, of 7B's MLP 51.5 | 45.6; backward 38.1 | 35.2, 102 | 89.7, 84.1 | 69.0; 8192 x
+// 8192, four, 179 | 172 and 265 | 237.  Where nothing reads x again soon, these calls take longer and the linears beside them
+// shorter: it seems that x takes the place of lines which another call wrote and which then go to memory here instead of there.
+// Steps with every tensor cold, us, forward non-temporal | not: 7B's MLP fake-quant 143 | 148, linears 391 | 385, whole step 546 |
+// 545, 13B 307 | 305, 848 | 853, 1167 | 1170; backward non-temporal | not: 146 | 148, 391 | 385, 550 | 545 and 318 | 305, 850 |
+// 853, 1180 | 1170.
 #include "sasq_device.h"
 #include <cstdlib>
 #include <cmath>
