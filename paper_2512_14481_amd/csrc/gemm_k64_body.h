@@ -34,6 +34,13 @@ enum { KW_I8 = 0, KW_I8B = 2, KW_I4B = 3 };
 
 constexpr int kFacBytes = 1024;      // per wave: the epilogue's per-column factors (BN/2 floats, loaded twice over)
 template <int BM, int BN> constexpr int lds_bytes_k64() { return Tile<BM, BN>::kLds + 4 * kFacBytes; }
+// OP 2 (below): three slots of two K tiles of X, four stages of the weights, no factors.
+template <int BM, int BN> constexpr int lds_bytes_lines()
+{
+    using T = Tile<BM, BN>;
+    constexpr int ring = 3 * 2 * T::kXBytes + kStages * T::kWBytes, epi = 4 * T::kEpiBytes;
+    return ring > epi ? ring : epi;
+}
 
 // One direct 128-bit-per-lane load from global memory into LDS: lane i deposits its 16 bytes at
 // LDS address lds_addr + 16 i.  The memory address is a scalar base plus a 32-bit per-lane offset,
@@ -74,6 +81,11 @@ __device__ __forceinline__ void lds_load16(uint32_t lds_a, uint32_t lds_b, const
 // row gathered per lane as for row-major weights), the weight operand from 1 KB blocks; K is the contraction length in
 // BYTES; the accumulators are fp32, written out rounded to 16 bits without any factor (s_ptr, s_w, bias unused), and
 // acc_out receives the fp32 sums.  This is the backward GEMM of the frozen linear (linear_bwd.hip).
+// OP 2: OP 1 with X read in whole cache lines, an even number of K tiles: a load takes 8 rows x 128 bytes, two K tiles, instead of 16
+// rows x 64 bytes, which are half a line each: L2 then answers two requests for a line, and memory delivers it in halves, two K tiles
+// apart.  X has a ring of its own, three slots of two K tiles, that fills the LDS to its 160 KB (256x256) and is requested four to five
+// K tiles ahead.  us, halves | lines, operands from memory: f16 4096 x 11008 -> 4096 281 | 246, 4096 x 4096 -> 11008 286 | 272, bf16 282 |
+// 237 and 275 | 261, 8192^3 735 | 691, 1024 x 5120 -> 5120 77 | 65, 777 x 4096 -> 4096 31.3 | 28.8; in the caches 268 | 264.
 template <int DT, int WMODE, int BM, int BN, bool ROWS, int GROUPED = 0, int OP = 0>
 __device__ __forceinline__
 void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq,
@@ -84,7 +96,7 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
 {
     static_assert(!GROUPED || (BM == 128 && !ROWS), "grouped factors: 128-row tiles");
     static_assert(OP == 0 || (WMODE == KW_I8B && !ROWS && !GROUPED), "float contraction: pre-arranged weight blocks, no factors");
-    constexpr bool FLT = OP != 0;
+    constexpr bool FLT = OP != 0, XL = OP == 2;
     using AccT = std::conditional_t<FLT, f32x4, i32x4>;
     using S = Store16<DT>;
     using T = Tile<BM, BN>;
@@ -94,7 +106,11 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
     constexpr int WSL = I4 ? WS / 2 : WS;              // weight loads per wave per K tile (packed int4: half the bytes)
     constexpr int kLoads = XS + WSL;                   // direct loads per wave per K tile
     constexpr int kAccShift = I4 ? 4 : 0;
-    auto stage_ptr = [&](int st, int operand) -> char* { return &lds[st * T::kStageBytes + operand * T::kXBytes]; };
+    // LDS: four stages of X and weights; XL: three slots of two K tiles of X, then four stages of weights
+    constexpr int kXSlot = 2 * T::kXBytes, kXSlots = 3;
+    constexpr int kWArea = XL ? kXSlots * kXSlot : T::kXBytes, kWStep = XL ? T::kWBytes : T::kStageBytes;
+    auto x_stage = [&](int st) -> char* { return &lds[st * T::kStageBytes]; };
+    auto w_stage = [&](int st) -> char* { return &lds[kWArea + st * kWStep]; };
 
     const int m0 = tm * BM, n0 = tn * BN;
     const int lane = threadIdx.x & 63;
@@ -113,10 +129,12 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
     constexpr int kXTileStep = FLT ? kBK : 1024;
     const int8_t* wpanel = reinterpret_cast<const int8_t*>(wq) + (WMODE == KW_I8B ? (int64_t)(n0 >> 4) * KT * 1024
                                                                   : I4 ? (int64_t)(n0 >> 5) * KT * 1024 : (int64_t)n0 * K);
-    uint32_t xoff[XS], woff[WSL];
+    constexpr int XO = XL ? 2 * XS : XS;
+    uint32_t xoff[XO], woff[WSL];
 #pragma unroll
-    for (int j = 0; j < XS; ++j)
-        xoff[j] = FLT ? (uint32_t)(min((4 * j + wave) * 16 + lrow, M - 1 - m0) * K + lchunk * 16)
+    for (int j = 0; j < XO; ++j)
+        xoff[j] = XL  ? (uint32_t)(min((4 * j + wave) * 8 + (lane >> 3), M - 1 - m0) * K + (((lane & 7) ^ (lane >> 3)) << 4))
+                : FLT ? (uint32_t)(min((4 * j + wave) * 16 + lrow, M - 1 - m0) * K + lchunk * 16)
                       : (uint32_t)(min(4 * j + wave, last_rb - (m0 >> 4)) * KT * 1024 + lane * 16);
 #pragma unroll
     for (int j = 0; j < WSL; ++j) {
@@ -126,13 +144,19 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
     }
     constexpr int kWTileStep = (WMODE == KW_I8B || I4) ? 1024 : kBK;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_ptr_t)&lds[0] + (uint32_t)wave * 1024u;
-    auto dma_at = [&](const int8_t* xtile, const int8_t* wtile, int j, int st) {   // loads 0..XS-1: activations, XS..: weights
-        const uint32_t st_off = (uint32_t)st * T::kStageBytes;
-        if (j < XS) lds_load16(lds_base + j * 4096, st_off, xtile, xoff[j]);
-        else        lds_load16(lds_base + T::kXBytes + (j - XS) * 4096, st_off, wtile, woff[j - XS < WSL ? j - XS : 0]);
+    // loads 0..XS-1: activations, XS..: weights.  XL: the activations are half `xh` (rows 0..BM/2 or BM/2..BM) of the pair of K tiles at
+    // xtile, into the slot at xslot.
+    auto dma_at = [&](const int8_t* xtile, const int8_t* wtile, int j, int st, int xh, uint32_t xslot) {
+        if (j >= XS)  lds_load16(lds_base + kWArea + (j - XS) * 4096, (uint32_t)(st * kWStep), wtile, woff[j - XS < WSL ? j - XS : 0]);
+        else if (XL)  lds_load16(lds_base + (xh * XS + j) * 4096, xslot, xtile, xoff[XL ? xh * XS + j : 0]);
+        else          lds_load16(lds_base + j * 4096, (uint32_t)st * T::kStageBytes, xtile, xoff[j < XS ? j : 0]);
     };
-    auto dma = [&](int Tk, int j, int st) {          // K tile Tk into stage st = Tk & 3
-        dma_at(xpanel + (int64_t)Tk * kXTileStep, wpanel + (int64_t)Tk * kWTileStep, j, st);
+    // K tile Tk into stage st = Tk & 3.  XL: with an odd tile go the first halves of the pair that begins with the tile after it, with an
+    // even one the second halves of its own pair; past the last pair it is fetched again, into a slot that is free, to keep the counts.
+    auto dma = [&](int Tk, int j, int st) {
+        const int pair = (Tk + 1) >> 1;
+        dma_at(XL ? xpanel + (int64_t)min(pair, KT / 2 - 1) * (2 * kBK) : xpanel + (int64_t)Tk * kXTileStep, wpanel + (int64_t)Tk * kWTileStep, j, st,
+               1 - (Tk & 1), (uint32_t)(pair % kXSlots * kXSlot));
     };
     // The steady loop keeps the operands' addresses at its current group of four K tiles here: a load of
     // tile i + 4 then adds a constant to them.
@@ -149,14 +173,17 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
     using WFrag = std::conditional_t<I4, u32x2, i32x4>;
     i32x4 fx[2][MF];
     WFrag fw[2][NF];
-    auto read_frag = [&](int set, int st, int idx) {   // the MF activation fragments first, then the NF weight ones
+    // XL: row r of a slot holds 128 bytes, chunk c at position c ^ (r & 7); the second K tile's chunks are 4 .. 7
+    const int xl_off = (wm * (BM / 2) + frow) * 2 * kBK + ((fq ^ (frow & 7)) << 4);
+    auto read_frag = [&](int set, int st, int idx, uint32_t xslot, int odd) {   // the MF activation fragments first, then the NF weight ones
         if (idx < MF) {
-            fx[set][idx] = *reinterpret_cast<const i32x4*>(stage_ptr(st, 0) + xbase + idx * 16 * kBK + foff);
+            fx[set][idx] = *reinterpret_cast<const i32x4*>(XL ? &lds[xslot + (xl_off ^ (odd * kBK)) + idx * 32 * kBK]
+                                                              : x_stage(st) + xbase + idx * 16 * kBK + foff);
         } else if constexpr (I4) {
             const int g = idx - MF;
-            fw[set][g] = *reinterpret_cast<const u32x2*>(stage_ptr(st, 1) + (wn * (BN / 64) + (g >> 1)) * 1024 + 256 * fq + 8 * (16 * (g & 1) + frow));
+            fw[set][g] = *reinterpret_cast<const u32x2*>(w_stage(st) + (wn * (BN / 64) + (g >> 1)) * 1024 + 256 * fq + 8 * (16 * (g & 1) + frow));
         } else {
-            fw[set][idx - MF] = *reinterpret_cast<const i32x4*>(stage_ptr(st, 1) + wbase + (idx - MF) * 16 * kBK + foff);
+            fw[set][idx - MF] = *reinterpret_cast<const i32x4*>(w_stage(st) + wbase + (idx - MF) * 16 * kBK + foff);
         }
     };
     auto wfrag_piece = [&](const WFrag& f, int j) -> int {   // output dword j of the unpacked operand
@@ -210,6 +237,8 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
                     fsum[GROUPED ? g : 0][GROUPED ? b : 0][e] =
                         __builtin_fmaf((float)((int)acc[g][b][e] >> kAccShift), sg, fsum[GROUPED ? g : 0][GROUPED ? b : 0][e]);
     };
+    // XL: the slots of the steady trip's first three pairs; the fourth and fifth take the first two's
+    uint32_t slot0 = 0, slot1 = kXSlot, slot2 = 2 * kXSlot;
     auto iteration = [&](int i, auto cur_tag, auto stage_tag, auto first_tag, auto tail_tag) {
         constexpr int CUR = decltype(cur_tag)::value;
         constexpr int STG = decltype(stage_tag)::value;        // i & 3 where the copy of the body knows it, else -1
@@ -227,6 +256,8 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
         asm volatile("" ::: "memory");
         const int stn = STG >= 0 ? (STG + 1) & 3 : (i + 1) & 3;
         const bool more = !TAIL || i + 1 < KT;                 // a next tile to read fragments of
+        const int rodd = STG >= 0 ? (STG + 1) & 1 : (i + 1) & 1;
+        const uint32_t rslot = !XL ? 0 : STG >= 0 ? (STG == 0 ? slot0 : STG == 3 ? slot2 : slot1) : (uint32_t)(((i + 1) >> 1) % kXSlots * kXSlot);
         i32x4 xhalf[GROUPED == 2 ? MF : 1];                    // GROUPED 2: the fragments with one half of the channels zeroed
         if constexpr (GROUPED == 2) {
 #pragma unroll
@@ -259,11 +290,12 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
                 __builtin_amdgcn_sched_barrier(0);
                 const int t = g * MF + bi;
                 if (t < kFragStep * NFR) {
-                    if (t % kFragStep == 0 && more) read_frag(1 - CUR, stn, t / kFragStep);
+                    if (t % kFragStep == 0 && more) read_frag(1 - CUR, stn, t / kFragStep, rslot, rodd);
                 } else if (!TAIL || i + 4 < KT) {
                     const int u = t - kFragStep * NFR;
                     if (u % kLoadStep == 0 && u / kLoadStep < kLoads) {
-                        if constexpr (STG >= 0) dma_at(xrun + (STG + 4) * kXTileStep, wrun + (STG + 4) * kWTileStep, u / kLoadStep, STG);
+                        if constexpr (STG >= 0) dma_at(xrun + (XL ? (STG + 5) / 2 * 2 : STG + 4) * kXTileStep, wrun + (STG + 4) * kWTileStep, u / kLoadStep, STG,
+                                                       1 - (STG & 1), STG == 0 ? slot2 : STG == 3 ? slot1 : slot0);
                         else                    dma(i + 4, u / kLoadStep, i & 3);
                     }
                 }
@@ -318,6 +350,10 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
     SASQ_TILE_TS(0);
     // fill: the first four tiles requested, tile 0 landed for everyone, its fragments read
     const int nfill = min(KT, 4);
+    if constexpr (XL) {
+#pragma unroll
+        for (int j = 0; j < XS; ++j) dma(-1, j, 3);            // the first pair's first halves
+    }
     for (int t = 0; t < nfill; ++t)
 #pragma unroll
         for (int j = 0; j < kLoads; ++j) dma(t, j, t);
@@ -328,7 +364,7 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 #pragma unroll
-    for (int k = 0; k < NFR; ++k) read_frag(0, 0, k);
+    for (int k = 0; k < NFR; ++k) read_frag(0, 0, k, 0, 0);
     if constexpr (I4) wv_ahead = wfrag(fw[0][0]);
     SASQ_TILE_TS(1);
     // A multiple of four steady iterations (they always have a tile i+4 to request), then the tail.
@@ -338,7 +374,8 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
     // (Whole-tile groups keep two iterations with run-time stages: their body exists once per accumulator
     // mode already, and four copies of each push the register allocator into scratch memory.)
     constexpr bool kBy4 = GROUPED != 1;
-    const int steady = !kBy4 ? (KT >= 6 ? ((KT - 4) & ~1) : 0) : KT >= 8 ? ((KT - 4) & ~3) : 0;
+    // XL: its last steady iteration requests the first halves of a pair that is there.
+    const int steady = XL ? (KT >= 10 ? ((KT - 6) & ~3) : 0) : !kBy4 ? (KT >= 6 ? ((KT - 4) & ~1) : 0) : KT >= 8 ? ((KT - 4) & ~3) : 0;
     if constexpr (!kBy4) {
         if (steady > 0) {
             step(0, C0{}, SR{}, Yes{}, No{});
@@ -358,6 +395,12 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
         for (int it = 4; it < steady; it += 4) {
             xrun += 4 * kXTileStep;
             wrun += 4 * kWTileStep;
+            if constexpr (XL) {                                // the pairs 2 it + 4 .. of this trip
+                const uint32_t first = slot2;
+                slot2 = slot1;
+                slot1 = slot0;
+                slot0 = first;
+            }
             step(it, C0{}, S0{}, No{}, No{});
             step(it + 1, C1{}, S1{}, No{}, No{});
             step(it + 2, C0{}, S2{}, No{}, No{});
@@ -382,7 +425,7 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
                    (uint32_t)(lane & (BN / 8 - 1)) * 16u);   // lanes past BN/8 fetch the same factors again: no lane reads past the block
     if constexpr (kBy4) {
 #pragma unroll 1
-        for (int i = steady; i < KT; i += 2) {                  // KT - steady is 1 .. 7, steady is even
+        for (int i = steady; i < KT; i += 2) {                  // KT - steady is 1 .. 9, steady is even
             step(i, C0{}, SR{}, No{}, Yes{});
             if (i + 1 < KT) step(i + 1, C1{}, SR{}, No{}, Yes{});
         }

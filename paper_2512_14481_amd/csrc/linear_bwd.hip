@@ -331,18 +331,18 @@ static void launch_bwd(const void* dy, const void* wt, void* dx, float* acc_out,
 // (gemm_k64_body.h): 16x16 tiles, one MFMA per 64-byte stage row, scalar-addressed direct loads, chunked epilogue.
 // The default: a register-only loop of the 16x16x32 form sustains about 18 % more than 32x32x16 on this
 // power-limited part (1.97 against 1.67 PFLOP/s for f16).  dY is the body's row-major operand, the prepared
-// weight its block operand; K of the body is the contraction length in bytes.
-template <int DT, int BM, int BN>
+// weight its block operand; K of the body is the contraction length in bytes.  LINES: dY in whole cache lines, N a multiple of 64.
+template <int DT, int BM, int BN, bool LINES>
 __global__ __launch_bounds__(kGemmThreads)
 __attribute__((amdgpu_waves_per_eu(Tile<BM, BN>::kWavesPerSimd, Tile<BM, BN>::kWavesPerSimd)))
 void linear_bwd_k32_kernel(const uint8_t* __restrict__ dy, const uint8_t* __restrict__ wt,
                            uint16_t* __restrict__ dx, float* __restrict__ acc_out,
                            int M, int N, int K, int tiles_m, int tiles_n)
 {
-    __shared__ __attribute__((aligned(1024))) char lds[lds_bytes_k64<BM, BN>()];
+    __shared__ __attribute__((aligned(1024))) char lds[LINES ? lds_bytes_lines<BM, BN>() : lds_bytes_k64<BM, BN>()];
     int tm, tn;
     if (!tile_of_block((int)blockIdx.x, tiles_m, tiles_n, tm, tn)) return;
-    gemm_k64_body<DT, KW_I8B, BM, BN, false, false, 1>(reinterpret_cast<const int8_t*>(dy), wt, nullptr, nullptr, nullptr, dx,
+    gemm_k64_body<DT, KW_I8B, BM, BN, false, false, LINES ? 2 : 1>(reinterpret_cast<const int8_t*>(dy), wt, nullptr, nullptr, nullptr, dx,
                                                         reinterpret_cast<int32_t*>(acc_out), M, K, N * 2, tm, tn, lds);
 }
 
@@ -351,9 +351,13 @@ static void launch_bwd_k32(const void* dy, const void* wt, void* dx, float* acc_
 {
     const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (int)((K + BN - 1) / BN);
     const int grid = ((tiles_m * tiles_n + 7) / 8) * 8;
-    linear_bwd_k32_kernel<DT, BM, BN><<<grid, kGemmThreads, 0, st>>>(
-        static_cast<const uint8_t*>(dy), static_cast<const uint8_t*>(wt), static_cast<uint16_t*>(dx), acc_out,
-        (int)M, (int)N, (int)K, tiles_m, tiles_n);
+    auto launch = [&](auto lines_tag) {
+        linear_bwd_k32_kernel<DT, BM, BN, decltype(lines_tag)::value><<<grid, kGemmThreads, 0, st>>>(
+            static_cast<const uint8_t*>(dy), static_cast<const uint8_t*>(wt), static_cast<uint16_t*>(dx), acc_out,
+            (int)M, (int)N, (int)K, tiles_m, tiles_n);
+    };
+    if (N % (2 * kBwdCols) == 0) launch(std::true_type{});          // rows of dY are whole 128-byte pieces: the body's OP 2
+    else                         launch(std::false_type{});
 }
 
 // The 32x32x16 kernel: 256x256 tiles unless they would leave most of the 256 CUs idle for a round; then 128x128
