@@ -2,8 +2,7 @@
 // and for some hundred rows where the GEMM's tiles are too few to fill the chip (a chunk of a prefill), in row blocks.
 //
 // What bounds it: the weight bytes (a 7B layer's seven projections at 8 rows, int8: 202 MB in 36 us = 5.6 TB/s, the GEMM's
-// tiles took 93; a 13B layer's at one row, int4: 159 MB in 27.5 us, from 128; row-major int8, whose rows are gathered in
-// 64-byte pieces: 51 us).  The tiled GEMM hands out 256 (or 128) weight rows per workgroup, which at small M is
+// tiles took 93; a 13B layer's at one row, int4: 159 MB in 26.6 us, from 128; row-major int8, eight rows of a line each a load: 36 us).  The tiled GEMM hands out 256 (or 128) weight rows per workgroup, which at small M is
 // a few dozen workgroups with a K loop that nothing overlaps.  Here a workgroup owns 16 NT weight rows and its NW waves
 // share out K: a wave streams its part of the weights straight from memory into MFMA operand registers (a pre-arranged
 // 1 KB block IS one operand read of a wave), D K tiles ahead, with no LDS and no barrier until the waves' int32 sums are
@@ -35,6 +34,17 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_rsrc(const void* base,
 
 // Row tiles whose sums meet in LDS at a time (128 KB at most).
 template <int MT, int NT, int NW> constexpr int skinny_rows_per_phase() { return NW * NT * MT <= 128 ? MT : MT / 2; }
+// A wave's own LDS in the K loop, where its operands turn from the order of memory into that of the MFMA.
+template <int WMODE, int MT, int NT, bool QX, bool EVEN, bool FLT, bool ANYK> constexpr int skinny_turn_bytes()
+{
+    constexpr bool w = WMODE == 0 && !ANYK, x = FLT || (QX && !ANYK);
+    return (w && !EVEN ? 2 : 1) * ((w ? NT : 0) + (x ? MT : 0)) * 1024;
+}
+template <int WMODE, int MT, int NT, int NW, bool QX, bool EVEN, bool FLT, bool ANYK> constexpr int skinny_lds_bytes()
+{
+    constexpr int sums = NW * NT * skinny_rows_per_phase<MT, NT, NW>() * 1024, turn = NW * skinny_turn_bytes<WMODE, MT, NT, QX, EVEN, FLT, ANYK>();
+    return sums > turn ? sums : turn;
+}
 
 // FLT: the backward GEMM of the frozen linear.  x is dY, 16-bit and row-major, K the contraction's bytes per row, the weight blocks
 // hold 16 rows x 32 numbers, the sums are fp32 (the waves' parts added in their order) and go out rounded, without factors.
@@ -51,15 +61,20 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
     static_assert(!ANYK || (ROWMAJOR && !EVEN), "rows at any byte: plain loads");
     using AccT = std::conditional_t<FLT, f32x4, i32x4>;
     constexpr int WL = I4 ? NT / 2 : NT;               // 128-bit weight loads per lane and K tile
+    constexpr bool WTURN = ROWMAJOR && !ANYK, XTURN = QX && !ANYK;
+    constexpr bool LINES = WTURN && !EVEN;
+    constexpr int TS = LINES ? 2 : 1;                  // K tiles per step
+    constexpr int DS = (D + TS - 1) / TS;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int frow = lane & 15, fq = lane >> 4;
     const int M = it.M, N = it.N, K = it.K, KT = K >> 6;
     const int m0 = mblk * 16 * MT, n0 = nblk * 16 * NT;
 
-    // This wave's K tiles: an equal run of consecutive ones.
-    const int per = (KT + NW - 1) / NW;
-    const int t0 = min(wave * per, KT), count = min(per, KT - t0);
+    // This wave's steps: an equal run of consecutive ones.  KT odd: the last step of two K tiles has one.
+    const int steps = (KT + TS - 1) / TS, per = (steps + NW - 1) / NW;
+    const int s0 = min(wave * per, steps), count = min(per, steps - s0), t0 = s0 * TS;
+    const int half_step = LINES && (KT & 1) && s0 + count == steps ? count - 1 : -1;
 
     // One scalar base per operand, advanced 1 KB (or 64 bytes of a row) per K tile, + a 32-bit lane offset per stream: the products of 96
     // rows leave no registers for 64-bit lane addresses.  At K <= 131071 the codes are at most 8 row blocks of 2 MB; FLT's 96 rows stay
@@ -68,10 +83,14 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
     const int wblk = I4 ? n0 >> 5 : n0 >> 4, wlast = I4 ? (N - 1) >> 5 : (N - 1) >> 4;
     const char* wbase = reinterpret_cast<const char*>(it.wq) +
                         (ROWMAJOR ? (int64_t)n0 * K + (int64_t)t0 * 64 : ((int64_t)wblk * KT + t0) * 1024);
-    uint32_t woff[WL];
+    // a load takes 8 rows x 128 bytes or 16 rows x 64 bytes in the order of memory (see the turn below)
+    const int lrow = lane >> 3, lchunk = lane & 7, prow = lane >> 2, pchunk = lane & 3;
+    uint32_t woff[TS * WL];
 #pragma unroll
-    for (int j = 0; j < WL; ++j) {
-        if (ROWMAJOR) {
+    for (int j = 0; j < TS * WL; ++j) {
+        if (LINES)      woff[j] = (uint32_t)min(8 * j + lrow, N - 1 - n0) * (uint32_t)K + 16 * lchunk;
+        else if (WTURN) woff[j] = (uint32_t)min(16 * j + prow, N - 1 - n0) * (uint32_t)K + 16 * pchunk;
+        else if (ROWMAJOR) {
             woff[j] = (uint32_t)min(16 * j + frow, N - 1 - n0) * (uint32_t)K + 16 * fq;
         } else {
             // int4: lane l takes 16 bytes: the K tile's codes 16 (l/16) .. + 15 of the weight rows 2 (l%16) and 2 (l%16) + 1.
@@ -79,47 +98,54 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
             woff[j] = (uint32_t)min(j, wlast - wblk) * (uint32_t)KT * 1024 + in_block;
         }
     }
-    constexpr int kWStep = ROWMAJOR ? 64 : 1024;
+    constexpr int kWStep = ROWMAJOR ? 64 * TS : 1024;
     const char* xbase = FLT ? reinterpret_cast<const char*>(it.x) + (int64_t)m0 * K + (int64_t)t0 * 64
                       : QX ? reinterpret_cast<const char*>(it.x) + ((int64_t)m0 * K + (int64_t)t0 * 64) * 2
                       : ANYK ? reinterpret_cast<const char*>(it.xq) + (int64_t)m0 * K + (int64_t)t0 * 64
                            : reinterpret_cast<const char*>(it.xq) + ((int64_t)(m0 >> 4) * KT + t0) * 1024;
-    uint32_t xoff[MT];
+    uint32_t xoff[XTURN ? 2 * MT : MT];
 #pragma unroll
-    for (int b = 0; b < MT; ++b) {
-        if (FLT || (ANYK && !QX)) xoff[b] = (uint32_t)min(16 * b + frow, M - 1 - m0) * (uint32_t)K + 16 * fq;
+    for (int b = 0; b < (XTURN ? 2 * MT : MT); ++b) {
+        if (XTURN)             xoff[b] = (uint32_t)min(8 * b + lrow, M - 1 - m0) * (uint32_t)K * 2 + 16 * lchunk;
+        else if (FLT)          xoff[b] = (uint32_t)min(16 * b + prow, M - 1 - m0) * (uint32_t)K + 16 * pchunk;
+        else if (ANYK && !QX) xoff[b] = (uint32_t)min(16 * b + frow, M - 1 - m0) * (uint32_t)K + 16 * fq;
         else if (QX) xoff[b] = (uint32_t)min(16 * b + frow, M - 1 - m0) * (uint32_t)K * 2 + fq * 32;
         else         xoff[b] = (uint32_t)min(b, ((M - 1) >> 4) - (m0 >> 4)) * (uint32_t)KT * 1024 + (4 * frow + (fq ^ swz64(frow))) * 16;
     }
-    constexpr int kXStep = FLT || (ANYK && !QX) ? 64 : QX ? 128 : 1024;
+    constexpr int kXStep = FLT || (ANYK && !QX) ? 64 : (QX ? 128 : 1024) * TS;
     const QConst qk = FLT ? QConst{} : make_qconst(*it.s, a_bits);
 
+    constexpr int WN = TS * WL, XN = (QX ? 2 : 1) * TS;                // loads per step
     struct Frag {
-        u32x4 w[WL];
-        u32x4 x[MT][QX ? 2 : 1];
+        u32x4 w[WN];
+        u32x4 x[MT][XN];
     };
+    const bool few = XTURN && MT == 1 && M <= 8;        // then a K tile's second load would be of rows past the last
     auto load = [&](Frag& f, int t) {
         int bytes = -1;                                 // in so many words: from a select the compiler builds the buffers in vector registers
         if (EVEN) asm("s_cmp_lt_i32 %1, %2\n\ts_cselect_b32 %0, -1, 0" : "=s"(bytes) : "s"(t), "s"(count) : "scc");
         const __amdgpu_buffer_rsrc_t wrsrc = operand_rsrc(wbase, bytes), xrsrc = operand_rsrc(xbase, bytes);
         // ONCE: no other workgroup reads these weights.  Where row blocks share them they have to stay in L2 (333 x 4096 x 4096
-        // 18.8 us non-temporal, 16.8 cached), and row-major a K tile is half a 128-byte line of each row, the other half the next
-        // K tile's (the 7B layer below: 54 us and 51).
+        // 18.8 us non-temporal, 16.8 cached).
         constexpr int kNonTemporal = 2;
-        // Few row-major rows: plain loads (7B layer, 8 rows 50.6 us through buffers, 49.8 so; 12 x 2368 x 28544's MLP 72.9, 70.0).
-        constexpr bool kPlain = ROWMAJOR && !EVEN;
+        // a step of one K tile takes that one twice: nothing behind a row's end is read
+        const bool half = LINES && t == half_step;
+        const uint32_t back = half && lchunk >= 4 ? 64 : 0;
 #pragma unroll
-        for (int j = 0; j < WL; ++j)
-            if constexpr (ANYK)        f.w[j] = load_piece<u32x4>(reinterpret_cast<const uint8_t*>(wbase) + (int64_t)t * kWStep + woff[j]);
-            else if constexpr (kPlain) f.w[j] = *reinterpret_cast<const u32x4*>(wbase + (int64_t)t * kWStep + woff[j]);
+        for (int j = 0; j < WN; ++j)
+            if constexpr (ANYK)       f.w[j] = load_piece<u32x4>(reinterpret_cast<const uint8_t*>(wbase) + (int64_t)t * kWStep + woff[j]);
+            else if constexpr (LINES) f.w[j] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, woff[j] - back, t * kWStep, ONCE ? kNonTemporal : 0);
             else                  f.w[j] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, woff[j], t * kWStep, ONCE && !ROWMAJOR ? kNonTemporal : 0);
 #pragma unroll
         for (int b = 0; b < MT; ++b)
 #pragma unroll
-            for (int h = 0; h < (QX ? 2 : 1); ++h) {
-                if constexpr (ANYK)        f.x[b][h] = load_piece<u32x4>(reinterpret_cast<const uint8_t*>(xbase) + (int64_t)t * kXStep + xoff[b] + 16 * h);
-                else if constexpr (kPlain) f.x[b][h] = *reinterpret_cast<const u32x4*>(xbase + (int64_t)t * kXStep + xoff[b] + 16 * h);
-                else                  f.x[b][h] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff[b] + 16 * h, t * kXStep, 0);
+            for (int h = 0; h < XN; ++h) {
+                constexpr int kTile = QX ? 2 : 1;                       // loads of a K tile
+                const int step = t * kXStep + (half ? 0 : h / kTile * (QX ? 128 : 1024));
+                if constexpr (ANYK) f.x[b][h] = load_piece<u32x4>(reinterpret_cast<const uint8_t*>(xbase) + (int64_t)t * kXStep + xoff[b] + 16 * h);
+                else if constexpr (XTURN) {
+                    if (h % 2 == 0 || !few) f.x[b][h] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff[2 * b + h % 2], step, 0);
+                } else f.x[b][h] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff[b], step, 0);
             }
     };
     AccT acc[NT][MT];
@@ -127,39 +153,77 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
     for (int g = 0; g < NT; ++g)
 #pragma unroll
         for (int b = 0; b < MT; ++b) acc[g][b] = AccT{0, 0, 0, 0};
-    auto multiply = [&](const Frag& f) {
-        i32x4 xv[MT];
+    // The turn: operands that memory holds in rows are loaded in memory's order and go through the wave's own LDS into the MFMA's (a
+    // wave's LDS accesses are served in order: no wait, no barrier).  Loaded in the MFMA's order, sixteen rows side by side, the four
+    // lanes that the L1 cache looks at together want the same banks of four lines and get them one by one: 9.6 TB/s out of the L2s where
+    // rows are whole lines apart, 28 to 30 in memory's order.  Few rows of row-major weights also take whole lines: memory delivers the
+    // halves one by one.  us, MFMA's order | memory's: weights, 7B layer, row-major, 8 rows 50 | 36, 16 rows 60 | 41, 40 rows 64 | 48, 8 x
+    // 4096 -> 11008 16.3 | 13.1; dY, the 7B layer's training step of 200 rows 405 | 350, attention, hidden 2048, of 130 rows 58 | 53; the
+    // activations quantized here, 7B layer, pre-arranged, 16 rows 43.4 | 38.6, 13B int4, 16 rows 36.8 | 33.4, one row 28.0 | 26.6.
+    constexpr int kTurn = skinny_turn_bytes<WMODE, MT, NT, QX, EVEN, FLT, ANYK>();
+    char* wturn = lds + wave * kTurn;
+    char* xturn = wturn + (WTURN ? NT * TS * 1024 : 0);
+    const int line_put = lrow * 128 + ((lchunk ^ lrow) << 4), line_get = frow * 128 + ((fq ^ (frow & 7)) << 4);
+    const int piece_put = prow * 64 + ((pchunk ^ swz64(prow)) << 4), piece_get = frow * 64 + ((fq ^ swz64(frow)) << 4);
+    auto quantize8 = [&](const u32x4& v) -> u32x2 {
+        float c[8];
 #pragma unroll
-        for (int b = 0; b < MT; ++b) {
-            if constexpr (QX) {
+        for (int w = 0; w < 4; ++w) {
+            c[2 * w] = quantize(S::lo(v[w]), qk).c;
+            c[2 * w + 1] = quantize(S::hi(v[w]), qk).c;
+        }
+        return u32x2{pack_codes4(c[0], c[1], c[2], c[3]), pack_codes4(c[4], c[5], c[6], c[7])};
+    };
+    auto multiply = [&](const Frag& f, int t) {
+        if constexpr (WTURN) {
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    float c[8];
+            for (int j = 0; j < WN; ++j) *reinterpret_cast<u32x4*>(wturn + j * 1024 + (LINES ? line_put : piece_put)) = f.w[j];
+        }
+        if constexpr (FLT) {
 #pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        c[2 * w] = quantize(S::lo(f.x[b][h][w]), qk).c;
-                        c[2 * w + 1] = quantize(S::hi(f.x[b][h][w]), qk).c;
+            for (int b = 0; b < MT; ++b) *reinterpret_cast<u32x4*>(xturn + b * 1024 + piece_put) = f.x[b][0];
+        }
+        if constexpr (XTURN) {
+#pragma unroll
+            for (int b = 0; b < MT; ++b)
+#pragma unroll
+                for (int h = 0; h < XN; ++h)
+                    if (h % 2 == 0 || !few) {
+                        const int r = 8 * (h % 2) + lrow;
+                        *reinterpret_cast<u32x2*>(xturn + (h / 2 * MT + b) * 1024 + r * 64 + (((lchunk >> 1) ^ swz64(r)) << 4) + 8 * (lchunk & 1)) = quantize8(f.x[b][h]);
                     }
-                    xv[b][2 * h] = (int)pack_codes4(c[0], c[1], c[2], c[3]);
-                    xv[b][2 * h + 1] = (int)pack_codes4(c[4], c[5], c[6], c[7]);
-                }
-            } else {
-                xv[b] = __builtin_bit_cast(i32x4, f.x[b][0]);
-            }
         }
 #pragma unroll
-        for (int g = 0; g < NT; ++g) {
-            i32x4 wv;
-            if constexpr (I4) {
-                const uint32_t p0 = f.w[g / 2][2 * (g & 1)], p1 = f.w[g / 2][2 * (g & 1) + 1];   // 16 x the code in every byte
-                wv = i32x4{(int)((p0 << 4) & 0xF0F0F0F0u), (int)(p0 & 0xF0F0F0F0u), (int)((p1 << 4) & 0xF0F0F0F0u), (int)(p1 & 0xF0F0F0F0u)};
-            } else {
-                wv = __builtin_bit_cast(i32x4, f.w[g]);
-            }
+        for (int p = 0; p < TS; ++p) {
+            if (p == 1 && t == half_step) break;
+            i32x4 xv[MT];
 #pragma unroll
             for (int b = 0; b < MT; ++b) {
-                if constexpr (FLT) acc[g][b] = Mfma16x16<DT>::mma(wv, xv[b], acc[g][b]);
-                else               acc[g][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wv, xv[b], acc[g][b], 0, 0, 0);
+                if constexpr (FLT || XTURN) {
+                    xv[b] = *reinterpret_cast<const i32x4*>(xturn + (p * MT + b) * 1024 + piece_get);
+                } else if constexpr (QX) {
+                    const u32x2 lo = quantize8(f.x[b][0]), hi = quantize8(f.x[b][1]);
+                    xv[b] = i32x4{(int)lo[0], (int)lo[1], (int)hi[0], (int)hi[1]};
+                } else {
+                    xv[b] = __builtin_bit_cast(i32x4, f.x[b][p]);
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < NT; ++g) {
+                i32x4 wv;
+                if constexpr (I4) {
+                    const uint32_t p0 = f.w[g / 2][2 * (g & 1)], p1 = f.w[g / 2][2 * (g & 1) + 1];   // 16 x the code in every byte
+                    wv = i32x4{(int)((p0 << 4) & 0xF0F0F0F0u), (int)(p0 & 0xF0F0F0F0u), (int)((p1 << 4) & 0xF0F0F0F0u), (int)(p1 & 0xF0F0F0F0u)};
+                } else if constexpr (WTURN) {
+                    wv = *reinterpret_cast<const i32x4*>(wturn + (LINES ? g * 2048 + (line_get ^ (64 * p)) : g * 1024 + piece_get));
+                } else {
+                    wv = __builtin_bit_cast(i32x4, f.w[g]);
+                }
+#pragma unroll
+                for (int b = 0; b < MT; ++b) {
+                    if constexpr (FLT) acc[g][b] = Mfma16x16<DT>::mma(wv, xv[b], acc[g][b]);
+                    else               acc[g][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wv, xv[b], acc[g][b], 0, 0, 0);
+                }
             }
         }
     };
@@ -196,54 +260,54 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
                     rest.x[b][h] = load_piece_edge<u32x4>(x + (int64_t)min(m0 + 16 * b + frow, M - 1) * K * kBytes, (KT * 64 + 16 * fq) * kBytes + 16 * h, K * kBytes);
         }
     }
-    Frag ring[D];
+    Frag ring[DS];
     if constexpr (EVEN) {
-        // D K tiles in flight.  Loads and products carry no conditions (tiles past the last are zeros), so that the wait in front of
+        // DS steps in flight.  Loads and products carry no conditions (tiles past the last are zeros), so that the wait in front of
         // a product counts exactly the loads behind its own; the barriers keep the scheduler from moving all products of a round in
         // front of all its loads, which exposed the whole latency once a round.
 #pragma unroll
-        for (int j = 0; j < D; ++j) {
+        for (int j = 0; j < DS; ++j) {
             load(ring[j], j);
             __builtin_amdgcn_sched_barrier(0);
         }
         load_factors();
         asm volatile("" ::: "memory");                  // here, not behind the loop
 #pragma unroll 1
-        for (int i = 0; i < count; i += D) {
+        for (int i = 0; i < count; i += DS) {
 #pragma unroll
-            for (int j = 0; j < D; ++j) {
-                multiply(ring[j]);
-                load(ring[j], i + j + D);
+            for (int j = 0; j < DS; ++j) {
+                multiply(ring[j], i + j);
+                load(ring[j], i + j + DS);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
     } else {
 #pragma unroll
-        for (int j = 0; j < D; ++j)
+        for (int j = 0; j < DS; ++j)
             if (j < count) load(ring[j], j);
         load_factors();
         asm volatile("" ::: "memory");
         int i = 0;
 #pragma unroll 1
-        for (; i + 2 * D <= count; i += D) {
+        for (; i + 2 * DS <= count; i += DS) {
 #pragma unroll
-            for (int j = 0; j < D; ++j) {
-                multiply(ring[j]);
-                load(ring[j], i + j + D);
+            for (int j = 0; j < DS; ++j) {
+                multiply(ring[j], i + j);
+                load(ring[j], i + j + DS);
             }
         }
 #pragma unroll
-        for (int j = 0; j < D; ++j)
+        for (int j = 0; j < DS; ++j)
             if (i + j < count) {
-                multiply(ring[j]);
-                if (i + j + D < count) load(ring[j], i + j + D);
+                multiply(ring[j], i + j);
+                if (i + j + DS < count) load(ring[j], i + j + DS);
             }
 #pragma unroll
-        for (int j = 0; j < D; ++j)
-            if (i + D + j < count) multiply(ring[j]);
+        for (int j = 0; j < DS; ++j)
+            if (i + DS + j < count) multiply(ring[j], i + DS + j);
     }
     if constexpr (ANYK) {
-        if (has_rest) multiply(rest);
+        if (has_rest) multiply(rest, 0);
     }
 
     // The waves' sums meet in LDS, as many row tiles at a time as fit; wave w finishes the output tiles w, w + NW, ...
@@ -252,7 +316,7 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
     const float s = qk.s;
 #pragma unroll
     for (int b0 = 0; b0 < MT; b0 += kRows) {
-        if (b0 > 0) __syncthreads();
+        if (b0 > 0 || kTurn > 0) __syncthreads();
 #pragma unroll
         for (int g = 0; g < NT; ++g)
 #pragma unroll
@@ -306,7 +370,7 @@ template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, 
 __global__ __launch_bounds__(64 * NW)
 void skinny_kernel(const LinBatch b, int a_bits, int32_t* __restrict__ acc_out)
 {
-    __shared__ __attribute__((aligned(1024))) char lds[NW * NT * skinny_rows_per_phase<MT, NT, NW>() * 1024];
+    __shared__ __attribute__((aligned(1024))) char lds[skinny_lds_bytes<WMODE, MT, NT, NW, QX, EVEN, false, ANYK>()];
     const int k = lin_item_of(b, (int)blockIdx.x);
     // Eight neighbours in the id go to the eight XCDs: the row blocks of one run of weight rows stay on one, 8 ids apart.
     const int id = (int)blockIdx.x - b.first_block[k], octet = id >> 3, tiles_m = b.it[k].tiles_m;
@@ -332,29 +396,54 @@ static void launch_one(LinBatch& b, int a_bits, int32_t* acc_out, hipStream_t st
     skinny_kernel<DT, WMODE, MT, NT, NW, D, QX, ONCE, EVEN, ANYK><<<b.first_block[b.count], 64 * NW, 0, st>>>(b, a_bits, acc_out);
 }
 
+// Row-major weights of a call up to half of the 256 MB Infinity Cache keep the ordinary cache policy, as they may be found there by the
+// next call.  us, ordinary | non-temporal, found there: 8 x 4096 -> 11008 10.1 | 12.2, attention, hidden 4096, of 20 rows 15.9 | 18.4; not
+// found: 13.1 | 12.4 and 20.0 | 18.7; the 7B layer, 202 MB, 8 rows 40 | 36.
+constexpr int64_t kCachedWeights = INT64_C(128) << 20;
+static int64_t weight_bytes(const LinBatch& b)
+{
+    int64_t n = 0;
+    for (int i = 0; i < b.count; ++i) n += (int64_t)b.it[i].N * b.it[i].K;
+    return n;
+}
+
 // Wide or narrow workgroups: the narrow form (16 weight rows, K over eight waves) gives more workgroups for the same weights, the
 // wide one reads the activations half or a quarter as often.  Measured at 8 rows, int8, wide (then K over four waves) | narrow:
 // 4096 x 4096 (256 tiles of 16 rows) 8.3 | 6.5 us, 4096 x 11008 17.3 | 12.8, 11008 x 4096 (688 tiles) 12.3 | 13.4, the 7B
 // layer (2656 tiles) 36 | 51; the line lies at 512 tiles.
-// Waves of the wide form, four with four K tiles in flight | eight with three: the 7B layer at 8 rows 35.0 | 35.0, its MLP 29.7 |
-// 26.4, 8192 x 16384 28.0 | 25.7; row-major int8, whose lines are shared between K tiles, 7B layer 50.9 | 51.3.
-template <int DT, int WMODE, int MT, bool QX, bool ANYK = false>
+// Waves of the wide form and K tiles each has in flight, quantizing in the kernel, us, eight with three | eight with two | four with four |
+// four with six: the 7B layer at 8 rows 37.3 | 35.9 | 34.9 | 35.9, at 16 44.2 | 40.4 | 38.7 | 40.3, hidden 2048 at 12 15.3 | 14.4 | 12.8 |
+// 13.9, 8 x 8192 -> 16384 28.8 | 28.1 | 31.4 | 28.5, 8192 -> 28672 (512 and 896 workgroups, rows of 128 K tiles) - | 44.9 | 47.1 | 44.8:
+// six where the rows are 8192 and more codes long.  With codes from the pre-pass eight with three: MLP of 30 rows 32.5 | - | 36.0 | 32.1,
+// hidden 2048 at 24 17.1 | - | 18.9 | 19.1.  int4, blocks twice as wide, the 13B layer at 16 rows, eight with two | four with two, three,
+// four: 35.2 | 45.7, 35.2, 33.4, at one row 26.9 | 31.9, 27.3, 26.6.  Row-major, in steps of two K tiles, layer at 1, 8, 16 rows, four waves with
+// four | four with two | eight with two: 39.9, 39.3, 42.5 | 34.7, 36.2, 41.0 | 33.6, 36.4, 42.2; row tiles of 32, MLP of 30 rows 34.1 | 36.9 | 33.7,
+// of 20 rows, hidden 2048, 12.7 | 13.4 | 13.1; narrow, 30 and 40 x 4096 -> 4096, eight with four | two: 9.4, 10.1 | 8.7, 9.5.
+template <int DT, int WMODE, int MT, bool QX, bool ANYK = false, bool ONCE = true>
 static void launch_mt(LinBatch& b, int64_t tiles16, int a_bits, int32_t* acc_out, hipStream_t st)
 {
-    const bool wide = tiles16 >= 512;
+    if constexpr (WMODE == 0 && !ANYK && ONCE) {
+        if (weight_bytes(b) <= kCachedWeights) return launch_mt<DT, WMODE, MT, QX, ANYK, false>(b, tiles16, a_bits, acc_out, st);
+    }
+    const bool wide = tiles16 >= 512, long_rows = weight_bytes(b) >= 8192 * 16 * tiles16;
     if constexpr (ANYK) {                              // as row-major int8 below
         if (!wide)                 launch_one<DT, WMODE, MT, 1, 8, 4, QX, true, false, true>(b, a_bits, acc_out, st);
         else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, false, true>(b, a_bits, acc_out, st);
         else                       launch_one<DT, WMODE, MT, 2, 4, 4, QX, true, false, true>(b, a_bits, acc_out, st);
     } else if constexpr (WMODE == 3) {                 // int4: half the bytes per tile, a block is two tiles
         if (!wide)             launch_one<DT, WMODE, MT, 2, 8, 2, QX, true, false>(b, a_bits, acc_out, st);
-        else if constexpr (QX) launch_one<DT, WMODE, MT, 4, 8, 2, QX, true, false>(b, a_bits, acc_out, st);
+        else if constexpr (QX) launch_one<DT, WMODE, MT, 4, 4, 4, QX, true, false>(b, a_bits, acc_out, st);
         else                   launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, false>(b, a_bits, acc_out, st);
+    } else if constexpr (WMODE == 0) {
+        if (!wide)                 launch_one<DT, WMODE, MT, 1, 8, 2, QX, ONCE, false>(b, a_bits, acc_out, st);
+        else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, ONCE, false>(b, a_bits, acc_out, st);
+        else                       launch_one<DT, WMODE, MT, 2, 4, MT == 1 ? 2 : 4, QX, ONCE, false>(b, a_bits, acc_out, st);
     } else {
-        if (!wide)               launch_one<DT, WMODE, MT, 1, 8, 4, QX, true, false>(b, a_bits, acc_out, st);
+        if (!wide)                 launch_one<DT, WMODE, MT, 1, 8, 4, QX, true, false>(b, a_bits, acc_out, st);
         else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, false>(b, a_bits, acc_out, st);
-        else if constexpr (WMODE == 0) launch_one<DT, WMODE, MT, 2, 4, 4, QX, true, false>(b, a_bits, acc_out, st);
-        else                     launch_one<DT, WMODE, MT, 2, 8, 3, QX, true, false>(b, a_bits, acc_out, st);
+        else if constexpr (!QX)    launch_one<DT, WMODE, MT, 2, 8, 3, QX, true, false>(b, a_bits, acc_out, st);
+        else if (long_rows)        launch_one<DT, WMODE, MT, 2, 4, 6, QX, true, false>(b, a_bits, acc_out, st);
+        else                       launch_one<DT, WMODE, MT, 2, 4, 4, QX, true, false>(b, a_bits, acc_out, st);
     }
 }
 
@@ -629,7 +718,7 @@ template <int DT, int MT, int NT, int NW, int D, bool ONCE, bool EVEN>
 __global__ __launch_bounds__(64 * NW)
 void bwd_skinny_kernel(const LinItem it, float* __restrict__ acc_out)
 {
-    __shared__ __attribute__((aligned(1024))) char lds[NW * NT * skinny_rows_per_phase<MT, NT, NW>() * 1024];
+    __shared__ __attribute__((aligned(1024))) char lds[skinny_lds_bytes<2, MT, NT, NW, false, EVEN, true, false>()];
     const int id = (int)blockIdx.x, octet = id >> 3;                 // as in skinny_kernel
     const int mblk = octet % it.tiles_m, nblk = octet / it.tiles_m * 8 + (id & 7);
     if (nblk >= it.tiles_n) return;
