@@ -1,4 +1,4 @@
-// Host-side interface of the 16x16x64 int8 GEMM kernels (static_linear_k64.hip), used by the entry
+// Host-side interface of the 16x16x64 int8 GEMM kernels (static_linear_k64.hip, grouped_k64.hip), used by the entry
 // points in static_linear.hip.
 #pragma once
 

@@ -1,6 +1,6 @@
 // The tile body shared by the GEMM kernels on the 16-row MFMA shapes (v_mfma_i32_16x16x64_i8 for the static linear,
 // v_mfma_f32_16x16x32_{f16,bf16} for the backward of the frozen linear): K pipeline, fragment reads, epilogue.
-// Included by static_linear_k64.hip and linear_bwd.hip; the description of the machine shape is at the top of the former.
+// Included by static_linear_k64.hip, grouped_k64.hip and linear_bwd.hip; the description of the machine shape is at the top of the former.
 #pragma once
 
 #include "sasq_device.h"
@@ -31,6 +31,10 @@ template <> struct Mfma16x16<SASQ_BF16> {
 // moved to the high half of a byte is the int8 value 16 w, so two mask/shift operations per dword turn 8 nibbles into
 // 8 bytes; the accumulators are then exactly 16 acc and are shifted back in the epilogue).
 enum { KW_I8 = 0, KW_I8B = 2, KW_I4B = 3 };
+
+// Groups of channels with a factor each (GROUPED below): none; 32 channels, half a K tile; one K tile; two; a multiple of four; another even
+// number; another odd one.
+enum { GR_NONE = 0, GR_HALF, GR_ONE, GR_TWO, GR_FOURS, GR_EVEN, GR_ODD };
 
 constexpr int kFacBytes = 1024;      // per wave: the epilogue's per-column factors (BN/2 floats, loaded twice over)
 template <int BM, int BN> constexpr int lds_bytes_k64() { return Tile<BM, BN>::kLds + 4 * kFacBytes; }
@@ -72,7 +76,7 @@ __device__ __forceinline__ void lds_load16(uint32_t lds_a, uint32_t lds_b, const
 // f = fma(fl32(acc), s_g, f) in ascending group order; the epilogue applies s_w and the bias to f,
 // and acc_out receives f (as float bits).  Tiles of 128 rows only (f doubles the accumulator registers);
 // with 128x128 tiles two waves share a SIMD and one wave's fold runs under the other's MFMAs.
-// GROUPED = 2: groups of 32 channels, two per K tile.  One MFMA contracts the whole 64-byte stage, so every K tile
+// GR_HALF: groups of 32 channels, two per K tile.  One MFMA contracts the whole 64-byte stage, so every K tile
 // is multiplied twice, once with the activation fragments of channels 32..63 zeroed and once with those of 0..31
 // zeroed (lanes 32..63 resp. 0..31 of a fragment), each pass into zero accumulators and folded with its own factor:
 // twice the matrix work and a fold per 32 channels, and faster than sums on the VALUs all the same.
@@ -86,7 +90,7 @@ __device__ __forceinline__ void lds_load16(uint32_t lds_a, uint32_t lds_b, const
 // apart.  X has a ring of its own, three slots of two K tiles, that fills the LDS to its 160 KB (256x256) and is requested four to five
 // K tiles ahead.  us, halves | lines, operands from memory: f16 4096 x 11008 -> 4096 281 | 246, 4096 x 4096 -> 11008 286 | 272, bf16 282 |
 // 237 and 275 | 261, 8192^3 735 | 691, 1024 x 5120 -> 5120 77 | 65, 777 x 4096 -> 4096 31.3 | 28.8; in the caches 268 | 264.
-template <int DT, int WMODE, int BM, int BN, bool ROWS, int GROUPED = 0, int OP = 0>
+template <int DT, int WMODE, int BM, int BN, bool ROWS, int GROUPED = GR_NONE, int OP = 0>
 __device__ __forceinline__
 void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq,
                    const float* __restrict__ s_ptr, const float* __restrict__ s_w,
@@ -97,6 +101,7 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
     static_assert(!GROUPED || (BM == 128 && !ROWS), "grouped factors: 128-row tiles");
     static_assert(OP == 0 || (WMODE == KW_I8B && !ROWS && !GROUPED), "float contraction: pre-arranged weight blocks, no factors");
     constexpr bool FLT = OP != 0, XL = OP == 2;
+    constexpr bool WHOLE = GROUPED && GROUPED != GR_HALF && GROUPED != GR_ONE;       // groups of whole K tiles
     using AccT = std::conditional_t<FLT, f32x4, i32x4>;
     using S = Store16<DT>;
     using T = Tile<BM, BN>;
@@ -226,8 +231,10 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
     constexpr int kFragStep = NM / 2 / NFR >= 1 ? NM / 2 / NFR : 1;
     constexpr int kLoadStep = (NM - kFragStep * NFR) / kLoads;
     static_assert(kLoadStep >= 1, "side work does not fit behind the MFMAs");
-    auto fold = [&](int group_idx) {                           // f = fma(fl32(acc), s_g, f) for every accumulator
-        const float sg = s_ptr[GROUPED ? group_idx : 0];
+    // The constant address space keeps a group's factor a scalar load; as a vector load it would stand behind the stages' loads and wait
+    // for all of them.
+    const auto factors = (const __attribute__((address_space(4))) float*)s_ptr;
+    auto fold = [&](float sg) {                                // f = fma(fl32(acc), s_g, f) for every accumulator
 #pragma unroll
         for (int g = 0; g < NF; ++g)
 #pragma unroll
@@ -258,8 +265,8 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
         const bool more = !TAIL || i + 1 < KT;                 // a next tile to read fragments of
         const int rodd = STG >= 0 ? (STG + 1) & 1 : (i + 1) & 1;
         const uint32_t rslot = !XL ? 0 : STG >= 0 ? (STG == 0 ? slot0 : STG == 3 ? slot2 : slot1) : (uint32_t)(((i + 1) >> 1) % kXSlots * kXSlot);
-        i32x4 xhalf[GROUPED == 2 ? MF : 1];                    // GROUPED 2: the fragments with one half of the channels zeroed
-        if constexpr (GROUPED == 2) {
+        i32x4 xhalf[GROUPED == GR_HALF ? MF : 1];                    // groups of 32: the fragments with one half of the channels zeroed
+        if constexpr (GROUPED == GR_HALF) {
 #pragma unroll
             for (int b = 0; b < MF; ++b) xhalf[b] = fq < 2 ? fx[CUR][b] : i32x4{0, 0, 0, 0};
         }
@@ -284,7 +291,7 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
                     acc[g][b] = Mfma16x16<DT>::mma(wv, fx[CUR][b], FIRST ? zero : acc[g][b]);
                 } else {
                     const i32x4 zero = {0, 0, 0, 0};
-                    acc[g][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wv, GROUPED == 2 ? xhalf[GROUPED == 2 ? b : 0] : fx[CUR][b],
+                    acc[g][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wv, GROUPED == GR_HALF ? xhalf[GROUPED == GR_HALF ? b : 0] : fx[CUR][b],
                                                                       FIRST ? zero : acc[g][b], 0, 0, 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -294,7 +301,8 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
                 } else if (!TAIL || i + 4 < KT) {
                     const int u = t - kFragStep * NFR;
                     if (u % kLoadStep == 0 && u / kLoadStep < kLoads) {
-                        if constexpr (STG >= 0) dma_at(xrun + (XL ? (STG + 5) / 2 * 2 : STG + 4) * kXTileStep, wrun + (STG + 4) * kWTileStep, u / kLoadStep, STG,
+                        if constexpr (WHOLE) dma(min(i + 4, KT - 1), u / kLoadStep, STG >= 0 ? STG : i & 3);
+                        else if constexpr (STG >= 0) dma_at(xrun + (XL ? (STG + 5) / 2 * 2 : STG + 4) * kXTileStep, wrun + (STG + 4) * kWTileStep, u / kLoadStep, STG,
                                                        1 - (STG & 1), STG == 0 ? slot2 : STG == 3 ? slot1 : slot0);
                         else                    dma(i + 4, u / kLoadStep, i & 3);
                     }
@@ -306,9 +314,9 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
             }
             if constexpr (I4) wv_ahead = wv_next;
         }
-        if constexpr (GROUPED == 2) {
+        if constexpr (GROUPED == GR_HALF) {
             // channels 0..31 of this K tile are in acc: fold them, then the same tile with channels 32..63
-            fold(2 * i);
+            fold(factors[2 * i]);
 #pragma unroll
             for (int b = 0; b < MF; ++b) xhalf[b] = fq < 2 ? i32x4{0, 0, 0, 0} : fx[CUR][b];
 #pragma unroll
@@ -316,9 +324,9 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
                 const i32x4 wv = wfrag(fw[CUR][g]);
 #pragma unroll
                 for (int b = 0; b < MF; ++b)
-                    acc[g][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wv, xhalf[GROUPED == 2 ? b : 0], i32x4{0, 0, 0, 0}, 0, 0, 0);
+                    acc[g][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wv, xhalf[GROUPED == GR_HALF ? b : 0], i32x4{0, 0, 0, 0}, 0, 0, 0);
             }
-            fold(2 * i + 1);
+            fold(factors[2 * i + 1]);
         }
     };
     using C0 = std::integral_constant<int, 0>;
@@ -330,33 +338,26 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
     using SR = std::integral_constant<int, -1>;               // stage known only at run time
     using Yes = std::true_type;
     using No = std::false_type;
-    // one K tile; with grouped factors also the group bookkeeping (all of it uniform)
-    int in_group = 0, group_idx = 0;
     auto step = [&](int i, auto cur_tag, auto stage_tag, auto first_tag, auto tail_tag) {
-        if constexpr (!GROUPED) {
-            iteration(i, cur_tag, stage_tag, first_tag, tail_tag);
-        } else if constexpr (GROUPED == 2) {
+        if constexpr (GROUPED == GR_HALF) {
             iteration(i, cur_tag, stage_tag, Yes{}, tail_tag);     // both folds of the tile happen inside
+        } else if constexpr (GROUPED == GR_ONE) {
+            iteration(i, cur_tag, stage_tag, Yes{}, tail_tag);
+            fold(factors[i]);
         } else {
-            if (in_group == 0) iteration(i, cur_tag, stage_tag, Yes{}, tail_tag);
-            else               iteration(i, cur_tag, stage_tag, No{}, tail_tag);
-            if (++in_group == group_tiles) {
-                fold(group_idx);
-                in_group = 0;
-                ++group_idx;
-            }
+            iteration(i, cur_tag, stage_tag, first_tag, tail_tag);
         }
     };
     SASQ_TILE_TS(0);
     // fill: the first four tiles requested, tile 0 landed for everyone, its fragments read
-    const int nfill = min(KT, 4);
+    const int nfill = WHOLE ? 4 : min(KT, 4);
     if constexpr (XL) {
 #pragma unroll
         for (int j = 0; j < XS; ++j) dma(-1, j, 3);            // the first pair's first halves
     }
     for (int t = 0; t < nfill; ++t)
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) dma(t, j, t);
+        for (int j = 0; j < kLoads; ++j) dma(WHOLE ? min(t, KT - 1) : t, j, t);
     if (nfill == 4)      __builtin_amdgcn_s_waitcnt(waitcnt_vm(3 * kLoads));
     else if (nfill == 3) __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * kLoads));
     else if (nfill == 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm(kLoads));
@@ -371,22 +372,9 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
     // The steady loop is written out four iterations at a time: every copy of the body then knows
     // its fragment set and its LDS stages at compile time, and the addresses of its fragment reads
     // and loads are constants instead of a chain of scalar arithmetic in front of the first read.
-    // (Whole-tile groups keep two iterations with run-time stages: their body exists once per accumulator
-    // mode already, and four copies of each push the register allocator into scratch memory.)
-    constexpr bool kBy4 = GROUPED != 1;
     // XL: its last steady iteration requests the first halves of a pair that is there.
-    const int steady = XL ? (KT >= 10 ? ((KT - 6) & ~3) : 0) : !kBy4 ? (KT >= 6 ? ((KT - 4) & ~1) : 0) : KT >= 8 ? ((KT - 4) & ~3) : 0;
-    if constexpr (!kBy4) {
-        if (steady > 0) {
-            step(0, C0{}, SR{}, Yes{}, No{});
-            step(1, C1{}, SR{}, No{}, No{});
-#pragma unroll 1
-            for (int it = 2; it < steady; it += 2) {
-                step(it, C0{}, SR{}, No{}, No{});
-                step(it + 1, C1{}, SR{}, No{}, No{});
-            }
-        }
-    } else if (steady > 0) {
+    const int steady = XL ? (KT >= 10 ? ((KT - 6) & ~3) : 0) : WHOLE ? 0 : KT >= 8 ? ((KT - 4) & ~3) : 0;
+    if (!WHOLE && steady > 0) {
         step(0, C0{}, S0{}, Yes{}, No{});
         step(1, C1{}, S1{}, No{}, No{});
         step(2, C0{}, S2{}, No{}, No{});
@@ -423,23 +411,89 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
     if (cols_inside)
         lds_load16(lds_base - (uint32_t)wave * 1024u + T::kLds + (uint32_t)wave * kFacBytes, s_w + wn0,
                    (uint32_t)(lane & (BN / 8 - 1)) * 16u);   // lanes past BN/8 fetch the same factors again: no lane reads past the block
-    if constexpr (kBy4) {
+    if constexpr (WHOLE) {
+        // Groups in straight lines: where a branch decided between the first K tile's body and the others', the compiler kept the
+        // accumulators of both apart and spilled inside the loop.  Requests are unconditional: past the end the last tile comes again and
+        // a stage's old fragments are read, which nothing uses.  us, branches and a separate tail | straight lines, int8: 2048 x 4096 ->
+        // 11008 in groups of 64, 128, 256 164, 141, 134 | 157, 138, 123; 2048 x 4096 -> 4096 64, 53, 50 | 61, 49, 45; 700 x 8192 -> 5000 76,
+        // 62, 53 | 69, 54, 46; int4, 2048 x 4096 -> 11008 187, 156, 134 | 185, 145, 130.  One K tile a group takes the loop of the plain GEMM.
+        // Not kept: the fold tile by tile between the next group's first MFMAs (128, 256, 512: 148, 124, 116 against 139, 123, 120).
+        auto first = [&](int i, auto cur_tag, auto stage_tag) { iteration(i, cur_tag, stage_tag, Yes{}, No{}); };
+        auto rest = [&](int i, auto cur_tag, auto stage_tag) { iteration(i, cur_tag, stage_tag, No{}, No{}); };
+        auto rest_of_group = [&](int& i, int tiles, auto cur_tag) {      // an even number of tiles
+            using CUR = decltype(cur_tag);
+#pragma unroll 1
+            for (; tiles > 0; tiles -= 2, i += 2) {
+                rest(i, CUR{}, SR{});
+                rest(i + 1, std::integral_constant<int, 1 - CUR::value>{}, SR{});
+            }
+        };
+        // A group's factor is requested when the one before it is folded: it then lands under the K tiles between.
+        const int groups = KT / group_tiles;
+        int group_idx = 0;
+        float sg = factors[0];
+        auto fold_group = [&] {
+            fold(sg);
+            group_idx = min(group_idx + 1, groups - 1);
+            sg = factors[group_idx];
+        };
+        int i = 0;
+        if constexpr (GROUPED == GR_TWO) {                          // two K tiles each, stages known in every copy of the body
+            auto group = [&](auto stage_tag) {
+                constexpr int S = decltype(stage_tag)::value;
+                first(i + S, C0{}, stage_tag);
+                rest(i + S + 1, C1{}, std::integral_constant<int, S + 1>{});
+                fold_group();
+            };
+#pragma unroll 1
+            for (; i + 4 <= KT; i += 4) {
+                group(S0{});
+                group(S2{});
+            }
+            if (i < KT) group(S0{});
+        } else if constexpr (GROUPED == GR_FOURS) {                   // multiples of four
+#pragma unroll 1
+            do {
+                first(i, C0{}, S0{});
+                rest(i + 1, C1{}, S1{});
+                rest(i + 2, C0{}, S2{});
+                rest(i + 3, C1{}, S3{});
+                i += 4;
+#pragma unroll 1
+                for (int tiles = group_tiles - 4; tiles > 0; tiles -= 4, i += 4) {
+                    rest(i, C0{}, S0{});
+                    rest(i + 1, C1{}, S1{});
+                    rest(i + 2, C0{}, S2{});
+                    rest(i + 3, C1{}, S3{});
+                }
+                fold_group();
+            } while (i < KT);
+        } else if constexpr (GROUPED == GR_EVEN) {                   // other even numbers
+#pragma unroll 1
+            do {
+                first(i, C0{}, SR{});
+                rest(i + 1, C1{}, SR{});
+                i += 2;
+                rest_of_group(i, group_tiles - 2, C0{});
+                fold_group();
+            } while (i < KT);
+        } else {                                               // an odd number: the next group's fragments move back to set 0
+#pragma unroll 1
+            do {
+                first(i++, C0{}, SR{});
+                rest_of_group(i, group_tiles - 1, C1{});
+                fold_group();
+#pragma unroll
+                for (int b = 0; b < MF; ++b) fx[0][b] = fx[1][b];
+#pragma unroll
+                for (int g = 0; g < NF; ++g) fw[0][g] = fw[1][g];
+            } while (i < KT);
+        }
+    } else {
 #pragma unroll 1
         for (int i = steady; i < KT; i += 2) {                  // KT - steady is 1 .. 9, steady is even
             step(i, C0{}, SR{}, No{}, Yes{});
             if (i + 1 < KT) step(i + 1, C1{}, SR{}, No{}, Yes{});
-        }
-    } else {
-        step(steady, C0{}, SR{}, No{}, Yes{});                  // KT - steady is 1 .. 5
-        if (steady + 1 < KT) {
-            step(steady + 1, C1{}, SR{}, No{}, Yes{});
-            if (steady + 2 < KT) {
-                step(steady + 2, C0{}, SR{}, No{}, Yes{});
-                if (steady + 3 < KT) {
-                    step(steady + 3, C1{}, SR{}, No{}, Yes{});
-                    if (steady + 4 < KT) step(steady + 4, C0{}, SR{}, No{}, Yes{});
-                }
-            }
         }
     }
     SASQ_TILE_TS(2);
