@@ -2,8 +2,8 @@
 // 1376), row-major weights with any row alignment, over row-major activation codes.  (Few rows of int8: static_linear_skinny.hip.)
 //
 // What bounds it: at 1000 x 4096 x 1376 the 17 MB of operands and output take 3 us and the 11.3 G operations as much; the
-// rest is the latency of a short K loop.  One thread per output walking its row and column byte by byte took 10.65 ms
-// there, this kernel with its pre-pass 19.4 us (0.58 POP/s).
+// rest is the latency of a short K loop and the operands out of the L2s.  One thread per output walking its row and column byte by byte took
+// 10.65 ms there, this kernel with its pre-pass 18.1 us on 64x128 tiles of four waves, 16.5 on 128x128 tiles of eight (0.68 POP/s).
 // The pre-arranged formats and the direct memory -> LDS loads of the other GEMMs need rows of whole 16-byte pieces.  Here a
 // row starts at any byte, so 16 codes travel through registers: an unaligned 128-bit load (the memory pipeline splits it
 // where it has to), requested D stages ahead, then an aligned LDS write.  A stage is 128 channels, so that a row's piece is
@@ -18,17 +18,18 @@ namespace sasq {
 
 constexpr int kAnyStage = 128;                     // channels per LDS stage
 
-// Four waves, 2 x 2, each (BM/2) x (BN/2) of the tile as 16x16 tiles of v_mfma_i32_16x16x64_i8; two LDS buffers, D stages
+// WM x 2 waves, each (BM/WM) x (BN/2) of the tile as 16x16 tiles of v_mfma_i32_16x16x64_i8; two LDS buffers, D stages
 // in flight in registers.  LDS rows are 128 bytes, 16-byte chunk c of row r at position c ^ (r & 7).
-template <int DT, bool INT4, bool ROWS, int BM, int BN, int D>
-__global__ __launch_bounds__(256, 2) void linear_anyk_kernel(
+template <int DT, bool INT4, bool ROWS, int BM, int BN, int D, int WM = 2>
+__global__ __launch_bounds__(128 * WM, 2) void linear_anyk_kernel(
     const uint8_t* __restrict__ xq, const uint8_t* __restrict__ wq, const float* __restrict__ s_ptr,
     const float* __restrict__ s_w, const float* __restrict__ bias, uint16_t* __restrict__ y,
     int32_t* __restrict__ acc_out, int M, int N, int K, int tiles_m, int tiles_n, int first)
 {
     using S = Store16<DT>;
     using WPiece = std::conditional_t<INT4, u32x2, u32x4>;
-    constexpr int MF = BM / 32, NF = BN / 32, XL = BM / 32, WL = BN / 32;
+    constexpr int kRows = 16 * WM;                                 // rows that a load of every thread takes
+    constexpr int MF = BM / (16 * WM), NF = BN / 32, XL = BM / kRows, WL = BN / kRows;
     constexpr int kXBytes = BM * kAnyStage, kBufBytes = (BM + BN) * kAnyStage;
     static_assert(D % 2 == 0, "the unrolled loop knows its LDS buffer at compile time");
     __shared__ __attribute__((aligned(128))) char lds[2 * kBufBytes];
@@ -40,15 +41,15 @@ __global__ __launch_bounds__(256, 2) void linear_anyk_kernel(
     const int stages = (K + kAnyStage - 1) / kAnyStage;
     const int wlen = INT4 ? K / 2 : K;                             // bytes of a weight row
 
-    // thread t moves chunk t%8 of rows t/8 + 32 j; rows past the edge repeat the last one
+    // thread t moves chunk t%8 of rows t/8 + kRows j; rows past the edge repeat the last one
     const int lrow = tid >> 3, lch = tid & 7;
     const uint8_t* xb = xq + (int64_t)m0 * K;
     const uint8_t* wb = wq + (int64_t)n0 * wlen;
     uint32_t xo[XL], wo[WL];                                       // at most 128 rows of 131071 bytes
 #pragma unroll
-    for (int j = 0; j < XL; ++j) xo[j] = (uint32_t)min(lrow + 32 * j, M - 1 - m0) * (uint32_t)K;
+    for (int j = 0; j < XL; ++j) xo[j] = (uint32_t)min(lrow + kRows * j, M - 1 - m0) * (uint32_t)K;
 #pragma unroll
-    for (int j = 0; j < WL; ++j) wo[j] = (uint32_t)min(lrow + 32 * j, N - 1 - n0) * (uint32_t)wlen;
+    for (int j = 0; j < WL; ++j) wo[j] = (uint32_t)min(lrow + kRows * j, N - 1 - n0) * (uint32_t)wlen;
     struct Regs { u32x4 x[XL]; WPiece w[WL]; };
     Regs ring[D];
     constexpr int kWPiece = (int)sizeof(WPiece);
@@ -69,13 +70,13 @@ __global__ __launch_bounds__(256, 2) void linear_anyk_kernel(
     auto put = [&](const Regs& r, int buf) {
         char* base = &lds[buf * kBufBytes];
 #pragma unroll
-        for (int j = 0; j < XL; ++j) *reinterpret_cast<u32x4*>(base + slot + j * 32 * kAnyStage) = r.x[j];
+        for (int j = 0; j < XL; ++j) *reinterpret_cast<u32x4*>(base + slot + j * kRows * kAnyStage) = r.x[j];
 #pragma unroll
         for (int j = 0; j < WL; ++j) {
             u32x4 v;
             if constexpr (INT4) v = widen_int4(r.w[j]);
             else                v = r.w[j];
-            *reinterpret_cast<u32x4*>(base + kXBytes + slot + j * 32 * kAnyStage) = v;
+            *reinterpret_cast<u32x4*>(base + kXBytes + slot + j * kRows * kAnyStage) = v;
         }
     };
     // this wave's LDS traffic is done, then everyone's
@@ -87,7 +88,7 @@ __global__ __launch_bounds__(256, 2) void linear_anyk_kernel(
     };
 
     const int frow = lane & 15, fq = lane >> 4;
-    const int xbase = (wave & 1) * (BM / 2) * kAnyStage, wbase = kXBytes + (wave >> 1) * (BN / 2) * kAnyStage;
+    const int xbase = wave % WM * (BM / WM) * kAnyStage, wbase = kXBytes + wave / WM * (BN / 2) * kAnyStage;
     i32x4 acc[NF][MF];
 #pragma unroll
     for (int g = 0; g < NF; ++g)
@@ -110,7 +111,7 @@ __global__ __launch_bounds__(256, 2) void linear_anyk_kernel(
         }
     };
 
-    const int wn0 = n0 + (wave >> 1) * (BN / 2), wm0 = m0 + (wave & 1) * (BM / 2);
+    const int wn0 = n0 + wave / WM * (BN / 2), wm0 = m0 + wave % WM * (BM / WM);
     float srow[MF], sw[NF][4], bv[NF][4];
     auto load_factors = [&]() {
 #pragma unroll
@@ -218,21 +219,32 @@ __global__ __launch_bounds__(256) void linear_short_row_kernel(
     if (acc_out) acc_out[i] = acc;
 }
 
-template <int DT, bool INT4, bool ROWS, int BM, int BN, int D>
+template <int DT, bool INT4, bool ROWS, int BM, int BN, int D, int WM = 2>
 static void launch_anyk_one(const GemmK64Args& a, hipStream_t st)
 {
     const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (int)((a.N + BN - 1) / BN);
-    launch_in_parts((tiles_m * tiles_n + 7) / 8 * 8, 256, [&](unsigned blocks, int first) {
-        linear_anyk_kernel<DT, INT4, ROWS, BM, BN, D><<<blocks, 256, 0, st>>>(
+    launch_in_parts((tiles_m * tiles_n + 7) / 8 * 8, 128 * WM, [&](unsigned blocks, int first) {
+        linear_anyk_kernel<DT, INT4, ROWS, BM, BN, D, WM><<<blocks, 128 * WM, 0, st>>>(
             reinterpret_cast<const uint8_t*>(a.xq), a.wq, a.s, a.s_w, a.bias, a.y, a.acc_out, (int)a.M, (int)a.N, (int)a.K, tiles_m, tiles_n, first);
     });
 }
 
-// Big tiles read the operands less often, small ones put more CUs to work.  Measured, int8, us on 128x128 / 64x128 / 64x64 /
-// 32x64 tiles: 4096 x 4096 x 1376 (1024 tiles of 128x128) 48.0 / 52.5 / 65.3, 2000 x 4096 x 1376 (512) 28.2 / 33.1 / 36.5,
-// 1500 x 4096 x 4000 (384) 49.7 / 49.3 / 60.9, 1000 x 4096 x 1376 (256; 512 of 64x128) 20.0 / 19.4 / 23.2 / 26.4;
-// 512 x 1024 x 3000 (64 of 64x128, 256 of 32x64) 28.2 / 21.5 / 16.3 / 14.9, 64 x 4096 x 3976 (128 of 32x64) 31.3 / 24.8 /
-// 19.4 / 16.7.
+// Big tiles read the operands less often, small ones put more CUs to work.  Eight waves a workgroup from 64x128 tiles on: the loads in
+// flight that it takes to keep the L2s busy then fit a tile of twice the outputs, which asks for three quarters of the operands (rows that
+// begin inside cache lines cost two lines for most of their pieces).  Measured, us with the pre-pass, the earlier choice of 128x128, 64x128
+// (from 256 tiles) and smaller tiles of four waves | 64x128 | 128x128 | 256x128 of eight, by number of 128x128 tiles:
+//   96: 333 x 4000, K = 1376 int8 12.4 | 12.3 | 15.2 | 21.6, K = 1801 19.1 | 16.6 | 20.8 | 30.5, int4 15.2 | 14.7 | 17.6 | 23.2
+//   128: 1000 x 2048, K = 1376 15.2 | 13.8 | 16.6 | 23.2, K = 3976 30.0 | 28.4 | 32.9 | 47.5, int4 39.6 | 34.3 | 38.7 | 52.2
+//   160: 1000 x 2560, K = 1376 18.8 | 18.4 | 17.2 | 23.9, K = 1801 28.2 | 28.0 | 23.1 | 33.5, int4 23.6 | 22.0 | 19.2 | 25.5
+//   256: 1000 x 4096, K = 1376 20.5 | 19.6 | 18.7 | 24.6, K = 3976 42.1 | 42.8 | 35.7 | 49.2, int4 55.8 | 56.1 | 42.1 | 55.1
+//   320: 1000 x 5000, K = 1376 25.9 | 24.8 | 24.3 | 24.6, K = 3976 57.1 | 54.9 | 51.0 | 49.0, int4 69.0 | 72.5 | 59.8 | 55.2
+//   448: 1000 x 7168, K = 1376 33.2 | 32.1 | 27.4 | 27.3, K = 3976 79.2 | 82.8 | 57.2 | 55.2, int4 93.1 | 94.4 | 68.1 | 59.8
+//   768 (384 of 256x128, a round and a half): 2000 x 6144, K = 1376 44.3 | 46.9 | 40.0 | 49.3, K = 3976 97.2 | 120 | 95.3 | 101
+//   1024 (512, two rounds): 4096 x 4096, K = 1376 56.3 | 64.7 | 53.5 | 53.3, K = 3976 126 | 160 | 124 | 115, int4 148 | 188 | 133 | 128
+// Beyond, four waves: 8192 x 16384 (8192), K = 1040 293 | - | - | 393, int4 327 | - | - | 374; and where the larger tile has many rows past the
+// end: 300 x 16385, K = 200 17.7 | - | 19.1 | -, K = 1040 25.8 | - | 27.2 | -.
+// Fewer tiles, four waves, 128x128 / 64x128 / 64x64 / 32x64: 512 x 1024 x 3000 (64 of 64x128, 256 of 32x64) 28.2 / 21.5 / 16.3 / 14.9, 64 x
+// 4096 x 3976 (128 of 32x64) 31.3 / 24.8 / 19.4 / 16.7.
 template <int DT, bool INT4, bool ROWS>
 static void launch_anyk_w(const GemmK64Args& a, hipStream_t st)
 {
@@ -243,8 +255,15 @@ static void launch_anyk_w(const GemmK64Args& a, hipStream_t st)
         return;
     }
     auto tiles = [&](int64_t bm, int64_t bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
-    if (tiles(128, 128) >= 512)     launch_anyk_one<DT, INT4, ROWS, 128, 128, 2>(a, st);
-    else if (tiles(64, 128) >= 256) launch_anyk_one<DT, INT4, ROWS, 64, 128, 2>(a, st);
+    const int64_t t256 = tiles(256, 128), t128 = tiles(128, 128), t64 = tiles(64, 128);
+    const bool mid = t128 <= 1024 && t128 * 20 <= t64 * 11;          // and at most a tenth of the rows past the matrix's end
+    // rounds of 256x128 tiles, one a CU, that are nearly full
+    const bool rounds_fill = (t256 <= 256 || t256 * 10 >= (t256 + 255) / 256 * 2304) && t256 * 20 <= t128 * 11;
+    if (mid && t128 > 256 && rounds_fill) launch_anyk_one<DT, INT4, ROWS, 256, 128, 2, 4>(a, st);
+    else if (mid && t64 > 256)      launch_anyk_one<DT, INT4, ROWS, 128, 128, 2, 4>(a, st);
+    else if (t128 >= 512)           launch_anyk_one<DT, INT4, ROWS, 128, 128, 2>(a, st);
+    else if (t64 > 256)             launch_anyk_one<DT, INT4, ROWS, 64, 128, 2>(a, st);
+    else if (t64 >= 192)            launch_anyk_one<DT, INT4, ROWS, 64, 128, 2, 4>(a, st);
     else if (tiles(64, 64) >= 256)  launch_anyk_one<DT, INT4, ROWS, 64, 64, 4>(a, st);
     else                            launch_anyk_one<DT, INT4, ROWS, 32, 64, 4>(a, st);
 }
