@@ -396,16 +396,18 @@ static void launch_one(LinBatch& b, int a_bits, int32_t* acc_out, hipStream_t st
     skinny_kernel<DT, WMODE, MT, NT, NW, D, QX, ONCE, EVEN, ANYK><<<b.first_block[b.count], 64 * NW, 0, st>>>(b, a_bits, acc_out);
 }
 
-// Row-major weights of a call up to half of the 256 MB Infinity Cache keep the ordinary cache policy, as they may be found there by the
-// next call.  us, ordinary | non-temporal, found there: 8 x 4096 -> 11008 10.1 | 12.2, attention, hidden 4096, of 20 rows 15.9 | 18.4; not
-// found: 13.1 | 12.4 and 20.0 | 18.7; the 7B layer, 202 MB, 8 rows 40 | 36.
-constexpr int64_t kCachedWeights = INT64_C(128) << 20;
 static int64_t weight_bytes(const LinBatch& b)
 {
     int64_t n = 0;
     for (int i = 0; i < b.count; ++i) n += (int64_t)b.it[i].N * b.it[i].K;
     return n;
 }
+
+// Whether a call's weights go past the caches (ONCE).  Row-major weights up to half of the 256 MB Infinity Cache keep the ordinary policy, as
+// they may be found there by the next call.  us, ordinary | non-temporal, found there: 8 x 4096 -> 11008 10.1 | 12.2, attention, hidden 4096, of
+// 20 rows 15.9 | 18.4; not found: 13.1 | 12.4 and 20.0 | 18.7; the 7B layer, 202 MB, 8 rows 40 | 36.
+constexpr int64_t kCachedWeights = INT64_C(128) << 20;
+bool linear_streams(const LinBatch& b, int wmode) { return wmode != 0 || weight_bytes(b) > kCachedWeights; }
 
 // Wide or narrow workgroups: the narrow form (16 weight rows, K over eight waves) gives more workgroups for the same weights, the
 // wide one reads the activations half or a quarter as often.  Measured at 8 rows, int8, wide (then K over four waves) | narrow:
@@ -423,7 +425,7 @@ template <int DT, int WMODE, int MT, bool QX, bool ANYK = false, bool ONCE = tru
 static void launch_mt(LinBatch& b, int64_t tiles16, int a_bits, int32_t* acc_out, hipStream_t st)
 {
     if constexpr (WMODE == 0 && !ANYK && ONCE) {
-        if (weight_bytes(b) <= kCachedWeights) return launch_mt<DT, WMODE, MT, QX, ANYK, false>(b, tiles16, a_bits, acc_out, st);
+        if (!linear_streams(b, WMODE)) return launch_mt<DT, WMODE, MT, QX, ANYK, false>(b, tiles16, a_bits, acc_out, st);
     }
     const bool wide = tiles16 >= 512, long_rows = weight_bytes(b) >= 8192 * 16 * tiles16;
     if constexpr (ANYK) {                              // as row-major int8 below
@@ -656,8 +658,11 @@ static void launch_wmode(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, hip
         else if (block == 96)                launch_one<DT, WMODE, 6, 4, 8, 2, false, true, true>(b, a_bits, acc_out, st);
         else if (rows > 128)                 launch_one<DT, WMODE, 8, 4, 8, 2, false, false, true>(b, a_bits, acc_out, st);
         else                                 launch_one<DT, WMODE, 8, 4, 8, 2, false, true, true>(b, a_bits, acc_out, st);
-    } else if (qx && rows > 32)               launch_one<DT, WMODE, 4, WMODE == 3 ? 2 : 1, 8, 2, true, true, false>(b, a_bits, acc_out, st);
-    else if (qx && rows > kSkinnyQuantRows) launch_one<DT, WMODE, 2, WMODE == 3 ? 2 : 1, 8, 2, true, true, false>(b, a_bits, acc_out, st);
+    } else if (qx && rows > kSkinnyQuantRows) {
+        constexpr bool kOnce = WMODE != 0;             // row-major: at most 8 MB (linear_quantizes_in_kernel), never streamed
+        if (rows > 32) launch_one<DT, WMODE, 4, WMODE == 3 ? 2 : 1, 8, 2, true, kOnce, false>(b, a_bits, acc_out, st);
+        else           launch_one<DT, WMODE, 2, WMODE == 3 ? 2 : 1, 8, 2, true, kOnce, false>(b, a_bits, acc_out, st);
+    }
     else if (qx)       launch_mt<DT, WMODE, 1, true>(b, tiles16, a_bits, acc_out, st);
     else if (rows <= 32) launch_mt<DT, WMODE, 2, false>(b, tiles16, a_bits, acc_out, st);
     else if (rows <= 48) launch_mt<DT, WMODE, 3, false>(b, tiles16, a_bits, acc_out, st);

@@ -44,10 +44,30 @@ class _LinBatch(ctypes.Structure):
     _fields_ = [("it", _LinItem * 8), ("first_block", ctypes.c_int * 9)] + [(f, ctypes.c_int) for f in ("count", "split_first", "split_count", "trim_rows")]
 
 
-def linear_block_rows(items, wf):
-    """Rows per workgroup of the linear's row blocks for (rows, columns, K) items of more than 64 rows, 32: small blocks, 0: the GEMM's
-    tiles (sasq::linear_block_rows)."""
+def _batch(items):
     batch = _LinBatch(count=len(items))
     for i, (m, n, k) in enumerate(items):
         batch.it[i].M, batch.it[i].N, batch.it[i].K = m, n, k
-    return _function("_ZN4sasq17linear_block_rowsERKNS_8LinBatchEi", ctypes.POINTER(_LinBatch), ctypes.c_int)(ctypes.byref(batch), wf)
+    return ctypes.byref(batch)
+
+
+def linear_block_rows(items, wf):
+    """Rows per workgroup of the linear's row blocks for (rows, columns, K) items of more than 64 rows, 32: small blocks, 0: the GEMM's
+    tiles (sasq::linear_block_rows)."""
+    return _function("_ZN4sasq17linear_block_rowsERKNS_8LinBatchEi", ctypes.POINTER(_LinBatch), ctypes.c_int)(_batch(items), wf)
+
+
+def linear_takes_few_rows(items, wf):
+    """Whether the items take the few-row, small-block or row-block kernels (sasq::linear_takes_skinny)."""
+    return bool(_function("_ZN4sasq19linear_takes_skinnyERKNS_8LinBatchEi", ctypes.POINTER(_LinBatch), ctypes.c_int)(_batch(items), wf) & 1)
+
+
+def linear_quantizes(items, wf):
+    """Whether such a call quantizes the activations in the kernel (sasq::linear_quantizes_in_kernel)."""
+    f = _function("_ZN4sasq26linear_quantizes_in_kernelERKNS_8LinBatchEib", ctypes.POINTER(_LinBatch), ctypes.c_int, ctypes.c_bool)
+    return bool(f(_batch(items), wf, False) & 1)
+
+
+def linear_streams(items, wf):
+    """Whether such a call reads its weights past the caches (sasq::linear_streams)."""
+    return bool(_function("_ZN4sasq14linear_streamsERKNS_8LinBatchEi", ctypes.POINTER(_LinBatch), ctypes.c_int)(_batch(items), wf) & 1)
