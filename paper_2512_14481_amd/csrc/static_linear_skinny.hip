@@ -405,9 +405,17 @@ static int64_t weight_bytes(const LinBatch& b)
 
 // Whether a call's weights go past the caches (ONCE).  Row-major weights up to half of the 256 MB Infinity Cache keep the ordinary policy, as
 // they may be found there by the next call.  us, ordinary | non-temporal, found there: 8 x 4096 -> 11008 10.1 | 12.2, attention, hidden 4096, of
-// 20 rows 15.9 | 18.4; not found: 13.1 | 12.4 and 20.0 | 18.7; the 7B layer, 202 MB, 8 rows 40 | 36.
+// 20 rows 15.9 | 18.4; not found: 13.1 | 12.4 and 20.0 | 18.7; the 7B layer, 202 MB, 8 rows 40 | 36.  Over 460 calls of up to 16 rows, 128 to
+// 256 MB, ordinary in parts of non-temporal: not in the caches 1.08 to 1.10, in them 0.86 to 0.89.  Rows off whole 128-byte lines (K / 64 odd)
+// keep it at any size: neighbouring pieces then share a line, which the first read would give up; 260 such calls 0.92 to 0.95 and 0.72 to 0.74.
 constexpr int64_t kCachedWeights = INT64_C(128) << 20;
-bool linear_streams(const LinBatch& b, int wmode) { return wmode != 0 || weight_bytes(b) > kCachedWeights; }
+bool linear_streams(const LinBatch& b, int wmode)
+{
+    if (wmode != 0) return true;
+    for (int i = 0; i < b.count; ++i)
+        if (b.it[i].K % 128) return false;
+    return weight_bytes(b) > kCachedWeights;
+}
 
 // Wide or narrow workgroups: the narrow form (16 weight rows, K over eight waves) gives more workgroups for the same weights, the
 // wide one reads the activations half or a quarter as often.  Measured at 8 rows, int8, wide (then K over four waves) | narrow:

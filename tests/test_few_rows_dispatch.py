@@ -22,3 +22,10 @@ def test_weights_that_the_caches_hold_are_not_streamed():
     assert not linear_streams([(8, 11008, 4096)], ROW_MAJOR) and not linear_streams([(32, 16384, 8192)], ROW_MAJOR)
     assert linear_streams([(8, 22016, 8192)], ROW_MAJOR) and linear_streams([(8, 16385, 8192)], ROW_MAJOR)
     assert linear_streams([(1, 256, 256)], BLOCKED8) and linear_streams([(1, 256, 256)], BLOCKED4)
+
+
+def test_rows_off_whole_lines_are_not_streamed():
+    """K an odd multiple of 64: two pieces of a row share most cache lines."""
+    assert not linear_streams([(8, 22016, 8256)], ROW_MAJOR) and not linear_streams([(40, 28672, 7232)], ROW_MAJOR)
+    assert not linear_streams([(8, 16384, 8192), (8, 11008, 4160)], ROW_MAJOR)
+    assert linear_streams([(8, 22016, 8320)], ROW_MAJOR) and linear_streams([(8, 22016, 8256)], BLOCKED8)
