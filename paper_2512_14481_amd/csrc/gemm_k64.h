@@ -45,6 +45,7 @@ bool linear_takes_skinny(const LinBatch& b, int wmode);
 int linear_block_rows(const LinBatch& b, int wmode);
 bool linear_quantizes_in_kernel(const LinBatch& b, int wmode, bool any_k);
 bool linear_streams(const LinBatch& b, int wmode);
+bool linear_long_rows(const LinBatch& b);
 void launch_linear_skinny(LinBatch& b, sasq_dtype dt, int wmode, bool qx, int a_bits, int32_t* acc_out, hipStream_t st);
 // The same for K that is not a multiple of 64, a single call with row-major int8 weights (row-major codes in xq).
 bool linear_anyk_takes_skinny(int64_t M, int64_t N, int64_t K);

@@ -403,6 +403,14 @@ static int64_t weight_bytes(const LinBatch& b)
     return n;
 }
 
+// Whether the weights' rows are 8192 and more codes long, on average over the columns.
+bool linear_long_rows(const LinBatch& b)
+{
+    int64_t columns = 0;
+    for (int i = 0; i < b.count; ++i) columns += b.it[i].N;
+    return weight_bytes(b) >= 8192 * columns;
+}
+
 // Whether a call's weights go past the caches (ONCE).  Row-major weights up to half of the 256 MB Infinity Cache keep the ordinary policy, as
 // they may be found there by the next call.  us, ordinary | non-temporal, found there: 8 x 4096 -> 11008 10.1 | 12.2, attention, hidden 4096, of
 // 20 rows 15.9 | 18.4; not found: 13.1 | 12.4 and 20.0 | 18.7; the 7B layer, 202 MB, 8 rows 40 | 36.  Over 460 calls of up to 16 rows, 128 to
@@ -435,7 +443,7 @@ static void launch_mt(LinBatch& b, int64_t tiles16, int a_bits, int32_t* acc_out
     if constexpr (WMODE == 0 && !ANYK && ONCE) {
         if (!linear_streams(b, WMODE)) return launch_mt<DT, WMODE, MT, QX, ANYK, false>(b, tiles16, a_bits, acc_out, st);
     }
-    const bool wide = tiles16 >= 512, long_rows = weight_bytes(b) >= 8192 * 16 * tiles16;
+    const bool wide = tiles16 >= 512, long_rows = linear_long_rows(b);
     if constexpr (ANYK) {                              // as row-major int8 below
         if (!wide)                 launch_one<DT, WMODE, MT, 1, 8, 4, QX, true, false, true>(b, a_bits, acc_out, st);
         else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, false, true>(b, a_bits, acc_out, st);

@@ -71,3 +71,8 @@ def linear_quantizes(items, wf):
 def linear_streams(items, wf):
     """Whether such a call reads its weights past the caches (sasq::linear_streams)."""
     return bool(_function("_ZN4sasq14linear_streamsERKNS_8LinBatchEi", ctypes.POINTER(_LinBatch), ctypes.c_int)(_batch(items), wf) & 1)
+
+
+def linear_long_rows(items):
+    """Whether the wide few-row form keeps six K tiles a wave in flight (sasq::linear_long_rows)."""
+    return bool(_function("_ZN4sasq16linear_long_rowsERKNS_8LinBatchE", ctypes.POINTER(_LinBatch))(_batch(items)) & 1)
