@@ -44,6 +44,7 @@ bool linear_takes_skinny(const LinBatch& b, int wmode);
 // More than kSkinnyRows rows: 32, small blocks; 64, 96 or 128, rows per workgroup of the row blocks; 0, the GEMM's tiles.
 int linear_block_rows(const LinBatch& b, int wmode);
 bool linear_quantizes_in_kernel(const LinBatch& b, int wmode, bool any_k);
+bool linear_turns(const LinBatch& b, int wmode, bool qx);
 bool linear_streams(const LinBatch& b, int wmode);
 bool linear_long_rows(const LinBatch& b);
 void launch_linear_skinny(LinBatch& b, sasq_dtype dt, int wmode, bool qx, int a_bits, int32_t* acc_out, hipStream_t st);

@@ -35,14 +35,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_rsrc(const void* base,
 // Row tiles whose sums meet in LDS at a time (128 KB at most).
 template <int MT, int NT, int NW> constexpr int skinny_rows_per_phase() { return NW * NT * MT <= 128 ? MT : MT / 2; }
 // A wave's own LDS in the K loop, where its operands turn from the order of memory into that of the MFMA.
-template <int WMODE, int MT, int NT, bool QX, bool EVEN, bool FLT, bool ANYK> constexpr int skinny_turn_bytes()
+template <int WMODE, int MT, int NT, bool QX, bool EVEN, bool FLT, bool TURN> constexpr int skinny_turn_bytes()
 {
-    constexpr bool w = WMODE == 0 && !ANYK, x = FLT || (QX && !ANYK);
+    constexpr bool w = TURN && WMODE == 0, x = TURN && (FLT || QX);
     return (w && !EVEN ? 2 : 1) * ((w ? NT : 0) + (x ? MT : 0)) * 1024;
 }
-template <int WMODE, int MT, int NT, int NW, bool QX, bool EVEN, bool FLT, bool ANYK> constexpr int skinny_lds_bytes()
+template <int WMODE, int MT, int NT, int NW, bool QX, bool EVEN, bool FLT, bool TURN> constexpr int skinny_lds_bytes()
 {
-    constexpr int sums = NW * NT * skinny_rows_per_phase<MT, NT, NW>() * 1024, turn = NW * skinny_turn_bytes<WMODE, MT, NT, QX, EVEN, FLT, ANYK>();
+    constexpr int sums = NW * NT * skinny_rows_per_phase<MT, NT, NW>() * 1024, turn = NW * skinny_turn_bytes<WMODE, MT, NT, QX, EVEN, FLT, TURN>();
     return sums > turn ? sums : turn;
 }
 
@@ -50,7 +50,8 @@ template <int WMODE, int MT, int NT, int NW, bool QX, bool EVEN, bool FLT, bool 
 // hold 16 rows x 32 numbers, the sums are fp32 (the waves' parts added in their order) and go out rounded, without factors.
 // ANYK: K not a multiple of 64, few rows of row-major int8; the activation codes are row-major too.  Rows then start at any byte, and
 // the last wave multiplies the rest of the row, with zeros behind, after its whole K tiles.
-template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool EVEN, bool FLT = false, bool ANYK = false>
+// TURN: operands that lie in rows are loaded in memory's order and turned in LDS (below).
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool EVEN, bool TURN, bool FLT = false, bool ANYK = false>
 __device__ __forceinline__
 void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __restrict__ acc_out, char* lds)
 {
@@ -58,10 +59,10 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
     constexpr bool I4 = WMODE == 3, ROWMAJOR = WMODE == 0;
     static_assert(!I4 || NT % 2 == 0, "int4 blocks hold 32 weight rows");
     static_assert(!FLT || (WMODE == 2 && !QX), "float contraction: weight blocks, no codes");
-    static_assert(!ANYK || (ROWMAJOR && !EVEN), "rows at any byte: plain loads");
+    static_assert(!ANYK || (ROWMAJOR && !EVEN && !TURN), "rows at any byte: plain loads");
     using AccT = std::conditional_t<FLT, f32x4, i32x4>;
     constexpr int WL = I4 ? NT / 2 : NT;               // 128-bit weight loads per lane and K tile
-    constexpr bool WTURN = ROWMAJOR && !ANYK, XTURN = QX && !ANYK;
+    constexpr bool WTURN = TURN && ROWMAJOR, XTURN = TURN && QX, FTURN = TURN && FLT;
     constexpr bool LINES = WTURN && !EVEN;
     constexpr int TS = LINES ? 2 : 1;                  // K tiles per step
     constexpr int DS = (D + TS - 1) / TS;
@@ -107,8 +108,8 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
 #pragma unroll
     for (int b = 0; b < (XTURN ? 2 * MT : MT); ++b) {
         if (XTURN)             xoff[b] = (uint32_t)min(8 * b + lrow, M - 1 - m0) * (uint32_t)K * 2 + 16 * lchunk;
-        else if (FLT)          xoff[b] = (uint32_t)min(16 * b + prow, M - 1 - m0) * (uint32_t)K + 16 * pchunk;
-        else if (ANYK && !QX) xoff[b] = (uint32_t)min(16 * b + frow, M - 1 - m0) * (uint32_t)K + 16 * fq;
+        else if (FTURN)        xoff[b] = (uint32_t)min(16 * b + prow, M - 1 - m0) * (uint32_t)K + 16 * pchunk;
+        else if (FLT || (ANYK && !QX)) xoff[b] = (uint32_t)min(16 * b + frow, M - 1 - m0) * (uint32_t)K + 16 * fq;
         else if (QX) xoff[b] = (uint32_t)min(16 * b + frow, M - 1 - m0) * (uint32_t)K * 2 + fq * 32;
         else         xoff[b] = (uint32_t)min(b, ((M - 1) >> 4) - (m0 >> 4)) * (uint32_t)KT * 1024 + (4 * frow + (fq ^ swz64(frow))) * 16;
     }
@@ -128,12 +129,15 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
         // ONCE: no other workgroup reads these weights.  Where row blocks share them they have to stay in L2 (333 x 4096 x 4096
         // 18.8 us non-temporal, 16.8 cached).
         constexpr int kNonTemporal = 2;
+        // Row-major in the MFMA's order: plain loads (7B layer, 8 rows 50.6 us through buffers, 49.8 so; 12 x 2368 x 28544's MLP 72.9, 70.0).
+        constexpr bool kPlain = ROWMAJOR && !ANYK && !EVEN && !TURN;
         // a step of one K tile takes that one twice: nothing behind a row's end is read
         const bool half = LINES && t == half_step;
         const uint32_t back = half && lchunk >= 4 ? 64 : 0;
 #pragma unroll
         for (int j = 0; j < WN; ++j)
             if constexpr (ANYK)       f.w[j] = load_piece<u32x4>(reinterpret_cast<const uint8_t*>(wbase) + (int64_t)t * kWStep + woff[j]);
+            else if constexpr (kPlain) f.w[j] = *reinterpret_cast<const u32x4*>(wbase + (int64_t)t * kWStep + woff[j]);
             else if constexpr (LINES) f.w[j] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, woff[j] - back, t * kWStep, ONCE ? kNonTemporal : 0);
             else                  f.w[j] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, woff[j], t * kWStep, ONCE && !ROWMAJOR ? kNonTemporal : 0);
 #pragma unroll
@@ -142,10 +146,11 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
             for (int h = 0; h < XN; ++h) {
                 constexpr int kTile = QX ? 2 : 1;                       // loads of a K tile
                 const int step = t * kXStep + (half ? 0 : h / kTile * (QX ? 128 : 1024));
-                if constexpr (ANYK) f.x[b][h] = load_piece<u32x4>(reinterpret_cast<const uint8_t*>(xbase) + (int64_t)t * kXStep + xoff[b] + 16 * h);
+                if constexpr (kPlain) f.x[b][h] = *reinterpret_cast<const u32x4*>(xbase + (int64_t)t * kXStep + xoff[b] + 16 * h);
+                else if constexpr (ANYK) f.x[b][h] = load_piece<u32x4>(reinterpret_cast<const uint8_t*>(xbase) + (int64_t)t * kXStep + xoff[b] + 16 * h);
                 else if constexpr (XTURN) {
                     if (h % 2 == 0 || !few) f.x[b][h] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff[2 * b + h % 2], step, 0);
-                } else f.x[b][h] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff[b], step, 0);
+                } else f.x[b][h] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, xoff[b] + (QX ? 16 * h : 0), step, 0);
             }
     };
     AccT acc[NT][MT];
@@ -160,7 +165,7 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
     // halves one by one.  us, MFMA's order | memory's: weights, 7B layer, row-major, 8 rows 50 | 36, 16 rows 60 | 41, 40 rows 64 | 48, 8 x
     // 4096 -> 11008 16.3 | 13.1; dY, the 7B layer's training step of 200 rows 405 | 350, attention, hidden 2048, of 130 rows 58 | 53; the
     // activations quantized here, 7B layer, pre-arranged, 16 rows 43.4 | 38.6, 13B int4, 16 rows 36.8 | 33.4, one row 28.0 | 26.6.
-    constexpr int kTurn = skinny_turn_bytes<WMODE, MT, NT, QX, EVEN, FLT, ANYK>();
+    constexpr int kTurn = skinny_turn_bytes<WMODE, MT, NT, QX, EVEN, FLT, TURN>();
     char* wturn = lds + wave * kTurn;
     char* xturn = wturn + (WTURN ? NT * TS * 1024 : 0);
     const int line_put = lrow * 128 + ((lchunk ^ lrow) << 4), line_get = frow * 128 + ((fq ^ (frow & 7)) << 4);
@@ -179,7 +184,7 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
 #pragma unroll
             for (int j = 0; j < WN; ++j) *reinterpret_cast<u32x4*>(wturn + j * 1024 + (LINES ? line_put : piece_put)) = f.w[j];
         }
-        if constexpr (FLT) {
+        if constexpr (FTURN) {
 #pragma unroll
             for (int b = 0; b < MT; ++b) *reinterpret_cast<u32x4*>(xturn + b * 1024 + piece_put) = f.x[b][0];
         }
@@ -199,7 +204,7 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
             i32x4 xv[MT];
 #pragma unroll
             for (int b = 0; b < MT; ++b) {
-                if constexpr (FLT || XTURN) {
+                if constexpr (FTURN || XTURN) {
                     xv[b] = *reinterpret_cast<const i32x4*>(xturn + (p * MT + b) * 1024 + piece_get);
                 } else if constexpr (QX) {
                     const u32x2 lo = quantize8(f.x[b][0]), hi = quantize8(f.x[b][1]);
@@ -366,20 +371,20 @@ void skinny_body(const LinItem& it, int mblk, int nblk, int a_bits, int32_t* __r
     }
 }
 
-template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool EVEN, bool ANYK>
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool EVEN, bool TURN, bool ANYK>
 __global__ __launch_bounds__(64 * NW)
 void skinny_kernel(const LinBatch b, int a_bits, int32_t* __restrict__ acc_out)
 {
-    __shared__ __attribute__((aligned(1024))) char lds[skinny_lds_bytes<WMODE, MT, NT, NW, QX, EVEN, false, ANYK>()];
+    __shared__ __attribute__((aligned(1024))) char lds[skinny_lds_bytes<WMODE, MT, NT, NW, QX, EVEN, false, TURN>()];
     const int k = lin_item_of(b, (int)blockIdx.x);
     // Eight neighbours in the id go to the eight XCDs: the row blocks of one run of weight rows stay on one, 8 ids apart.
     const int id = (int)blockIdx.x - b.first_block[k], octet = id >> 3, tiles_m = b.it[k].tiles_m;
     const int mblk = octet % tiles_m, nblk = octet / tiles_m * 8 + (id & 7);
     if (nblk >= b.it[k].tiles_n) return;
-    skinny_body<DT, WMODE, MT, NT, NW, D, QX, ONCE, EVEN, false, ANYK>(b.it[k], mblk, nblk, a_bits, acc_out, lds);
+    skinny_body<DT, WMODE, MT, NT, NW, D, QX, ONCE, EVEN, TURN, false, ANYK>(b.it[k], mblk, nblk, a_bits, acc_out, lds);
 }
 
-template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool EVEN, bool ANYK = false>
+template <int DT, int WMODE, int MT, int NT, int NW, int D, bool QX, bool ONCE, bool EVEN, bool TURN, bool ANYK = false>
 static void launch_one(LinBatch& b, int a_bits, int32_t* acc_out, hipStream_t st)
 {
     b.first_block[0] = 0;
@@ -393,9 +398,15 @@ static void launch_one(LinBatch& b, int a_bits, int32_t* acc_out, hipStream_t st
         }
         b.first_block[i + 1] = b.first_block[i] + blocks;
     }
-    skinny_kernel<DT, WMODE, MT, NT, NW, D, QX, ONCE, EVEN, ANYK><<<b.first_block[b.count], 64 * NW, 0, st>>>(b, a_bits, acc_out);
+    skinny_kernel<DT, WMODE, MT, NT, NW, D, QX, ONCE, EVEN, TURN, ANYK><<<b.first_block[b.count], 64 * NW, 0, st>>>(b, a_bits, acc_out);
 }
 
+static int longest(const LinBatch& b)
+{
+    int k = 0;
+    for (int i = 0; i < b.count; ++i) k = b.it[i].K > k ? b.it[i].K : k;
+    return k;
+}
 static int64_t weight_bytes(const LinBatch& b)
 {
     int64_t n = 0;
@@ -437,31 +448,47 @@ bool linear_streams(const LinBatch& b, int wmode)
 // four: 35.2 | 45.7, 35.2, 33.4, at one row 26.9 | 31.9, 27.3, 26.6.  Row-major, in steps of two K tiles, layer at 1, 8, 16 rows, four waves with
 // four | four with two | eight with two: 39.9, 39.3, 42.5 | 34.7, 36.2, 41.0 | 33.6, 36.4, 42.2; row tiles of 32, MLP of 30 rows 34.1 | 36.9 | 33.7,
 // of 20 rows, hidden 2048, 12.7 | 13.4 | 13.1; narrow, 30 and 40 x 4096 -> 4096, eight with four | two: 9.4, 10.1 | 8.7, 9.5.
-template <int DT, int WMODE, int MT, bool QX, bool ANYK = false, bool ONCE = true>
+// Without the turn, the forms that were the best before it: int8 eight waves with three, int4 with two, row-major four with four; of up to four K
+// tiles four waves, as half of eight have none (0.93 to 1.05 of eight's time).  Narrow int8 with the turn takes 133 registers with four K tiles
+// in flight, so that one workgroup fits a CU, 109 with three: from 257 workgroups on four took 1.2 to 1.4 of the time without the turn.
+template <int DT, int WMODE, int MT, bool QX, bool TURN, bool ANYK = false, bool ONCE = true>
 static void launch_mt(LinBatch& b, int64_t tiles16, int a_bits, int32_t* acc_out, hipStream_t st)
 {
-    if constexpr (WMODE == 0 && !ANYK && ONCE) {
-        if (!linear_streams(b, WMODE)) return launch_mt<DT, WMODE, MT, QX, ANYK, false>(b, tiles16, a_bits, acc_out, st);
+    if constexpr (WMODE == 0 && TURN && ONCE) {
+        if (!linear_streams(b, WMODE)) return launch_mt<DT, WMODE, MT, QX, TURN, ANYK, false>(b, tiles16, a_bits, acc_out, st);
     }
     const bool wide = tiles16 >= 512, long_rows = linear_long_rows(b);
-    if constexpr (ANYK) {                              // as row-major int8 below
-        if (!wide)                 launch_one<DT, WMODE, MT, 1, 8, 4, QX, true, false, true>(b, a_bits, acc_out, st);
-        else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, false, true>(b, a_bits, acc_out, st);
-        else                       launch_one<DT, WMODE, MT, 2, 4, 4, QX, true, false, true>(b, a_bits, acc_out, st);
-    } else if constexpr (WMODE == 3) {                 // int4: half the bytes per tile, a block is two tiles
-        if (!wide)             launch_one<DT, WMODE, MT, 2, 8, 2, QX, true, false>(b, a_bits, acc_out, st);
-        else if constexpr (QX) launch_one<DT, WMODE, MT, 4, 4, 4, QX, true, false>(b, a_bits, acc_out, st);
-        else                   launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, false>(b, a_bits, acc_out, st);
+    if constexpr (WMODE == 0 && !TURN) {               // K not a multiple of 64 too (ANYK)
+        if (!wide)                 launch_one<DT, WMODE, MT, 1, 8, 4, QX, false, false, false, ANYK>(b, a_bits, acc_out, st);
+        else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, false, false, false, ANYK>(b, a_bits, acc_out, st);
+        else                       launch_one<DT, WMODE, MT, 2, 4, 4, QX, false, false, false, ANYK>(b, a_bits, acc_out, st);
     } else if constexpr (WMODE == 0) {
-        if (!wide)                 launch_one<DT, WMODE, MT, 1, 8, 2, QX, ONCE, false>(b, a_bits, acc_out, st);
-        else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, ONCE, false>(b, a_bits, acc_out, st);
-        else                       launch_one<DT, WMODE, MT, 2, 4, MT == 1 ? 2 : 4, QX, ONCE, false>(b, a_bits, acc_out, st);
+        if (!wide)                 launch_one<DT, WMODE, MT, 1, 8, 2, QX, ONCE, false, true>(b, a_bits, acc_out, st);
+        else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, ONCE, false, true>(b, a_bits, acc_out, st);
+        else                       launch_one<DT, WMODE, MT, 2, 4, MT == 1 ? 2 : 4, QX, ONCE, false, true>(b, a_bits, acc_out, st);
+    } else if constexpr (WMODE == 3) {                 // int4: half the bytes per tile, a block is two tiles
+        if (!wide)                     launch_one<DT, WMODE, MT, 2, 8, 2, QX, true, false, TURN>(b, a_bits, acc_out, st);
+        else if constexpr (QX && TURN) launch_one<DT, WMODE, MT, 4, 4, 4, QX, true, false, TURN>(b, a_bits, acc_out, st);
+        else if constexpr (QX) {
+            if (longest(b) <= 256) launch_one<DT, WMODE, MT, 4, 4, 4, QX, true, false, TURN>(b, a_bits, acc_out, st);
+            else                   launch_one<DT, WMODE, MT, 4, 8, 2, QX, true, false, TURN>(b, a_bits, acc_out, st);
+        }
+        else                           launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, false, TURN>(b, a_bits, acc_out, st);
     } else {
-        if (!wide)                 launch_one<DT, WMODE, MT, 1, 8, 4, QX, true, false>(b, a_bits, acc_out, st);
-        else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, false>(b, a_bits, acc_out, st);
-        else if constexpr (!QX)    launch_one<DT, WMODE, MT, 2, 8, 3, QX, true, false>(b, a_bits, acc_out, st);
-        else if (long_rows)        launch_one<DT, WMODE, MT, 2, 4, 6, QX, true, false>(b, a_bits, acc_out, st);
-        else                       launch_one<DT, WMODE, MT, 2, 4, 4, QX, true, false>(b, a_bits, acc_out, st);
+        if (!wide) {
+            if constexpr (TURN) {
+                if (tiles16 > 256) return launch_one<DT, WMODE, MT, 1, 8, 3, QX, true, false, TURN>(b, a_bits, acc_out, st);
+            }
+            launch_one<DT, WMODE, MT, 1, 8, 4, QX, true, false, TURN>(b, a_bits, acc_out, st);
+        }
+        else if constexpr (MT > 2) launch_one<DT, WMODE, MT, 4, 4, 2, QX, true, false, TURN>(b, a_bits, acc_out, st);
+        else if constexpr (!QX)    launch_one<DT, WMODE, MT, 2, 8, 3, QX, true, false, TURN>(b, a_bits, acc_out, st);
+        else if constexpr (!TURN) {
+            if (longest(b) <= 256) launch_one<DT, WMODE, MT, 2, 4, 4, QX, true, false, TURN>(b, a_bits, acc_out, st);
+            else                   launch_one<DT, WMODE, MT, 2, 8, 3, QX, true, false, TURN>(b, a_bits, acc_out, st);
+        }
+        else if (long_rows)        launch_one<DT, WMODE, MT, 2, 4, 6, QX, true, false, TURN>(b, a_bits, acc_out, st);
+        else                       launch_one<DT, WMODE, MT, 2, 4, 4, QX, true, false, TURN>(b, a_bits, acc_out, st);
     }
 }
 
@@ -643,14 +670,51 @@ bool linear_quantizes_in_kernel(const LinBatch& b, int wmode, bool any_k)
     return rows <= kSkinnyRows && (int64_t)(rows <= 32 ? 32 : 64) * k_max <= 32768 && tiles16 < 512;
 }
 
-template <int DT, int WMODE, bool QX>
+// Whether operands that lie in rows go through LDS (TURN).  It saves accesses of the L1 cache with every K tile, most of them where rows are
+// whole 128-byte lines apart (an even number of K tiles of row-major weights), and costs each wave the way through LDS once and registers:
+// a wave with one or two K tiles is done sooner in the MFMA's order.  Time with the turn by time without it over 35 000 calls of 1 to 600
+// rows, half of them on cached weights, by K tiles:
+//   row-major, quantized here, at most 16 rows: 1 to 4 1.05 to 1.10; even 6 1.01 to 1.03 (wide 0.92 to 0.95), 8 1.00 (0.89), 16 0.91, 64 0.80; odd
+//     7 1.00 to 1.04, 9 1.01 to 1.04, 11 0.97 to 1.01, 33 and more 0.85 to 0.91, but 1.02 to 1.07 on 64 K tiles and more, 1500 to 4096
+//     columns, that are not in the caches;  small blocks, 17 to 32 rows: even 6 1.01 to 1.05, 8 0.96 to 1.00, 14 0.87 to 0.92; odd 7 1.03
+//     to 1.11, 9 1.00 to 1.06, 11 0.97 to 1.01
+//   row-major, codes from the pre-pass: even 6 1.03 to 1.10, 8 0.99 to 1.01, 10 0.96 to 1.02, 16 0.85 to 0.98; odd 9 1.04 to 1.11, 17 and more rows
+//     than 32 0.98 to 1.02, others 1.02 to 1.07 up to 27, 0.95 to 1.02 from 33 on
+//   pre-arranged weights, of which the activations turn: small blocks of 16 rows 1 to 5 1.04 to 1.07, 8 0.99 to 1.01, 16 0.94 to 0.96; of 32 rows 1 to 6
+//     1.03 to 1.11, 12 0.97 to 1.01; 17 to 32 rows 6 1.02, 8 0.96; at most 8 rows, narrow, int8 8 1.05, 16 0.99, 64 0.86, int4 8 1.01, 10 0.98, 64 0.86;
+//     9 to 16 rows int8 16 1.03, 32 0.99, 64 0.92, int4 64 and more 1.15 to 1.23 (0.95 to 1.10 on cached weights of 16 to 63); wide 5 to 31 K
+//     tiles 0.97 to 1.13, 32 and more 0.92 to 0.98
+// More than 32 rows quantized here have at most 8 K tiles: 1.39 (one) to 1.05 (eight).
+bool linear_turns(const LinBatch& b, int wmode, bool qx)
+{
+    int rows = 0, k_max = 0;
+    int64_t tiles16 = 0;
+    for (int i = 0; i < b.count; ++i) {
+        rows = b.it[i].M > rows ? b.it[i].M : rows;
+        k_max = b.it[i].K > k_max ? b.it[i].K : k_max;
+        tiles16 += (b.it[i].N + 15) / 16;
+    }
+    const int kt = k_max / 64;
+    const bool lines = kt % 2 == 0, wide = tiles16 >= 512;
+    const SmallBlock small = small_block(b.it, b.count, wmode);
+    if (qx && !small.mt && rows > 32) return false;
+    if (wmode == 0 && qx) return kt >= (!lines ? 11 : rows <= kSkinnyQuantRows && wide ? 6 : 8);
+    if (wmode == 0) return kt >= (lines ? 12 : small.mt || rows <= 32 ? 28 : 17);
+    if (!qx) return false;
+    if (small.mt) return kt >= (small.mt == 1 ? 8 : 12);
+    if (rows > kSkinnyQuantRows) return kt >= 8;
+    if (wide) return kt >= 32;
+    return wmode == 2 ? kt >= (rows <= 8 ? 16 : 32) : rows <= 8 && kt >= 9;
+}
+
+template <int DT, int WMODE, bool QX, bool TURN>
 static void launch_small(LinBatch& b, SmallBlock f, int a_bits, int32_t* acc_out, hipStream_t st)
 {
-    if (f.nt == 4)                launch_one<DT, WMODE, 2, 4, 8, 2, QX, false, false>(b, a_bits, acc_out, st);
-    else if (f.mt == 2 && f.nt == 2) launch_one<DT, WMODE, 2, 2, 8, 3, QX, false, false>(b, a_bits, acc_out, st);
-    else if constexpr (WMODE == 3)   launch_one<DT, WMODE, 1, 2, 8, 3, QX, false, false>(b, a_bits, acc_out, st);
-    else if (f.mt == 2)              launch_one<DT, WMODE, 2, 1, 8, 3, QX, false, false>(b, a_bits, acc_out, st);
-    else                             launch_one<DT, WMODE, 1, 1, 8, 3, QX, false, false>(b, a_bits, acc_out, st);
+    if (f.nt == 4)                launch_one<DT, WMODE, 2, 4, 8, 2, QX, false, false, TURN>(b, a_bits, acc_out, st);
+    else if (f.mt == 2 && f.nt == 2) launch_one<DT, WMODE, 2, 2, 8, 3, QX, false, false, TURN>(b, a_bits, acc_out, st);
+    else if constexpr (WMODE == 3)   launch_one<DT, WMODE, 1, 2, 8, 3, QX, false, false, TURN>(b, a_bits, acc_out, st);
+    else if (f.mt == 2)              launch_one<DT, WMODE, 2, 1, 8, 3, QX, false, false, TURN>(b, a_bits, acc_out, st);
+    else                             launch_one<DT, WMODE, 1, 1, 8, 3, QX, false, false, TURN || (WMODE == 0 && !QX)>(b, a_bits, acc_out, st);
 }
 
 template <int DT, int WMODE>
@@ -663,27 +727,38 @@ static void launch_wmode(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, hip
         rows = b.it[i].M > rows ? b.it[i].M : rows;
     }
     const SmallBlock small = small_block(b.it, b.count, WMODE);
+    const bool turn = linear_turns(b, WMODE, qx);
+    constexpr bool kTurnPre = WMODE == 0;                               // codes from the pre-pass: only row-major weights lie in rows
     if (small.mt) {
-        if (qx) launch_small<DT, WMODE, true>(b, small, a_bits, acc_out, st);
-        else    launch_small<DT, WMODE, false>(b, small, a_bits, acc_out, st);
+        if (qx && turn)       launch_small<DT, WMODE, true, true>(b, small, a_bits, acc_out, st);
+        else if (qx)          launch_small<DT, WMODE, true, false>(b, small, a_bits, acc_out, st);
+        else if (turn)        launch_small<DT, WMODE, false, kTurnPre>(b, small, a_bits, acc_out, st);
+        else                  launch_small<DT, WMODE, false, false>(b, small, a_bits, acc_out, st);
     } else if (rows > kSkinnyRows) {
         const int block = block_rows(b, WMODE);
-        if (block == 64 && blocks_of(b, 64) > 256) launch_one<DT, WMODE, 4, 4, 4, 2, false, false, true>(b, a_bits, acc_out, st);
-        else if (block == 64)                launch_one<DT, WMODE, 4, 4, 8, 2, false, false, true>(b, a_bits, acc_out, st);
-        else if (block == 96 && rows > 96)   launch_one<DT, WMODE, 6, 4, 8, 2, false, false, true>(b, a_bits, acc_out, st);
-        else if (block == 96)                launch_one<DT, WMODE, 6, 4, 8, 2, false, true, true>(b, a_bits, acc_out, st);
-        else if (rows > 128)                 launch_one<DT, WMODE, 8, 4, 8, 2, false, false, true>(b, a_bits, acc_out, st);
-        else                                 launch_one<DT, WMODE, 8, 4, 8, 2, false, true, true>(b, a_bits, acc_out, st);
-    } else if (qx && rows > kSkinnyQuantRows) {
-        // Row-major ones too go past the caches, though they are at most 8 MB: with the ordinary policy 2900 calls of them took 1.00 of the
-        // time on weights that the caches hold and 1.01 to 1.05 on others.
-        if (rows > 32) launch_one<DT, WMODE, 4, WMODE == 3 ? 2 : 1, 8, 2, true, true, false>(b, a_bits, acc_out, st);
-        else           launch_one<DT, WMODE, 2, WMODE == 3 ? 2 : 1, 8, 2, true, true, false>(b, a_bits, acc_out, st);
+        if (block == 64 && blocks_of(b, 64) > 256) launch_one<DT, WMODE, 4, 4, 4, 2, false, false, true, kTurnPre>(b, a_bits, acc_out, st);
+        else if (block == 64)                launch_one<DT, WMODE, 4, 4, 8, 2, false, false, true, kTurnPre>(b, a_bits, acc_out, st);
+        else if (block == 96 && rows > 96)   launch_one<DT, WMODE, 6, 4, 8, 2, false, false, true, kTurnPre>(b, a_bits, acc_out, st);
+        else if (block == 96)                launch_one<DT, WMODE, 6, 4, 8, 2, false, true, true, kTurnPre>(b, a_bits, acc_out, st);
+        else if (rows > 128)                 launch_one<DT, WMODE, 8, 4, 8, 2, false, false, true, kTurnPre>(b, a_bits, acc_out, st);
+        else                                 launch_one<DT, WMODE, 8, 4, 8, 2, false, true, true, kTurnPre>(b, a_bits, acc_out, st);
+    } else if (qx && rows > 32)              launch_one<DT, WMODE, 4, WMODE == 3 ? 2 : 1, 8, 2, true, true, false, false>(b, a_bits, acc_out, st);
+    else if (qx && rows > kSkinnyQuantRows) {
+        if (turn) launch_one<DT, WMODE, 2, WMODE == 3 ? 2 : 1, 8, 2, true, true, false, true>(b, a_bits, acc_out, st);
+        else      launch_one<DT, WMODE, 2, WMODE == 3 ? 2 : 1, 8, 2, true, true, false, false>(b, a_bits, acc_out, st);
+    } else if (qx) {
+        if (turn) launch_mt<DT, WMODE, 1, true, true>(b, tiles16, a_bits, acc_out, st);
+        else      launch_mt<DT, WMODE, 1, true, false>(b, tiles16, a_bits, acc_out, st);
+    } else {
+        auto by_rows = [&](auto turn_tag) {
+            constexpr bool TURN = decltype(turn_tag)::value;
+            if (rows <= 32)      launch_mt<DT, WMODE, 2, false, TURN>(b, tiles16, a_bits, acc_out, st);
+            else if (rows <= 48) launch_mt<DT, WMODE, 3, false, TURN>(b, tiles16, a_bits, acc_out, st);
+            else                 launch_mt<DT, WMODE, 4, false, TURN>(b, tiles16, a_bits, acc_out, st);
+        };
+        if (turn) by_rows(std::integral_constant<bool, kTurnPre>{});
+        else      by_rows(std::false_type{});
     }
-    else if (qx)       launch_mt<DT, WMODE, 1, true>(b, tiles16, a_bits, acc_out, st);
-    else if (rows <= 32) launch_mt<DT, WMODE, 2, false>(b, tiles16, a_bits, acc_out, st);
-    else if (rows <= 48) launch_mt<DT, WMODE, 3, false>(b, tiles16, a_bits, acc_out, st);
-    else                 launch_mt<DT, WMODE, 4, false>(b, tiles16, a_bits, acc_out, st);
 }
 
 void launch_linear_skinny(LinBatch& b, sasq_dtype dt, int wmode, bool qx, int a_bits, int32_t* acc_out, hipStream_t st)
@@ -721,12 +796,12 @@ static void launch_anyk_dt(LinBatch& b, bool qx, int a_bits, int32_t* acc_out, h
 {
     const int rows = b.it[0].M;
     const int64_t tiles16 = ((int64_t)b.it[0].N + 15) / 16;
-    if (qx && rows > 32)                    launch_one<DT, 0, 4, 1, 8, 2, true, true, false, true>(b, a_bits, acc_out, st);
-    else if (qx && rows > kSkinnyQuantRows) launch_one<DT, 0, 2, 1, 8, 2, true, true, false, true>(b, a_bits, acc_out, st);
-    else if (qx)         launch_mt<DT, 0, 1, true, true>(b, tiles16, a_bits, acc_out, st);
-    else if (rows <= 32) launch_mt<DT, 0, 2, false, true>(b, tiles16, a_bits, acc_out, st);
-    else if (rows <= 48) launch_mt<DT, 0, 3, false, true>(b, tiles16, a_bits, acc_out, st);
-    else                 launch_mt<DT, 0, 4, false, true>(b, tiles16, a_bits, acc_out, st);
+    if (qx && rows > 32)                    launch_one<DT, 0, 4, 1, 8, 2, true, false, false, false, true>(b, a_bits, acc_out, st);
+    else if (qx && rows > kSkinnyQuantRows) launch_one<DT, 0, 2, 1, 8, 2, true, false, false, false, true>(b, a_bits, acc_out, st);
+    else if (qx)         launch_mt<DT, 0, 1, true, false, true, false>(b, tiles16, a_bits, acc_out, st);
+    else if (rows <= 32) launch_mt<DT, 0, 2, false, false, true, false>(b, tiles16, a_bits, acc_out, st);
+    else if (rows <= 48) launch_mt<DT, 0, 3, false, false, true, false>(b, tiles16, a_bits, acc_out, st);
+    else                 launch_mt<DT, 0, 4, false, false, true, false>(b, tiles16, a_bits, acc_out, st);
 }
 
 void launch_linear_anyk_skinny(LinBatch& b, sasq_dtype dt, bool qx, int a_bits, int32_t* acc_out, hipStream_t st)
@@ -736,23 +811,23 @@ void launch_linear_anyk_skinny(LinBatch& b, sasq_dtype dt, bool qx, int a_bits, 
 }
 
 // ---- the backward GEMM ----------------------------------------------------------------------
-template <int DT, int MT, int NT, int NW, int D, bool ONCE, bool EVEN>
+template <int DT, int MT, int NT, int NW, int D, bool ONCE, bool EVEN, bool TURN>
 __global__ __launch_bounds__(64 * NW)
 void bwd_skinny_kernel(const LinItem it, float* __restrict__ acc_out)
 {
-    __shared__ __attribute__((aligned(1024))) char lds[skinny_lds_bytes<2, MT, NT, NW, false, EVEN, true, false>()];
+    __shared__ __attribute__((aligned(1024))) char lds[skinny_lds_bytes<2, MT, NT, NW, false, EVEN, true, TURN>()];
     const int id = (int)blockIdx.x, octet = id >> 3;                 // as in skinny_kernel
     const int mblk = octet % it.tiles_m, nblk = octet / it.tiles_m * 8 + (id & 7);
     if (nblk >= it.tiles_n) return;
-    skinny_body<DT, 2, MT, NT, NW, D, false, ONCE, EVEN, true>(it, mblk, nblk, 8, reinterpret_cast<int32_t*>(acc_out), lds);
+    skinny_body<DT, 2, MT, NT, NW, D, false, ONCE, EVEN, TURN, true>(it, mblk, nblk, 8, reinterpret_cast<int32_t*>(acc_out), lds);
 }
 
-template <int DT, int MT, int NT, int NW, int D, bool ONCE, bool EVEN>
+template <int DT, int MT, int NT, int NW, int D, bool ONCE, bool EVEN, bool TURN>
 static void launch_bwd_one(LinItem& it, float* acc_out, hipStream_t st)
 {
     it.tiles_m = (it.M + 16 * MT - 1) / (16 * MT);
     it.tiles_n = (it.N + 16 * NT - 1) / (16 * NT);
-    bwd_skinny_kernel<DT, MT, NT, NW, D, ONCE, EVEN><<<(it.tiles_n + 7) / 8 * 8 * it.tiles_m, 64 * NW, 0, st>>>(it, acc_out);
+    bwd_skinny_kernel<DT, MT, NT, NW, D, ONCE, EVEN, TURN><<<(it.tiles_n + 7) / 8 * 8 * it.tiles_m, 64 * NW, 0, st>>>(it, acc_out);
 }
 
 static LinItem bwd_item(const void* dy, const void* wt, void* dx, int64_t M, int64_t N, int64_t K)
@@ -806,20 +881,20 @@ static void launch_bwd_dt(LinItem& it, float* acc_out, int rows, hipStream_t st)
 {
     if (rows == 32) {
         const SmallBlock f = small_block(&it, 1, 2);
-        if (f.nt == 4)      launch_bwd_one<DT, 2, 4, 8, 2, false, false>(it, acc_out, st);
-        else if (f.nt == 2) launch_bwd_one<DT, 2, 2, 8, 3, false, false>(it, acc_out, st);
-        else if (f.mt == 2) launch_bwd_one<DT, 2, 1, 8, 3, false, false>(it, acc_out, st);
-        else                launch_bwd_one<DT, 1, 1, 8, 3, false, false>(it, acc_out, st);
+        if (f.nt == 4)      launch_bwd_one<DT, 2, 4, 8, 2, false, false, true>(it, acc_out, st);
+        else if (f.nt == 2) launch_bwd_one<DT, 2, 2, 8, 3, false, false, true>(it, acc_out, st);
+        else if (f.mt == 2) launch_bwd_one<DT, 2, 1, 8, 3, false, false, true>(it, acc_out, st);
+        else                launch_bwd_one<DT, 1, 1, 8, 3, false, false, true>(it, acc_out, st);
     } else if (it.M > 64) {
-        if (rows == 64) launch_bwd_one<DT, 4, 4, 8, 2, false, true>(it, acc_out, st);
-        else            launch_bwd_one<DT, 6, 4, 8, 2, false, true>(it, acc_out, st);
+        if (rows == 64) launch_bwd_one<DT, 4, 4, 8, 2, false, true, true>(it, acc_out, st);
+        else            launch_bwd_one<DT, 6, 4, 8, 2, false, true, true>(it, acc_out, st);
     } else if (it.M <= 16) {
-        if (it.N > 4096) launch_bwd_one<DT, 1, 2, 8, 3, true, false>(it, acc_out, st);
-        else             launch_bwd_one<DT, 1, 1, 8, 4, true, false>(it, acc_out, st);
+        if (it.N > 4096) launch_bwd_one<DT, 1, 2, 8, 3, true, false, true>(it, acc_out, st);
+        else             launch_bwd_one<DT, 1, 1, 8, 4, true, false, true>(it, acc_out, st);
     } else if (it.M <= 32) {
-        launch_bwd_one<DT, 2, 2, 8, 3, true, false>(it, acc_out, st);
+        launch_bwd_one<DT, 2, 2, 8, 3, true, false, true>(it, acc_out, st);
     } else {
-        launch_bwd_one<DT, 4, 4, 8, 2, true, false>(it, acc_out, st);
+        launch_bwd_one<DT, 4, 4, 8, 2, true, false, true>(it, acc_out, st);
     }
 }
 

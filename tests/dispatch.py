@@ -76,3 +76,9 @@ def linear_streams(items, wf):
 def linear_long_rows(items):
     """Whether the wide few-row form keeps six K tiles a wave in flight (sasq::linear_long_rows)."""
     return bool(_function("_ZN4sasq16linear_long_rowsERKNS_8LinBatchE", ctypes.POINTER(_LinBatch))(_batch(items)) & 1)
+
+
+def linear_turns(items, wf):
+    """Whether the operands of a few-row, small-block or row-block call turn in LDS, as it quantizes in the kernel or not (sasq::linear_turns)."""
+    f = _function("_ZN4sasq12linear_turnsERKNS_8LinBatchEib", ctypes.POINTER(_LinBatch), ctypes.c_int, ctypes.c_bool)
+    return bool(f(_batch(items), wf, linear_quantizes(items, wf)) & 1)
