@@ -70,6 +70,7 @@ struct RoundTime {
 // Longest contraction of the kernels that reach a block's rows by 32-bit byte offsets (256 rows of dY, 2 GB; 64 columns' weight blocks).
 constexpr int64_t kBwdOffsetCols = INT64_C(1) << 22;
 int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_us);
+bool bwd_turns(int64_t M, int64_t N, int64_t K);
 void launch_bwd_skinny(const void* dy, const void* wt, void* dx, float* acc_out, int64_t M, int64_t N, int64_t K, sasq_dtype dt, int rows, hipStream_t st);
 // Batches of at least so many workgroup ids, and at most 128, go as half tiles throughout.
 constexpr int kHalvesFrom = 32;

@@ -876,33 +876,60 @@ int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_us)
 }
 
 // At most 16 rows: narrow workgroups (16 columns) while they make one round of at most 256, wide ones from then on.
-template <int DT>
+template <int DT, bool TURN>
 static void launch_bwd_dt(LinItem& it, float* acc_out, int rows, hipStream_t st)
 {
     if (rows == 32) {
         const SmallBlock f = small_block(&it, 1, 2);
-        if (f.nt == 4)      launch_bwd_one<DT, 2, 4, 8, 2, false, false, true>(it, acc_out, st);
-        else if (f.nt == 2) launch_bwd_one<DT, 2, 2, 8, 3, false, false, true>(it, acc_out, st);
-        else if (f.mt == 2) launch_bwd_one<DT, 2, 1, 8, 3, false, false, true>(it, acc_out, st);
-        else                launch_bwd_one<DT, 1, 1, 8, 3, false, false, true>(it, acc_out, st);
+        if (f.nt == 4)      launch_bwd_one<DT, 2, 4, 8, 2, false, false, TURN>(it, acc_out, st);
+        else if (f.nt == 2) launch_bwd_one<DT, 2, 2, 8, 3, false, false, TURN>(it, acc_out, st);
+        else if (f.mt == 2) launch_bwd_one<DT, 2, 1, 8, 3, false, false, TURN>(it, acc_out, st);
+        else                launch_bwd_one<DT, 1, 1, 8, 3, false, false, TURN>(it, acc_out, st);
     } else if (it.M > 64) {
-        if (rows == 64) launch_bwd_one<DT, 4, 4, 8, 2, false, true, true>(it, acc_out, st);
-        else            launch_bwd_one<DT, 6, 4, 8, 2, false, true, true>(it, acc_out, st);
+        if (rows == 64) launch_bwd_one<DT, 4, 4, 8, 2, false, true, TURN>(it, acc_out, st);
+        else            launch_bwd_one<DT, 6, 4, 8, 2, false, true, TURN>(it, acc_out, st);
     } else if (it.M <= 16) {
-        if (it.N > 4096) launch_bwd_one<DT, 1, 2, 8, 3, true, false, true>(it, acc_out, st);
-        else             launch_bwd_one<DT, 1, 1, 8, 4, true, false, true>(it, acc_out, st);
+        if (it.N > 4096) launch_bwd_one<DT, 1, 2, 8, 3, true, false, TURN>(it, acc_out, st);
+        else             launch_bwd_one<DT, 1, 1, 8, 4, true, false, TURN>(it, acc_out, st);
     } else if (it.M <= 32) {
-        launch_bwd_one<DT, 2, 2, 8, 3, true, false, true>(it, acc_out, st);
+        launch_bwd_one<DT, 2, 2, 8, 3, true, false, TURN>(it, acc_out, st);
     } else {
-        launch_bwd_one<DT, 4, 4, 8, 2, true, false, true>(it, acc_out, st);
+        launch_bwd_one<DT, 4, 4, 8, 2, true, false, TURN>(it, acc_out, st);
     }
+}
+
+// Whether dY turns in LDS (linear_turns; its rows are whole lines apart where the contraction has an even number of tiles of 32).  Time with the
+// turn by time without it over 23 000 calls, half of them on cached weights, by contraction tiles:
+//   at most 8 rows, of which a load brings as many that are none: 1.02 to 1.06 at any length (wide 1.00 to 1.04);  9 to 16 rows: even 8
+//     1.00, 12 0.98, 64 0.95, wide 32 1.00, 64 0.98; odd 33 1.01, 65 0.98
+//   small blocks: even 2 1.02 to 1.05, 6 0.98 to 1.00, 8 0.95 to 0.97, 32 0.80 to 0.86; odd 9 to 27 1.00 to 1.06, 33 0.96 to 0.98, 65 0.84 to 0.92; of
+//     32 x 64: even 8 to 10 1.00 to 1.03, 14 0.99, 64 0.84; odd 9 to 27 1.04 to 1.09, 33 1.00, 65 0.95
+//   17 to 32 rows: even 8 1.01, 16 0.98; odd 1.01 to 1.07 at any length;  33 to 64 rows: even 20 1.05, 32 0.99, 64 0.94; odd 33 1.02, 65 0.96
+//   row blocks: even 0.80 to 0.87; odd 25 to 31 1.05, 33 0.97
+bool bwd_turns(int64_t M, int64_t N, int64_t K)
+{
+    const int64_t kt = N / 32;
+    const bool lines = kt % 2 == 0;
+    const LinItem it = bwd_item(nullptr, nullptr, nullptr, M, N, K);
+    const SmallBlock small = small_block(&it, 1, 2);
+    if (small.mt) return kt >= (small.nt == 4 ? (lines ? 14 : 64) : (lines ? 8 : 32));
+    if (M <= 8) return false;
+    if (M <= 16) return kt >= (lines && K <= 4096 ? 10 : 64);
+    if (M <= 32) return lines && kt >= 16;
+    if (M <= 64) return kt >= (lines ? 32 : 64);
+    return lines || kt >= 32;
 }
 
 void launch_bwd_skinny(const void* dy, const void* wt, void* dx, float* acc_out, int64_t M, int64_t N, int64_t K, sasq_dtype dt, int rows, hipStream_t st)
 {
     LinItem it = bwd_item(dy, wt, dx, M, N, K);
-    if (dt == SASQ_F16) launch_bwd_dt<SASQ_F16>(it, acc_out, rows, st);
-    else                launch_bwd_dt<SASQ_BF16>(it, acc_out, rows, st);
+    auto by_dt = [&](auto turn_tag) {
+        constexpr bool TURN = decltype(turn_tag)::value;
+        if (dt == SASQ_F16) launch_bwd_dt<SASQ_F16, TURN>(it, acc_out, rows, st);
+        else                launch_bwd_dt<SASQ_BF16, TURN>(it, acc_out, rows, st);
+    };
+    if (bwd_turns(M, N, K)) by_dt(std::true_type{});
+    else                    by_dt(std::false_type{});
 }
 
 }  // namespace sasq

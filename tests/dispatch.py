@@ -18,6 +18,12 @@ def bwd_rows(M, N, K):
     return _function("_ZN4sasq8bwd_rowsElll", i64, i64, i64)(M, N, K)
 
 
+def bwd_turns(M, N, K):
+    """Whether dY turns in LDS in the backward linear's few-row and row-block kernels (sasq::bwd_turns)."""
+    i64 = ctypes.c_int64
+    return bool(_function("_ZN4sasq9bwd_turnsElll", i64, i64, i64)(M, N, K) & 1)
+
+
 def bwd_tile(M, N, K):
     """The backward GEMM's tile, rows and columns (sasq::bwd_tile)."""
     i64 = ctypes.c_int64

@@ -4,7 +4,9 @@ from __future__ import annotations
 
 import random
 
-from tests.dispatch import bwd_rows, bwd_tile
+import pytest
+
+from tests.dispatch import bwd_rows, bwd_tile, bwd_turns
 
 MOST = 2 ** 40                                              # the entry point's limit on each product of two sizes
 
@@ -46,3 +48,15 @@ def test_few_rows_and_row_blocks_where_each_was_measured_fastest():
     for shape, rows in (((1, 4096, 4096), 64), ((16, 4096, 27456), 64), ((17, 9696, 9728), 64), ((25, 13248, 8896), 64), ((64, 256, 256), 32),
                         ((334, 11072, 1536), 64), ((198, 128, 1984), 32)):
         assert bwd_rows(*shape) == rows, shape
+
+
+# (rows, outputs, the first even and the first odd number of contraction tiles that turn), None: none does
+TURNS = [(1, 1000, None, None), (8, 9000, None, None), (12, 1000, 10, 65), (16, 9000, 64, 65), (40, 500, 8, 33), (64, 1500, 8, 33), (100, 4000, 14, 65),
+         (30, 6000, 16, None), (50, 9000, 32, 65), (200, 9000, 2, 33)]
+
+
+@pytest.mark.parametrize("M,K,even,odd", TURNS)
+def test_short_contractions_keep_the_order_of_the_matrix_units(M, K, even, odd):
+    for first, parity in ((even, 0), (odd, 1)):
+        for tiles in range(2 - parity, 400, 2):
+            assert bwd_turns(M, 32 * tiles, K) == (first is not None and tiles >= first), (M, tiles, K)
