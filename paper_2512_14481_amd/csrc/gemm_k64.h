@@ -54,6 +54,7 @@ void launch_linear_anyk_skinny(LinBatch& b, sasq_dtype dt, bool qx, int a_bits, 
 // The choice of kernels in linear_bwd.hip: rows per workgroup without tiles, 0: tiles; the tile, 0: 256x256, 1: 128x256, 2: 128x128.
 int bwd_rows(int64_t M, int64_t N, int64_t K);
 int bwd_tile(int64_t M, int64_t N, int64_t K);
+bool bwd_reads_lines(int64_t N, int tile_rows);
 // The backward GEMM dX[M, K] = dY[M, N] . B^T over the prepared weight (linear_bwd.hip), for few rows or too few tiles; N a multiple
 // of 32.  bwd_takes_skinny: rows per workgroup, 0: the tiles, which take tile_us, are better, or the contraction is too long.
 // An estimate of a launch's time in us: its workgroups go in rounds of 256, one a CU; a round costs what a workgroup takes to start and end,

@@ -331,7 +331,7 @@ static void launch_bwd(const void* dy, const void* wt, void* dx, float* acc_out,
 // (gemm_k64_body.h): 16x16 tiles, one MFMA per 64-byte stage row, scalar-addressed direct loads, chunked epilogue.
 // The default: a register-only loop of the 16x16x32 form sustains about 18 % more than 32x32x16 on this
 // power-limited part (1.97 against 1.67 PFLOP/s for f16).  dY is the body's row-major operand, the prepared
-// weight its block operand; K of the body is the contraction length in bytes.  LINES: dY in whole cache lines, N a multiple of 64.
+// weight its block operand; K of the body is the contraction length in bytes.  LINES: dY in whole cache lines (bwd_reads_lines).
 template <int DT, int BM, int BN, bool LINES>
 __global__ __launch_bounds__(kGemmThreads)
 __attribute__((amdgpu_waves_per_eu(Tile<BM, BN>::kWavesPerSimd, Tile<BM, BN>::kWavesPerSimd)))
@@ -346,6 +346,12 @@ void linear_bwd_k32_kernel(const uint8_t* __restrict__ dy, const uint8_t* __rest
                                                         reinterpret_cast<int32_t*>(acc_out), M, K, N * 2, tm, tn, lds);
 }
 
+// Whether a tile of so many rows reads dY in whole cache lines (the body's OP 2): rows of whole 128-byte pieces, and enough of them that what
+// the ring's longer fill and tail cost is made up.  Whole lines in parts of halves over 2000 calls, half of them on cached weights, by contraction
+// tiles of 32: tiles of 128 rows 2 to 6 1.02, 8 1.10, 12 1.08, 16 1.04, 24 1.00, 32 to 63 0.97, 64 0.92, 128 0.89; of 256 rows 8 to 24
+// 1.02 to 1.06, 32 to 63 1.01, 64 0.99, 128 0.96, 256 0.93.
+bool bwd_reads_lines(int64_t N, int tile_rows) { return N % (2 * kBwdCols) == 0 && N >= (tile_rows == 256 ? 64 : 32) * kBwdCols; }
+
 template <int DT, int BM, int BN>
 static void launch_bwd_k32(const void* dy, const void* wt, void* dx, float* acc_out, int64_t M, int64_t N, int64_t K, hipStream_t st)
 {
@@ -356,8 +362,8 @@ static void launch_bwd_k32(const void* dy, const void* wt, void* dx, float* acc_
             static_cast<const uint8_t*>(dy), static_cast<const uint8_t*>(wt), static_cast<uint16_t*>(dx), acc_out,
             (int)M, (int)N, (int)K, tiles_m, tiles_n);
     };
-    if (N % (2 * kBwdCols) == 0) launch(std::true_type{});          // rows of dY are whole 128-byte pieces: the body's OP 2
-    else                         launch(std::false_type{});
+    if (bwd_reads_lines(N, BM)) launch(std::true_type{});
+    else                        launch(std::false_type{});
 }
 
 // The 32x32x16 kernel: 256x256 tiles unless they would leave most of the 256 CUs idle for a round; then 128x128

@@ -30,6 +30,11 @@ def bwd_tile(M, N, K):
     return ((256, 256), (128, 256), (128, 128))[_function("_ZN4sasq8bwd_tileElll", i64, i64, i64)(M, N, K)]
 
 
+def bwd_reads_lines(N, tile_rows):
+    """Whether the backward GEMM's tiles of so many rows read dY in whole cache lines (sasq::bwd_reads_lines)."""
+    return bool(_function("_ZN4sasq15bwd_reads_linesEli", ctypes.c_int64, ctypes.c_int)(N, tile_rows) & 1)
+
+
 def grouped_form(M, N, K, group, blocked):
     """The form of the grouped linear's split kernel, 0: the other kernels (sasq::grouped_takes_split)."""
     i64 = ctypes.c_int64

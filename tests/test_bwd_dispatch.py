@@ -6,7 +6,7 @@ import random
 
 import pytest
 
-from tests.dispatch import bwd_rows, bwd_tile, bwd_turns
+from tests.dispatch import bwd_reads_lines, bwd_rows, bwd_tile, bwd_turns
 
 MOST = 2 ** 40                                              # the entry point's limit on each product of two sizes
 
@@ -60,3 +60,9 @@ def test_short_contractions_keep_the_order_of_the_matrix_units(M, K, even, odd):
     for first, parity in ((even, 0), (odd, 1)):
         for tiles in range(2 - parity, 400, 2):
             assert bwd_turns(M, 32 * tiles, K) == (first is not None and tiles >= first), (M, tiles, K)
+
+
+@pytest.mark.parametrize("tile_rows,first", [(128, 32), (256, 64)])
+def test_short_contractions_read_half_lines(tile_rows, first):
+    for tiles in range(1, 300):
+        assert bwd_reads_lines(32 * tiles, tile_rows) == (tiles % 2 == 0 and tiles >= first), tiles
