@@ -50,6 +50,7 @@ bool linear_long_rows(const LinBatch& b);
 void launch_linear_skinny(LinBatch& b, sasq_dtype dt, int wmode, bool qx, int a_bits, int32_t* acc_out, hipStream_t st);
 // The same for K that is not a multiple of 64, a single call with row-major int8 weights (row-major codes in xq).
 bool linear_anyk_takes_skinny(int64_t M, int64_t N, int64_t K);
+int linear_anyk_tile(int64_t M, int64_t N, int64_t K);
 void launch_linear_anyk_skinny(LinBatch& b, sasq_dtype dt, bool qx, int a_bits, int32_t* acc_out, hipStream_t st);
 // The choice of kernels in linear_bwd.hip: rows per workgroup without tiles, 0: tiles; the tile, 0: 256x256, 1: 128x256, 2: 128x128.
 int bwd_rows(int64_t M, int64_t N, int64_t K);

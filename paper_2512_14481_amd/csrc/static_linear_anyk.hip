@@ -45,7 +45,7 @@ __global__ __launch_bounds__(128 * WM, 2) void linear_anyk_kernel(
     const int lrow = tid >> 3, lch = tid & 7;
     const uint8_t* xb = xq + (int64_t)m0 * K;
     const uint8_t* wb = wq + (int64_t)n0 * wlen;
-    uint32_t xo[XL], wo[WL];                                       // at most 128 rows of 131071 bytes
+    uint32_t xo[XL], wo[WL];                                       // at most 256 rows of 131071 bytes
 #pragma unroll
     for (int j = 0; j < XL; ++j) xo[j] = (uint32_t)min(lrow + kRows * j, M - 1 - m0) * (uint32_t)K;
 #pragma unroll
@@ -230,8 +230,9 @@ static void launch_anyk_one(const GemmK64Args& a, hipStream_t st)
 }
 
 // Big tiles read the operands less often, small ones put more CUs to work.  Eight waves a workgroup from 64x128 tiles on: the loads in
-// flight that it takes to keep the L2s busy then fit a tile of twice the outputs, which asks for three quarters of the operands (rows that
-// begin inside cache lines cost two lines for most of their pieces).  Measured, us with the pre-pass, the earlier choice of 128x128, 64x128
+// flight that it takes to keep the L2s busy then fit a tile of twice the outputs, which asks for two thirds
+// (64x128 -> 128x128) or three quarters (128x128 -> 256x128) of the operands (rows that begin inside cache lines cost two lines for most of their
+// pieces).  Measured, us with the pre-pass, the earlier choice of 128x128, 64x128
 // (from 256 tiles) and smaller tiles of four waves | 64x128 | 128x128 | 256x128 of eight, by number of 128x128 tiles:
 //   96: 333 x 4000, K = 1376 int8 12.4 | 12.3 | 15.2 | 21.6, K = 1801 19.1 | 16.6 | 20.8 | 30.5, int4 15.2 | 14.7 | 17.6 | 23.2
 //   128: 1000 x 2048, K = 1376 15.2 | 13.8 | 16.6 | 23.2, K = 3976 30.0 | 28.4 | 32.9 | 47.5, int4 39.6 | 34.3 | 38.7 | 52.2
@@ -245,6 +246,27 @@ static void launch_anyk_one(const GemmK64Args& a, hipStream_t st)
 // end: 300 x 16385, K = 200 17.7 | - | 19.1 | -, K = 1040 25.8 | - | 27.2 | -.
 // Fewer tiles, four waves, 128x128 / 64x128 / 64x64 / 32x64: 512 x 1024 x 3000 (64 of 64x128, 256 of 32x64) 28.2 / 21.5 / 16.3 / 14.9, 64 x
 // 4096 x 3976 (128 of 32x64) 31.3 / 24.8 / 19.4 / 16.7.
+// 257 to 511 tiles of 128x128 that are at most 768 of 64x128: the latter, of four waves, run three a CU, all at once, in parts of the larger
+// tiles' time, by K up to 255, 511, 1023, 2047 and beyond, 0.90 to 0.96, 0.90 to 0.95, 0.93 to 1.01, 0.97 to 1.10, 1.03 to 1.14; up to 512 of them,
+// two a CU, 0.78 to 0.83 at any K.  Two rounds of 256x128 tiles, K under 1024: 128x128 0.94 to 0.99 of their time.  192 to 255 tiles of 64x128, K
+// under 256: 64x64 0.95 to 0.99 of the time of eight waves.
+// 0: 256x128, eight waves; 1: 128x128, eight; 2: 128x128, four; 3: 64x128, eight; 4: 64x128, four; 5: 64x64; 6: 32x64.
+int linear_anyk_tile(int64_t M, int64_t N, int64_t K)
+{
+    auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    const int64_t t256 = tiles(256, 128), t128 = tiles(128, 128), t64 = tiles(64, 128);
+    const bool mid = t128 <= 1024 && t128 * 20 <= t64 * 11;          // and at most a tenth of the rows past the matrix's end
+    // rounds of 256x128 tiles, one a CU, that are nearly full
+    const bool rounds_fill = (t256 <= 256 || t256 * 10 >= (t256 + 255) / 256 * 2304) && t256 * 20 <= t128 * 11;
+    if (t128 > 256 && t128 < 512 && t64 <= (K < 1024 ? 768 : 512)) return 4;
+    if (mid && t128 > 256 && rounds_fill && (t128 <= 512 || K >= 1024)) return 0;
+    if (mid && t64 > 256)          return 1;
+    if (t128 >= 512)               return 2;
+    if (t64 > 256)                 return 4;
+    if (t64 == 256 || (t64 >= 192 && K >= 256)) return 3;
+    return tiles(64, 64) >= 256 ? 5 : 6;
+}
+
 template <int DT, bool INT4, bool ROWS>
 static void launch_anyk_w(const GemmK64Args& a, hipStream_t st)
 {
@@ -254,18 +276,15 @@ static void launch_anyk_w(const GemmK64Args& a, hipStream_t st)
             a.xq, a.wq, a.s, a.s_w, a.bias, a.y, a.acc_out, (int)(a.M * a.N), (int)a.N, (int)a.K);
         return;
     }
-    auto tiles = [&](int64_t bm, int64_t bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
-    const int64_t t256 = tiles(256, 128), t128 = tiles(128, 128), t64 = tiles(64, 128);
-    const bool mid = t128 <= 1024 && t128 * 20 <= t64 * 11;          // and at most a tenth of the rows past the matrix's end
-    // rounds of 256x128 tiles, one a CU, that are nearly full
-    const bool rounds_fill = (t256 <= 256 || t256 * 10 >= (t256 + 255) / 256 * 2304) && t256 * 20 <= t128 * 11;
-    if (mid && t128 > 256 && rounds_fill) launch_anyk_one<DT, INT4, ROWS, 256, 128, 2, 4>(a, st);
-    else if (mid && t64 > 256)      launch_anyk_one<DT, INT4, ROWS, 128, 128, 2, 4>(a, st);
-    else if (t128 >= 512)           launch_anyk_one<DT, INT4, ROWS, 128, 128, 2>(a, st);
-    else if (t64 > 256)             launch_anyk_one<DT, INT4, ROWS, 64, 128, 2>(a, st);
-    else if (t64 >= 192)            launch_anyk_one<DT, INT4, ROWS, 64, 128, 2, 4>(a, st);
-    else if (tiles(64, 64) >= 256)  launch_anyk_one<DT, INT4, ROWS, 64, 64, 4>(a, st);
-    else                            launch_anyk_one<DT, INT4, ROWS, 32, 64, 4>(a, st);
+    switch (linear_anyk_tile(a.M, a.N, a.K)) {
+        case 0: launch_anyk_one<DT, INT4, ROWS, 256, 128, 2, 4>(a, st); break;
+        case 1: launch_anyk_one<DT, INT4, ROWS, 128, 128, 2, 4>(a, st); break;
+        case 2: launch_anyk_one<DT, INT4, ROWS, 128, 128, 2>(a, st); break;
+        case 3: launch_anyk_one<DT, INT4, ROWS, 64, 128, 2, 4>(a, st); break;
+        case 4: launch_anyk_one<DT, INT4, ROWS, 64, 128, 2>(a, st); break;
+        case 5: launch_anyk_one<DT, INT4, ROWS, 64, 64, 4>(a, st); break;
+        default: launch_anyk_one<DT, INT4, ROWS, 32, 64, 4>(a, st); break;
+    }
 }
 
 void launch_linear_anyk(const GemmK64Args& a, sasq_dtype dt, bool int4, bool rows, hipStream_t st)

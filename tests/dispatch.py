@@ -47,6 +47,15 @@ def anyk_few_rows(M, N, K):
     return bool(_function("_ZN4sasq24linear_anyk_takes_skinnyElll", i64, i64, i64)(M, N, K) & 1)
 
 
+ANYK_TILES = ((256, 128, 8), (128, 128, 8), (128, 128, 4), (64, 128, 8), (64, 128, 4), (64, 64, 4), (32, 64, 4))
+
+
+def anyk_tile(M, N, K):
+    """The tile of a linear with K not a multiple of 64 and more rows: rows, columns, waves (sasq::linear_anyk_tile)."""
+    i64 = ctypes.c_int64
+    return ANYK_TILES[_function("_ZN4sasq16linear_anyk_tileElll", i64, i64, i64)(M, N, K)]
+
+
 class _LinItem(ctypes.Structure):
     _fields_ = [(f, ctypes.c_void_p) for f in ("x", "xq", "s", "wq", "s_w", "bias", "y")] + [(f, ctypes.c_int) for f in ("M", "N", "K", "tiles_m", "tiles_n")]
 
