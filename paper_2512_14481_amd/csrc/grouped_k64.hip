@@ -31,8 +31,9 @@ static void launch_grouped_one(const GemmK64Args& a, int group_tiles, hipStream_
             a.xq, a.wq, a.s, a.s_w, a.bias, a.y, a.acc_out, (int)a.M, (int)a.N, (int)a.K, tiles_m, tiles_n, group_tiles);
     };
     // 128x256 tiles, for tests, have the two general forms only
-    if (group_tiles == 0)          launch(std::integral_constant<int, GR_HALF>{});
-    else if (group_tiles % 4 == 0) launch(std::integral_constant<int, BN == 128 ? GR_FOURS : GR_EVEN>{});
+    if (group_tiles == 0) {
+        if constexpr (BN == 128) launch(std::integral_constant<int, GR_HALF>{});
+    } else if (group_tiles % 4 == 0) launch(std::integral_constant<int, BN == 128 ? GR_FOURS : GR_EVEN>{});
     else if (group_tiles == 2)     launch(std::integral_constant<int, BN == 128 ? GR_TWO : GR_EVEN>{});
     else if (group_tiles == 1)     launch(std::integral_constant<int, BN == 128 ? GR_ONE : GR_ODD>{});
     else if (group_tiles % 2 == 0) launch(std::integral_constant<int, GR_EVEN>{});
