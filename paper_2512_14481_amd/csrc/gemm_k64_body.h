@@ -88,8 +88,9 @@ __device__ __forceinline__ void lds_load16(uint32_t lds_a, uint32_t lds_b, const
 // OP 2: OP 1 with X read in whole cache lines, an even number of K tiles: a load takes 8 rows x 128 bytes, two K tiles, instead of 16
 // rows x 64 bytes, which are half a line each: L2 then answers two requests for a line, and memory delivers it in halves, two K tiles
 // apart.  X has a ring of its own, three slots of two K tiles, that fills the LDS to its 160 KB (256x256) and is requested four to five
-// K tiles ahead.  us, halves | lines, operands from memory: f16 4096 x 11008 -> 4096 281 | 246, 4096 x 4096 -> 11008 286 | 272, bf16 282 |
-// 237 and 275 | 261, 8192^3 735 | 691, 1024 x 5120 -> 5120 77 | 65, 777 x 4096 -> 4096 31.3 | 28.8; in the caches 268 | 264.
+// K tiles ahead.  us, halves | lines, operands from memory: f16 4096 x 11008 -> 4096 254 | 231, 4096 x 4096 -> 11008 273 | 258, bf16 255 | 231
+// and 268 | 258, 4096 x 4096 -> 4096 101 | 94, 1024 x 5120 -> 5120 79 | 66, 777 x 4096 -> 4096 36 | 36; weights in the caches, f16 241 | 234, 259 |
+// 258, bf16 235 | 227, 258 | 257, 95 | 93, 71 | 62, 32 | 29.
 template <int DT, int WMODE, int BM, int BN, bool ROWS, int GROUPED = GR_NONE, int OP = 0>
 __device__ __forceinline__
 void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq,
@@ -279,8 +280,8 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
             const i32x4 wv = I4 ? wv_ahead : wfrag(fw[CUR][g]);
             const bool ahead_in_tile = g + 1 < NF;
             // Rows go back and forth, so that every MFMA keeps one operand of the one before it: fewer bits toggle, and with data the
-            // clock is what the power leaves.  A register-only loop sustains 1.1 % more (f16 1862 -> 1878 TFLOP/s, int8 4087 -> 4133
-            // TOP/s; 3.5 % less where both operands change every time), the GEMMs 0.2 to 0.9 % (8192 x 8192 x 8192 int8 401 -> 398 us).
+            // clock is what the power leaves.  A register-only loop sustains 0.6 to 1 % more (f16 1957 -> 1973 TFLOP/s, int8 on the
+            // workload's codes 4606 -> 4648 TOP/s, on random bytes 4175 -> 4217), the GEMMs 0.2 to 0.9 % (8192 x 8192 x 8192 int8 401 -> 398 us).
             const WFrag& fnext = ahead_in_tile ? fw[CUR][g + 1 < NF ? g + 1 : 0] : fw[1 - CUR][0];
 #pragma unroll
             for (int bi = 0; bi < MF; ++bi) {
@@ -412,12 +413,16 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
         lds_load16(lds_base - (uint32_t)wave * 1024u + T::kLds + (uint32_t)wave * kFacBytes, s_w + wn0,
                    (uint32_t)(lane & (BN / 8 - 1)) * 16u);   // lanes past BN/8 fetch the same factors again: no lane reads past the block
     if constexpr (WHOLE) {
-        // Groups in straight lines: where a branch decided between the first K tile's body and the others', the compiler kept the
-        // accumulators of both apart and spilled inside the loop.  Requests are unconditional: past the end the last tile comes again and
-        // a stage's old fragments are read, which nothing uses.  us, branches and a separate tail | straight lines, int8: 2048 x 4096 ->
-        // 11008 in groups of 64, 128, 256 164, 141, 134 | 157, 138, 123; 2048 x 4096 -> 4096 64, 53, 50 | 61, 49, 45; 700 x 8192 -> 5000 76,
-        // 62, 53 | 69, 54, 46; int4, 2048 x 4096 -> 11008 187, 156, 134 | 185, 145, 130.  One K tile a group takes the loop of the plain GEMM.
-        // Not kept: the fold tile by tile between the next group's first MFMAs (128, 256, 512: 148, 124, 116 against 139, 123, 120).
+        // Groups in straight lines: a branch that decides between the first K tile's body and the others' costs a copy of each in the loop and
+        // registers (254 and 256, int8 20 of them spilled around the loops; 192 to 226 so).  Requests are unconditional: past the end the
+        // last tile comes again and a stage's old fragments are read, which nothing uses.  us, branches and a separate tail | straight lines,
+        // weights in the caches, groups of 64, 128, 256, 512: int8 2048 x 4096 -> 11008 137, 116, 110, 102 | 132, 107, 99, 93; 2048 x 4096 ->
+        // 4096 54, 48, 45, 43 | 52, 44, 42, 40; 700 x 8192 -> 5000 69, 57, 47, 43 | 60, 47, 41, 38; int4 157, 128, 109, 100 | 155, 120, 102,
+        // 93 and 62, 51, 45, 44 | 63, 49, 43, 41.  One K tile a group takes the loop of the plain GEMM; int4 is slower so where some CUs hold two
+        // workgroups and the rest one, or the last of several rounds does (257 to 511, 768 to 1023 tiles), by 1.03 to 1.09 at 16 to 31 K tiles
+        // and 1.00 to 1.03 beyond, 0.94 to 1.00 elsewhere.  Not kept for it: straight lines (1.02 to 1.06 there, 0.98 to 1.02 beyond),
+        // two K tiles a trip with run-time stages (1.07 to 1.20).  Nor the fold tile by tile between the next group's first MFMAs (128, 256,
+        // 512: 148, 124, 116 against 139, 123, 120, one series).
         auto first = [&](int i, auto cur_tag, auto stage_tag) { iteration(i, cur_tag, stage_tag, Yes{}, No{}); };
         auto rest = [&](int i, auto cur_tag, auto stage_tag) { iteration(i, cur_tag, stage_tag, No{}, No{}); };
         auto rest_of_group = [&](int& i, int tiles, auto cur_tag) {      // an even number of tiles
@@ -491,7 +496,7 @@ void gemm_k64_body(const int8_t* __restrict__ xq, const uint8_t* __restrict__ wq
         }
     } else {
 #pragma unroll 1
-        for (int i = steady; i < KT; i += 2) {                  // KT - steady is 1 .. 9, steady is even
+        for (int i = steady; i < KT; i += 2) {                  // KT - steady is 1 .. 8, steady is even
             step(i, C0{}, SR{}, No{}, Yes{});
             if (i + 1 < KT) step(i + 1, C1{}, SR{}, No{}, Yes{});
         }

@@ -376,7 +376,8 @@ static bool bwd_small_tiles(int64_t M, int64_t K)
     if (tuning(SASQ_TUNE_BWD_TILE) == 2) return true;
     return rounds128(M, K) < rounds256(M, K);
 }
-// The tile of the 16x16x32 kernel: 0: 256x256, 1: 128x256, 2: 128x128, by the rounds of a 256x256 tile's time that a launch takes.  A
+// The tile of the 16x16x32 kernel: 0: 256x256, 1: 128x256, 2: 128x128, by the rounds of a 256x256 tile's time that a launch takes (all figures
+// here with dY in half lines).  A
 // 128x256 tile alone on its CU takes 0.65 of it (several rounds of them 0.68 each), a 128x128 tile 0.44, two of them on a CU 0.8: of 257
 // to 512 tiles of 128x128 some CUs hold two, and as 128x256 they all run at once.  But the one wave a SIMD of a 128x256 tile has nothing
 // beside it while it fills its pipeline, stores, or waits for weights that the caches have not seen, as those of a training step: it pays from
@@ -400,8 +401,9 @@ int bwd_tile(int64_t M, int64_t N, int64_t K)
     return c0 <= c1 && c0 <= c2 ? 0 : c1 < c2 ? 1 : 2;
 }
 // The time of those tiles, us, for the choice between them and the few-row and row-block kernels: least squares over 3900 calls of 1 to 4000
-// rows, contractions of 64 to 14000 and outputs of 128 to 28000, each tile timed in all of them (rms error 7 %, 8 % and 10 %).  Of 128x128
-// tiles a CU holds two in rounds of more than 256.
+// rows, contractions of 64 to 14000 and outputs of 128 to 28000, each tile timed in all of them (rms error 7 %, 8 % and 10 %), with dY in half
+// lines; an even number of 32 and more contraction tiles now takes 0.87 to 1.01 of that (bwd_reads_lines).  Of 128x128 tiles a CU holds two in
+// rounds of more than 256.
 static double bwd_tile_us(int64_t M, int64_t N, int64_t K)
 {
     auto tiles = [&](int64_t bm, int64_t bn) { return ((M + bm - 1) / bm) * ((K + bn - 1) / bn); };

@@ -242,8 +242,8 @@ static void launch_anyk_one(const GemmK64Args& a, hipStream_t st)
 //   448: 1000 x 7168, K = 1376 33.2 | 32.1 | 27.4 | 27.3, K = 3976 79.2 | 82.8 | 57.2 | 55.2, int4 93.1 | 94.4 | 68.1 | 59.8
 //   768 (384 of 256x128, a round and a half): 2000 x 6144, K = 1376 44.3 | 46.9 | 40.0 | 49.3, K = 3976 97.2 | 120 | 95.3 | 101
 //   1024 (512, two rounds): 4096 x 4096, K = 1376 56.3 | 64.7 | 53.5 | 53.3, K = 3976 126 | 160 | 124 | 115, int4 148 | 188 | 133 | 128
-// Beyond, four waves: 8192 x 16384 (8192), K = 1040 293 | - | - | 393, int4 327 | - | - | 374; and where the larger tile has many rows past the
-// end: 300 x 16385, K = 200 17.7 | - | 19.1 | -, K = 1040 25.8 | - | 27.2 | -.
+// Beyond, four waves: 8192 x 16384 (8192), K = 1040 293 | - | - | 393, int4 327 | - | - | 374 (128x128 of eight, not taken there: 0.95 to 0.98 over
+// 880 calls of 1025 to 8192 tiles); and where the larger tile has many rows past the end: 300 x 16385, K = 200 17.7 | - | 19.1 | -, K = 1040 25.8 | - | 27.2 | -.
 // Fewer tiles, four waves, 128x128 / 64x128 / 64x64 / 32x64: 512 x 1024 x 3000 (64 of 64x128, 256 of 32x64) 28.2 / 21.5 / 16.3 / 14.9, 64 x
 // 4096 x 3976 (128 of 32x64) 31.3 / 24.8 / 19.4 / 16.7.
 // 257 to 511 tiles of 128x128 that are at most 768 of 64x128: the latter, of four waves, run three a CU, all at once, in parts of the larger

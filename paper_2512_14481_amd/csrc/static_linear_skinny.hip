@@ -1,12 +1,13 @@
 // int8 linear for few rows (token generation): Y = X . W^T where M is a handful of rows and the weights are what is read;
 // and for some hundred rows where the GEMM's tiles are too few to fill the chip (a chunk of a prefill), in row blocks.
 //
-// What bounds it: the weight bytes (a 7B layer's seven projections at 8 rows, int8: 202 MB in 36 us = 5.6 TB/s, the GEMM's
-// tiles took 93; a 13B layer's at one row, int4: 159 MB in 26.6 us, from 128; row-major int8, eight rows of a line each a load: 36 us).  The tiled GEMM hands out 256 (or 128) weight rows per workgroup, which at small M is
-// a few dozen workgroups with a K loop that nothing overlaps.  Here a workgroup owns 16 NT weight rows and its NW waves
-// share out K: a wave streams its part of the weights straight from memory into MFMA operand registers (a pre-arranged
-// 1 KB block IS one operand read of a wave), D K tiles ahead, with no LDS and no barrier until the waves' int32 sums are
-// added up at the end, so that some thousand waves each keep several KB in flight.  Integer sums make the split exact.
+// What bounds it: the weight bytes (a 7B layer's seven projections at 8 rows, int8: 202 MB in 34.8 us = 5.8 TB/s, the GEMM's
+// tiles took 93; a 13B layer's at one row, int4: 159 MB in 25.8 us, from 128; row-major int8, eight rows of a line each a load: 36 us).
+// The tiled GEMM hands out 256 (or 128) weight rows per workgroup, which at small M is a few dozen workgroups with a K loop that nothing
+// overlaps.  Here a workgroup owns 16 NT weight rows and its NW waves share out K: a wave streams its part of the weights straight from
+// memory into MFMA operand registers (a pre-arranged 1 KB block IS one operand read of a wave), D K tiles ahead, with no barrier, and LDS
+// only as each wave's own (operands that lie in rows turn there, below), until the waves' int32 sums are added up at the end, so that some
+// thousand waves each keep several KB in flight.  Integer sums make the split exact.
 // QX: the activations are quantized on the way into the operand registers, 16 elements per lane and K tile, which takes
 // the pre-pass's launch out of the call; each workgroup repeats that work, so it is for at most 16 rows, or for few codes
 // (linear_quantizes_in_kernel).  Otherwise the codes come from the pre-pass in their staging blocks.
@@ -514,8 +515,11 @@ static double tile_fill(const LinBatch& b, int64_t& tiles, int& k_max)
 //   single, int8, K = 4096, 64 rows:  N = 32768 (0.50) 38 | 33, 36864 (0.56) 39 | 43, 49152 (0.75) 45 | 54, 65536 (1.0) 56 | 61,
 //     69632 (two rounds, 0.53) 79 | 72, 81920 (0.63) 79 | 79, 131072 (1.0) 100 | 114; int4 98304 (0.75) 61 | 60; 48 rows: 49152
 //     (0.75) 45 | 44, 57344 (0.88) 50 | 57, int4 131072 (1.0) 76 | 69; 32 rows: never behind by more than 5 %
-//   row-major int8 (64-byte pieces of rows), part of the GEMM's time:  single, K = 8192, 8 rows 0.98 at most, 16 rows (0.44)
-//     0.93, (0.75) 1.07, (0.88) 1.28, 32 rows (0.75) 1.04, (0.88) 1.15, (1.0) 1.19; two, 64 rows: (0.50) 0.78, (0.63) 1.05, (0.75) 1.08
+//   row-major int8 in the MFMA's order, part of the GEMM's time:  single, K = 8192, 8 rows 0.98 at most, 16 rows (0.44) 0.93, (0.75)
+//     1.07, (0.88) 1.28, 32 rows (0.75) 1.04, (0.88) 1.15, (1.0) 1.19; two, 64 rows: (0.50) 0.78, (0.63) 1.05, (0.75) 1.08
+//   The lines are of then.  With the turn, single row-major projections, 3700 calls: 13 to 16 rows 0.86 to 0.90 up to (0.9); 17 to 32 rows (0.7)
+//     0.83 to 0.94, (0.8) 0.90 to 1.02; 33 to 48 (0.7) 0.85 to 1.00, (0.8) 0.92 to 1.06; 49 to 64 (0.5) 0.89 to 0.98, (0.6) 0.87 to 0.98, (0.7) 0.95
+//     to 1.03, (0.8) 1.00 to 1.07: what goes to the tiles below that takes up to 1.17 of its time here, 0.8 % over all of the calls
 // The layers of 7B, 13B and 70B (their long down projections leave most CUs to the rest: 0.28, 0.35 and 0.46) are better here.
 static bool tiles_are_better(const LinBatch& b, int rows, int wmode)
 {
@@ -544,8 +548,10 @@ static bool tiles_are_better(const LinBatch& b, int rows, int wmode)
 // backward 143 x 1280 x 1280 9.4 | 6.4 | 6.8, 143 x 2816 x 2816 16.5 | 16.4 | 11.3, 128 x 5248 -> 2048 26.8 | 15.4, 224 x 5248 -> 1792
 // 26.9 | - | 17.7.  Beyond a round: backward 171 x 1344 -> 1344 (36 blocks of 32 x 32 on one XCD) 9.4 | 10.4, 224 x 2240 -> 2240 (35 of
 // 32 x 64) 14.2 | - | 16.2, 64 x 4096 x 1024 (128 of 16 x 16) 7.0 | 8.4 | 7.5.
-// Row-major int8, whose few-row kernel has the better loads (plain ones), leaves it for blocks of 16 columns only, and of those for at least two
-// row blocks: 40 x 2048 -> 3000 7.4 | 9.0 as 32 x 32, 50 x 8192 -> 3500 14.3 | 15.9, 24 x 2048 -> 3000 6.8 | 7.8 as 32 x 16.
+// Row-major int8 leaves its few-row kernel for blocks of 16 columns only, and of those for at least two row blocks: in the MFMA's order,
+// 40 x 2048 -> 3000 7.4 | 9.0 as 32 x 32, 50 x 8192 -> 3500 14.3 | 15.9, 24 x 2048 -> 3000 6.8 | 7.8 as 32 x 16.  In the orders that both take
+// now, over 1160 calls, 32 x 16 at 17 to 32 rows 1.00 to 1.02 of the few-row kernel's time, but 32 x 32 at 33 to 64 rows 0.89 to 1.00 and 32 x 64
+// 0.75 to 0.95, the shorter the contraction the less.
 struct SmallBlock { int mt, nt; };                                       // in units of 16; 0: none
 static SmallBlock small_block(const LinItem* items, int count, int wmode)
 {
@@ -576,6 +582,8 @@ static SmallBlock small_block(const LinItem* items, int count, int wmode)
 // workgroup takes to start and end, and the operands of its K tiles.  The constants are least squares over 550 calls of 65 to 1200
 // rows, K and N from 1024 to 28672, single projections and layers, of times from 8 to 500 us: rms error 7 to 11 %.  Over those calls
 // the choice costs 0.8 % against the best of the four each time, and the calls take 0.87 of what they took with lines drawn by hand.
+// The constants of row-major int8 are of its loads in the MFMA's order: over 1900 such calls as they are now the choice costs 3.7 % against the best
+// of the four, 0.5 to 4 % where blocks are taken and 11 to 14 % where tiles are.
 // Row blocks are taken from 10 % less time on: the estimates are no better than that.  Blocks of 64 rows take four waves instead of eight from
 // a second round on: their sums then meet in 64 KB of LDS and two of them share a CU, 0.91 of the time at 257 to 768 blocks, 0.87 to 1536, 0.84
 // beyond, weights in the caches or not (eight waves are 1.00 to 1.04 of four in a single round).  us, GEMM tiles | 64 | 96 | 128 rows:
@@ -653,9 +661,10 @@ bool linear_takes_skinny(const LinBatch& b, int wmode)
 }
 
 // Whether such a call quantizes in the kernel: at most 16 rows, or so few codes in a workgroup's rows (of row tiles of 32 or 64, or of a
-// small block) that repeating them costs it less than a launch.  Measured, us, pre-pass | in the kernel: 32 rows, K = 256 4.8 | 3.3,
-// 1024 5.4 | 4.9, 2048 6.8 | 7.0, 4096 8.5 | 10.6; 64 rows, K = 256 5.1 | 3.7, 512 5.3 | 4.7, 1024 6.0 | 7.1; small blocks of 16 rows, K =
-// 1024 6.8 | 4.8, 4096 7.8 | 8.2.  any_k: K not a multiple of 64, where there are no small blocks.
+// small block) that repeating them costs it less than a launch.  Measured in the MFMA's order, us, pre-pass | in the kernel: 32 rows, K = 256
+// 4.8 | 3.3, 1024 5.4 | 4.9, 2048 6.8 | 7.0, 4096 8.5 | 10.6; 64 rows, K = 256 5.1 | 3.7, 512 5.3 | 4.7, 1024 6.0 | 7.1; small blocks of 16
+// rows, K = 1024 6.8 | 4.8, 4096 7.8 | 8.2.  In the orders taken now, of 6800 calls of 17 to 64 rows, K to 3072, in all three layouts, the
+// pre-pass would be ahead by more than 5 % in 19.  any_k: K not a multiple of 64, where there are no small blocks.
 bool linear_quantizes_in_kernel(const LinBatch& b, int wmode, bool any_k)
 {
     int rows = 0, k_max = 0;
@@ -849,7 +858,9 @@ static LinItem bwd_item(const void* dy, const void* wt, void* dx, int64_t M, int
 // 2400 -> 25216 20.2 | 31.3; that they have not seen, 40 x 4224 -> 17792 42.9 | 50.1, 51 x 960 -> 24960 11.7 | 17.7, but 17 x 9696 -> 9728 79 |
 // 49, 25 x 13248 -> 8896 107 | 77.  And 64 x 256 x 256 4.8 | 3.4, 131 x 2816 x 1344 23.4 | 17.3, 334 x 11072 x 1536 76.2 | 52.5.
 // So both sides are estimated, here from the same 3900 calls as the tiles, on weights that the caches have not seen (rms error 8 to 9 %), and
-// the tiles left from 10 % less time on: the calls then take 0.71 of what the tiles alone take, 2 % more than the best form of each.
+// the tiles left from 10 % less time on: the calls then take 0.71 of what the tiles alone take, 2 % more than the best form of each.  That is with
+// dY in the MFMA's order here and in half lines there; as both are now, over 4250 calls of 17 to 1500 rows, it is 2.1 %: up to 0.5 where these kernels
+// are taken, 4 to 9 on tiles of 128x128.
 int bwd_takes_skinny(int64_t M, int64_t N, int64_t K, double tile_us)
 {
     if (N > kBwdOffsetCols) return 0;                                // the body's lane offsets are 32-bit
