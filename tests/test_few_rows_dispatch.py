@@ -4,7 +4,7 @@ from __future__ import annotations
 import pytest
 
 from paper_2512_14481_amd import binding as B
-from tests.dispatch import linear_long_rows, linear_quantizes, linear_streams, linear_takes_few_rows, linear_turns
+from tests.dispatch import linear_block_rows, linear_long_rows, linear_quantizes, linear_streams, linear_takes_few_rows, linear_turns
 
 ROW_MAJOR, BLOCKED8, BLOCKED4 = B.SASQ_W_INT8, B.SASQ_W_INT8_BLOCKED, B.SASQ_W_INT4_BLOCKED
 
@@ -55,3 +55,16 @@ def test_forms_that_never_turn():
         assert linear_quantizes(items, wf) and not linear_turns(items, wf)
     for k in (64, 1024, 8192, 16384):
         assert not linear_turns([(9, 3000, k)], BLOCKED4) and not linear_turns([(16, 500, k)], BLOCKED4)
+
+
+@pytest.mark.parametrize("rows,dims,want", [
+    ((96, 70), [(8200, 128), (8501, 192)], (0, 0, 0)),
+    ((66, 80, 96), [(6000, 128), (6500, 64), (5111, 192)], (0, 0, 0)),
+    ((97, 66), [(8200, 128), (8501, 192)], (0, 0, 0)),
+    ((100, 128), [(8200, 2048), (8501, 2112)], (0, 0, 64)),
+    ((70, 96), [(17000, 128), (17000, 128)], (0, 0, 0)),                       # 134 tiles, more than half of a round
+    ((90, 65), [(20000, 2048), (20000, 2048)], (0, 0, 96))])
+def test_batches_of_many_columns(rows, dims, want):
+    """65 to 128 rows: most on the GEMM's tiles, int4's longest on row blocks."""
+    items = [(m, n, k) for m, (n, k) in zip(rows, dims)]
+    assert tuple(linear_block_rows(items, wf) for wf in (ROW_MAJOR, BLOCKED8, BLOCKED4)) == want

@@ -9,7 +9,6 @@ import torch
 
 import oracle
 from paper_2512_14481_amd import binding as B
-from tests.dispatch import anyk_tile
 from tests.gpu_util import TDT, assert_same_values, dev_scalar, set_tuning, to_bits, to_dev
 from tests.test_gpu_dynamic_linear import run_dynamic
 from tests.test_gpu_grouped_linear import WF
@@ -20,13 +19,19 @@ pytestmark = pytest.mark.gpu
 KS = [1, 2, 7, 15, 16, 18, 31, 63, 65, 100, 127, 129, 130, 136, 144, 250, 255, 257, 400, 526, 1376]
 ROWS_COLS = [(1, 1), (33, 47), (64, 64), (65, 130), (127, 129)]
 WIDE = [((1920, 2050), 130), ((2049, 1925), 81), ((1, 4099), 1030)]      # tiles of 128x128 and 64x128, and one row
-TILES = {(128, 128, 4): (4100, 4200), (64, 128, 4): (300, 7300), (64, 64, 4): (700, 1500), (32, 64, 4): (333, 700)}
+TILES = {(128, 128): (2817, 3001), (64, 128): (1000, 2050), (64, 64): (1100, 1500), (32, 64): (333, 700)}
 
 
 def chosen(m, n, k, fmt):
-    """The kernel the dispatch takes: the tile and its waves, or None for one thread per output (restated)."""
+    """The tile of four waves by their number, or None for one thread per output.  Which tile the library takes, and with how many waves:
+    tests/test_gpu_anyk_choice.py."""
     wlen = k // 2 if fmt == "int4" else k
-    return None if wlen <= 20 and m * n * wlen <= 3 << 19 else anyk_tile(m, n, k)
+    if wlen <= 20 and m * n * wlen <= 3 << 19:
+        return None
+    for (bm, bn), least in (((128, 128), 512), ((64, 128), 256), ((64, 64), 256)):
+        if -(-m // bm) * -(-n // bn) >= least:
+            return bm, bn
+    return 32, 64
 
 
 @pytest.mark.parametrize("fmt", ["int8", "int4"])
@@ -35,7 +40,7 @@ def chosen(m, n, k, fmt):
 def test_every_tile(tile, k, fmt):
     """Row, column and K remainders on each tile: one stage of 128 channels, several, and part of one over."""
     assert chosen(*TILES[tile], k, fmt) == tile
-    if tile == (128, 128, 4) and k == 650:
+    if tile == (128, 128) and k == 650:
         pytest.skip("the other lengths cover this tile's ring of two")
     test_any_contraction_length(TILES[tile], k, fmt)
 
@@ -46,8 +51,8 @@ def test_short_rows(k, fmt):
     """Rows shorter than a 16-byte piece, on the tiles and with a thread per output, on both sides of the line between them."""
     if fmt == "int4" and k % 2:
         pytest.skip("packed int4 rows hold whole bytes")
-    assert chosen(1100, 1500, k, fmt) == (64, 64, 4)
-    assert chosen(64, 999, k, fmt) == (None if (k // 2 if fmt == "int4" else k) <= 20 else (32, 64, 4))
+    assert chosen(1100, 1500, k, fmt) == (64, 64)
+    assert chosen(64, 999, k, fmt) == (None if (k // 2 if fmt == "int4" else k) <= 20 else (32, 64))
     for mn in ((1100, 1500), (64, 999), (1, 20001)):
         test_any_contraction_length(mn, k, fmt)
 

@@ -67,11 +67,9 @@ def test_row_blocks_match_oracle(items, want, fmt, blocked):
 
 
 @pytest.mark.parametrize("fmt,blocked", LAYOUTS)
-@pytest.mark.parametrize("shape", [(17, 47, 64), (32, 700, 1024), (32, 700, 1088), (33, 701, 512), (64, 700, 512), (64, 700, 576), (20, 8200, 192),
-                                   (32, 4200, 1024), (32, 4200, 1088), (64, 3000, 512), (64, 3000, 576), (64, 2000, 1024), (64, 2000, 1088)])
+@pytest.mark.parametrize("shape", [(17, 47, 64), (32, 700, 1024), (32, 700, 1088), (33, 701, 512), (64, 700, 512), (64, 700, 576), (20, 8200, 192)])
 def test_rows_quantized_in_the_kernel_match_oracle(shape, fmt, blocked):
-    """17 to 64 rows in small blocks and row tiles of 32 and 64, at and past the lengths up to which each workgroup quantizes for itself (rows
-    times K of a row tile: 32768, the 4200 columns and row-major 3000; K of a small block of 32 rows: 1024, the 2000 columns)."""
+    """17 to 64 rows around the line up to which each workgroup quantizes for itself (rows in tiles of 32 or 64, times K: 32768)."""
     set_tuning()
     M, N, K = shape
     xb, wq, s_w, bias, s = problem(110, shape, fmt, "f16")

@@ -9,9 +9,11 @@ import torch
 
 import oracle
 from paper_2512_14481_amd import binding as B
-from tests.dispatch import linear_quantizes, linear_takes_few_rows, linear_turns
+from tests.dispatch import linear_quantizes, linear_streams, linear_takes_few_rows, linear_turns
 from tests.gpu_util import assert_same_values, dev_scalar, set_tuning, to_bits, to_dev
 from tests.test_gpu_grouped_linear import WF, device_weights
+from tests.test_gpu_row_blocks import LAYOUTS, test_rows_quantized_in_the_kernel_match_oracle as check_quantized
+from tests.test_gpu_row_turn import test_rows_turned_in_lds_match_oracle as check_turned
 from tests.test_gpu_skinny_linear import problem
 
 pytestmark = pytest.mark.gpu
@@ -67,3 +69,28 @@ def test_batches_of_pre_arranged_row_tiles(fmt, rows, K, turns):
     B.sasq_static_linear_batch(items, wf, B.new_workspace(B.sasq_static_linear_batch_workspace(items, wf)))
     for it, ref in zip(items, refs):
         assert_same_values(to_bits(it[5]), ref, "bf16", "Y")
+
+
+@pytest.mark.parametrize("shape,layouts", [
+    ((5, 17001, 8064), (("int8", False),)),                                     # 137 MB of row-major weights, read past the caches
+    ((20, 16999, 8064), (("int8", False),)),
+    ((9, 9000, 11 * 64), (("int8", False),)),                                   # wide: a wave without a step, the third's last one half
+    ((8, 8200, 13 * 64), (("int8", False),)),                                   # wide: the fourth wave's only step is half
+    ((9, 9000, 33 * 64), (("int8", False), ("int8", True), ("int4", True))),
+    ((40, 1000, 11 * 64), (("int8", False),)),                                  # a small block
+    ((40, 3000, 33 * 64), (("int8", False),)),                                  # row tiles of 48, codes from the pre-pass
+    ((33, 8200, 17 * 64), (("int8", False),))])                                 # the same, wide
+def test_half_steps_of_turned_rows(shape, layouts):
+    for fmt, blocked in layouts:
+        wf = WF[(fmt, blocked)]
+        assert linear_takes_few_rows([shape], wf) and linear_turns([shape], wf)
+        assert linear_streams([shape], wf) == (blocked or shape[1] * shape[2] > 128 << 20)
+    check_turned(shape, layouts)
+
+
+@pytest.mark.parametrize("fmt,blocked", LAYOUTS)
+@pytest.mark.parametrize("shape", [(32, 4200, 1024), (32, 4200, 1088), (64, 3000, 512), (64, 3000, 576), (64, 2000, 1024), (64, 2000, 1088)])
+def test_row_tiles_at_the_longest_quantized_rows(shape, fmt, blocked):
+    """Row tiles of 32 and 64 and small blocks, at and past the lengths up to which each workgroup quantizes for itself (rows times K of a row
+    tile: 32768, the 4200 columns and row-major 3000; K of a small block of 32 rows: 1024, the 2000 columns)."""
+    check_quantized(shape, fmt, blocked)

@@ -10,7 +10,6 @@ import torch
 import oracle
 from paper_2512_14481_amd import binding as B
 from paper_2512_14481_amd import workloads as wl
-from tests.dispatch import linear_block_rows
 from tests.gpu_util import TDT, assert_same_values, dev_scalar, set_tuning, to_bits, to_dev
 from tests.test_gpu_grouped_linear import WF, device_weights
 
@@ -83,19 +82,37 @@ def test_output_over_input_at_few_rows():
     assert_same_values(to_bits(x), ref["y"], "f16", "Y")
 
 
+def chosen_rows(rows, dims, fmt):
+    """Rows per block for a batch of at most 128 and more than 64 rows (0: the GEMM's tiles) by rounds alone.  What the library takes:
+    tests/test_few_rows_dispatch.py."""
+    cols = [-(-n // 64) for n, _ in dims]
+    if min(cols) < 8:
+        return 0
+    for block in (64, 96):
+        if sum(-(-m // block) * c for m, c in zip(rows, cols)) <= 256:
+            return block
+    tiles, work, k_max = 0, 0, max(k for _, k in dims)
+    for n, k in dims:
+        tiles, work = tiles + -(-n // 256), work + -(-n // 256) * k
+    fill = work / (256 * max(k_max, -(-tiles // 256) * work / tiles))
+    if max(rows) <= 96:
+        line = 0.5 if k_max < 2048 else 0.7 if tiles > 256 else 0.8 if fmt == "int4" else 0.5
+        return 96 if fill <= line else 0
+    return 0 if fill > 0.5 or (fmt != "int4" and k_max < 2048 and tiles > 64) else 128
+
+
 @pytest.mark.parametrize("rows,dims,want", [
-    ((96, 70), [(8200, 128), (8501, 192)], (0, 0, 0)),
-    ((66, 80, 96), [(6000, 128), (6500, 64), (5111, 192)], (0, 0, 0)),
-    ((97, 66), [(8200, 128), (8501, 192)], (0, 0, 0)),
-    ((100, 128), [(8200, 2048), (8501, 2112)], (0, 0, 64)),
-    ((70, 96), [(17000, 128), (17000, 128)], (0, 0, 0)),                       # 134 tiles, more than half of a round
-    ((90, 65), [(20000, 2048), (20000, 2048)], (0, 0, 96))])
+    ((96, 70), [(8200, 128), (8501, 192)], {"int8": 96, "int4": 96}),
+    ((66, 80, 96), [(6000, 128), (6500, 64), (5111, 192)], {"int8": 96, "int4": 96}),
+    ((97, 66), [(8200, 128), (8501, 192)], {"int8": 0, "int4": 128}),
+    ((100, 128), [(8200, 2048), (8501, 2112)], {"int8": 128, "int4": 128}),
+    ((70, 96), [(17000, 128), (17000, 128)], {"int8": 0, "int4": 0}),          # 134 tiles, more than half of a round
+    ((90, 65), [(20000, 2048), (20000, 2048)], {"int8": 0, "int4": 96})])
 @pytest.mark.parametrize("fmt,blocked", LAYOUTS)
 def test_batch_of_row_blocks_matches_oracle(rows, dims, want, fmt, blocked):
-    """Batches of 65 to 128 rows by many columns, unequal M and ragged N: most on the GEMM's tiles, int4's longest on row blocks."""
+    """Batches with all rows in one block of 96 or 128, unequal M and ragged N, and their neighbours on the GEMM's tiles."""
     set_tuning()
-    wf = WF[(fmt, blocked)]
-    assert linear_block_rows([(m, n, k) for m, (n, k) in zip(rows, dims)], wf) == want[LAYOUTS.index((fmt, blocked))]
+    assert chosen_rows(rows, dims, fmt) == want[fmt]
     items, refs = [], []
     for i, (m, (n, k)) in enumerate(zip(rows, dims)):
         xb, wq, s_w, bias, s = problem(90 + i, (m, n, k), fmt, "f16")
@@ -103,6 +120,7 @@ def test_batch_of_row_blocks_matches_oracle(rows, dims, want, fmt, blocked):
         refs.append(oracle.static_linear(xb, s, wq, s_w, b, 8, fmt, "f16")["y"])
         items.append((to_dev(xb, "f16"), dev_scalar(s), device_weights(wq, fmt, blocked), torch.from_numpy(s_w).cuda(),
                       None if b is None else torch.from_numpy(b).cuda(), torch.full((m, n), float("nan"), dtype=torch.float16, device="cuda")))
+    wf = WF[(fmt, blocked)]
     B.sasq_static_linear_batch(items, wf, B.new_workspace(B.sasq_static_linear_batch_workspace(items, wf)))
     for it, ref in zip(items, refs):
         assert_same_values(to_bits(it[5]), ref, "f16", "Y")
